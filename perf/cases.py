@@ -88,6 +88,10 @@ def draw(rng):
                     "d_model": 8 * _log(rng, 32, 1024), "n_q": n_kv * group, "n_kv": n_kv, "head_dim": head_dim,
                     "rope_base": rng.choice([10000.0, 500000.0]), "batch": _log(rng, 1, MOST_BATCH), "kv": _log(rng, 1, 32768),
                     "layers": rng.randint(1, 4)}
+            if case["call"] == "stack":   # the bare stack stands for whole models: widths and head counts as they have them
+                case["d_model"] = 256 * _log(rng, 1, 32)
+                case["n_kv"] = rng.choice([1, 2, 4, 8, 16, 32])
+                case["n_q"] = case["n_kv"] * group
             if case["n_q"] * head_dim > 8192:
                 continue
             if case["call"] == "rows":   # every row's appended key and value is an output of its own
