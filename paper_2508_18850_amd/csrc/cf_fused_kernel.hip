@@ -1656,7 +1656,10 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
     const int cpw = (p.D + p.W - 1) / p.W;
     const int c0 = blockIdx.x * cpw;
     const int ncol = min(cpw, p.D - c0);
-    if (ncol <= 0) return;
+    if (ncol <= 0) {                                 // no column of its own (W * cpw > D): the hook runs all the same, a
+        after_polls();                               // stack's next layer counts on what it requests
+        return;
+    }
     const int nv = ncol * p.B;                       // values this workgroup produces
     for (int v0 = 0; v0 < nv; v0 += NT) {
         const int cb = min(NT, nv - v0);

@@ -315,3 +315,14 @@ def test_full_size_bare_stack_in_one_launch():
         tol = 1e-2 * np.abs(ref).max() + 1e-3
         _log("full-size bare stack, layer %d: max|err| %.3e tol %.3e max|ref| %.3e" % (l, err, tol, np.abs(ref).max()))
         assert np.isfinite(hidden[l + 1]).all() and err <= tol
+
+
+# A width that does not give every workgroup an output column of its own (1000 columns, 4 per workgroup: 250 of 256
+# have some): the others skip the last phase, and have to request the next layer's weights all the same.
+G4_RAGGED = cf_inputs.BlockShape("gqa4_ragged", 1000, 8, 2, 128, 500000.0, 0)
+M128_RAGGED = cf_inputs.BlockShape("mha128_ragged", 1000, 4, 4, 128, 10000.0, 0)
+
+
+@pytest.mark.parametrize("shape,batch", [(G4_RAGGED, 2), (M128_RAGGED, 1), (M128_RAGGED, 2)], ids=lambda v: getattr(v, "name", None))
+def test_stack_with_workgroups_that_own_no_output_column(shape, batch):
+    test_stack_matches_single_calls_and_oracle(shape, False, 0, True, batch, 3, 150)
