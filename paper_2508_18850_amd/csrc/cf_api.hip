@@ -45,6 +45,13 @@ struct cf_handle_s {
 namespace {
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
+// Rows of a projection slice: a multiple of eight where that leaves no slice empty, so that a slice of x starts at a
+// 16-byte boundary and is loaded in 16-byte pieces (d_model is a multiple of eight; the last slice may be shorter).
+int slice_rows(int d_model, int ks)
+{
+    const int exact = ceil_div(d_model, ks), up = ceil_div(exact, 8) * 8;
+    return (ks - 1) * up < d_model ? up : exact;
+}
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Register tile of the batch rows: 1, 4 (vector units) or 16 (MFMA).  The 16-row tile also wins at batch 3 and 4
@@ -66,8 +73,8 @@ int default_workgroups(const cf_handle_s *h)
     return w;
 }
 
-// Fill the work split of one call.  Returns CF_OK or an error.
-int make_plan(const cf_handle_s *h, int batch, int pos, Params *p)
+// Fill the work split of one call (even_slices: only slice counts that divide the team).  Returns CF_OK or an error.
+int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_slices = false)
 {
     const cf_config &c = h->cfg;
     const int hd = c.head_dim, G = h->G, bt = batch_tile(batch, c.head_dim);
@@ -77,40 +84,45 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p)
     p->W = W;
     p->TS = TS;
 
-    // projection: split the reduction dimension so that (G+2)*KS items balance over TS members
+    // projection: KS row slices x (TS / KS) groups of the G + 2 selectors; the members past KS * (TS / KS) have no
+    // part in it and go on to their cached rows at once.  KS need not divide TS: with G = 4 and 32 members 5 slices
+    // give 30 members one selector each (Llama-3-8B shape, batch 1, 2048 rows: 26.4 us against 27.7 us with 16
+    // slices; batch 4, 8192 rows: 45.2 against 45.8 us with 8).  A tuned KS has to divide it.
     {
-        int best = 0;
+        int best = 0, best_rows = 0;
         long best_cost = 0;
+        const size_t maxi = bt == 1 ? 4 : (bt <= 4 ? 2 : 1);
+        auto fits = [&](int rows) {
+            return (cf::x_lds_floats(hd, bt, rows) + maxi * cf::kWaves * bt * hd + (size_t)cf::kWaves * bt) * sizeof(float) <= kLdsLimit;
+        };
         for (int ks = 1; ks <= kMaxKS && ks <= TS; ++ks) {
-            if (TS % ks) continue;              // every member keeps one slice for all its selectors
             if (h->tune_ks > 0 && ks != h->tune_ks) continue;
-            const int rps = ceil_div(c.d_model, ks);
+            if ((h->tune_ks > 0 || even_slices) && TS % ks) continue;
+            int rps = slice_rows(c.d_model, ks);
+            if (!fits(rps)) rps = ceil_div(c.d_model, ks);
             if (rps < 8 && ks > 1) continue;
             if ((long)(ks - 1) * rps >= c.d_model) continue;   // no empty slice
-            const int maxi = bt == 1 ? 4 : (bt <= 4 ? 2 : 1);
-            const size_t lds = (cf::x_lds_floats(hd, bt, rps) + (size_t)maxi * cf::kWaves * bt * hd) * sizeof(float);
-            if (lds > kLdsLimit) continue;
+            if (!fits(rps)) continue;
             const int dsel = TS / ks;
             // rows a member streams, plus what its consumers pay for every further slice: KS partial sums per projected
-            // value to fetch, for every batch row (weighed by measurements on the grouped-query shapes: the
-            // Llama-3-8B shape takes 8 slices from batch 3 on, 16 below; the Llama-2-70B shape stays at 16)
-            const long cost = (long)(ceil_div(G, dsel) + ceil_div(2, dsel)) * rps + 12L * ks * (bt < 4 ? bt : 4);
+            // value to fetch, for every batch row (weighed by measurements; the Llama-2-70B shape stays at 16 slices:
+            // 75.0 us, 76.3 us with 3, 76.8 us with 8)
+            const long cost = (long)ceil_div(G + 2, dsel) * rps + 12L * ks * (bt < 4 ? bt : 4);
             if (!best || cost < best_cost) {
                 best = ks;
+                best_rows = rps;
                 best_cost = cost;
             }
         }
         if (!best) return h->tune_ks > 0 ? CF_EINVAL : CF_EUNSUPPORTED;
         p->KS = best;
-        p->RB = ceil_div(c.d_model, best);
+        p->RB = best_rows;
         // uneven slices (see the kernel's workgroup mapping): only when member parity == slice parity
         p->pairmap = (TS % 2 == 0 && W % 2 == 0 && h->balance_rows >= 0) ? 1 : 0;
         p->RD = 0;
-        if (p->pairmap && best % 2 == 0 && p->RB * best == c.d_model && p->RB >= 8 * h->balance_rows) {
-            const int maxi = bt == 1 ? 4 : (bt <= 4 ? 2 : 1);
-            const size_t lds = (cf::x_lds_floats(hd, bt, p->RB + h->balance_rows) + (size_t)maxi * cf::kWaves * bt * hd) * sizeof(float);
-            if (lds <= kLdsLimit) p->RD = h->balance_rows;
-        }
+        if (p->pairmap && TS % best == 0 && best % 2 == 0 && p->RB * best == c.d_model && p->RB >= 8 * h->balance_rows &&
+            fits(p->RB + h->balance_rows))
+            p->RD = h->balance_rows;
         p->RPS = p->RB + p->RD;
     }
     // attention: split the cached sequence so that B*NS items balance over TS members
@@ -175,15 +187,16 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p)
         p->NC3 = ceil_div(nch * cf::kOutChunk, p->CW3);
     }
     p->DSEL = TS / p->KS;
-    auto log2_or_minus1 = [](int v) {
-        for (int k = 0; k < 31; ++k)
-            if ((1 << k) == v) return k;
-        return -1;
+    auto divisor = [](int d) {                  // what the kernel's qdiv takes
+        for (uint32_t k = 0; k < 31; ++k)
+            if ((1 << k) == d) return k;
+        return (uint32_t)((0x100000000ull + d - 1) / d);
     };
-    p->sh_nkv = log2_or_minus1(c.n_kv_heads);
-    p->sh_ks = log2_or_minus1(p->KS);
-    p->sh_dsel = log2_or_minus1(p->DSEL);
-    p->sh_ns = log2_or_minus1(p->NS);
+    p->div_nkv = divisor(c.n_kv_heads);
+    p->div_ks = divisor(p->KS);
+    p->div_dsel = divisor(p->DSEL);
+    p->div_ns = divisor(p->NS);
+    p->div_p8 = divisor(p->RPS >= 8 ? p->RPS / 8 : 1);
     return CF_OK;
 }
 
@@ -377,10 +390,19 @@ static int decode_impl(cf_handle h, int packed, int32_t batch, const void *x, co
     if (rc != CF_OK) return rc;
     if (h->slot_area) {
         // the three slot arrays, sized for this call's plan, side by side in the fixed area
-        const size_t b1 = align_up((size_t)p.KS * batch * h->nqkv * sizeof(uint64_t), 256);
-        const size_t b2 = align_up((size_t)batch * h->cfg.n_q_heads * p.NS * (h->cfg.head_dim + cf::kP2Stride) * sizeof(uint64_t), 256);
-        const size_t b3 = align_up((size_t)h->cfg.n_q_heads * p.RS3 * batch * h->cfg.d_model * sizeof(uint64_t), 256);
-        if (b1 + b2 + b3 > h->slot_area_bytes) return CF_ESCRATCH;
+        size_t b1 = 0, b2 = 0, b3 = 0;
+        auto sizes = [&] {
+            b1 = align_up((size_t)p.KS * batch * h->nqkv * sizeof(uint64_t), 256);
+            b2 = align_up((size_t)batch * h->cfg.n_q_heads * p.NS * (h->cfg.head_dim + cf::kP2Stride) * sizeof(uint64_t), 256);
+            b3 = align_up((size_t)h->cfg.n_q_heads * p.RS3 * batch * h->cfg.d_model * sizeof(uint64_t), 256);
+            return b1 + b2 + b3 <= h->slot_area_bytes;
+        };
+        if (!sizes()) {
+            // (a slice count that does not divide the team may be the larger one)
+            rc = make_plan(h, batch, pos, &p, true);
+            if (rc != CF_OK) return rc;
+            if (!sizes()) return CF_ESCRATCH;
+        }
         p.p1 = reinterpret_cast<uint64_t *>(h->slot_area);
         p.p2 = reinterpret_cast<uint64_t *>(h->slot_area + b1);
         p.p3 = reinterpret_cast<uint64_t *>(h->slot_area + b1 + b2);

@@ -239,11 +239,11 @@ __device__ __forceinline__ float ll_sum(const Params &p, const Xbuf &x, size_t b
     }
 }
 
-// Division by a plan constant: a shift when the host found a power of two (sh >= 0).  Integer division
-// by a run-time value costs some thirty instructions, and a handful of them sat between the start of
-// the kernel and its first weight load.
-__device__ __forceinline__ int qdiv(int n, int d, int sh) { return sh >= 0 ? (n >> sh) : n / d; }
-__device__ __forceinline__ int qmod(int n, int d, int sh) { return sh >= 0 ? (n & (d - 1)) : n % d; }
+// Division by a plan constant d: m < 32 is log2 of a power of two, any other m is ceil(2^32 / d), whose high product
+// with n is n / d for n * d < 2^32.  Integer division by a run-time value costs some thirty instructions, and a
+// handful of them sat between the start of the kernel and its first weight load (0.3 us).
+__device__ __forceinline__ int qdiv(int n, uint32_t m) { return m < 32u ? (int)((uint32_t)n >> m) : (int)__umulhi((uint32_t)n, m); }
+__device__ __forceinline__ int qmod(int n, int d, uint32_t m) { return n - qdiv(n, m) * d; }
 
 // First weight column of selector `sel` for a team: sel < G query heads, G = key, G+1 = value.
 // Tokens cached for batch row b == index of the row's new token (b is uniform over the workgroup).
@@ -346,18 +346,18 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     const int tid = tid0, wv = tid >> 6, lig = tid % LPR, grp = tid / LPR;
     const int kg = (tid & 63) >> 4;                         // MF: contraction group of the lane (rows 8 kg .. 8 kg + 7 of a step)
     const int lrow = 32 * wv + 8 * kg;                      // MF: first row of the lane inside a 256-row batch
-    const int ks = qmod(member, p.KS, p.sh_ks);
-    const int sel0 = qdiv(member, p.KS, p.sh_ks), dsel = p.DSEL;
+    const int ks = qmod(member, p.KS, p.div_ks);
+    const int sel0 = qdiv(member, p.div_ks), dsel = p.DSEL;
     // slices with an even index (workgroups on the faster dies, see the workgroup mapping in the
     // kernel) are 2*RD rows longer than those with an odd index
     const int r0 = ks * p.RB + ((ks & 1) ? p.RD : 0);
     const int nrows = min(p.RB + ((ks & 1) ? -p.RD : p.RD), p.D - r0);   // > 0: the host never plans an empty slice
     const int iters = (nrows + NG - 1) / NG;
     const int nb = (iters + U - 1) / U;                     // load batches per selector
-    const int nA = sel0 < G ? qdiv(G - sel0 + dsel - 1, dsel, p.sh_dsel) : 0;
-    const int nB = sel0 < 2 ? qdiv(2 - sel0 + dsel - 1, dsel, p.sh_dsel) : 0;
-    const int nsteps = (nA + nB) * nb;
-    auto sel_of = [&](int si) { return si < nA ? sel0 + si * dsel : G + sel0 + (si - nA) * dsel; };
+    // selectors sel0, sel0 + dsel, ... of the team's G + 2 (the members past KS * DSEL have none)
+    const int nsel = sel0 < min(dsel, G + 2) ? qdiv(G + 2 - sel0 + dsel - 1, p.div_dsel) : 0;
+    const int nsteps = nsel * nb;
+    auto sel_of = [&](int si) { return sel0 + si * dsel; };
     float *xs = smem;                       // [BT][RPS]
     // MF: x as fp16 MFMA operands, [16][XS] halves (rows padded by 16 bytes: the sixteen lanes of an operand read
     // then fall into different banks), followed by a second array with the low parts of x * gamma (RMSNorm)
@@ -393,7 +393,6 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             c.sbase = blk_base(c.si);
         }
     };
-    const int nsel = nA + nB;
     Cursor cc = {0, 0, nsteps > 0 ? blk_base(0) : 0u};      // next step to consume
     Cursor lc = cc;                                         // next step to load
     constexpr int AHEAD = STACK ? P1Ahead<HD, G, BT>::n : 0;
@@ -432,8 +431,23 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     if (!(AHEAD >= 1 && primed)) load(wa, voff0);
     __builtin_amdgcn_sched_barrier(0);
     CF_STAMP(12);           // first weight batch issued
+    // Outside a stack x goes from memory to LDS in 16-byte pieces, XP of them per thread requested here (value by value it
+    // was up to seventeen 2-byte loads per thread, and as many of gamma, in front of the second weight batch, and a
+    // round trip per value for slices of more than 1024 rows).  The host makes the slices multiples of eight rows
+    // wherever that leaves no slice empty; the others are staged value by value.
+    constexpr bool XV = !STACK;
+    constexpr int XP = MF ? 4 : 2;
+    const bool xvec = XV && ((p.RB | p.RD) & 7) == 0;
+    const int P8 = p.RPS >> 3, npc = xvec ? p.B * P8 : 0;         // pieces of a row's slice, of all rows
+    const uint4 *xg4 = reinterpret_cast<const uint4 *>(p.x), *gg4 = reinterpret_cast<const uint4 *>(p.gamma ? p.gamma : p.x);
+    uint4 xp[XV ? XP : 1], gp[XV ? XP : 1];
+    auto piece_of = [&](int i, int &b, int &c) {                  // false: past the rows or past the slice
+        b = BT == 1 ? 0 : qdiv(i, p.div_p8);
+        c = i - b * P8;
+        return i < npc && 8 * c < nrows;
+    };
     constexpr int XR = BT + 1;                                    // x values per thread kept in registers
-    const bool x_in_regs = BT * p.RPS <= XR * NT;
+    const bool x_in_regs = !XV && BT * p.RPS <= XR * NT;
     // (all of them unconditional: a load inside a branch would be waited for at the branch's end)
     uint16_t xr[XR];
     u32x2 xs2[XR];                                                // layer > 0: the stamped slots of the same values
@@ -448,7 +462,14 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         xr[q] = 0;
         xs2[q] = u32x2{0u, 0u};
     }
-    if (from_slots) {
+    if constexpr (XV) {
+#pragma unroll
+        for (int q = 0; q < XP; ++q) {
+            int b, c;
+            const bool in = piece_of(tid + q * NT, b, c);
+            xp[q] = xg4[in ? ((size_t)b * p.D + r0) / 8 + c : 0];
+        }
+    } else if (from_slots) {
 #pragma unroll
         for (int q = 0; q < XR; ++q) {
             const int i = tid + q * NT, b = BT == 1 ? 0 : i / p.RPS, r = i - b * p.RPS;
@@ -471,26 +492,34 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 #pragma unroll
     for (int q = 0; q < XR; ++q) gr[q] = 0;
     if (norm) {             // (a wait behind this branch counts the loads of the path without it: nothing drains)
+        if constexpr (XV) {
 #pragma unroll
-        for (int q = 0; q < XR; ++q) {
-            const int i = tid + q * NT, b = BT == 1 ? 0 : i / p.RPS, r = i - b * p.RPS;
-            gr[q] = gsrc[xv[q] ? r0 + r : 0];
+            for (int q = 0; q < XP; ++q) {
+                int b, c;
+                const bool in = piece_of(tid + q * NT, b, c);
+                gp[q] = gg4[in ? r0 / 8 + c : 0];
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < XR; ++q) {
+                const int i = tid + q * NT, b = BT == 1 ? 0 : i / p.RPS, r = i - b * p.RPS;
+                gr[q] = gsrc[xv[q] ? r0 + r : 0];
+            }
         }
     }
     float *nrm = red + MAXI * NW * BT * HD;                       // [NW][BT] sums of squares, one per wavefront and row
-    constexpr int RG = BT < 4 ? BT : 4;                           // rows whose loads are in flight together
+    constexpr int RG = BT < 4 ? BT : (MF ? 8 : 4);                // rows whose loads are in flight together
     const int d8 = p.D >> 3;                                      // 16-byte pieces of a row
     const uint4 *x4 = reinterpret_cast<const uint4 *>(p.x);
     uint4 xq[RG][2];                                              // rows b0 .. b0 + RG - 1; needs D <= 2 * 8 * NT
-    bool ok[RG][2];
     auto load_rows = [&](int b0) {
 #pragma unroll
         for (int r = 0; r < RG; ++r)
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int c = tid + k * NT;
-                ok[r][k] = norm && b0 + r < p.B && c < d8;
-                xq[r][k] = x4[ok[r][k] ? (size_t)(b0 + r) * d8 + c : 0];
+                if (k == 0 || d8 > NT)                            // (uniform)
+                    xq[r][k] = x4[b0 + r < p.B && c < d8 ? (size_t)(b0 + r) * d8 + c : 0];
             }
     };
     auto square_rows = [&](int b0) {
@@ -504,7 +533,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
                 float t = 0.f;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) t = fmaf(f[j], f[j], t);
-                ss += ok[r][k] ? t : 0.f;
+                ss += (b0 + r < p.B && tid + k * NT < d8) ? t : 0.f;
             }
             ss = wave_sum(ss);
             if ((tid & 63) == 0 && b0 + r < BT) nrm[wv * BT + b0 + r] = ss;
@@ -513,11 +542,10 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 #pragma unroll
     for (int r = 0; r < RG; ++r)
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            xq[r][k] = uint4{0u, 0u, 0u, 0u};
-            ok[r][k] = false;
-        }
-    if (BT <= 4 && norm) load_rows(0);
+        for (int k = 0; k < 2; ++k) xq[r][k] = uint4{0u, 0u, 0u, 0u};
+    // (in front of the second weight batch: behind it the squares would wait for that batch; 16-row tile, 4 rows of
+    // 4096: x staged at 10.3 us with the loads behind the batch)
+    if (norm) load_rows(0);
     // for the RoPE tables, below: the frequency and the position of every table entry of this thread
     constexpr int NE = RopeRows<HD, BT>::NE;
     const bool own_pos = kLayer && p.row_pos != nullptr;
@@ -532,11 +560,6 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     if (!(AHEAD >= 2 && primed)) load(wb, voff0);
     __builtin_amdgcn_sched_barrier(0);
     CF_STAMP(21);           // second weight batch issued
-    if (BT > 4 && norm)     // large batches: four rows at a time, each group waits for its loads
-        for (int b0 = 0; b0 < p.B; b0 += RG) {
-            load_rows(b0);
-            square_rows(b0);
-        }
     // Launch number: every workgroup keeps, in a line of its own, the number of launches it has
     // completed; all workgroups of a launch hold the same count, so count + 1 stamps this launch
     // without any shared counter.  (One counter for all was read by 256 workgroups at once and
@@ -583,7 +606,42 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             xs[i] = v;
         }
     };
-    if (x_in_regs) {
+    if (XV && xvec) {
+        // (rows past the batch are left as they are: what they give lands in rows of the product nobody reads)
+        auto stage_piece = [&](int b, int c, const uint4 &xw, const uint4 &gw, bool in) {
+            const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+            h8 hi = in ? __builtin_bit_cast(h8, xw) : zero, lo = zero;
+            float f[8], g[8];
+            unpack8(hi, f);
+            if (norm) {
+                unpack8(__builtin_bit_cast(h8, gw), g);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) f[j] = in ? f[j] * g[j] : 0.f;
+            }
+            if constexpr (MF) {
+                if (norm) {
+                    split_hi_lo(f, hi, lo);
+                    *reinterpret_cast<h8 *>(xl + b * XS + 8 * c) = lo;
+                }
+                *reinterpret_cast<h8 *>(xh + b * XS + 8 * c) = hi;
+            } else {
+                float *dst = xs + b * p.RPS + 8 * c;
+                *reinterpret_cast<f32x4 *>(dst) = f32x4{f[0], f[1], f[2], f[3]};
+                *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{f[4], f[5], f[6], f[7]};
+            }
+        };
+#pragma unroll
+        for (int q = 0; q < XP; ++q) {
+            int b, c;
+            const bool in = piece_of(tid + q * NT, b, c);
+            if (tid + q * NT < npc) stage_piece(b, c, xp[q], norm ? gp[q] : xp[q], in);
+        }
+        for (int i = tid + XP * NT; i < npc; i += NT) {           // (batch 16: slices of more than 1024 rows)
+            int b, c;
+            const bool in = piece_of(i, b, c);
+            stage_piece(b, c, xg4[in ? ((size_t)b * p.D + r0) / 8 + c : 0], gg4[in ? r0 / 8 + c : 0], in);
+        }
+    } else if (x_in_regs) {
 #pragma unroll
         for (int q = 0; q < XR; ++q) {
             const int i = tid + q * NT;
@@ -609,7 +667,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             stage(i, in ? xval * (norm ? h2f(gsrc[r0 + r]) : 1.f) : 0.f);
         }
     }
-    if constexpr (MF) {
+    if (MF && !xvec) {
         // columns RPS .. XS-1 of every row (an operand read may reach up to seven columns past the slice)
         const int nz = XS - p.RPS;
         for (int e = tid; e < 16 * nz; e += NT) {
@@ -618,7 +676,13 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             xl[b * XS + r] = (_Float16)0.f;
         }
     }
-    if (BT <= 4 && norm) square_rows(0);
+    if (norm) {
+        square_rows(0);
+        for (int b0 = RG; b0 < p.B; b0 += RG) {       // large batches: the other rows
+            load_rows(b0);
+            square_rows(b0);
+        }
+    }
     // cos / sin of this position while the first weights are still on their way (the same for every layer of a stack)
 #pragma unroll
     for (int k = 0; k < NE; ++k) {
@@ -1753,8 +1817,8 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // once in front of the loop over the layers and be kept in registers across all phases)
     int tl = threadIdx.x, w = blockIdx.x;
     if (STACK) asm volatile("" : "+v"(tl), "+s"(w));
-    const int team = p.pairmap ? qmod(w >> 1, p.nkv, p.sh_nkv) : qmod(w, p.nkv, p.sh_nkv);
-    const int member = p.pairmap ? qdiv(w >> 1, p.nkv, p.sh_nkv) * 2 + (w & 1) : qdiv(w, p.nkv, p.sh_nkv);
+    const int team = p.pairmap ? qmod(w >> 1, p.nkv, p.div_nkv) : qmod(w, p.nkv, p.div_nkv);
+    const int member = p.pairmap ? qdiv(w >> 1, p.div_nkv) * 2 + (w & 1) : qdiv(w, p.div_nkv);
     // weights and caches of this layer (layer 0, and the only layer of a plain call: those of the parameters);
     // a reference into the argument block either way, so that each pointer is fetched where it is used
     static_assert(offsetof(Params, wo) == offsetof(Params, wqkv) + 8 && offsetof(Params, kc) == offsetof(Params, wqkv) + 16 &&
@@ -1762,9 +1826,9 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     const LayerPtrs &lp = (STACK && layer > 0) ? tab[layer] : *reinterpret_cast<const LayerPtrs *>(&p.wqkv);
     KvBuf<HD, G> kv;
     OutTile<HD> tile;
-    const int b_first = member < n2 ? qdiv(member, p.NS, p.sh_ns) : 0;     // batch row of the first attention item
+    const int b_first = member < n2 ? qdiv(member, p.div_ns) : 0;     // batch row of the first attention item
     const int pos_first = row_pos(p, b_first);
-    const int s_first = member < n2 ? qmod(member, p.NS, p.sh_ns) : 0;
+    const int s_first = member < n2 ? qmod(member, p.NS, p.div_ns) : 0;
     // (with positions per row the stream is set up only where phase 1 first needs it: the position comes from
     // memory, and waiting for it here would hold up the first weight loads)
     const bool own_pos = kLayer && p.row_pos != nullptr;
@@ -1783,7 +1847,7 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // a first look at the team's q partials (in a stack only for one batch row and attention on the vector ALU: no
     // registers are left for the sixteen pairs there, they would be spilled as they arrive)
     if (member < n2 && !(STACK && (AttnMfma<HD, G>::on || BT > 1)))
-        eq.issue<HD, G>(p, tl, team, qdiv(member, p.NS, p.sh_ns));
+        eq.issue<HD, G>(p, tl, team, qdiv(member, p.div_ns));
     st2.prefetch(kv, 1);
     CF_STAMP(1);
     // ---- phase 2 (attention); the last item already starts the W_o stream of phase 3
@@ -1805,14 +1869,14 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     for (int it = member; it < n2; it += p.TS) {
         const bool first = (it == member), final_item = (it + p.TS >= n2);
         if (!first) {
-            const int b_it = qdiv(it, p.NS, p.sh_ns);
-            st2 = P2Stream<HD, G>(p, lp, tl, team, b_it, qmod(it, p.NS, p.sh_ns), row_pos(p, b_it));
+            const int b_it = qdiv(it, p.div_ns);
+            st2 = P2Stream<HD, G>(p, lp, tl, team, b_it, qmod(it, p.NS, p.div_ns), row_pos(p, b_it));
             st2.prefetch(kv, 0);
             st2.prefetch(kv, 1);
         }
         // stage 1: first half of the output-projection tile, stage 2: second half
-        p2_item<HD, G>(p, lp, tl, team, qdiv(it, p.NS, p.sh_ns), qmod(it, p.NS, p.sh_ns), stamp, first, st2, kv, eq, smem,
-                       s_rope + (kLayer && p.row_pos ? qdiv(it, p.NS, p.sh_ns) * HD : 0), [&](int stage) {
+        p2_item<HD, G>(p, lp, tl, team, qdiv(it, p.div_ns), qmod(it, p.NS, p.div_ns), stamp, first, st2, kv, eq, smem,
+                       s_rope + (kLayer && p.row_pos ? qdiv(it, p.div_ns) * HD : 0), [&](int stage) {
             if (final_item) p3_prefetch(stage - 1);
         });
     }

@@ -61,11 +61,11 @@ struct Params {
     int RB, RD;            // rows of a split are RB + RD (even split index) or RB - RD (odd)
     int TD;                // attention: tokens of a split are TPS + TD (even split index) or TPS - TD (odd)
     int DSEL;              // TS / KS: selectors advance by this much from one step of a member to the next
-    int sh_nkv, sh_ks, sh_dsel, sh_ns;   // log2 of nkv, KS, DSEL, NS where that is a power of two, else -1
+    uint32_t div_nkv, div_ks, div_dsel, div_ns;   // for divisions by nkv, KS, DSEL, NS: log2 of a power of two, else ceil(2^32 / d)
     int pairmap;           // workgroup -> (team, member) keeps the parity of the workgroup id in the member id
     int NS, TPS;           // attention: splits of the cached sequence, tokens per split
     int NC3, CW3, RS3;     // output projection: column blocks, columns per block, row splits per head
-    int reserved0;
+    uint32_t div_p8;       // the same for RPS / 8
     int flags;             // kFlagPacked, kFlagResidual
     float qk_scale_log2e;  // log2(e)/sqrt(head_dim)
     float eps;             // RMSNorm: added to the mean square

@@ -238,3 +238,19 @@ def test_row_positions_outside_the_bound_are_clamped():
     ref = orc.decode_rows(inp["x"], None, 0.0, inp["w_qkv"], inp["w_o"], inp["k_cache"], inp["v_cache"], [40, 0],
                           shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.rope_base)
     check_rows(res, ref, inp, [40, 0], "clamped")
+
+
+# Slices that do not come out even, with the row norms of every batch tile: rows of more than 4096 values (two loads per
+# thread), batches that take a second group of rows (more than eight), slices staged in pieces of eight values.
+@pytest.mark.parametrize("d_model,nq,nkv,hd,batch", [(1000, 32, 8, 128, 1), (1000, 32, 8, 128, 3), (1032, 8, 8, 128, 9),
+                                                     (1032, 8, 8, 128, 16), (4104, 8, 4, 128, 10), (1288, 14, 7, 64, 2),
+                                                     (1288, 14, 7, 64, 16), (8192, 4, 4, 128, 1)])
+def test_layer_with_uneven_slices(d_model, nq, nkv, hd, batch):
+    shape, kv_len = cf_inputs.BlockShape("s", d_model, nq, nkv, hd, 10000.0, 60), 60
+    _log("layer d_model %d heads %d/%d x %d batch %d" % (d_model, nq, nkv, hd, batch))
+    inp = cf_inputs.make_inputs(shape, seed=29, batch=batch, kv_len=kv_len)
+    scale = np.array([0.25 * (b + 1) for b in range(batch)], dtype=np.float32)[:, None]
+    inp["x"] = (inp["x"].astype(np.float32) * scale).astype(np.float16)
+    gamma = gamma_for(shape, 9)
+    res = run_layer(shape, batch, inp, kv_len, gamma, 1e-5, True, True)
+    check(res, reference(shape, inp, kv_len, gamma, 1e-5, True), inp, kv_len, "uneven")

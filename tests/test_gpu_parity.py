@@ -360,3 +360,23 @@ def test_pack_weights_gives_the_documented_layout(d_model, nq, nkv, hd):
             want = w_o[i * hd:(i + 1) * hd, 512 * c:512 * c + cols].view(np.uint16)
             assert np.array_equal(got_o[i, c, :, :cols], want), (i, c)
             assert not got_o[i, c, :, cols:].any(), "columns past d_model are not zero"
+
+
+# Where the split of the projection or of the output projection does not come out even: slice counts that do not divide
+# the team (5 slices x 6 selectors over 32 members), slices of 8 rows, one slice, a last slice of 8 rows, more selector
+# groups than selectors, column blocks that are no power of two, a last block of 8 columns, blocks of two chunks.
+@pytest.mark.parametrize("d_model,nq,nkv,hd,batch,kv_len", [
+    (1000, 32, 8, 128, 1, 130), (1000, 32, 8, 128, 2, 130), (1000, 32, 8, 128, 5, 130), (1288, 7, 7, 64, 3, 100),
+    (1544, 14, 7, 64, 16, 61), (2056, 8, 4, 128, 16, 40), (1032, 24, 3, 128, 9, 70), (520, 40, 20, 64, 1, 33),
+    (64, 8, 8, 64, 4, 5), (16, 4, 4, 64, 1, 3), (3080, 32, 32, 64, 2, 50), (8200, 8, 8, 64, 1, 20), (2568, 62, 31, 128, 4, 17)])
+def test_uneven_splits_of_the_projections(d_model, nq, nkv, hd, batch, kv_len):
+    shape = cf_inputs.BlockShape("s", d_model, nq, nkv, hd, 10000.0, kv_len)
+    _log("d_model %d heads %d/%d x %d batch %d" % (d_model, nq, nkv, hd, batch))
+    inp = cf_inputs.make_inputs(shape, seed=d_model + batch, batch=batch, kv_len=kv_len)
+    ref = oracle(inp, shape, kv_len)
+    for packed in (False, True):
+        r = Runner(shape, batch, inp["max_seq"])
+        res = r.run(inp, kv_len, out_fill=float("nan"), packed=packed)
+        _log("plan %s" % r.blk.plan())
+        check(res, ref, inp, kv_len, "packed" if packed else "rows")
+        r.blk.close()
