@@ -165,15 +165,19 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
             p->TD = 0;
         }
     }
-    // output projection: G heads x NC3 column blocks x RS3 row splits per team
+    // output projection: G heads x NC3 column blocks x RS3 row splits per team.  A member walks its items chunk by chunk
+    // (512 columns); the first chunk is on its way since the attention, every further one costs its bytes and a load
+    // latency, about that of 96 rows (2.4 us a chunk of 8 rows: 2056 columns as 2 blocks of 3 chunks x 8 row splits took
+    // 27.3 us in all at batch 3, as 5 blocks of one chunk x 2 row splits 23.4 us).
     {
         const int nch = h->nch;
         int best_nc = 0, best_rs = 0;
         double best_cost = 0;
         for (int rs = 1; rs <= 8 && hd / rs >= cf::kWaves; rs *= 2) {
-            for (int nc = 1; nc <= nch; nc *= 2) {
-                const int cw = ceil_div(nch, nc) * cf::kOutChunk;
-                const double cost = (double)ceil_div(G * nc * rs, TS) * (hd / rs) * cw;
+            for (int nc = 1; nc <= nch; ++nc) {
+                const int cw = ceil_div(nch, nc), blocks = ceil_div(nch, cw);          // chunks of a block, blocks
+                const double chunks = (double)ceil_div(G * blocks * rs, TS) * cw;
+                const double cost = chunks * (hd / rs) + (chunks - 1) * 96;
                 if (!best_nc || cost < best_cost * 0.999) {
                     best_nc = nc;
                     best_rs = rs;
