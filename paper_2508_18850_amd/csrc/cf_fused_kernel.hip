@@ -518,13 +518,14 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int c = tid + k * NT;
-                if (k == 0 || d8 > NT)                            // (uniform)
-                    xq[r][k] = x4[b0 + r < p.B && c < d8 ? (size_t)(b0 + r) * d8 + c : 0];
+                if (b0 + r < p.B && (k == 0 || d8 > NT))          // (uniform)
+                    xq[r][k] = x4[c < d8 ? (size_t)(b0 + r) * d8 + c : 0];
             }
     };
     auto square_rows = [&](int b0) {
 #pragma unroll
         for (int r = 0; r < RG; ++r) {
+            if (b0 + r >= p.B) break;                             // (uniform)
             float ss = 0.f;
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
@@ -533,10 +534,10 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
                 float t = 0.f;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) t = fmaf(f[j], f[j], t);
-                ss += (b0 + r < p.B && tid + k * NT < d8) ? t : 0.f;
+                ss += tid + k * NT < d8 ? t : 0.f;
             }
             ss = wave_sum(ss);
-            if ((tid & 63) == 0 && b0 + r < BT) nrm[wv * BT + b0 + r] = ss;
+            if ((tid & 63) == 0) nrm[wv * BT + b0 + r] = ss;
         }
     };
 #pragma unroll
