@@ -888,7 +888,7 @@ struct cf_mla_s {
     char *ws = nullptr;
     size_t ws_bytes = 0;
     uint64_t *slots = nullptr;
-    float *zdbg = nullptr, *qdbg = nullptr;
+    float *zdbg = nullptr, *qdbg = nullptr, *zpart = nullptr;
     unsigned long long *counters = nullptr;
     uint32_t *err = nullptr;
     size_t x1 = 0, xq = 0, xkv = 0, x3 = 0, xs = 0, x5 = 0, x6 = 0, xqn = 0, xa = 0;
@@ -966,8 +966,8 @@ int cf_mla_create(const cf_mla_config *cfg, cf_mla *out)
     t->xs = t->x3 + items * HT * kPart;
     t->x5 = t->xs + B * c.n_heads;
     t->x6 = t->x5 + B * c.n_heads * TS * c.v_head_dim;
-    size_t hfirst[5];
-    const size_t hslots = cf::mla::heads_layout(c, c.max_batch < cf::mla::kHeadsMaxBatch ? c.max_batch : cf::mla::kHeadsMaxBatch, hfirst);
+    size_t hfirst[3];
+    const size_t hslots = cf::mla::heads_layout(c, hfirst);
     t->xqn = t->x6 + B * c.n_heads * c.d_model;                  // [B][heads][128] summed q_nope (16-row tile)
     t->xa = t->xqn + B * c.n_heads * 128;                         // [B][heads][128] summed a_head (16-row tile)
     const size_t rslots = t->xa + B * c.n_heads * 128;
@@ -976,7 +976,8 @@ int cf_mla_create(const cf_mla_config *cfg, cf_mla *out)
     const size_t head_al = (head + 255) / 256 * 256;
     const size_t slot_bytes = (nslots * sizeof(uint64_t) + 255) / 256 * 256;
     const size_t zbytes = (B * c.n_heads * L * sizeof(float) + 255) / 256 * 256;
-    t->ws_bytes = head_al + slot_bytes + zbytes + B * c.n_heads * LR * sizeof(float);
+    const size_t qbytes = (B * c.n_heads * LR * sizeof(float) + 255) / 256 * 256;
+    t->ws_bytes = head_al + slot_bytes + zbytes + qbytes + (size_t)c.n_heads * TS * (2 + L) * sizeof(float);
     if (nslots * sizeof(uint64_t) > 0xfffffff0ull) {
         delete t;
         return CF_EUNSUPPORTED;
@@ -994,6 +995,7 @@ int cf_mla_create(const cf_mla_config *cfg, cf_mla *out)
     t->slots = reinterpret_cast<uint64_t *>(t->ws + head_al);
     t->zdbg = reinterpret_cast<float *>(t->ws + head_al + slot_bytes);
     t->qdbg = reinterpret_cast<float *>(t->ws + head_al + slot_bytes + zbytes);
+    t->zpart = reinterpret_cast<float *>(t->ws + head_al + slot_bytes + zbytes + qbytes);
     *out = t;
     return CF_OK;
 }
@@ -1015,8 +1017,8 @@ int cf_mla_decode(cf_mla t, int32_t batch, const void *x, const void *W_q, const
     for (const void *p : ptrs)
         if (reinterpret_cast<uintptr_t>(p) & 15u) return CF_EINVAL;
     const cf_mla_config &c = t->cfg;
-    if (batch <= kHeadsBatch && t->max_splits == 0) {
-        // one or two batch rows: the head-team kernel (every head scans the cached rows itself; see cf_mla_heads.hip)
+    if (batch <= kHeadsBatch && t->max_splits == 0 && cf::mla::heads_fits(c)) {
+        // the head-team kernel (every head scans the cached rows itself; see cf_mla_heads.hip)
         cf::mla::HeadsArgs h;
         std::memset(&h, 0, sizeof h);
         h.x = static_cast<const uint16_t *>(x);
@@ -1027,15 +1029,13 @@ int cf_mla_decode(cf_mla t, int32_t batch, const void *x, const void *W_q, const
         h.wo = static_cast<const uint16_t *>(W_o);
         h.cache = static_cast<uint16_t *>(kv_cache);
         h.out = static_cast<uint16_t *>(out);
-        h.qdbg = t->qdbg, h.zdbg = t->zdbg;
+        h.qdbg = t->qdbg, h.zpart = t->zpart;
         h.slots = t->slots, h.counters = t->counters, h.err = t->err;
-        size_t first[5];
-        (void)cf::mla::heads_layout(c, batch, first);
-        h.x1 = first[0], h.x2 = first[1], h.x3 = first[2], h.x5 = first[3], h.x6 = first[4];
-        h.D = c.d_model, h.nh = c.n_heads, h.n = c.nope_dim, h.v = c.v_head_dim, h.B = batch, h.pos = pos;
-        h.max_seq = c.max_seq, h.W = t->W;
-        h.cq = (c.n_heads * (c.nope_dim + R) / 8 + 15) / 16;
-        h.ckv = (LR / 8 + 15) / 16;
+        size_t first[3];
+        (void)cf::mla::heads_layout(c, first);
+        h.x1 = first[0], h.x3 = first[1], h.x6 = first[2];
+        h.D = c.d_model, h.nh = c.n_heads, h.n = c.nope_dim, h.v = c.v_head_dim, h.pos = pos, h.W = t->W;
+        cf::mla::heads_slices(c, &h.ksa, &h.rows);
         h.scale_log2e = 1.4426950408889634f / std::sqrt((float)(c.nope_dim + R));
         h.log2_base = std::log2((double)c.rope_base);
         h.spin_ticks = t->spin_ticks;
@@ -1113,7 +1113,27 @@ int cf_mla_debug_export(cf_mla t, int32_t what, void *host_dst, size_t bytes, vo
     const size_t per = what == 1 ? R : L;
     if (bytes != B * nh * per * sizeof(float)) return CF_EINVAL;
     hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
-    if (e == hipSuccess && what == 2) e = hipMemcpy(host_dst, t->zdbg, bytes, hipMemcpyDeviceToHost);
+    if (e == hipSuccess && what == 2 && t->last_heads) {
+        // the head-team kernel merges behind W_Down: z is put together here from the members' partials
+        std::vector<float> part(nh * TS * (2 + L));
+        e = hipMemcpy(part.data(), t->zpart, part.size() * sizeof(float), hipMemcpyDeviceToHost);
+        float *dst = static_cast<float *>(host_dst);
+        for (size_t h = 0; e == hipSuccess && h < nh; ++h) {
+            const float *p = part.data() + h * TS * (2 + L);
+            float M = p[0];
+            for (int s = 1; s < TS; ++s) M = std::fmax(M, p[s * (2 + L)]);
+            double ls = 0.0;
+            std::vector<double> z(L, 0.0);
+            for (int s = 0; s < TS; ++s) {
+                const double f = std::exp2((double)p[s * (2 + L)] - M);
+                ls += f * p[s * (2 + L) + 1];
+                for (int d = 0; d < L; ++d) z[d] += f * p[s * (2 + L) + 2 + d];
+            }
+            for (int d = 0; d < L; ++d) dst[h * L + d] = (float)(z[d] / ls);
+        }
+    } else if (e == hipSuccess && what == 2) {
+        e = hipMemcpy(host_dst, t->zdbg, bytes, hipMemcpyDeviceToHost);
+    }
     if (e == hipSuccess && what != 2 && t->last_heads) {
         std::vector<float> q(B * nh * LR);
         e = hipMemcpy(q.data(), t->qdbg, q.size() * sizeof(float), hipMemcpyDeviceToHost);

@@ -11,25 +11,28 @@
 namespace cf {
 namespace mla {
 
-constexpr int kHeadsMaxBatch = 4;   // batch rows the head-team kernel's register tiles hold
-
 struct HeadsArgs {
     const uint16_t *x, *wq, *wkv, *wup, *wdown, *wo;
     uint16_t *cache, *out;
-    float *qdbg, *zdbg;             // [B][nh][L + R] query (latent | rotated rotary part), [B][nh][L] z: for cf_mla_debug_export
+    float *qdbg, *zpart;            // for cf_mla_debug_export: [nh][L + R] query (latent | rotated rotary part); [nh][16][2 + L]
+                                    // the members' attention partials (maximum, sum, latent vector relative to the maximum)
     uint64_t *slots;
     unsigned long long *counters;
     uint32_t *err;
-    size_t x1, x2, x3, x5, x6;      // first slot of each exchange area
-    int D, nh, n, v, B, pos, max_seq, W;
-    int cq, ckv;                    // 16-byte pieces (8 columns) of W_Q / W_KV per column block
+    size_t x1, x3, x6;              // first slot of each exchange area
+    int D, nh, n, v, pos, W;
+    int ksa, rows;                  // row slices of the projections, rows per slice (a multiple of eight)
     float scale_log2e;              // log2(e) / sqrt(nope_dim + rope_dim)
     double log2_base;
     long long spin_ticks;
 };
 
-// first slot of the five exchange areas for batch B; returns the number of slots in all
-size_t heads_layout(const cf_mla_config &c, int B, size_t (&first)[5]);
+// first slot of the three exchange areas; returns the number of slots in all
+size_t heads_layout(const cf_mla_config &c, size_t (&first)[3]);
+// HeadsArgs::ksa and ::rows
+void heads_slices(const cf_mla_config &c, int *ksa, int *rows);
+// whether the projections' work items fit the workgroups (they do for every shape cf_mla_create takes)
+bool heads_fits(const cf_mla_config &c);
 // sets the kernel's LDS attribute; false if no workgroup fits a compute unit
 bool heads_prepare();
 // enqueues the kernel (a.W workgroups); returns the hipError_t of the launch

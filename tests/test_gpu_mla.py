@@ -228,3 +228,15 @@ def test_unsupported_shapes_and_bad_arguments_are_refused():
     with pytest.raises(CfError) as e:
         MlaBlock(2048, 16, 128, 64, 512, 128, 17, 64, 10000.0)         # batch above the 16-row tile
     assert e.value.code == -2
+
+
+# The head-team kernel (batch 1): row slices of the projections (1 to 4), heads on one die (8, 16) and spread (3, 11), the
+# smallest blocks, ragged last tiles of columns, members without cached rows, a short and a long last batch of rows.
+@pytest.mark.parametrize("heads,d_model,nope,v", [(1, 32, 8, 8), (3, 384, 128, 40), (8, 1024, 72, 128), (11, 1216, 104, 24),
+                                                  (16, 2048, 8, 128), (16, 96, 128, 8)])
+@pytest.mark.parametrize("kv_len", [0, 1, 17, 2049, 5000])
+def test_head_team_kernel_edges(heads, d_model, nope, v, kv_len):
+    shape = cf_inputs.MlaShape("s", d_model, heads, nope, 64, 512, v, 10000.0, 0)
+    _log("heads %d d_model %d nope %d v %d L %d" % (heads, d_model, nope, v, kv_len))
+    inp = cf_inputs.make_mla_inputs(shape, seed=heads + kv_len, batch=1, kv_len=kv_len)
+    check(run(shape, inp, kv_len), oracle(shape, inp, kv_len), inp, kv_len, "heads %d L %d" % (heads, kv_len))
