@@ -2,21 +2,30 @@
 // kernel for gfx950, behind the C ABI (cf_mla_* in include/cfdecode.h).
 //
 // Alg. 4 runs one cluster per head and moves data between its blocks with three ClusterGathers and three
-// ClusterReduces.  Here 16 co-resident workgroups per head share the weights of that head, every hand-over is one
-// hop through stamped {value, stamp} slots in global memory (cf_team_device.h), five hops in all, and every weight
-// matrix is read in contiguous rows:
+// ClusterReduces.  This kernel (batch 2 to 16; batch 1: cf_mla_heads.hip) has 16 co-resident workgroups per head and
+// five hand-overs through global memory; all products run on MFMA tiles with the batch (or the heads) as the 16-row edge:
 //
-//   A  projections        [q | kv_new] = x [W_Q | W_KV]           16 row slices x 16 column blocks, partial sums
-//   B  up-projection      q_lat_i = q_nope_i W_Up[i]              member j: 1/16 of the kv_lora_rank columns; the same
-//                         workgroups finish q_rope_i and the new cache row (sum of the partials, RoPE, append)
-//   C  attention          unit of work = (batch row, token range), NOT the head: all heads share every cached row
-//                         (one latent "head": MQA), so the scores and the weighted sums of the 16 heads against a tile
-//                         of 128 rows are two dense products on MFMA tiles; a row is read from HBM once for all heads
-//   D  merge + down-proj. (head i, member j): merges 1/16 of the latent dimensions of the range partials (Alg. 4's
-//                         online-softmax reduction) and multiplies them by the same rows of W_Down[i]
-//   E1 output projection  rows of W_O of head i, 1/16 of the output columns per member: a partial of out per head
+//   A  projections        [q | kv_new] = x [W_Q | W_KV]           64 columns x up to 4 row slices per workgroup
+//   B  up-projection      q_lat_i = q_nope_i W_Up[i]              (head i, member j): 1/16 of the kv_lora_rank columns, and
+//                         two of the rotary pairs of q_i
+//   C  attention          unit of work = (batch row, token range, group of heads), NOT the head: all heads share every
+//                         cached row (one latent "head": MQA), so the scores and the weighted sums of the heads against
+//                         a tile of 64 rows are two dense products; a row is read from HBM once for all heads.  The
+//                         first range also appends the new row and counts the new token
+//   D  merge              (head i, member j): 1/16 of the latent dimensions over the ranges (Alg. 4's online-softmax
+//                         reduction)
+//   E1 down- and output   every member: a_i = z_i W_Down[i], redundantly (131 KB, from the die's L2, for one hand-over
+//      projection         less), then rows of W_O of head i, 1/16 of the output columns: a partial of out per head
 //   E2 sum over heads     every workgroup: 1/W of the output columns (the paper's atomicAdd)
 //
+// Two kinds of hand-over.  The last one, few values per reader, goes through stamped {value, stamp} slots
+// (cf_team_device.h): one trip.  The others move 32 - 64 KB per reader, where 8 bytes per value and polling every one of
+// them is what takes the time (74 KB of query slots took 8 us): the values are written as they are, 4 bytes each, with
+// write-through stores; a workgroup waits until its stores have been acknowledged, then writes one flag word, the
+// stamp of the launch; a reader polls the flags of its sources and fetches the values with 16-byte loads that, like the
+// polls, do not look into its caches.
+//
+// @@TIMES@@
 // Each stage requests its weights (or cached rows) before it waits for its input.  All waits are bounded
 // (CF_ETIMEOUT), all workgroups have to be resident at once.
 #include "cf_mfma_device.h"
@@ -37,23 +46,26 @@ using cf::team::pair_t;
 constexpr int NT = 512;             // threads per workgroup
 constexpr int NW = NT / 64;
 constexpr int TS = 16;              // workgroups per head (team)
-constexpr int KS = 16;              // row slices of the projections
 constexpr int L = 512;              // kv_lora_rank the lane mapping is written for
 constexpr int R = 64;               // rope_dim
 constexpr int LR = L + R;
-constexpr int HT = 16;              // heads of one MFMA tile: the most the kernel takes
+constexpr int LJ = L / TS;          // latent dimensions per member: 32
+constexpr int HT = 16;              // heads (batch rows) of one MFMA tile: the most the kernel takes
 constexpr int MAXBATCH = 16;
-constexpr int MAXCOLS = 256;        // projection columns per column block
+constexpr int kMaxSlices = 4;       // row slices of the projections
 constexpr int kCounterStride = 16;
 constexpr int kTile = 64;           // cached rows per attention tile of a workgroup (held in LDS)
 constexpr int KSTR = LR + 8;        // row stride (fp16 values) of the tile in LDS
 constexpr int kSteps = LR / 32;     // MFMA steps of a score product (contraction over 576 dimensions)
 constexpr int kQops = kSteps * 64;  // 16-byte query operands (one per step and lane)
-constexpr int PS = kTile + 8;       // row stride (fp16 values) of the probabilities in LDS
-constexpr int QS = LR + 8;          // row stride (floats) of the fp32 query in LDS
-constexpr int kPart = 2 + L;        // slots of an attention partial per head: m, l, acc[L]
+constexpr int SSTR = kTile + 4;     // row stride (floats) of the scores in LDS
+constexpr int AS = 132;             // row stride (floats) of a_i in LDS
 constexpr int kMaxSplits = 32;      // token ranges per batch row at most
-constexpr size_t kLdsFloats = 29440;    // 115 KiB: the largest stage (C: query operands, a tile of rows, the rest)
+// LDS, floats.  A: [NW][16][64]; B: [4][16][LJ]; C: query operands, new row, scores, maxima / sums, tile (later the second
+// half's accumulators); E1: a_i, [NW][16][128]; E2: [4][128]
+constexpr int kLdsC = 2 * kQops * 4 + LR + HT + 2 * HT * SSTR + 4 * HT, kLdsTile = kTile * KSTR / 2;
+constexpr size_t kLdsFloats = kLdsC + (kLdsTile > HT * L ? kLdsTile : HT * L);
+static_assert(kLdsFloats >= 16 * AS + NW * 16 * 128 && kLdsFloats * 4 <= 160 * 1024, "largest stage");
 constexpr float kNegBig = -1.0e30f;
 constexpr int kHeadsBatch = 1;      // up to this batch cf_mla_decode runs the head-team kernel (measured cross-over)
 
@@ -62,87 +74,41 @@ using cf::mfma::h8;
 using cf::mfma::mfma16;
 using cf::mfma::transpose8;
 using cf::mfma::u32x4;
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 
 struct MlaArgs {
     const uint16_t *x, *wq, *wkv, *wup, *wdown, *wo;
     uint16_t *cache, *out;
     float *zdbg;                    // [B][nh][L]: the normalised latent vectors z of the call (for cf_mla_debug_export)
-    uint64_t *slots;
+    uint64_t *slots;                // stamped slots of the last hand-over: [nh][B][D]
+    float *data;                    // the other hand-overs' values, 4 bytes each
+    uint32_t *flags;                // their flags: [4][256]
     unsigned long long *counters;
     uint32_t *err;
-    size_t x1, xq, xkv, x3, xs, x5, x6, xqn, xa;     // first slot of each exchange area
+    size_t x1, xq, x3, xml, xz;     // first value of each exchange area: [ksa][B][CQ], [B][nh][LR], [item][HT][L],
+                                    // [item][HT][2], [B][nh][L]
     int D, nh, n, v, B, pos, max_seq, W;
     int NS, tps, HG;                // token ranges per batch row, cached rows per range, heads per attention item
-    int cq, ckv;                    // 16-byte pieces (8 columns) of W_Q / W_KV per column block
+    int ksa, rows;                  // row slices of the projections, rows per slice
     float scale_log2e;              // log2(e) / sqrt(nope_dim + rope_dim)
     double log2_base;
     long long spin_ticks;
 };
 
-__device__ __forceinline__ float h2f(uint16_t b) { return (float)__builtin_bit_cast(_Float16, b); }
 __device__ __forceinline__ uint16_t f2h(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }
 
-// Sums of NV sets of n <= 16 stamped values each: set v is idx[v], idx[v] + stride, ... (added in that order).
-// All NV * 16 polls are in flight together: one round trip when the values are there.
-template <int NV>
-__device__ __forceinline__ void take_sums(const Exchange &x, __amdgpu_buffer_rsrc_t r, const size_t (&idx)[NV], size_t stride,
-                                          int n, float (&out)[NV])
-{
-    constexpr int NP = 16;
-    pair_t q[NV][NP];
-    long long t0 = 0;
-    for (;;) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-#pragma unroll
-            for (int k = 0; k < NP; ++k) q[v][k] = cf::team::peek(r, idx[v] + (size_t)min(k, n - 1) * stride);
-        __builtin_amdgcn_sched_barrier(0);
-        bool ok = true;
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-#pragma unroll
-            for (int k = 0; k < NP; ++k) ok &= q[v][k].y == x.stamp;
-        if (ok || cf::team::gave_up(x, t0)) break;
-    }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        float s = 0.f;
-#pragma unroll
-        for (int k = 0; k < NP; ++k)
-            if (k < n) s += __builtin_bit_cast(float, q[v][k].x);
-        out[v] = s;
-    }
-}
-
-// All threads: fetch cnt <= 4 * NT stamped values into LDS, value i (at slot_of(i)) to dst[i]; all polls of a thread are
-// in flight together (one round trip).  No barrier inside.
-template <class SlotOf>
-__device__ __forceinline__ void fetch4(const Exchange &x, __amdgpu_buffer_rsrc_t r, int cnt, float *dst, SlotOf &&slot_of)
-{
-    pair_t q[4];
-    long long t0 = 0;
-    for (;;) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            q[k] = pair_t{0u, x.stamp};
-            if (NT * k < cnt) q[k] = cf::team::peek(r, slot_of(min((int)threadIdx.x + NT * k, cnt - 1)));     // (uniform)
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        bool ok = true;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) ok &= q[k].y == x.stamp;
-        if (ok || cf::team::gave_up(x, t0)) break;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if ((int)threadIdx.x + NT * k < cnt) dst[threadIdx.x + NT * k] = __builtin_bit_cast(float, q[k].x);
-}
+// Exchanged values without stamps: write-through stores, loads that bypass the caches (agent scope, as put / peek).
+struct Data {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ explicit Data(const float *base)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, 0xfffffff0u, 0x00020000)) {}
+    __device__ __forceinline__ float ld1(size_t i) const { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (unsigned)(i * 4), 0, 16)); }
+    __device__ __forceinline__ f32x4 ld4(size_t i) const { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (unsigned)(i * 4), 0, 16)); }
+    __device__ __forceinline__ void st1(size_t i, float v) const { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (unsigned)(i * 4), 0, 16); }
+    __device__ __forceinline__ void st4(size_t i, const f32x4 &v) const { __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (unsigned)(i * 4), 0, 16); }
+};
 
 // Workgroup barrier that orders LDS accesses only.  __syncthreads() would also wait for every outstanding global
-// access of the wavefront (vmcnt(0)): for the write-through stores of the last hand-over to reach memory and for the
-// loads a stage keeps in flight across it.  Nothing here passes data between the threads of a workgroup through
-// global memory.
+// access of the wavefront (vmcnt(0)).  Nothing here passes data between the threads of a workgroup through global memory.
 __device__ __forceinline__ void lds_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -150,53 +116,38 @@ __device__ __forceinline__ void lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Product of the B rows of `in` (LDS, row b at in + b * ld_in, nrows values each) with a [nrows x PCS * 8] block of
-// fp16 weights that the threads hold in registers: thread (piece pc = tid % PCS, batch quad bq, row group rg) has
-// rows rg, rg + RG, ... of piece pc in wr[].  The partial sums of the row groups are added inside the wavefront by
-// shuffles and across wavefronts through s_red ([NW][BT][PCS * 8] floats); sink(b, column, sum) gets the result.
-// All threads of the workgroup call; contains barriers.
-template <int BT, int PCS, int RPT, class Sink>
-__device__ __forceinline__ void small_product(const h8 (&wr)[RPT], const float *in, int ld_in, int nrows, int B, float *s_red,
-                                              Sink &&sink)
+// All threads: once every store of the workgroup has been acknowledged (a store counts in vmcnt until then, and a
+// write-through store is acknowledged by the memory side), the flag says so.
+__device__ __forceinline__ void post(uint32_t *flag, uint32_t stamp)
 {
-    constexpr int BQ = BT / 4, G = PCS * BQ, RG = NT / G;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int pc = tid % PCS, bq = (tid / PCS) % BQ, rg = tid / G;
-    float acc[4][8];
-#pragma unroll
-    for (int bb = 0; bb < 4; ++bb)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[bb][c] = 0.f;
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-        const int row = min(rg + RG * k, nrows - 1);                 // rows past the block carry zero weights
-#pragma unroll
-        for (int bb = 0; bb < 4; ++bb) {
-            const float xin = in[min(4 * bq + bb, B - 1) * ld_in + row];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) acc[bb][c] = fmaf(xin, (float)wr[k][c], acc[bb][c]);
-        }
-    }
-#pragma unroll
-    for (int bb = 0; bb < 4; ++bb)
-        if (BT > 4 || bb < B) {                                       // (BT == 4: the same for all threads)
-#pragma unroll
-            for (int off = G; off < 64; off <<= 1)
-#pragma unroll
-                for (int c = 0; c < 8; ++c) acc[bb][c] += __shfl_xor(acc[bb][c], off);
-            if (lane < G) {
-#pragma unroll
-                for (int c = 0; c < 8; ++c) s_red[(wv * BT + 4 * bq + bb) * (PCS * 8) + pc * 8 + c] = acc[bb][c];
-            }
-        }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_sync();
-    for (int i = tid; i < B * PCS * 8; i += NT) {
-        const int b = i / (PCS * 8), cc = i % (PCS * 8);
-        float sum = 0.f;
+    asm volatile("" ::: "memory");
+    if (threadIdx.x == 0) __hip_atomic_store(flag, stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waits for one flag (threads with nothing to wait for pass `on` = false).
+__device__ __forceinline__ void wait_flag(const Exchange &x, const uint32_t *flag, bool on)
+{
+    long long t0 = 0;
+    while (on && __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != x.stamp)
+        if (cf::team::gave_up(x, t0)) break;
+    asm volatile("" ::: "memory");              // what the flag announces is fetched behind it
+}
+
+// v = hi + lo with both parts fp16: an MFMA operand whose fp32 value must not lose bits
+__device__ __forceinline__ void split_hi_lo(const float (&v)[8], h8 &hi, h8 &lo)
+{
 #pragma unroll
-        for (int w8 = 0; w8 < NW; ++w8) sum += s_red[(w8 * BT + b) * (PCS * 8) + cc];
-        sink(b, cc, sum);
+    for (int k = 0; k < 8; ++k) {
+        hi[k] = (_Float16)v[k];
+        lo[k] = (_Float16)(v[k] - (float)hi[k]);
     }
+}
+
+__device__ __forceinline__ float ror8_add(float v)     // v + the value of the lane 8 further in the row of 16 lanes
+{
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xF, 0xF, true));
 }
 
 // Dimension of a cached row that contraction slot (step m, lane group g, element 0) of a score product stands for:
@@ -215,670 +166,550 @@ __device__ unsigned long long g_mla_ts[256 * kMlaStamps];
 #define MLA_STAMP(k)
 #endif
 
-// BT: batch rows the register tiles are written for (4 or 16)
-template <int BT>
 __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
 {
-    constexpr int BQ = BT / 4;
     extern __shared__ __align__(16) float smem[];                    // carved anew by every stage
     __shared__ float s_rope[R];                         // cos, sin of the rotary angles
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, w = blockIdx.x;
-    const int head = w / TS, j = w % TS;
+    // workgroup w runs on die w % 8; with a multiple of eight heads a head's members share one die and its L2
+    const int head = a.nh % 8 == 0 ? w % 8 + 8 * (w / 8 / TS) : w / TS, j = a.nh % 8 == 0 ? w / 8 % TS : w % TS;
     const int B = a.B, nr = a.n + R, CQq = a.nh * nr, CQ = CQq + LR;
+    const int g = lane >> 4, c = lane & 15;                            // contraction group, operand row / column of the lane
+    const h8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+    uint32_t *fA = a.flags, *fB = a.flags + 256, *fC = a.flags + 512, *fD = a.flags + 768;
 #if CF_STAMPS
     __shared__ unsigned long long s_ts[kMlaStamps];
     if (tid < kMlaStamps) s_ts[tid] = 0;
 #endif
     MLA_STAMP(0);
 
+    // ---- A: projections.  Work item (t, sl): columns [64 t, +64) of [W_Q | W_KV], row slice sl.  A wavefront takes 64 rows:
+    //      lane (g, rs = c / 8, piece c % 8) loads rows 32 rs + 8 g + 0..7 of its piece (whole 128-byte lines), transposed
+    //      inside the lane.  The columns of an MFMA share their contraction rows, so each of the two row sets goes through
+    //      the matrix unit with the other one's lanes zeroed.
+    const int T = (CQ + 63) / 64, tA = w % T, slA = w / T;
     unsigned long long launches;
-    asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)"
-                 : "=s"(launches)
-                 : "s"(a.counters + (size_t)w * kCounterStride)
-                 : "memory");
-    const unsigned long long cnt = launches + 1ull;
-    const Exchange x = {a.slots, 0, (uint32_t)(cnt + (cnt >> 32)), a.err, a.spin_ticks};
-    const __amdgpu_buffer_rsrc_t r = cf::team::slots_rsrc(x);
-    if (tid < R / 2) {
-        const double inv_freq = exp2(-2.0 * (double)tid / (double)R * a.log2_base);
-        cf::rope_cos_sin(a.pos, inv_freq, s_rope[tid], s_rope[R / 2 + tid]);
-    }
-
-    constexpr int LJ = L / TS;                                         // latent dimensions per member: 32
-    constexpr int RPT_B = (128 * 4 * BQ + NT - 1) / NT;                // rows per thread: W_Up (nope_dim <= 128),
-    constexpr int RPT_D = (LJ * 16 * BQ + NT - 1) / NT;                //   W_Down slice (LJ rows),
-    constexpr int RPT_E = (128 * 16 * BQ + NT - 1) / NT;               //   W_O (v_head_dim <= 128 rows)
-    constexpr int G4 = 4 * BQ, RG4 = NT / G4, G16 = 16 * BQ, RG16 = NT / G16;
-
-    // ---- A: partial projections.  Work item (kb, cb): rows [kb*RK, +RK) of x, column block cb of W_Q and of W_KV.
-    //      A thread owns one 16-byte piece (8 columns) of the block and every 16th row of the slice: lanes run
-    //      along the columns, so a row of the block is one contiguous read; the two row groups of a wavefront
-    //      are added by a shuffle, the eight wavefronts through LDS (eight batch rows at a time).
+    Exchange x;
     {
-        constexpr int RB = BT < 8 ? BT : 8;
-        float *s_x = smem;                                             // [BT][RK], RK <= 512
-        float *s_red = smem + BT * 512;                                // [NW][RB][MAXCOLS]; 16-row tile: [4][BT][MAXCOLS]
-        const int RK = a.D / KS;
-        const int qv = CQq / 8, kvv = LR / 8;                          // 16-byte pieces of a row of W_Q / W_KV
-        for (int item = w; item < KS * 16; item += a.W) {
-            const int kb = item / 16, cb = item % 16;
-            if constexpr (BT == 16) {
-                // Matrix cores: one 16 x 16 x 32 step per 32 rows of the slice and eight columns: A = x (batch rows by
-                // slice rows, fp16 as given), B = eight rows of a 16-byte piece of the weights, transposed inside
-                // the lane; fp32 accumulation.  Wavefront wv takes the pieces [16 (wv & 1), +16) of the block and the
-                // steps wv / 2, wv / 2 + 4, ...; the four wavefronts of a piece set are added through LDS.
-                const int g = lane >> 4, c = lane & 15, pv = 16 * (wv & 1) + c, sw = wv >> 1;
-                const bool isq = pv < a.cq;
-                const int piece = isq ? cb * a.cq + pv : cb * a.ckv + (pv - a.cq);
-                const bool live = pv < a.cq + a.ckv && piece < (isq ? qv : kvv);
-                const h8 *wp = reinterpret_cast<const h8 *>(isq ? a.wq : a.wkv) + piece;
-                const size_t ld = isq ? qv : kvv;                      // row stride in pieces
-                h8 wr[8];
-                auto request = [&](int st) {
+        const int rs = c >> 3, piece = 8 * tA + (c & 7), qv = CQq / 8;
+        const int r0 = slA * a.rows, rend = min(r0 + a.rows, a.D);
+        const int row = r0 + 64 * wv + 32 * rs + 8 * g;                // (rows, D: multiples of eight)
+        const bool live = slA < a.ksa && piece < CQ / 8 && row < rend;
+        const bool isq = piece < qv;
+        const size_t ld = isq ? qv : LR / 8;                           // row stride in pieces
+        const h8 *wp = reinterpret_cast<const h8 *>(isq ? a.wq : a.wkv) + (live ? (size_t)row * ld + (isq ? piece : piece - qv) : 0);
+        h8 wr[8], xa[2], f8[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int rr = 32 * st + 8 * g + u;
-                        wr[u] = (live && rr < RK) ? wp[(size_t)(kb * RK + rr) * ld] : h8{0, 0, 0, 0, 0, 0, 0, 0};
-                    }
-                };
-                request(sw);                                            // the first weights go out before the slice of x
-                lds_sync();
-                for (int i = tid; i < B * RK; i += NT) s_x[i] = h2f(a.x[(size_t)(i / RK) * a.D + kb * RK + i % RK]);
-                lds_sync();
-                f32x4 acc[8];                                           // [jj][rr]: batch row 4 g + rr, column 8 pv + jj
+        for (int u = 0; u < 8; ++u) wr[u] = wp[live ? u * ld : 0];
 #pragma unroll
-                for (int jj = 0; jj < 8; ++jj) acc[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
-                for (int st = sw; 32 * st < RK; st += 4) {
-                    if (st != sw) request(st);
-                    h8 xa;
+        for (int h = 0; h < 2; ++h) {
+            const int xr = r0 + 64 * wv + 32 * h + 8 * g;
+            const bool on = c < B && xr < rend;
+            const h8 xv = *reinterpret_cast<const h8 *>(a.x + (on ? (size_t)c * a.D + xr : 0));
+            xa[h] = on ? xv : zero8;
+        }
+        asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)"
+                     : "=s"(launches)
+                     : "s"(a.counters + (size_t)w * kCounterStride)
+                     : "memory");
+        if (tid < R / 2) {
+            const double inv_freq = exp2(-2.0 * (double)tid / (double)R * a.log2_base);
+            cf::rope_cos_sin(a.pos, inv_freq, s_rope[tid], s_rope[R / 2 + tid]);
+        }
+        const unsigned long long cnt = launches + 1ull;
+        x = Exchange{a.slots, 0, (uint32_t)(cnt + (cnt >> 32)), a.err, a.spin_ticks};
+        transpose8(wr, f8);
+        f32x4 acc[8];                                                  // [jj][rr]: batch row 4 g + rr, column 8 (c % 8) + jj
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const int rr = 32 * st + 8 * g + i;
-                        xa[i] = (c < B && rr < RK) ? (_Float16)s_x[c * RK + rr] : (_Float16)0.f;
-                    }
-                    h8 f8[8];
-                    transpose8(wr, f8);
+        for (int jj = 0; jj < 8; ++jj) {
+            acc[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int jj = 0; jj < 8; ++jj) acc[jj] = mfma16(xa, f8[jj], acc[jj]);
-                }
+            for (int h = 0; h < 2; ++h) acc[jj] = mfma16(xa[h], live && rs == h ? f8[jj] : zero8, acc[jj]);
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) acc[jj][rr] = ror8_add(acc[jj][rr]);
+        }
+        if (c < 8)
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                float *dst = smem + (wv * 16 + 4 * g + rr) * 64 + 8 * c;
+                *reinterpret_cast<f32x4 *>(dst) = f32x4{acc[0][rr], acc[1][rr], acc[2][rr], acc[3][rr]};
+                *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{acc[4][rr], acc[5][rr], acc[6][rr], acc[7][rr]};
+            }
+        lds_sync();
+    }
+    const Data X(a.data);
+    const __amdgpu_buffer_rsrc_t r = cf::team::slots_rsrc(x);
+    if (slA < a.ksa) {                                                 // (uniform)
+        for (int i = tid; i < B * 64; i += NT) {
+            const int b = i / 64, col = 64 * tA + i % 64;
+            float sum = 0.f;
+#pragma unroll
+            for (int w8 = 0; w8 < NW; ++w8) sum += smem[w8 * 16 * 64 + i];
+            if (col < CQ) X.st1(a.x1 + ((size_t)slA * B + b) * CQ + col, sum);
+        }
+        post(fA + slA * T + tA, x.stamp);
+    }
+    MLA_STAMP(1);           // A done
+
+    // ---- B: member j of head `head`: columns [LJ*j, +LJ) of the up-projection (wavefront 0..3: 32 of the nope dimensions
+    //      each, four 16-byte pieces of the rows), RoPE pairs 2j, 2j + 1 of the head's rotary query (wavefront 4).  Every
+    //      wavefront waits for its sources itself and adds the row slices as it fetches them.
+    {
+        h8 wup[8];
+        const int row = 32 * (wv & 3) + 8 * g;                         // (n: a multiple of eight)
+        const bool mine = wv < 4 && row < a.n;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            wup[u] = mine && c < 4 ? *reinterpret_cast<const h8 *>(a.wup + ((size_t)head * a.n + row + u) * L + LJ * j + c * 8) : zero8;
+        const int ta = head * nr / 64, nt = (head * nr + nr - 1) / 64 - ta + 1;      // tiles of the head's columns: at most 4
+        if (wv < 5) wait_flag(x, fA + min(lane / max(nt, 1), a.ksa - 1) * T + ta + lane % max(nt, 1), lane < nt * a.ksa);
+        if (wv < 4) {
+            float q8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            const size_t src = a.x1 + (size_t)min(c, B - 1) * CQ + head * nr + (mine ? row : 0);
+            f32x4 p[kMaxSlices][2];
+#pragma unroll
+            for (int k = 0; k < kMaxSlices; ++k)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) p[k][h] = X.ld4(src + (size_t)min(k, a.ksa - 1) * B * CQ + 4 * h);
+#pragma unroll
+            for (int k = 0; k < kMaxSlices; ++k)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) q8[e] += mine && k < a.ksa ? p[k][e >> 2][e & 3] : 0.f;
+            h8 hi, lo, f8[8];
+            split_hi_lo(q8, hi, lo);
+            transpose8(wup, f8);
+            f32x4 acc[8];
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj) {
+                acc[jj] = mfma16(hi, f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
+                acc[jj] = mfma16(lo, f8[jj], acc[jj]);
+            }
+            if (c < 4)
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr) {
-                    float *dst = s_red + (sw * BT + 4 * g + rr) * MAXCOLS + pv * 8;
-                    *reinterpret_cast<float4 *>(dst) = make_float4(acc[0][rr], acc[1][rr], acc[2][rr], acc[3][rr]);
-                    *reinterpret_cast<float4 *>(dst + 4) = make_float4(acc[4][rr], acc[5][rr], acc[6][rr], acc[7][rr]);
+                    float *dst = smem + NW * 16 * 64 + (wv * 16 + 4 * g + rr) * LJ + 8 * c;      // (behind the sums of A)
+                    *reinterpret_cast<f32x4 *>(dst) = f32x4{acc[0][rr], acc[1][rr], acc[2][rr], acc[3][rr]};
+                    *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{acc[4][rr], acc[5][rr], acc[6][rr], acc[7][rr]};
                 }
-                lds_sync();
-                for (int i = tid; i < BT * MAXCOLS; i += NT) {
-                    const int b = i / MAXCOLS, cc = i % MAXCOLS, p2 = cc / 8;
-                    const bool q2 = p2 < a.cq;
-                    const int piece2 = q2 ? cb * a.cq + p2 : cb * a.ckv + (p2 - a.cq);
-                    if (b < B && p2 < a.cq + a.ckv && piece2 < (q2 ? qv : kvv)) {
-                        float sum = 0.f;
+        } else if (wv == 4) {
+            // lane (batch row, k): k = 0, 1: the pairs' first elements, k = 2, 3: their partners
+            const int b = lane >> 2, k = lane & 3, pr = 2 * j + (k & 1);
+            float s = 0.f, p[kMaxSlices];
 #pragma unroll
-                        for (int k4 = 0; k4 < 4; ++k4) sum += s_red[(k4 * BT + b) * MAXCOLS + cc];
-                        const int gcol = (q2 ? 0 : CQq) + piece2 * 8 + cc % 8;
-                        cf::team::put(r, a.x1 + ((size_t)kb * B + b) * CQ + gcol, sum, x.stamp);
-                    }
-                }
-                lds_sync();
-            } else {
-                const int pv = tid % 32, g = tid / 32;                     // piece of the block, row group 0..15
-                const bool isq = pv < a.cq;
-                const int piece = isq ? cb * a.cq + pv : cb * a.ckv + (pv - a.cq);
-                const bool live = pv < a.cq + a.ckv && piece < (isq ? qv : kvv);
-                const h8 *wp = reinterpret_cast<const h8 *>(isq ? a.wq : a.wkv) + piece;
-                const size_t ld = isq ? qv : kvv;                          // row stride in pieces
-                h8 wr[8];                                                   // eight rows of this thread in flight
-                auto request = [&](int r0) {
-    #pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const int rr = r0 + 16 * k;
-                        wr[k] = (live && rr < RK) ? wp[(size_t)(kb * RK + rr) * ld] : h8{0, 0, 0, 0, 0, 0, 0, 0};
-                    }
-                };
-                request(g);                                                 // the first weights go out before the slice of x
-                lds_sync();                                                 // (all threads, whatever their row group)
-                for (int i = tid; i < B * RK; i += NT) s_x[i] = h2f(a.x[(size_t)(i / RK) * a.D + kb * RK + i % RK]);
-                lds_sync();
-                // RB batch rows per pass (the accumulators of 16 rows do not fit beside the weights); a slice of up to
-                // 128 rows is one batch of loads and stays in registers over the passes
-                for (int b0 = 0; b0 < B; b0 += RB) {
-                    float acc[RB][8];
-    #pragma unroll
-                    for (int bb = 0; bb < RB; ++bb)
-    #pragma unroll
-                        for (int c = 0; c < 8; ++c) acc[bb][c] = 0.f;
-                    for (int r0 = g; r0 < RK; r0 += 16 * 8) {
-                        if (r0 != g || (b0 > 0 && RK > 16 * 8)) request(r0);
-    #pragma unroll
-                        for (int k = 0; k < 8; ++k) {
-                            const int rr = min(r0 + 16 * k, RK - 1);
-                            float wf[8];
-    #pragma unroll
-                            for (int c = 0; c < 8; ++c) wf[c] = (float)wr[k][c];
-    #pragma unroll
-                            for (int bb = 0; bb < RB; ++bb) {
-                                const float xv = s_x[min(b0 + bb, B - 1) * RK + rr];
-    #pragma unroll
-                                for (int c = 0; c < 8; ++c) acc[bb][c] = fmaf(xv, wf[c], acc[bb][c]);
-                            }
-                        }
-                    }
-                    // (all shuffles of a row first, then the stores: a store between two shuffles makes each one wait)
-    #pragma unroll
-                    for (int bb = 0; bb < RB; ++bb)
-                        if (b0 + bb < B) {
-    #pragma unroll
-                            for (int c = 0; c < 8; ++c) acc[bb][c] += __shfl_xor(acc[bb][c], 32);
-                            if (lane < 32) {
-    #pragma unroll
-                                for (int c = 0; c < 8; ++c) s_red[(wv * RB + bb) * MAXCOLS + pv * 8 + c] = acc[bb][c];
-                            }
-                        }
-                    lds_sync();
-                    for (int i = tid; i < RB * MAXCOLS; i += NT) {
-                        const int bb = i / MAXCOLS, b = b0 + bb, cc = i % MAXCOLS, p2 = cc / 8;
-                        const bool q2 = p2 < a.cq;
-                        const int piece2 = q2 ? cb * a.cq + p2 : cb * a.ckv + (p2 - a.cq);
-                        if (b < B && p2 < a.cq + a.ckv && piece2 < (q2 ? qv : kvv)) {
-                            float sum = 0.f;
-    #pragma unroll
-                            for (int w8 = 0; w8 < NW; ++w8) sum += s_red[(w8 * RB + bb) * MAXCOLS + cc];
-                            const int gcol = (q2 ? 0 : CQq) + piece2 * 8 + cc % 8;
-                            cf::team::put(r, a.x1 + ((size_t)kb * B + b) * CQ + gcol, sum, x.stamp);
-                        }
-                    }
-                    lds_sync();
-                }
-            }
+            for (int q = 0; q < kMaxSlices; ++q)
+                p[q] = X.ld1(a.x1 + ((size_t)min(q, a.ksa - 1) * B + min(b, B - 1)) * CQ + head * nr + a.n + pr + (k >> 1) * (R / 2));
+#pragma unroll
+            for (int q = 0; q < kMaxSlices; ++q) s += q < a.ksa ? p[q] : 0.f;
+            const float o = __shfl_xor(s, 2), cs = s_rope[pr], sn = s_rope[R / 2 + pr];
+            const float v = k < 2 ? s * cs - o * sn : s * cs + o * sn;
+            if (b < B) X.st1(a.xq + ((size_t)b * a.nh + head) * LR + L + pr + (k >> 1) * (R / 2), v);
         }
-    }
-
-    MLA_STAMP(1);           // A done
-    // ---- B: member j of head `head`: columns [LJ*j, +LJ) of the up-projection; RoPE pairs 2j, 2j + 1 of the head's
-    //      rotary query; and, spread over all workgroups, the new cache row (latent dimensions w, w + W, ..., rotary
-    //      pairs w, w + W, ...): sums of the KS partials, RoPE, the append (Sec. 2.1) and a copy in fp32 for stage C.
-    {
-        constexpr int NVB = BT == 4 ? 2 : 1;        // (16-row tile: at most 256 jobs, see J3 below)
-        // (the weights do not depend on what the stage waits for: they are requested first)
-        h8 wupr[RPT_B];
+        lds_sync();
+        MLA_STAMP(2);       // up-projection done
         {
-            const int pc = tid % 4, rg = tid / G4;
-#pragma unroll
-            for (int k = 0; k < RPT_B; ++k) {
-                const int row = rg + RG4 * k;
-                wupr[k] = row < a.n ? *reinterpret_cast<const h8 *>(a.wup + ((size_t)head * a.n + row) * L + LJ * j + pc * 8)
-                                    : h8{0, 0, 0, 0, 0, 0, 0, 0};
-            }
+            const int b = tid / LJ, cc = tid % LJ;
+            const float *src = smem + NW * 16 * 64 + tid;
+            const float sum = (src[0] + src[16 * LJ]) + (src[2 * 16 * LJ] + src[3 * 16 * LJ]);
+            if (b < B) X.st1(a.xq + ((size_t)b * a.nh + head) * LR + LJ * j + cc, sum);
         }
-        float *s_job = smem;                                           // sums of the jobs below
-        const int nlat = w < L ? (L - w + a.W - 1) / a.W : 0, npair = w < R / 2 ? (R / 2 - w + a.W - 1) / a.W : 0;
-        // 16-row tile: the sums of q_nope go in two levels (this member adds the KS partials of 1/16 of the head's
-        // nope dimensions and publishes them, then fetches all of them): 16 times fewer polls per workgroup, which at
-        // this batch outweighs the extra hand-over
-        constexpr bool TWO = BT == 16;
-        const int cpm = (a.n + TS - 1) / TS;                           // nope dimensions per member (two levels)
-        const int J0 = TWO ? B * cpm : B * a.n, J1 = J0 + 4 * B, J2 = J1 + B * nlat, J3 = J2 + 2 * B * npair;
-        float *s_red = smem + (J3 + 3) / 4 * 4;                        // [NW][BT][LJ]
-        float *s_qn = TWO ? s_red + NW * BT * LJ : s_job;               // [B][n] q_nope of this head
-        auto job_slot = [&](int i) -> size_t {                          // the first of the KS partials of job i
-            if (i < J0) {
-                const int b = TWO ? i / cpm : i / a.n, c = TWO ? min(cpm * j + i % cpm, a.n - 1) : i % a.n;
-                return a.x1 + (size_t)b * CQ + head * nr + c;
-            }
-            i -= J0;
-            if (i < 4 * B) {
-                const int k = i % 4;                                    // lo of pair 2j, 2j + 1, then their partners
-                return a.x1 + (size_t)(i / 4) * CQ + head * nr + a.n + (k >> 1) * (R / 2) + 2 * j + (k & 1);
-            }
-            i -= 4 * B;
-            if (i < B * nlat) return a.x1 + (size_t)(i / nlat) * CQ + CQq + w + a.W * (i % nlat);
-            i -= B * nlat;
-            const int k = i % (2 * npair);                              // (lo, hi) of pair w + W * (k / 2)
-            return a.x1 + (size_t)(i / (2 * npair)) * CQ + CQq + L + w + a.W * (k >> 1) + (R / 2) * (k & 1);
-        };
-        lds_sync();
-        for (int i0 = tid; i0 < J3; i0 += NT * NVB) {
-            size_t idx[NVB];
-            float sum[NVB];
-#pragma unroll
-            for (int v = 0; v < NVB; ++v) idx[v] = job_slot(min(i0 + NT * v, J3 - 1));
-            take_sums<NVB>(x, r, idx, (size_t)B * CQ, KS, sum);
-#pragma unroll
-            for (int v = 0; v < NVB; ++v)
-                if (i0 + NT * v < J3) s_job[i0 + NT * v] = sum[v];
-        }
-        lds_sync();
-        if (TWO) {
-            for (int i = tid; i < J0; i += NT) {
-                const int b = i / cpm, c = cpm * j + i % cpm;
-                if (c < a.n) cf::team::put(r, a.xqn + ((size_t)b * a.nh + head) * 128 + c, s_job[i], x.stamp);
-            }
-            for (int i0 = 0; i0 < B * a.n; i0 += 4 * NT)
-                fetch4(x, r, min(4 * NT, B * a.n - i0), s_qn + i0, [&](int i) {
-                    return a.xqn + ((size_t)((i0 + i) / a.n) * a.nh + head) * 128 + (i0 + i) % a.n;
-                });
-            lds_sync();
-        }
-        MLA_STAMP(2);           // q_nope, q_rope and the new row summed
-        for (int i = tid; i < 2 * B; i += NT) {                         // rotary query, pairs (p, p + R/2)
-            const int b = i / 2, pp = i % 2, p = 2 * j + pp;
-            const float lo = s_job[J0 + 4 * b + pp], hi = s_job[J0 + 4 * b + 2 + pp], c = s_rope[p], sn = s_rope[R / 2 + p];
-            const size_t dst = a.xq + ((size_t)b * a.nh + head) * LR + L + p;
-            cf::team::put(r, dst, lo * c - hi * sn, x.stamp);
-            cf::team::put(r, dst + R / 2, hi * c + lo * sn, x.stamp);
-        }
-        for (int i = tid; i < B * nlat; i += NT) {                      // latent part of the new row
-            const int b = i / nlat, d = w + a.W * (i % nlat);
-            const float v = s_job[J1 + i];
-            cf::team::put(r, a.xkv + (size_t)b * LR + d, v, x.stamp);
-            a.cache[((size_t)b * a.max_seq + a.pos) * LR + d] = f2h(v);
-        }
-        for (int i = tid; i < B * npair; i += NT) {                     // rotary part of the new row
-            const int b = i / npair, p = w + a.W * (i % npair);
-            const float lo = s_job[J2 + 2 * i], hi = s_job[J2 + 2 * i + 1], c = s_rope[p], sn = s_rope[R / 2 + p];
-            const float rl = lo * c - hi * sn, rh = hi * c + lo * sn;
-            cf::team::put(r, a.xkv + (size_t)b * LR + L + p, rl, x.stamp);
-            cf::team::put(r, a.xkv + (size_t)b * LR + L + p + R / 2, rh, x.stamp);
-            uint16_t *row = a.cache + ((size_t)b * a.max_seq + a.pos) * LR + L + p;
-            row[0] = f2h(rl);
-            row[R / 2] = f2h(rh);
-        }
-        small_product<BT, 4, RPT_B>(wupr, s_qn, a.n, a.n, B, s_red, [&](int b, int cc, float sum) {
-            cf::team::put(r, a.xq + ((size_t)b * a.nh + head) * LR + LJ * j + cc, sum, x.stamp);
-        });
+        post(fB + head * TS + j, x.stamp);
     }
-
     MLA_STAMP(3);           // B done
-    // ---- C: attention.  Work item (b, s): cached rows [t0, t1) of batch row b against the queries of all heads.
-    //      A tile is 64 rows, read from memory once and kept in LDS for both products (read twice, the second
-    //      read of a row misses the L2 at batch 16 and the stage is bound by that traffic).  Scores: wavefronts
-    //      0..3 take 16 rows each, S^T = K Q^T as one 16 x 16 tile (rows = tokens, columns = heads), the contraction
-    //      over the 576 dimensions in 18 steps with the query as a pair of fp16 operands (value = hi + lo, so the
-    //      fp32 query loses nothing).  Online softmax per head over the tile (the wavefronts exchange their maxima
-    //      through LDS).  Weighted sum: wavefront (kq, th) takes the latent dimensions [128 kq, +128) and the rows
-    //      [32 th, +32) of the tile: A = probabilities (fp16, from LDS), B = the rows themselves, eight at a time
-    //      transposed inside the lane.  The item with s = 0 also scores the new token (its row is taken in fp32
-    //      from stage B).
-    {
+
+    // ---- C: attention.  Work item (b, s, hg): cached rows [t0, t1) of batch row b against the queries of the heads
+    //      [h0, h1).  A tile is 64 rows, read from memory once and kept in LDS for both products.  Scores: wavefront (dh, tq)
+    //      takes 16 rows and 288 of the 576 dimensions, S^T = K Q^T as a 16 x 16 tile (rows = tokens, columns = heads),
+    //      the query as a pair of fp16 operands (value = hi + lo, so the fp32 query loses nothing).  Online softmax per
+    //      head over the 32 rows of one half of the tile, each half for itself (its four wavefronts hold the same state, so
+    //      nothing but the scores goes through LDS).  Weighted sum: wavefront (th, kq) takes the latent dimensions
+    //      [128 kq, +128) of the half th: A = probabilities (fp16), B = the rows, eight at a time transposed in the lane.
+    const int ngroups = (a.nh + a.HG - 1) / a.HG;
+    if (w < B * a.NS * ngroups) {                                      // one item per workgroup at most (the plan sees to it)
+        const int hg = w % ngroups, b = w / ngroups / a.NS, s = w / ngroups % a.NS;
+        const int h0 = hg * a.HG, h1 = min(h0 + a.HG, a.nh);           // the heads of this item
+        const int t0 = min(s * a.tps, a.pos), t1 = min(t0 + a.tps, a.pos);
         h8 *qop_hi = reinterpret_cast<h8 *>(smem);                      // [kSteps][64]
         h8 *qop_lo = qop_hi + kQops;
-        float *s_m = smem + 2 * kQops * 4;                              // [NW][HT] maxima of the wavefronts' rows
-        float *s_l = s_m + NW * HT;                                     // [NW][HT] sums of the wavefronts' probabilities
-        float *s_M = s_l + NW * HT;                                     // [HT]
-        float *s_kn = s_M + HT;                                         // [LR] the new row
-        _Float16 *sP = reinterpret_cast<_Float16 *>(s_kn + LR);         // [HT][PS]
-        float *sO = s_kn + LR + HT * PS / 2;                            // [HT][L], at the end of an item
-        float *s_q = sO;                                                // [HT][QS], at its start
-        _Float16 *sK = reinterpret_cast<_Float16 *>(sO);                // [kTile][KSTR] cached rows, between the two
-        const int g = lane >> 4, c = lane & 15, kq = wv & 3, th = wv >> 2;
-        const int ngroups = (a.nh + a.HG - 1) / a.HG;
-        for (int it = w; it < B * a.NS * ngroups; it += a.W) {
-            const int hg = it % ngroups, b = it / ngroups / a.NS, s = it / ngroups % a.NS;
-            const int h0 = hg * a.HG, h1 = min(h0 + a.HG, a.nh);        // the heads of this item
-            const int t0 = min(s * a.tps, a.pos), t1 = min(t0 + a.tps, a.pos);
-            const uint16_t *rows = a.cache + (size_t)b * a.max_seq * LR;
-            // A tile of rows goes from memory to LDS once (a thread carries nine 16-byte pieces of it, requested a
-            // tile ahead); both products take their operands from there.  Rows past the range are read from its last
-            // row (finite data) and get probability 0.
-            constexpr int kPieces = kTile * (LR / 8) / NT;              // 9
-            h8 kr[kPieces];
-            auto request = [&](int T0) {
+        float *s_kn = smem + 2 * kQops * 4;                             // [LR] the new row
+        float *s_sn = s_kn + LR;                                        // [HT] its scores
+        float *s_S = s_sn + HT;                                         // [2][HT][SSTR] scores, per half of the dimensions
+        float *s_ml = s_S + 2 * HT * SSTR;                              // [2][2][HT] maxima and sums of the two halves of the rows
+        float *sO = s_ml + 4 * HT;                                      // [HT][L], at the end
+        _Float16 *sK = reinterpret_cast<_Float16 *>(sO);                // [kTile][KSTR] cached rows
+        // A thread carries nine 16-byte pieces of the tile, requested a tile ahead.  Rows past the range are read from its
+        // last row (finite data) and get probability 0.
+        constexpr int kPieces = kTile * (LR / 8) / NT;                  // 9
+        const uint16_t *rows = a.cache + (size_t)b * a.max_seq * LR;
+        h8 kr[kPieces];
+        auto request = [&](int T0) {
 #pragma unroll
-                for (int k = 0; k < kPieces; ++k) {
-                    const int pc = tid + NT * k, row = pc / (LR / 8), col = pc % (LR / 8);
-                    kr[k] = *reinterpret_cast<const h8 *>(rows + (size_t)min(T0 + row, t1 - 1) * LR + 8 * col);
-                }
-            };
-            auto deposit = [&]() {
-#pragma unroll
-                for (int k = 0; k < kPieces; ++k) {
-                    const int pc = tid + NT * k, row = pc / (LR / 8), col = pc % (LR / 8);
-                    *reinterpret_cast<h8 *>(sK + row * KSTR + 8 * col) = kr[k];
-                }
-            };
-            if (t1 > t0) request(t0);                                   // (uniform) the rows do not wait for the query
-            lds_sync();                                                 // the previous item has left LDS
-            MLA_STAMP(13);
-            {
-                // the query of the item's heads, [head][LR] fp32 scaled by log2(e) / sqrt(d_k): consecutive lanes poll
-                // consecutive slots
-                constexpr int NQ = HT * LR / NT;
-                const int nq = (h1 - h0) * LR;
-                const size_t src = a.xq + ((size_t)b * a.nh + h0) * LR;
-                pair_t q[NQ];
-                long long tw = 0;
-                for (;;) {
-#pragma unroll
-                    for (int k = 0; k < NQ; ++k) {
-                        q[k] = pair_t{0u, x.stamp};
-                        if (NT * k < nq) q[k] = cf::team::peek(r, src + min(tid + NT * k, nq - 1));       // (uniform)
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    bool ok = true;
-#pragma unroll
-                    for (int k = 0; k < NQ; ++k) ok &= q[k].y == x.stamp;
-                    if (ok || cf::team::gave_up(x, tw)) break;
-                }
-#pragma unroll
-                for (int k = 0; k < NQ; ++k) {
-                    const int i = tid + NT * k;
-                    if (i < nq) s_q[(h0 + i / LR) * QS + i % LR] = __builtin_bit_cast(float, q[k].x) * a.scale_log2e;
-                }
+            for (int k = 0; k < kPieces; ++k) {
+                const int pc = tid + NT * k, row = pc / (LR / 8), col = pc % (LR / 8);
+                kr[k] = *reinterpret_cast<const h8 *>(rows + (size_t)min(T0 + row, t1 - 1) * LR + 8 * col);
             }
-            if (s == 0) {                                               // the new row, for the score of the new token
-                for (int i0 = tid; i0 < LR; i0 += NT) {
-                    long long tw = 0;
-                    for (;;) {
-                        const pair_t q = cf::team::peek(r, a.xkv + (size_t)b * LR + i0);
-                        if (q.y == x.stamp || cf::team::gave_up(x, tw)) {
-                            s_kn[i0] = __builtin_bit_cast(float, q.x);
-                            break;
-                        }
-                    }
-                }
+        };
+        if (t1 > t0) request(t0);                                       // (uniform) the rows do not wait for the query
+        {
+            const int nq = (h1 - h0) * TS;                              // at most 256
+            wait_flag(x, fB + h0 * TS + min(tid, nq - 1), tid < nq);
+            if (s == 0) {                                               // the new row's tiles: at most 10 x 4
+                const int ta = CQq / 64, nt = (CQ - 1) / 64 - ta + 1, i = tid - 256;
+                wait_flag(x, fA + (i >= 0 ? min(i / nt, a.ksa - 1) * T + ta + i % nt : 0), i >= 0 && i < nt * a.ksa);
             }
-            lds_sync();
-            // query operands: entry e = (step m, lane (g2, head c2)) holds the eight dimensions score_dim(m, g2) + 0..7
-            // of head c2 as fp16 pairs (value = hi + lo); heads outside the item's group are zero
-            for (int e = tid; e < kQops; e += NT) {
-                const int m = e >> 6, g2 = (e >> 4) & 3, c2 = e & 15;
-                const bool mine = c2 >= h0 && c2 < h1;
-                const float *src = s_q + (mine ? c2 : h0) * QS + score_dim(m, g2);
-                h8 hi, lo;
+        }
+        lds_sync();                                                     // (also: the sums of A and B have been read)
+        asm volatile("" ::: "memory");
+        MLA_STAMP(13);      // sources ready
+        // query operands: entry e = (step m, lane (g2, head c2)) holds the eight dimensions score_dim(m, g2) + 0..7 of head c2,
+        // scaled by log2(e) / sqrt(d_k), as fp16 pairs; heads outside the item's group are zero
+        constexpr int NE = (kQops + NT - 1) / NT;
+        f32x4 qv[NE][2];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float v = mine ? src[i] : 0.f;
-                    hi[i] = (_Float16)v;
-                    lo[i] = (_Float16)(v - (float)hi[i]);
-                }
+        for (int k = 0; k < NE; ++k) {
+            const int e = min(tid + NT * k, kQops - 1), m = e >> 6, g2 = (e >> 4) & 3, c2 = min(max(e & 15, h0), h1 - 1);
+            const size_t src = a.xq + ((size_t)b * a.nh + c2) * LR + score_dim(m, g2);
+            qv[k][0] = X.ld4(src);
+            qv[k][1] = X.ld4(src + 4);
+        }
+        float kn[2] = {0.f, 0.f};
+        if (s == 0)                                                     // (uniform)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int d = min(tid + NT * k, LR - 1);
+                float p[kMaxSlices];
+#pragma unroll
+                for (int q = 0; q < kMaxSlices; ++q) p[q] = X.ld1(a.x1 + ((size_t)min(q, a.ksa - 1) * B + b) * CQ + CQq + d);
+#pragma unroll
+                for (int q = 0; q < kMaxSlices; ++q) kn[k] += q < a.ksa ? p[q] : 0.f;
+            }
+#pragma unroll
+        for (int k = 0; k < NE; ++k) {
+            const int e = tid + NT * k, c2 = e & 15;
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = c2 >= h0 && c2 < h1 ? qv[k][i >> 2][i & 3] * a.scale_log2e : 0.f;
+            h8 hi, lo;
+            split_hi_lo(v, hi, lo);
+            if (e < kQops) {
                 qop_hi[e] = hi;
                 qop_lo[e] = lo;
             }
-            if (s == 0) {
-                // score of the new token: 32 lanes per head, 18 dimensions each
-                const int h = min(h0 + (tid >> 5), h1 - 1), part = tid & 31;
-                float d = 0.f;
+        }
+        if (s == 0) {
+            // the new row: RoPE on the rotary part (dimension 512 + lane of wavefront 0), append (Sec. 2.1).  Its scores are
+            // taken behind the tiles (in front of them these items were 3 us behind the others).
+            const float o = __shfl_xor(kn[1], 32), cs = s_rope[lane & 31], sn = s_rope[R / 2 + (lane & 31)];
+            kn[1] = lane < 32 ? kn[1] * cs - o * sn : kn[1] * cs + o * sn;
 #pragma unroll
-                for (int k = 0; k < LR / 32; ++k) d = fmaf(s_q[h * QS + part * (LR / 32) + k], s_kn[part * (LR / 32) + k], d);
+            for (int k = 0; k < 2; ++k)
+                if (tid + NT * k < LR) {
+                    s_kn[tid + NT * k] = kn[k];
+                    if (hg == 0) a.cache[((size_t)b * a.max_seq + a.pos) * LR + tid + NT * k] = f2h(kn[k]);
+                }
+            if (t1 <= t0) lds_sync();                                   // (uniform; otherwise the tiles' barriers follow)
+        }
+        MLA_STAMP(4);           // query operands built
+        const int th = wv >> 2, kq = wv & 3;                            // half of the tile rows, quarter of the latent dimensions
+        float M = kNegBig, lw = 0.f;                                    // of head c: running maximum; sum over this lane's rows
+        f32x4 O[8];                                                     // [jj][rr]: head 4 g + rr, dimension 128 kq + 8 c + jj
 #pragma unroll
-                for (int off = 1; off < 32; off <<= 1) d += __shfl_xor(d, off);
-                if (part == 0 && h0 + (tid >> 5) < h1) cf::team::put(r, a.xs + (size_t)b * a.nh + h, d, x.stamp);
+        for (int jj = 0; jj < 8; ++jj) O[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int T0 = t0; T0 < t1; T0 += kTile) {                       // uniform over the workgroup
+#pragma unroll
+            for (int k = 0; k < kPieces; ++k) {
+                const int pc = tid + NT * k, row = pc / (LR / 8), col = pc % (LR / 8);
+                *reinterpret_cast<h8 *>(sK + row * KSTR + 8 * col) = kr[k];
+            }
+            if (T0 + kTile < t1) request(T0 + kTile);
+            lds_sync();
+            {
+                const int tq = wv & 3, dh = wv >> 2;
+                const _Float16 *krow = sK + (16 * tq + c) * KSTR;
+                f32x4 S0 = {0.f, 0.f, 0.f, 0.f}, S1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < kSteps / 2; ++i) {
+                    const int m = dh * (kSteps / 2) + i;
+                    const h8 ka = *reinterpret_cast<const h8 *>(krow + score_dim(m, g));
+                    S0 = mfma16(ka, qop_hi[m * 64 + lane], S0);
+                    S1 = mfma16(ka, qop_lo[m * 64 + lane], S1);
+                }
+                *reinterpret_cast<f32x4 *>(s_S + (dh * HT + c) * SSTR + 16 * tq + 4 * g) = S0 + S1;     // head c, tokens 16 tq + 4 g + 0..3
             }
             lds_sync();
-            MLA_STAMP(4);           // query operands built
-            if (t1 > t0) {                                              // uniform over the workgroup
-                float M = kNegBig, lw = 0.f;                            // of head c: running maximum; sum over this lane's rows
-                f32x4 O[8];                                             // [jj][rr]: head 4 g + rr, dimension 128 kq + 8 c + jj
+            float sc[8], mx = kNegBig;                                  // head c, tokens 32 th + 8 g + 0..7 of the tile
+            bool ok[8];
 #pragma unroll
-                for (int jj = 0; jj < 8; ++jj) O[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
-                for (int T0 = t0; T0 < t1; T0 += kTile) {
-                    deposit();
-                    if (T0 + kTile < t1) request(T0 + kTile);
-                    lds_sync();
-                    f32x4 S = {0.f, 0.f, 0.f, 0.f};                     // rows = tokens T0 + 16 wv + 4 g + rr, column = head c
-                    if (wv < kTile / 16) {                              // (uniform per wavefront)
-                        const _Float16 *krow = sK + (16 * wv + c) * KSTR;
+            for (int e = 0; e < 2; ++e) {
+                const float *src = s_S + c * SSTR + 32 * th + 8 * g + 4 * e;
+                const f32x4 p = *reinterpret_cast<const f32x4 *>(src) + *reinterpret_cast<const f32x4 *>(src + HT * SSTR);
 #pragma unroll
-                        for (int m = 0; m < kSteps; ++m) {
-                            const h8 ka = *reinterpret_cast<const h8 *>(krow + score_dim(m, g));
-                            S = mfma16(ka, qop_hi[m * 64 + lane], S);
-                            S = mfma16(ka, qop_lo[m * 64 + lane], S);
-                        }
-                        float mx = kNegBig;
-#pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) {
-                            S[rr] = (T0 + 16 * wv + 4 * g + rr < t1) ? S[rr] : kNegBig;
-                            mx = fmaxf(mx, S[rr]);
-                        }
-                        mx = fmaxf(mx, __shfl_xor(mx, 16));
-                        mx = fmaxf(mx, __shfl_xor(mx, 32));
-                        if (lane < HT) s_m[wv * HT + c] = mx;
-                    }
-                    lds_sync();
-                    float mt = s_m[c];
-#pragma unroll
-                    for (int w4 = 1; w4 < kTile / 16; ++w4) mt = fmaxf(mt, s_m[w4 * HT + c]);
-                    const float Mn = fmaxf(M, mt);                      // > kNegBig: the tile has a row inside the range
-                    const float f = __builtin_amdgcn_exp2f(M - Mn);
-                    M = Mn;
-                    if (wv < kTile / 16) {
-                        float psum = 0.f;
-                        h4 ph;
-#pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) {
-                            const float pw = __builtin_amdgcn_exp2f(S[rr] - Mn);
-                            ph[rr] = (_Float16)pw;
-                            psum += pw;
-                        }
-                        lw = fmaf(lw, f, psum);
-                        *reinterpret_cast<uint2 *>(sP + c * PS + 16 * wv + 4 * g) = __builtin_bit_cast(uint2, ph);
-                    }
-                    float fr[4];                                        // factor of the heads this lane accumulates
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) fr[rr] = __shfl(f, 4 * g + rr);
-#pragma unroll
-                    for (int jj = 0; jj < 8; ++jj)
-#pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) O[jj][rr] *= fr[rr];
-                    lds_sync();
-                    {
-                        const h8 pa = *reinterpret_cast<const h8 *>(sP + c * PS + 32 * th + 8 * g);
-                        h8 vr[8], f8[8];
-#pragma unroll
-                        for (int u = 0; u < 8; ++u)
-                            vr[u] = *reinterpret_cast<const h8 *>(sK + (32 * th + 8 * g + u) * KSTR + 128 * kq + 8 * c);
-                        transpose8(vr, f8);
-#pragma unroll
-                        for (int jj = 0; jj < 8; ++jj) O[jj] = mfma16(pa, f8[jj], O[jj]);
-                    }
-                    lds_sync();                                         // the tile is consumed: the next one may land
+                for (int i = 0; i < 4; ++i) {
+                    ok[4 * e + i] = T0 + 32 * th + 8 * g + 4 * e + i < t1;
+                    sc[4 * e + i] = ok[4 * e + i] ? p[i] : kNegBig;
+                    mx = fmaxf(mx, sc[4 * e + i]);
                 }
-                MLA_STAMP(11);          // rows consumed
-                lw += __shfl_xor(lw, 16);
-                lw += __shfl_xor(lw, 32);
-                if (lane < HT) {
-                    s_l[wv * HT + c] = lw;
-                    if (wv == 0) s_M[c] = M;
-                }
-                // the two halves of the tile rows are added through LDS (all wavefronts hold the same maxima)
-                if (th == 1) {
+            }
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float Mn = fmaxf(M, mx);
+            if (__any(Mn > M)) {                                        // a maximum has grown: rescale
+                const float f = __builtin_amdgcn_exp2f(M - Mn);
+                lw *= f;
 #pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        float *dst = sO + (4 * g + rr) * L + 128 * kq + 8 * c;
-                        *reinterpret_cast<float4 *>(dst) = make_float4(O[0][rr], O[1][rr], O[2][rr], O[3][rr]);
-                        *reinterpret_cast<float4 *>(dst + 4) = make_float4(O[4][rr], O[5][rr], O[6][rr], O[7][rr]);
+                for (int rr = 0; rr < 4; ++rr) {
+                    const float fr = __shfl(f, 4 * g + rr);             // factor of the heads this lane accumulates
+#pragma unroll
+                    for (int jj = 0; jj < 8; ++jj) O[jj][rr] *= fr;
+                }
+                M = Mn;
+            }
+            h8 pa;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float pw = ok[i] ? __builtin_amdgcn_exp2f(sc[i] - Mn) : 0.f;
+                pa[i] = (_Float16)pw;
+                lw += pw;
+            }
+            {
+                h8 vr[8], f8[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) vr[u] = *reinterpret_cast<const h8 *>(sK + (32 * th + 8 * g + u) * KSTR + 128 * kq + 8 * c);
+                transpose8(vr, f8);
+#pragma unroll
+                for (int jj = 0; jj < 8; ++jj) O[jj] = mfma16(pa, f8[jj], O[jj]);
+            }
+            lds_sync();                                                 // the tile is consumed: the next one may land
+        }
+        MLA_STAMP(11);          // rows consumed
+        if (s == 0) {
+            // score of the new token (its row is not rounded): 32 lanes per head, over the operands (step, group) of the head
+            const int h = min(h0 + (tid >> 5), h1 - 1), part = tid & 31;
+            float d = 0.f;
+            for (int e4 = part; e4 < kSteps * 4; e4 += 32) {
+                const int m = e4 >> 2, g2 = e4 & 3, e = m * 64 + g2 * 16 + h;
+                const h8 hi = qop_hi[e], lo = qop_lo[e];
+                const f32x4 *kd = reinterpret_cast<const f32x4 *>(s_kn + score_dim(m, g2));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) d = fmaf((float)hi[i] + (float)lo[i], kd[i >> 2][i & 3], d);
+            }
+#pragma unroll
+            for (int off = 1; off < 32; off <<= 1) d += __shfl_xor(d, off);
+            if (part == 0 && h0 + (tid >> 5) < h1) s_sn[h] = d;
+        }
+        // the two halves (and the new token) -> one partial (m, l, acc) per head
+        lw += __shfl_xor(lw, 16);
+        lw += __shfl_xor(lw, 32);
+        if (kq == 0 && lane < HT) {
+            s_ml[th * 2 * HT + c] = M;
+            s_ml[th * 2 * HT + HT + c] = lw;
+        }
+        if (th == 1) {
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                float *dst = sO + (4 * g + rr) * L + 128 * kq + 8 * c;
+                *reinterpret_cast<f32x4 *>(dst) = f32x4{O[0][rr], O[1][rr], O[2][rr], O[3][rr]};
+                *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{O[4][rr], O[5][rr], O[6][rr], O[7][rr]};
+            }
+        }
+        lds_sync();
+        if (th == 0) {
+            const size_t dst = a.x3 + (size_t)w * HT * L;
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                const int h = 4 * g + rr;
+                if (h >= h0 && h < h1) {
+                    const float M0 = s_ml[h], M1 = s_ml[2 * HT + h], sn = s == 0 ? s_sn[h] : kNegBig, Mx = fmaxf(fmaxf(M0, M1), sn);
+                    const float f0 = __builtin_amdgcn_exp2f(M0 - Mx), f1 = __builtin_amdgcn_exp2f(M1 - Mx);
+                    const float fn = s == 0 ? __builtin_amdgcn_exp2f(sn - Mx) : 0.f;
+                    const float *src = sO + h * L + 128 * kq + 8 * c;
+                    f32x4 o[2];
+#pragma unroll
+                    for (int jj = 0; jj < 8; ++jj) o[jj >> 2][jj & 3] = O[jj][rr] * f0 + src[jj] * f1;
+                    if (s == 0)
+#pragma unroll
+                        for (int jj = 0; jj < 8; ++jj) o[jj >> 2][jj & 3] = fmaf(s_kn[128 * kq + 8 * c + jj], fn, o[jj >> 2][jj & 3]);
+                    X.st4(dst + (size_t)h * L + 128 * kq + 8 * c, o[0]);
+                    X.st4(dst + (size_t)h * L + 128 * kq + 8 * c + 4, o[1]);
+                    if (kq == 0 && c == 0) {
+                        X.st1(a.xml + ((size_t)w * HT + h) * 2, Mx);
+                        X.st1(a.xml + ((size_t)w * HT + h) * 2 + 1, s_ml[HT + h] * f0 + s_ml[3 * HT + h] * f1 + fn);
                     }
-                }
-                lds_sync();
-                if (th == 0) {
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        float *dst = sO + (4 * g + rr) * L + 128 * kq + 8 * c;
-                        const float4 lo4 = *reinterpret_cast<const float4 *>(dst), hi4 = *reinterpret_cast<const float4 *>(dst + 4);
-                        *reinterpret_cast<float4 *>(dst) =
-                            make_float4(O[0][rr] + lo4.x, O[1][rr] + lo4.y, O[2][rr] + lo4.z, O[3][rr] + lo4.w);
-                        *reinterpret_cast<float4 *>(dst + 4) =
-                            make_float4(O[4][rr] + hi4.x, O[5][rr] + hi4.y, O[6][rr] + hi4.z, O[7][rr] + hi4.w);
-                    }
-                }
-                lds_sync();
-                MLA_STAMP(12);          // wavefronts merged
-                const size_t dst = a.x3 + ((size_t)b * a.NS + s) * HT * kPart;
-                for (int i = h0 * L + tid; i < h1 * L; i += NT)
-                    cf::team::put(r, dst + (size_t)(i / L) * kPart + 2 + i % L, sO[i], x.stamp);
-                if (tid >= h0 && tid < h1) {
-                    float ls = 0.f;
-#pragma unroll
-                    for (int w8 = 0; w8 < NW; ++w8) ls += s_l[w8 * HT + tid];
-                    cf::team::put(r, dst + (size_t)tid * kPart, s_M[tid], x.stamp);
-                    cf::team::put(r, dst + (size_t)tid * kPart + 1, ls, x.stamp);
                 }
             }
         }
+        post(fC + w, x.stamp);
     }
-
     MLA_STAMP(5);           // C done
-    // ---- D: merge latent dimensions [LJ*j, +LJ) of head `head` over the token ranges and the new token (online
-    //      softmax, Alg. 4 steps 8-10) and multiply them by the same rows of W_Down[head]: a partial of a_head per
-    //      member, no hop in between
-    {
-        float *s_z = smem;                                              // [B][LJ]
-        float *s_red = smem + BT * LJ;                                  // [NW][BT][128]
-        h8 wdr[RPT_D];
-        {
-            const int pc = tid % 16, rg = tid / G16;
-#pragma unroll
-            for (int k = 0; k < RPT_D; ++k) {
-                const int row = rg + RG16 * k;
-                wdr[k] = (pc < a.v / 8 && row < LJ)
-                             ? *reinterpret_cast<const h8 *>(a.wdown + ((size_t)head * L + LJ * j + row) * a.v + pc * 8)
-                             : h8{0, 0, 0, 0, 0, 0, 0, 0};
-            }
-        }
-        lds_sync();
-        const int n_used = (a.pos + a.tps - 1) / a.tps;
-        if (tid < LJ * B) {
-            // lane sl of a group of 32 fetches the maximum and the sum of range sl (at most 32 ranges) and the group
-            // shares them by shuffles; every lane fetches its own dimension of all ranges: one round trip in all
-            const int b = tid / LJ, sl = tid % LJ, d = LJ * j + sl, nu1 = max(n_used, 1);
-            pair_t qa[kMaxSplits], qm, ql, qn, qc;
-            long long tw = 0;
-            for (;;) {
-                const size_t mine = a.x3 + (((size_t)b * a.NS + min(sl, nu1 - 1)) * HT + head) * kPart;
-                qm = cf::team::peek(r, mine);
-                ql = cf::team::peek(r, mine + 1);
-                qn = cf::team::peek(r, a.xs + (size_t)b * a.nh + head);
-                qc = cf::team::peek(r, a.xkv + (size_t)b * LR + d);
-#pragma unroll
-                for (int k = 0; k < kMaxSplits; ++k) {
-                    qa[k] = pair_t{0u, x.stamp};
-                    if (k < nu1) qa[k] = cf::team::peek(r, a.x3 + (((size_t)b * a.NS + k) * HT + head) * kPart + 2 + d);     // (uniform)
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                bool ok = (qn.y == x.stamp) & (qc.y == x.stamp) & ((sl >= n_used) | ((qm.y == x.stamp) & (ql.y == x.stamp)));
-#pragma unroll
-                for (int k = 0; k < kMaxSplits; ++k) ok &= (k >= n_used) | (qa[k].y == x.stamp);
-                if (ok || cf::team::gave_up(x, tw)) break;
-            }
-            const float snew = __builtin_bit_cast(float, qn.x);
-            const float ms = sl < n_used ? __builtin_bit_cast(float, qm.x) : kNegBig;
-            float M = fmaxf(ms, snew);
-#pragma unroll
-            for (int off = 1; off < LJ; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
-            const float fs = sl < n_used ? __builtin_amdgcn_exp2f(ms - M) : 0.f;
-            float Ls = __builtin_bit_cast(float, ql.x) * fs;
-#pragma unroll
-            for (int off = 1; off < LJ; off <<= 1) Ls += __shfl_xor(Ls, off);
-            const float fn = __builtin_amdgcn_exp2f(snew - M);          // the new token: weight 1 at its own score
-            Ls += fn;
-            float A = __builtin_bit_cast(float, qc.x) * fn;
-#pragma unroll
-            for (int k = 0; k < kMaxSplits; ++k) {
-                const float fk = __shfl(fs, (lane & 32) + k);
-                A = fmaf(k < n_used ? __builtin_bit_cast(float, qa[k].x) : 0.f, fk, A);
-            }
-            const float z = A / Ls;
-            s_z[b * LJ + sl] = z;
-            a.zdbg[((size_t)b * a.nh + head) * L + d] = z;
-        }
-        lds_sync();
-        MLA_STAMP(6);           // z slice merged
-        small_product<BT, 16, RPT_D>(wdr, s_z, LJ, LJ, B, s_red, [&](int b, int cc, float sum) {
-            if (cc < a.v) cf::team::put(r, a.x5 + (((size_t)b * a.nh + head) * TS + j) * a.v + cc, sum, x.stamp);
-        });
-    }
-    MLA_STAMP(7);           // D done
 
-    // ---- E1: rows of W_O that belong to this head, column block j of the output: a partial of out per head
-    {
-        constexpr int NVE = BT == 4 ? 1 : 4;
-        float *s_a = smem;                                              // [B][v]
-        float *s_red = smem + BT * 128;                                 // [NW][BT][128]
-        const int dpE = a.D / 8, pcsE = (dpE + TS - 1) / TS;            // 16-byte pieces of an output row; per member
-        h8 wor[RPT_E];
-        auto wo_rows = [&](int p0) {
-            const int pc = tid % 16, rg = tid / G16;
-            const int piece = j * pcsE + p0 + pc;
-            const bool live = p0 + pc < pcsE && piece < dpE;
+    // ---- D: merge latent dimensions [LJ*j, +LJ) of head `head` over the token ranges (online softmax, Alg. 4 steps 8-10).
+    //      The weights of E1 are requested first: W_Down[head], wavefront wv: rows [64 wv, +64); W_O, rows of the head, column
+    //      block j, wavefront wv: rows [32 (wv % 4), +32).
+    const int dpE = a.D / 8, pcsE = (dpE + TS - 1) / TS;                // 16-byte pieces of an output row; per member (<= 16)
+    h8 wdn[16], wor[8];
 #pragma unroll
-            for (int k = 0; k < RPT_E; ++k) {
-                const int row = rg + RG16 * k;
-                wor[k] = (live && row < a.v) ? *reinterpret_cast<const h8 *>(a.wo + ((size_t)head * a.v + row) * a.D + piece * 8)
-                                             : h8{0, 0, 0, 0, 0, 0, 0, 0};
+    for (int u = 0; u < 16; ++u) {
+        const int row = 64 * wv + 32 * (u >> 3) + 8 * g + (u & 7);
+        wdn[u] = c < a.v / 8 ? *reinterpret_cast<const h8 *>(a.wdown + ((size_t)head * L + row) * a.v + c * 8) : zero8;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int row = 32 * (wv & 3) + 8 * g + u, piece = j * pcsE + c;
+        wor[u] = c < pcsE && piece < dpE && row < a.v
+                     ? *reinterpret_cast<const h8 *>(a.wo + ((size_t)head * a.v + row) * a.D + piece * 8)
+                     : zero8;
+    }
+    {
+        const int hgr = head / a.HG, ni = B * a.NS;                     // ni <= 256 sources
+        wait_flag(x, fC + min(tid, ni - 1) * ngroups + hgr, tid < ni);
+        lds_sync();
+        asm volatile("" ::: "memory");
+        MLA_STAMP(12);      // sources ready
+        // half-wavefront = batch row; lane s of it: maximum and sum of range s; and (sq, d4): four dimensions of every
+        // fourth range
+        const int b = tid >> 5, l5 = tid & 31, sq = l5 >> 3, d4 = l5 & 7, bb = min(b, B - 1);
+        const size_t it0 = (size_t)bb * a.NS * ngroups + hgr;           // item of range 0; ngroups further per range
+        const size_t ml = a.xml + ((it0 + (size_t)min(l5, a.NS - 1) * ngroups) * HT + head) * 2;
+        float m = X.ld1(ml), l = X.ld1(ml + 1);
+        f32x4 p[kMaxSplits / 4];
+#pragma unroll
+        for (int k = 0; k < kMaxSplits / 4; ++k) {
+            p[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (4 * k < a.NS)                                           // (uniform)
+                p[k] = X.ld4(a.x3 + ((it0 + (size_t)min(sq + 4 * k, a.NS - 1) * ngroups) * HT + head) * L + LJ * j + 4 * d4);
+        }
+        if (l5 >= a.NS) m = kNegBig, l = 0.f;
+        float M = m;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
+        float f = l5 < a.NS ? __builtin_amdgcn_exp2f(m - M) : 0.f, Ls = l * f;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) Ls += __shfl_xor(Ls, off);
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kMaxSplits / 4; ++k) {
+            const float fk = __shfl(f, (lane & 32) + sq + 4 * k);       // 0 past the ranges
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[i] = fmaf(p[k][i], fk, z[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            z[i] += __shfl_xor(z[i], 8);
+            z[i] += __shfl_xor(z[i], 16);
+            z[i] /= Ls;
+        }
+        if (sq == 0 && b < B) {
+            const size_t at = ((size_t)b * a.nh + head) * L + LJ * j + 4 * d4;
+            X.st4(a.xz + at, z);
+            *reinterpret_cast<f32x4 *>(a.zdbg + at) = z;
+        }
+        post(fD + head * TS + j, x.stamp);
+    }
+    MLA_STAMP(6);           // z posted
+
+    // ---- E1: a_head = z W_Down[head] (contraction over 512: 64 rows per wavefront, added through LDS), then the rows of
+    //      W_O that belong to this head (contraction over v <= 128: wavefront (part, st) 32 rows, part: high or low half of
+    //      the fp16 pairs of a), column block j of the output
+    {
+        float *s_a = smem, *s_red = smem + 16 * AS;                     // [16][AS], [NW][16][128]
+        wait_flag(x, fD + head * TS + min(lane, TS - 1), lane < TS);
+        f32x4 zv[2][2];
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) zv[st][h] = X.ld4(a.xz + ((size_t)min(c, B - 1) * a.nh + head) * L + 64 * wv + 32 * st + 8 * g + 4 * h);
+        f32x4 acc[8];
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) acc[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = zv[st][i >> 2][i & 3];
+            h8 hi, lo, f8[8];
+            split_hi_lo(v, hi, lo);
+            transpose8(wdn + 8 * st, f8);
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj) {
+                acc[jj] = mfma16(hi, f8[jj], acc[jj]);
+                acc[jj] = mfma16(lo, f8[jj], acc[jj]);
+            }
+        }
+        auto spill = [&]() {
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                float *dst = s_red + (wv * 16 + 4 * g + rr) * 128 + 8 * c;
+                *reinterpret_cast<f32x4 *>(dst) = f32x4{acc[0][rr], acc[1][rr], acc[2][rr], acc[3][rr]};
+                *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{acc[4][rr], acc[5][rr], acc[6][rr], acc[7][rr]};
             }
         };
-        wo_rows(0);
+        spill();
         lds_sync();
-        if constexpr (BT == 16) {
-            // two levels as for q_nope: this member adds the TS partials of 1/16 of the head's dimensions
-            const int cpv = (a.v + TS - 1) / TS;
-            for (int i = tid; i < B * cpv; i += NT) {
-                const int b = i / cpv, c = cpv * j + i % cpv;
-                size_t idx[1] = {a.x5 + ((size_t)b * a.nh + head) * TS * a.v + min(c, a.v - 1)};
-                float sum[1];
-                take_sums<1>(x, r, idx, (size_t)a.v, TS, sum);
-                if (c < a.v) cf::team::put(r, a.xa + ((size_t)b * a.nh + head) * 128 + c, sum[0], x.stamp);
-            }
-            for (int i0 = 0; i0 < B * a.v; i0 += 4 * NT)
-                fetch4(x, r, min(4 * NT, B * a.v - i0), s_a + i0, [&](int i) {
-                    return a.xa + ((size_t)((i0 + i) / a.v) * a.nh + head) * 128 + (i0 + i) % a.v;
-                });
-        } else {
-            for (int i0 = tid; i0 < B * a.v; i0 += NT * NVE) {
-                size_t idx[NVE];
-                float sum[NVE];
+        for (int i = tid; i < 16 * 128; i += NT) {
+            float sum = 0.f;
 #pragma unroll
-                for (int v = 0; v < NVE; ++v) {
-                    const int i = min(i0 + NT * v, B * a.v - 1);
-                    idx[v] = a.x5 + ((size_t)(i / a.v) * a.nh + head) * TS * a.v + i % a.v;
-                }
-                take_sums<NVE>(x, r, idx, (size_t)a.v, TS, sum);
-#pragma unroll
-                for (int v = 0; v < NVE; ++v)
-                    if (i0 + NT * v < B * a.v) s_a[i0 + NT * v] = sum[v];
-            }
+            for (int w8 = 0; w8 < NW; ++w8) sum += s_red[w8 * 16 * 128 + i];
+            s_a[i / 128 * AS + i % 128] = sum;
         }
         lds_sync();
-        MLA_STAMP(8);           // a_head arrived
-        for (int p0 = 0; p0 < pcsE; p0 += 16) {
-            if (p0 > 0) {
-                lds_sync();
-                wo_rows(p0);
+        MLA_STAMP(8);           // a_head ready
+        {
+            const int st = wv & 3;
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = s_a[c * AS + 32 * st + 8 * g + i];
+            h8 hi, lo, f8[8];
+            split_hi_lo(v, hi, lo);
+            const h8 mine = wv < 4 ? hi : lo;
+            transpose8(wor, f8);
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj) acc[jj] = mfma16(mine, f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
+        }
+        spill();
+        lds_sync();
+        for (int i = tid; i < B * 128; i += NT) {
+            const int b = i / 128, cc = i % 128, col = j * pcsE * 8 + cc;
+            if (cc < 8 * pcsE && col < a.D) {
+                float sum = 0.f;
+#pragma unroll
+                for (int w8 = 0; w8 < NW; ++w8) sum += s_red[w8 * 16 * 128 + i];
+                cf::team::put(r, ((size_t)head * B + b) * a.D + col, sum, x.stamp);
             }
-            small_product<BT, 16, RPT_E>(wor, s_a, a.v, a.v, B, s_red, [&](int b, int cc, float sum) {
-                const int piece2 = j * pcsE + p0 + cc / 8;
-                if (p0 + cc / 8 < pcsE && piece2 < dpE)
-                    cf::team::put(r, a.x6 + ((size_t)b * a.nh + head) * a.D + piece2 * 8 + cc % 8, sum, x.stamp);
-            });
         }
     }
     MLA_STAMP(10);          // E1 done
 
-    // ---- E2: sum over the heads (what the paper does with atomicAdd), columns [CW*w, +CW) of the output
+    // ---- E2: sum over the heads (what the paper does with atomicAdd), columns [CW*w, +CW) of the output: thread (quarter,
+    //      value): the value's partials of four heads
     {
-        const int CW = (a.D + a.W - 1) / a.W;
-        if (tid < B * CW) {
-            const int b = tid / CW, col = CW * w + tid % CW;
-            if (col < a.D) {
-                const size_t idx[1] = {a.x6 + (size_t)b * a.nh * a.D + col};
-                float sum[1];
-                take_sums<1>(x, r, idx, (size_t)a.D, a.nh, sum);
-                a.out[(size_t)b * a.D + col] = f2h(sum[0]);
-            }
+        const int CW = (a.D + a.W - 1) / a.W, nv = B * CW;             // CW <= 8, nv <= 128
+        float *s_o = smem;                                              // [4][128] (a_head has been read)
+        const int qtr = tid >> 7, v = tid & 127, b = v / CW, col = CW * w + v % CW;
+        const bool on = v < nv && col < a.D;
+        pair_t q[4];
+        long long tw = 0;
+        for (;;) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[k] = cf::team::peek(r, on ? ((size_t)min(4 * qtr + k, a.nh - 1) * B + b) * a.D + col : 0);
+            __builtin_amdgcn_sched_barrier(0);
+            bool ok = true;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) ok &= q[k].y == x.stamp;
+            if (!on || ok || cf::team::gave_up(x, tw)) break;
         }
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum += 4 * qtr + k < a.nh ? __builtin_bit_cast(float, q[k].x) : 0.f;
+        s_o[tid] = sum;
+        lds_sync();
+        if (qtr == 0 && on) a.out[(size_t)b * a.D + col] = f2h((s_o[v] + s_o[128 + v]) + (s_o[256 + v] + s_o[384 + v]));
     }
-    if (tid == 0) a.counters[(size_t)w * kCounterStride] = cnt;
+    if (tid == 0) a.counters[(size_t)w * kCounterStride] = launches + 1ull;
     MLA_STAMP(9);
 #if CF_STAMPS
     lds_sync();
     if (tid < kMlaStamps && w < 256) g_mla_ts[w * kMlaStamps + tid] = s_ts[tid];
 #endif
 }
-
-using MlaFn = void (*)(const MlaArgs);
-
-MlaFn pick(int batch) { return batch <= 4 ? fused_mla_decode<4> : fused_mla_decode<16>; }
 
 }  // namespace
 
@@ -887,11 +718,13 @@ struct cf_mla_s {
     int W = 0;
     char *ws = nullptr;
     size_t ws_bytes = 0;
-    uint64_t *slots = nullptr;
+    uint64_t *slots = nullptr, *hslots = nullptr;    // stamped slots of the token-range kernel, of the head-team kernel
+    float *data = nullptr;          // values of the token-range kernel's other hand-overs
+    uint32_t *flags = nullptr;      // their flags
     float *zdbg = nullptr, *qdbg = nullptr, *zpart = nullptr;
     unsigned long long *counters = nullptr;
     uint32_t *err = nullptr;
-    size_t x1 = 0, xq = 0, xkv = 0, x3 = 0, xs = 0, x5 = 0, x6 = 0, xqn = 0, xa = 0;
+    size_t x1 = 0, xq = 0, x3 = 0, xml = 0, xz = 0;
     long long spin_ticks = 200000000LL;
     int max_splits = 0;             // 0: chosen by the library
     int last_batch = 0;
@@ -936,49 +769,41 @@ int cf_mla_create(const cf_mla_config *cfg, cf_mla *out)
     // what the kernel is written for
     const int W = c.n_heads * TS;
     const int CQq = c.n_heads * (c.nope_dim + R);
-    const int cq = (CQq / 8 + 15) / 16, ckv = (LR / 8 + 15) / 16;          // 16-byte pieces per column block
-    if (c.kv_lora_rank != L || c.rope_dim != R || c.max_batch > MAXBATCH || c.n_heads > HT || c.d_model % (2 * KS) ||
-        c.d_model / KS > NT || c.v_head_dim % 8 || c.v_head_dim > 128 || cq + ckv > 32 || c.nope_dim % 8 ||
-        c.nope_dim > 128 || c.d_model > 8 * W || c.d_model % 8)
+    if (c.kv_lora_rank != L || c.rope_dim != R || c.max_batch > MAXBATCH || c.n_heads > HT || c.d_model % 32 ||
+        c.d_model > 16 * NT || c.v_head_dim % 8 || c.v_head_dim > 128 || c.nope_dim % 8 || c.nope_dim > 128 || c.d_model > 8 * W)
         return CF_EUNSUPPORTED;
+    int ksa = 0, rows = 0;
+    if (!cf::mla::slices(c, &ksa, &rows)) return CF_EUNSUPPORTED;
     int dev = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return CF_EHIP;
     if (W > prop.multiProcessorCount) return CF_EUNSUPPORTED;        // all workgroups resident, one per compute unit
     const size_t lds = kLdsFloats * sizeof(float);
-    for (int batch : {1, MAXBATCH}) {
-        int per_cu = 0;
-        const void *fn = reinterpret_cast<const void *>(pick(batch));
-        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, NT, lds) != hipSuccess || per_cu < 1)
-            return CF_EUNSUPPORTED;
-    }
+    int per_cu = 0;
+    const void *fn = reinterpret_cast<const void *>(fused_mla_decode);
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, NT, lds) != hipSuccess || per_cu < 1)
+        return CF_EUNSUPPORTED;
     if (!cf::mla::heads_prepare()) return CF_EUNSUPPORTED;
     cf_mla t = new (std::nothrow) cf_mla_s();
     if (!t) return CF_ENOMEM;
     t->cfg = c;
     t->W = W;
-    const size_t B = c.max_batch, CQ = (size_t)CQq + LR, items = (size_t)(W > c.max_batch ? W : c.max_batch);
+    const size_t B = c.max_batch, CQ = (size_t)CQq + LR, nh = c.n_heads;
     t->x1 = 0;
-    t->xq = t->x1 + (size_t)KS * B * CQ;
-    t->xkv = t->xq + B * c.n_heads * LR;
-    t->x3 = t->xkv + B * LR;
-    t->xs = t->x3 + items * HT * kPart;
-    t->x5 = t->xs + B * c.n_heads;
-    t->x6 = t->x5 + B * c.n_heads * TS * c.v_head_dim;
+    t->xq = t->x1 + (size_t)kMaxSlices * B * CQ;
+    t->x3 = t->xq + B * nh * LR;                                  // (an item per workgroup at most)
+    t->xml = t->x3 + (size_t)W * HT * L;
+    t->xz = t->xml + (size_t)W * HT * 2;
+    const size_t ndata = t->xz + B * nh * L;
     size_t hfirst[3];
-    const size_t hslots = cf::mla::heads_layout(c, hfirst);
-    t->xqn = t->x6 + B * c.n_heads * c.d_model;                  // [B][heads][128] summed q_nope (16-row tile)
-    t->xa = t->xqn + B * c.n_heads * 128;                         // [B][heads][128] summed a_head (16-row tile)
-    const size_t rslots = t->xa + B * c.n_heads * 128;
-    const size_t nslots = rslots > hslots ? rslots : hslots;         // the two kernels use the same slots, never together
-    const size_t head = 256 + (size_t)W * kCounterStride * sizeof(unsigned long long);
-    const size_t head_al = (head + 255) / 256 * 256;
-    const size_t slot_bytes = (nslots * sizeof(uint64_t) + 255) / 256 * 256;
-    const size_t zbytes = (B * c.n_heads * L * sizeof(float) + 255) / 256 * 256;
-    const size_t qbytes = (B * c.n_heads * LR * sizeof(float) + 255) / 256 * 256;
-    t->ws_bytes = head_al + slot_bytes + zbytes + qbytes + (size_t)c.n_heads * TS * (2 + L) * sizeof(float);
-    if (nslots * sizeof(uint64_t) > 0xfffffff0ull) {
+    // every kind of hand-over has memory of its own: a flag or a stamp never lies where other data has been
+    const size_t nslots = B * nh * c.d_model, nhslots = cf::mla::heads_layout(c, hfirst);
+    auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+    const size_t head_b = up(256 + (size_t)W * kCounterStride * sizeof(unsigned long long)), flag_b = 4 * 256 * sizeof(uint32_t);
+    const size_t slot_b = up(nslots * 8), hslot_b = up(nhslots * 8), data_b = up(ndata * 4), z_b = up(B * nh * L * 4), q_b = up(nh * LR * 4);
+    t->ws_bytes = head_b + flag_b + slot_b + hslot_b + data_b + z_b + q_b + nh * TS * (2 + L) * sizeof(float);
+    if (slot_b > 0xfffffff0ull || data_b > 0xfffffff0ull) {
         delete t;
         return CF_EUNSUPPORTED;
     }
@@ -992,10 +817,14 @@ int cf_mla_create(const cf_mla_config *cfg, cf_mla *out)
     }
     t->err = reinterpret_cast<uint32_t *>(t->ws + 128);
     t->counters = reinterpret_cast<unsigned long long *>(t->ws + 256);
-    t->slots = reinterpret_cast<uint64_t *>(t->ws + head_al);
-    t->zdbg = reinterpret_cast<float *>(t->ws + head_al + slot_bytes);
-    t->qdbg = reinterpret_cast<float *>(t->ws + head_al + slot_bytes + zbytes);
-    t->zpart = reinterpret_cast<float *>(t->ws + head_al + slot_bytes + zbytes + qbytes);
+    char *cur = t->ws + head_b;
+    t->flags = reinterpret_cast<uint32_t *>(cur);
+    t->slots = reinterpret_cast<uint64_t *>(cur += flag_b);
+    t->hslots = reinterpret_cast<uint64_t *>(cur += slot_b);
+    t->data = reinterpret_cast<float *>(cur += hslot_b);
+    t->zdbg = reinterpret_cast<float *>(cur += data_b);
+    t->qdbg = reinterpret_cast<float *>(cur += z_b);
+    t->zpart = reinterpret_cast<float *>(cur += q_b);
     *out = t;
     return CF_OK;
 }
@@ -1017,7 +846,7 @@ int cf_mla_decode(cf_mla t, int32_t batch, const void *x, const void *W_q, const
     for (const void *p : ptrs)
         if (reinterpret_cast<uintptr_t>(p) & 15u) return CF_EINVAL;
     const cf_mla_config &c = t->cfg;
-    if (batch <= kHeadsBatch && t->max_splits == 0 && cf::mla::heads_fits(c)) {
+    if (batch <= kHeadsBatch && t->max_splits == 0) {
         // the head-team kernel (every head scans the cached rows itself; see cf_mla_heads.hip)
         cf::mla::HeadsArgs h;
         std::memset(&h, 0, sizeof h);
@@ -1030,12 +859,12 @@ int cf_mla_decode(cf_mla t, int32_t batch, const void *x, const void *W_q, const
         h.cache = static_cast<uint16_t *>(kv_cache);
         h.out = static_cast<uint16_t *>(out);
         h.qdbg = t->qdbg, h.zpart = t->zpart;
-        h.slots = t->slots, h.counters = t->counters, h.err = t->err;
+        h.slots = t->hslots, h.counters = t->counters, h.err = t->err;
         size_t first[3];
         (void)cf::mla::heads_layout(c, first);
         h.x1 = first[0], h.x3 = first[1], h.x6 = first[2];
         h.D = c.d_model, h.nh = c.n_heads, h.n = c.nope_dim, h.v = c.v_head_dim, h.pos = pos, h.W = t->W;
-        cf::mla::heads_slices(c, &h.ksa, &h.rows);
+        (void)cf::mla::slices(c, &h.ksa, &h.rows);
         h.scale_log2e = 1.4426950408889634f / std::sqrt((float)(c.nope_dim + R));
         h.log2_base = std::log2((double)c.rope_base);
         h.spin_ticks = t->spin_ticks;
@@ -1058,21 +887,20 @@ int cf_mla_decode(cf_mla t, int32_t batch, const void *x, const void *W_q, const
     a.cache = static_cast<uint16_t *>(kv_cache);
     a.out = static_cast<uint16_t *>(out);
     a.zdbg = t->zdbg;
-    a.slots = t->slots;
+    a.slots = t->slots, a.data = t->data, a.flags = t->flags;
     a.counters = t->counters;
     a.err = t->err;
     // the exchange areas are laid out for max_batch; a smaller batch uses the front of each
-    a.x1 = t->x1, a.xq = t->xq, a.xkv = t->xkv, a.x3 = t->x3, a.xs = t->xs, a.x5 = t->x5, a.x6 = t->x6, a.xqn = t->xqn, a.xa = t->xa;
+    a.x1 = t->x1, a.xq = t->xq, a.x3 = t->x3, a.xml = t->xml, a.xz = t->xz;
     a.D = c.d_model, a.nh = c.n_heads, a.n = c.nope_dim, a.v = c.v_head_dim, a.B = batch, a.pos = pos;
     a.max_seq = c.max_seq, a.W = t->W;
     plan_splits(t, batch, pos, &a.NS, &a.tps, &a.HG);
-    a.cq = (c.n_heads * (c.nope_dim + R) / 8 + 15) / 16;
-    a.ckv = (LR / 8 + 15) / 16;
+    (void)cf::mla::slices(c, &a.ksa, &a.rows);
     a.scale_log2e = 1.4426950408889634f / std::sqrt((float)(c.nope_dim + R));
     a.log2_base = std::log2((double)c.rope_base);
     a.spin_ticks = t->spin_ticks;
     t->last_batch = batch, t->last_heads = false;
-    hipLaunchKernelGGL(pick(batch), dim3(t->W), dim3(NT), kLdsFloats * sizeof(float), static_cast<hipStream_t>(stream), a);
+    hipLaunchKernelGGL(fused_mla_decode, dim3(t->W), dim3(NT), kLdsFloats * sizeof(float), static_cast<hipStream_t>(stream), a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         t->last_hip = (int)e;
@@ -1142,17 +970,13 @@ int cf_mla_debug_export(cf_mla t, int32_t what, void *host_dst, size_t bytes, vo
             for (size_t i = 0; i < B * nh; ++i)
                 std::memcpy(dst + i * per, q.data() + i * LR + (what == 1 ? L : 0), per * sizeof(float));
     } else if (e == hipSuccess && what != 2) {
-        // the query of the last call still sits in its exchange slots: [b][head][L + R] {value, stamp} pairs
-        std::vector<uint64_t> pairs(B * nh * LR);
-        e = hipMemcpy(pairs.data(), t->slots + t->xq, pairs.size() * sizeof(uint64_t), hipMemcpyDeviceToHost);
+        // the query of the last call still sits in its exchange area: [b][head][L + R]
+        std::vector<float> q(B * nh * LR);
+        e = hipMemcpy(q.data(), t->data + t->xq, q.size() * sizeof(float), hipMemcpyDeviceToHost);
         float *dst = static_cast<float *>(host_dst);
         if (e == hipSuccess)
-            for (size_t b = 0; b < B; ++b)
-                for (size_t h = 0; h < nh; ++h)
-                    for (size_t k = 0; k < per; ++k) {
-                        const uint32_t bits = (uint32_t)pairs[(b * nh + h) * LR + (what == 1 ? L : 0) + k];
-                        std::memcpy(dst + (b * nh + h) * per + k, &bits, sizeof bits);
-                    }
+            for (size_t i = 0; i < B * nh; ++i)
+                std::memcpy(dst + i * per, q.data() + i * LR + (what == 1 ? L : 0), per * sizeof(float));
     }
     if (e != hipSuccess) {
         t->last_hip = (int)e;

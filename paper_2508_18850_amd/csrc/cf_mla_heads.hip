@@ -591,19 +591,13 @@ size_t heads_layout(const cf_mla_config &c, size_t (&first)[3])
     return first[2] + (size_t)c.n_heads * c.d_model;
 }
 
-void heads_slices(const cf_mla_config &c, int *ksa, int *rows)
+bool slices(const cf_mla_config &c, int *ksa, int *rows)
 {
     const int W = c.n_heads * TS, T = (c.n_heads * (c.nope_dim + R) + LR + 63) / 64;
     const int k = W / T < 1 ? 1 : W / T > kMaxSlices ? kMaxSlices : W / T;
     *rows = ((c.d_model + k - 1) / k + 7) / 8 * 8;
     *ksa = (c.d_model + *rows - 1) / *rows;
-}
-
-bool heads_fits(const cf_mla_config &c)
-{
-    int ksa, rows;
-    heads_slices(c, &ksa, &rows);
-    return ksa * ((c.n_heads * (c.nope_dim + R) + LR + 63) / 64) <= c.n_heads * TS && rows <= NT;
+    return *ksa * T <= W && *rows <= NT;
 }
 
 bool heads_prepare()

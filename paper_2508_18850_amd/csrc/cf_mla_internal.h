@@ -29,10 +29,9 @@ struct HeadsArgs {
 
 // first slot of the three exchange areas; returns the number of slots in all
 size_t heads_layout(const cf_mla_config &c, size_t (&first)[3]);
-// HeadsArgs::ksa and ::rows
-void heads_slices(const cf_mla_config &c, int *ksa, int *rows);
-// whether the projections' work items fit the workgroups (they do for every shape cf_mla_create takes)
-bool heads_fits(const cf_mla_config &c);
+// row slices of the projections and rows per slice (a multiple of eight, at most 512), such that slices x 64-column tiles
+// of [W_Q | W_KV] fit the 16 workgroups per head; false if they do not (no shape cf_mla_create takes)
+bool slices(const cf_mla_config &c, int *ksa, int *rows);
 // sets the kernel's LDS attribute; false if no workgroup fits a compute unit
 bool heads_prepare();
 // enqueues the kernel (a.W workgroups); returns the hipError_t of the launch
