@@ -63,7 +63,7 @@ constexpr int AS = 132;             // row stride (floats) of a_i in LDS
 constexpr int kMaxSplits = 32;      // token ranges per batch row at most
 // LDS, floats.  A: [NW][16][64]; B: [4][16][LJ]; C: query operands, new row, scores, maxima / sums, tile (later the second
 // half's accumulators); E1: a_i, [NW][16][128]; E2: [4][128]
-constexpr int kLdsC = 2 * kQops * 4 + LR + HT + 2 * HT * SSTR + 4 * HT, kLdsTile = kTile * KSTR / 2;
+constexpr int kLdsC = 2 * kQops * 4 + LR + NW * HT + 2 * HT * SSTR + 4 * HT, kLdsTile = kTile * KSTR / 2;
 constexpr size_t kLdsFloats = kLdsC + (kLdsTile > HT * L ? kLdsTile : HT * L);
 static_assert(kLdsFloats >= 16 * AS + NW * 16 * 128 && kLdsFloats * 4 <= 160 * 1024, "largest stage");
 constexpr float kNegBig = -1.0e30f;
@@ -331,8 +331,8 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
         h8 *qop_hi = reinterpret_cast<h8 *>(smem);                      // [kSteps][64]
         h8 *qop_lo = qop_hi + kQops;
         float *s_kn = smem + 2 * kQops * 4;                             // [LR] the new row
-        float *s_sn = s_kn + LR;                                        // [HT] its scores
-        float *s_S = s_sn + HT;                                         // [2][HT][SSTR] scores, per half of the dimensions
+        float *s_sn = s_kn + LR;                                        // [NW][HT] its scores, a wavefront's steps each
+        float *s_S = s_sn + NW * HT;                                         // [2][HT][SSTR] scores, per half of the dimensions
         float *s_ml = s_S + 2 * HT * SSTR;                              // [2][2][HT] maxima and sums of the two halves of the rows
         float *sO = s_ml + 4 * HT;                                      // [HT][L], at the end
         _Float16 *sK = reinterpret_cast<_Float16 *>(sO);                // [kTile][KSTR] cached rows
@@ -482,19 +482,17 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
         }
         MLA_STAMP(11);          // rows consumed
         if (s == 0) {
-            // score of the new token (its row is not rounded): 32 lanes per head, over the operands (step, group) of the head
-            const int h = min(h0 + (tid >> 5), h1 - 1), part = tid & 31;
+            // score of the new token (its row is not rounded): wavefront wv takes the operand steps wv, wv + 8, ...
             float d = 0.f;
-            for (int e4 = part; e4 < kSteps * 4; e4 += 32) {
-                const int m = e4 >> 2, g2 = e4 & 3, e = m * 64 + g2 * 16 + h;
-                const h8 hi = qop_hi[e], lo = qop_lo[e];
-                const f32x4 *kd = reinterpret_cast<const f32x4 *>(s_kn + score_dim(m, g2));
+            for (int m = wv; m < kSteps; m += NW) {
+                const h8 hi = qop_hi[m * 64 + lane], lo = qop_lo[m * 64 + lane];
+                const f32x4 *kd = reinterpret_cast<const f32x4 *>(s_kn + score_dim(m, g));
 #pragma unroll
                 for (int i = 0; i < 8; ++i) d = fmaf((float)hi[i] + (float)lo[i], kd[i >> 2][i & 3], d);
             }
-#pragma unroll
-            for (int off = 1; off < 32; off <<= 1) d += __shfl_xor(d, off);
-            if (part == 0 && h0 + (tid >> 5) < h1) s_sn[h] = d;
+            d += __shfl_xor(d, 16);
+            d += __shfl_xor(d, 32);
+            if (lane < HT) s_sn[wv * HT + c] = d;
         }
         // the two halves (and the new token) -> one partial (m, l, acc) per head
         lw += __shfl_xor(lw, 16);
@@ -518,7 +516,13 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
             for (int rr = 0; rr < 4; ++rr) {
                 const int h = 4 * g + rr;
                 if (h >= h0 && h < h1) {
-                    const float M0 = s_ml[h], M1 = s_ml[2 * HT + h], sn = s == 0 ? s_sn[h] : kNegBig, Mx = fmaxf(fmaxf(M0, M1), sn);
+                    float sn = kNegBig;
+                    if (s == 0) {
+                        sn = s_sn[h];
+#pragma unroll
+                        for (int w8 = 1; w8 < NW; ++w8) sn += s_sn[w8 * HT + h];
+                    }
+                    const float M0 = s_ml[h], M1 = s_ml[2 * HT + h], Mx = fmaxf(fmaxf(M0, M1), sn);
                     const float f0 = __builtin_amdgcn_exp2f(M0 - Mx), f1 = __builtin_amdgcn_exp2f(M1 - Mx);
                     const float fn = s == 0 ? __builtin_amdgcn_exp2f(sn - Mx) : 0.f;
                     const float *src = sO + h * L + 128 * kq + 8 * c;
