@@ -168,6 +168,23 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
+// Maximum / sum over the wavefront, the same value in every lane: four data-parallel-primitive steps inside each row of
+// 16 lanes, then the four row results are read out as scalars (no trip through the LDS crossbar).
+__device__ __forceinline__ float lane_of(float v, int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l)); }
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = fmaxf(v, dpp_move<0xB1>(v));
+    v = fmaxf(v, dpp_move<0x4E>(v));
+    v = fmaxf(v, dpp_move<0x141>(v));
+    v = fmaxf(v, dpp_move<0x140>(v));
+    return fmaxf(fmaxf(lane_of(v, 0), lane_of(v, 16)), fmaxf(lane_of(v, 32), lane_of(v, 48)));
+}
+__device__ __forceinline__ float wave_total(float v)
+{
+    v = row_sum<16>(v);
+    return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
+}
+
 // Exchange slots (partials handed from one workgroup to another).  A slot is a 64-bit
 // {fp32 bits, stamp} pair written by ONE 8-byte write-through store (agent scope), so a
 // reader sees either the old pair or the new one; the stamp of a launch is its number.
@@ -1475,111 +1492,122 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 
     {
         // ---- merge of the split-KV partials (Alg. 3 steps 5-7).  A pass handles up to NV * 512 values v = (batch row,
-        //      column).  NV == 1: value v is handled by SG threads, each folding every SG-th split with a running
-        //      maximum, MC splits per round trip; the SG (m, l, a) triples are then folded in split order through
-        //      LDS.  NV == 4 (more values than threads): a thread folds all splits of four values, so that a batch of
-        //      sixteen rows takes one pass (one round trip per MC splits) instead of four.  All loads of a round go
-        //      out together.
+        //      column).  NV == 1: value v is handled by SG threads, each adding every SG-th split; the SG sums are then
+        //      added through LDS.  NV > 1 (more values than threads): a thread adds all splits of NV values.  The maxima
+        //      and sums of a row's splits are fetched once per wavefront (a wavefront's values belong to one batch row):
+        //      lane s holds those of split s and, after two reductions over the wavefront, its weight e^(m_s - M) / L.
+        //      All loads of a round go out together, MC splits per round trip.  (Fetched by every thread beside each
+        //      value they were two thirds of the loads: tiny shape 17.2 -> 15.5 us, Llama-3-8B shape at batch 8 67.4 -> 65.9 us, 3000
+        //      columns at batch 5 29.1 -> 27.2 us; a branch around the loads past the last split costs more than they do.)
         const int V = p.B * HD;
         auto run = [&](auto nv_c, auto mc_c) {
             constexpr int NV = decltype(nv_c)::value, MC = decltype(mc_c)::value;
+            const bool wide = p.NS > 32;                                  // more splits than half a wavefront: two loads
             for (int v0 = 0; v0 < V; v0 += NT * NV) {
-                const int cv = min(NT * NV, V - v0);
+                const int cv = min(NT * NV, V - v0);                      // a multiple of 64
                 const int SG = NV == 1 ? max(1, min(NT / cv, p.NS)) : 1;
-                const int v = NV == 1 ? tid % cv : tid, sg = NV == 1 ? tid / cv : 0;
+                const int sg = NV == 1 ? __builtin_amdgcn_readfirstlane(tid / cv) : 0, v = tid - sg * cv;
                 if (sg < SG) {
-                    float mt[NV], lt[NV], at[NV];
+                    float at[NV], wgt[NV];
                     size_t src[NV];
                     int col[NV];
 #pragma unroll
                     for (int n = 0; n < NV; ++n) {
-                        mt[n] = kNegBig;
-                        lt[n] = 0.f;
                         at[n] = 0.f;
+                        wgt[n] = 0.f;
                         const int vi = min(v0 + v + n * NT, V - 1);        // a value past the end repeats the last one
                         const int b = vi / HD;
                         col[n] = vi - b * HD;
                         src[n] = ((size_t)b * p.nq + hq) * p.NS * PS;
                     }
                     for (int sb = sg; sb < p.NS; sb += MC * SG) {
+                        const bool head = sb == sg;                       // the first round
                         Spin spin;
-                        float mm[NV][MC], ll[NV][MC], aa[NV][MC];
+                        u32x2 vm[NV], vl[NV], va[NV][MC];
                         for (;;) {
-                            bool ok = true;
 #pragma unroll
-                            for (int n = 0; n < NV; ++n)
+                            for (int n = 0; n < NV; ++n) {
+                                if (head) {
+                                    const size_t o = src[n] + (size_t)min(wide ? lane : lane & 31, p.NS - 1) * PS;
+                                    vm[n] = x2.ld(o + (wide ? 0 : lane >> 5));
+                                    vl[n] = vm[n];
+                                    if (wide) vl[n] = x2.ld(o + 1);
+                                }
 #pragma unroll
                                 for (int k = 0; k < MC; ++k) {
-                                    const int s = sb + k * SG;
-                                    const size_t o = src[n] + (size_t)(s < p.NS ? s : sb) * PS;
-                                    const u32x2 vm = x2.ld(o), vl = x2.ld(o + 1), va = x2.ld(o + kP2Stride + col[n]);
-                                    ok &= (vm.y == stamp) & (vl.y == stamp) & (va.y == stamp);
-                                    mm[n][k] = __builtin_bit_cast(float, vm.x);
-                                    ll[n][k] = __builtin_bit_cast(float, vl.x);
-                                    aa[n][k] = __builtin_bit_cast(float, va.x);
+                                    const int s = sb + k * SG;            // (a load past the splits repeats one)
+                                    va[n][k] = x2.ld(src[n] + (size_t)(s < p.NS ? s : sb) * PS + kP2Stride + col[n]);
                                 }
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                            bool ok = true;
+#pragma unroll
+                            for (int n = 0; n < NV; ++n) {
+                                if (head) ok &= (vm[n].y == stamp) & (vl[n].y == stamp);
+#pragma unroll
+                                for (int k = 0; k < MC; ++k) ok &= va[n][k].y == stamp;
+                            }
                             if (ok || spin.expired(p)) break;
+                        }
+                        if (head) {
+#pragma unroll
+                            for (int n = 0; n < NV; ++n) {
+                                const float m = __builtin_bit_cast(float, vm[n].x);
+                                const float l = wide ? __builtin_bit_cast(float, vl[n].x) : __shfl(m, 32 + (lane & 31));
+                                const bool mine = lane < p.NS;            // (NS <= 32: lanes 32..63 hold sums)
+                                const float f = mine ? __builtin_amdgcn_exp2f(m - wave_max(mine ? m : kNegBig)) : 0.f;
+                                wgt[n] = f / wave_total(mine ? l * f : 0.f);
+                            }
                         }
 #pragma unroll
                         for (int n = 0; n < NV; ++n)
 #pragma unroll
                             for (int k = 0; k < MC; ++k) {
-                                if (sb + k * SG < p.NS) {
-                                    const float mn = fmaxf(mt[n], mm[n][k]);
-                                    const float fa = __builtin_amdgcn_exp2f(mt[n] - mn), fb = __builtin_amdgcn_exp2f(mm[n][k] - mn);
-                                    lt[n] = lt[n] * fa + ll[n][k] * fb;
-                                    at[n] = at[n] * fa + aa[n][k] * fb;
-                                    mt[n] = mn;
-                                }
+                                const int s = sb + k * SG;                // (uniform)
+                                const float w = lane_of(wgt[n], s & 63);
+                                if (s < p.NS) at[n] = fmaf(__builtin_bit_cast(float, va[n][k].x), w, at[n]);
                             }
                     }
-                    if (NV == 1) {
-                        red[(sg * cv + v) * 3 + 0] = mt[0];
-                        red[(sg * cv + v) * 3 + 1] = lt[0];
-                        red[(sg * cv + v) * 3 + 2] = at[0];
+                    if (NV == 1 && SG > 1) {
+                        red[sg * cv + v] = at[0];
                     } else {
 #pragma unroll
                         for (int n = 0; n < NV; ++n) {
                             const int vi = v0 + v + n * NT;
                             if (vi < V) {
-                                const float a = at[n] / lt[n];
-                                as[vi] = a;
-                                if (p.dbg_attn && c3 == 0 && rs == 0) p.dbg_attn[((size_t)(vi / HD) * p.nq + hq) * HD + col[n]] = a;
+                                as[vi] = at[n];
+                                if (p.dbg_attn && c3 == 0 && rs == 0) p.dbg_attn[((size_t)(vi / HD) * p.nq + hq) * HD + col[n]] = at[n];
                             }
                         }
                     }
                 }
-                lds_barrier();
-                if (NV == 1) {
+                if (NV == 1 && SG > 1) {
+                    lds_barrier();
                     if (tid < cv) {
-                        float mt = kNegBig, lt = 0.f, at = 0.f;
-                        for (int k = 0; k < SG; ++k) {
-                            const float mk = red[(k * cv + tid) * 3], lk = red[(k * cv + tid) * 3 + 1],
-                                        ak = red[(k * cv + tid) * 3 + 2];
-                            const float mn = fmaxf(mt, mk);
-                            const float fa = __builtin_amdgcn_exp2f(mt - mn), fb = __builtin_amdgcn_exp2f(mk - mn);
-                            lt = lt * fa + lk * fb;
-                            at = at * fa + ak * fb;
-                            mt = mn;
-                        }
-                        const float a = at / lt;
+                        float a = red[tid];
+                        for (int k = 1; k < SG; ++k) a += red[k * cv + tid];
                         as[v0 + tid] = a;
                         if (p.dbg_attn && c3 == 0 && rs == 0) {
                             const int b = (v0 + tid) / HD, c = (v0 + tid) - b * HD;
                             p.dbg_attn[((size_t)b * p.nq + hq) * HD + c] = a;
                         }
                     }
-                    lds_barrier();
                 }
             }
         };
         using std::integral_constant;
-        // (NV == 1 with eight splits per round trip was measured and is slower than four: a round is repeated as a
-        // whole until all its stamps are current, and the partials of a team do not arrive together)
-        if (V > NT)
-            run(integral_constant<int, 4>{}, integral_constant<int, 2>{});
-        else
+        if constexpr (BT > 4) {
+            if (V > 2 * NT)
+                run(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+            else if (V > NT)
+                run(integral_constant<int, 2>{}, integral_constant<int, 4>{});
+            else
+                run(integral_constant<int, 1>{}, integral_constant<int, 8>{});
+        } else if (p.NS * V > 4 * NT) {                                   // more than four splits per thread
+            run(integral_constant<int, 1>{}, integral_constant<int, 8>{});
+        } else {
             run(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+        }
         for (int e = V + tid; e < BT * HD; e += NT) as[e] = 0.f;
         lds_barrier();
     }

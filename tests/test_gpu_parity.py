@@ -380,3 +380,21 @@ def test_uneven_splits_of_the_projections(d_model, nq, nkv, hd, batch, kv_len):
         _log("plan %s" % r.blk.plan())
         check(res, ref, inp, kv_len, "packed" if packed else "rows")
         r.blk.close()
+
+
+# The merge of the split-KV partials: one split, splits that no thread count divides evenly, more splits than half a
+# wavefront, values in one, two and four per thread (batch rows x head_dim up to 512, 1024, 2048), empty splits (more
+# splits than cached rows).
+@pytest.mark.parametrize("hd,batch", [(64, 1), (64, 3), (64, 7), (64, 16), (128, 1), (128, 2), (128, 3), (128, 7), (128, 16)])
+@pytest.mark.parametrize("kv_splits", [1, 2, 32, 64])
+def test_merge_of_kv_splits(hd, batch, kv_splits):
+    shape = cf_inputs.BlockShape("s", 264, 4, 2, hd, 10000.0, 90)
+    _log("head_dim %d batch %d kv_splits %d" % (hd, batch, kv_splits))
+    inp = cf_inputs.make_inputs(shape, seed=80 + batch, batch=batch, kv_len=90, max_seq=99)
+    ref = {pos: oracle(inp, shape, pos) for pos in (90, 5)}
+    r = Runner(shape, batch, 99)
+    r.blk.set_tuning(kv_splits=kv_splits)
+    for pos in (90, 5):
+        res = r.run(inp, pos, out_fill=float("nan"), packed=True)
+        check(res, ref[pos], inp, pos, "splits %d pos %d" % (kv_splits, pos))
+    r.blk.close()
