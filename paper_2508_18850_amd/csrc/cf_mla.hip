@@ -721,7 +721,7 @@ struct cf_mla_s {
     cf_mla_config cfg;
     int W = 0;
     char *ws = nullptr;
-    size_t ws_bytes = 0;
+    size_t ws_bytes = 0, clear_bytes = 0;            // clear_bytes: counters, flags and stamped slots, at the front
     uint64_t *slots = nullptr, *hslots = nullptr;    // stamped slots of the token-range kernel, of the head-team kernel
     float *data = nullptr;          // values of the token-range kernel's other hand-overs
     uint32_t *flags = nullptr;      // their flags
@@ -806,13 +806,14 @@ int cf_mla_create(const cf_mla_config *cfg, cf_mla *out)
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t head_b = up(256 + (size_t)W * kCounterStride * sizeof(unsigned long long)), flag_b = 4 * 256 * sizeof(uint32_t);
     const size_t slot_b = up(nslots * 8), hslot_b = up(nhslots * 8), data_b = up(ndata * 4), z_b = up(B * nh * L * 4), q_b = up(nh * LR * 4);
-    t->ws_bytes = head_b + flag_b + slot_b + hslot_b + data_b + z_b + q_b + nh * TS * (2 + L) * sizeof(float);
+    t->clear_bytes = head_b + flag_b + slot_b + hslot_b;
+    t->ws_bytes = t->clear_bytes + data_b + z_b + q_b + nh * TS * (2 + L) * sizeof(float);
     if (slot_b > 0xfffffff0ull || data_b > 0xfffffff0ull) {
         delete t;
         return CF_EUNSUPPORTED;
     }
     hipError_t e = hipMalloc(reinterpret_cast<void **>(&t->ws), t->ws_bytes);
-    if (e == hipSuccess) e = hipMemset(t->ws, 0, t->ws_bytes);
+    if (e == hipSuccess) e = hipMemset(t->ws, 0, t->clear_bytes);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         if (t->ws) (void)hipFree(t->ws);
@@ -924,7 +925,7 @@ int cf_mla_status(cf_mla t, void *stream)
         return CF_EHIP;
     }
     if (flag) {
-        e = hipMemset(t->ws, 0, t->ws_bytes);        // launch counters and all stamps start afresh
+        e = hipMemset(t->ws, 0, t->clear_bytes);     // launch counters and all stamps start afresh
         if (e == hipSuccess) e = hipDeviceSynchronize();
         return e == hipSuccess ? CF_ETIMEOUT : CF_EHIP;
     }
