@@ -21,7 +21,9 @@ if ROOT not in sys.path:
 # HBM bytes per launch from rocprofv3 counters, (FETCH_SIZE KiB x 2.0000 + WRITE_SIZE KiB) x 1024
 # (profiles/fused_mla_deepseek_v2_lite_kv4096.md), DeepSeek-V2-Lite shape; None where no counter run exists
 MEASURED_TRAFFIC = {
-    "b16_kv4096": 243688448,            # 100782.5, 36412.0
+    "b1_kv4096": 68172652,              # 32678.9, 1217.0
+    "b4_kv4096": 84325868,              # 36158.9, 10031.6
+    "b16_kv4096": 153228398,            # 63070.0, 23497.1
 }
 
 

@@ -168,7 +168,7 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
     // output projection: G heads x NC3 column blocks x RS3 row splits per team.  A member walks its items chunk by chunk
     // (512 columns); the first chunk is on its way since the attention, every further one costs its bytes and a load
     // latency, about that of 96 rows (2.4 us a chunk of 8 rows: 2056 columns as 2 blocks of 3 chunks x 8 row splits took
-    // 27.3 us in all at batch 3, as 5 blocks of one chunk x 2 row splits 23.4 us).
+    // 27.5 us in all at batch 3, as 5 blocks of one chunk x 2 row splits 22.3 us).
     {
         const int nch = h->nch;
         int best_nc = 0, best_rs = 0;
