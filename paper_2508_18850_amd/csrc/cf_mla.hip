@@ -139,7 +139,8 @@ __device__ __forceinline__ void wait_flag(const Exchange &x, const uint32_t *fla
     asm volatile("" ::: "memory");              // what the flag announces is fetched behind it
 }
 
-// v = hi + lo with both parts fp16: an MFMA operand whose fp32 value must not lose bits
+// v = hi + lo with both parts fp16, for the query of the cached rows' scores: 22 bits of values around one, an absolute step
+// of 2^-24 below, no more than 65504.
 __device__ __forceinline__ void split_hi_lo(const float (&v)[8], h8 &hi, h8 &lo)
 {
 #pragma unroll
@@ -147,6 +148,57 @@ __device__ __forceinline__ void split_hi_lo(const float (&v)[8], h8 &hi, h8 &lo)
         hi[k] = (_Float16)v[k];
         lo[k] = (_Float16)(v[k] - (float)hi[k]);
     }
+}
+
+// An fp32 operand of a matrix product that has to count in full: every row of the operand (lane c of each contraction
+// group holds row c) is scaled by a power of two that brings its largest value into [2^14, 2^15) and each value is cut into
+// three fp16 parts of eleven bits.  Down to 2^-15 of the row's largest value the parts add up to the value exactly, below
+// that to 2^-38 of the largest one, whatever the row's magnitude (a pair without the scale: 2e-3 of a value at 1e-5, NaN
+// above 65504).  The scale is taken out where the wavefronts' partial products are added.  Three such products cost 0.65 us
+// of a step (batch 2 / 4 / 16: 32.4 / 33.5 / 44.6 us with unscaled pairs, 33.1 / 34.1 / 45.25 us); rounded parts, each with its
+// conversion back, and a scale taken out of every accumulator cost 1.45 us.
+struct Split3 {
+    h8 hi, mid, lo;
+};
+// largest magnitude of row c among this lane's values and those of the other contraction groups
+__device__ __forceinline__ float row_max(float m)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, m);
+    const auto t = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    const unsigned v = __builtin_bit_cast(unsigned, fmaxf(__builtin_bit_cast(float, (unsigned)t[0]), __builtin_bit_cast(float, (unsigned)t[1])));
+    const auto q = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return fmaxf(__builtin_bit_cast(float, (unsigned)q[0]), __builtin_bit_cast(float, (unsigned)q[1]));
+}
+__device__ __forceinline__ float max_abs(const float (&v)[8], float m)
+{
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(v[k]));
+    return m;
+}
+// exponent of the scale of a row from its largest magnitude (at most 126: the inverse is a normal number)
+__device__ __forceinline__ int scale_exp(float m) { return min(15 - (m <= 3.402823466e38f ? __builtin_amdgcn_frexp_expf(m) : 128), 126); }
+__device__ __forceinline__ Split3 split3(const float (&v)[8], int e, float m)
+{
+    u32x4 p[3];
+    float r[8], minus1 = -1.f;
+    asm("" : "+s"(minus1));                                               // (kept a product: one v_fma_mix_f32 in place of a conversion and a difference)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) r[k] = __builtin_amdgcn_ldexpf(v[k], e);
+#pragma unroll
+    for (int n = 0; n < 3; ++n)
+#pragma unroll
+        for (int k = 0; k < 8; k += 2) {
+            const auto t = __builtin_amdgcn_cvt_pkrtz(r[k], r[k + 1]);     // (cut off, not rounded: what is left keeps its sign)
+            p[n][k / 2] = __builtin_bit_cast(uint32_t, t);
+            r[k] = fmaf((float)t[0], minus1, r[k]);
+            r[k + 1] = fmaf((float)t[1], minus1, r[k + 1]);
+        }
+    Split3 s = {__builtin_bit_cast(h8, p[0]), __builtin_bit_cast(h8, p[1]), __builtin_bit_cast(h8, p[2])};
+    if (__any(!(m <= 3.402823466e38f)))                                   // an infinity stays one, in the first part
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (!(fabsf(v[k]) <= 3.402823466e38f)) s.mid[k] = s.lo[k] = (_Float16)0.f;
+    return s;
 }
 
 __device__ __forceinline__ float ror8_add(float v)     // v + the value of the lane 8 further in the row of 16 lanes
@@ -174,6 +226,7 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
 {
     extern __shared__ __align__(16) float smem[];                    // carved anew by every stage
     __shared__ float s_rope[R];                         // cos, sin of the rotary angles
+    __shared__ __align__(16) float s_f[16 * NW];        // 1 / scale of operand row (batch row) and wavefront
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, w = blockIdx.x;
     // workgroup w runs on die w % 8; with a multiple of eight heads a head's members share one die and its L2
     const int head = a.nh % 8 == 0 ? w % 8 + 8 * (w / 8 / TS) : w / TS, j = a.nh % 8 == 0 ? w / 8 % TS : w % TS;
@@ -279,14 +332,18 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
             for (int k = 0; k < kMaxSlices; ++k)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) q8[e] += mine && k < a.ksa ? p[k][e >> 2][e & 3] : 0.f;
-            h8 hi, lo, f8[8];
-            split_hi_lo(q8, hi, lo);
+            h8 f8[8];
+            const float m = row_max(max_abs(q8, 0.f));
+            const int e = scale_exp(m);
+            const Split3 q = split3(q8, e, m);
+            if (lane < 16) s_f[lane * NW + wv] = __builtin_amdgcn_ldexpf(1.f, -e);
             transpose8(wup, f8);
             f32x4 acc[8];
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) {
-                acc[jj] = mfma16(hi, f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
-                acc[jj] = mfma16(lo, f8[jj], acc[jj]);
+                acc[jj] = mfma16(q.hi, f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
+                acc[jj] = mfma16(q.mid, f8[jj], acc[jj]);
+                acc[jj] = mfma16(q.lo, f8[jj], acc[jj]);
             }
             if (c < 4)
 #pragma unroll
@@ -313,7 +370,8 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
         {
             const int b = tid / LJ, cc = tid % LJ;
             const float *src = smem + NW * 16 * 64 + tid;
-            const float sum = (src[0] + src[16 * LJ]) + (src[2 * 16 * LJ] + src[3 * 16 * LJ]);
+            const f32x4 f = *reinterpret_cast<const f32x4 *>(s_f + b * NW);
+            const float sum = (src[0] * f[0] + src[16 * LJ] * f[1]) + (src[2 * 16 * LJ] * f[2] + src[3 * 16 * LJ] * f[3]);
             if (b < B) X.st1(a.xq + ((size_t)b * a.nh + head) * LR + LJ * j + cc, sum);
         }
         post(fB + head * TS + j, x.stamp);
@@ -323,7 +381,7 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
     // ---- C: attention.  Work item (b, s, hg): cached rows [t0, t1) of batch row b against the queries of the heads
     //      [h0, h1).  A tile is 64 rows, read from memory once and kept in LDS for both products.  Scores: wavefront (dh, tq)
     //      takes 16 rows and 288 of the 576 dimensions, S^T = K Q^T as a 16 x 16 tile (rows = tokens, columns = heads),
-    //      the query as a pair of fp16 operands (value = hi + lo, so the fp32 query loses nothing).  Online softmax per
+    //      the query as a pair of fp16 operands (22 bits).  Online softmax per
     //      head over the 32 rows of one half of the tile, each half for itself (its four wavefronts hold the same state, so
     //      nothing but the scores goes through LDS).  Weighted sum: wavefront (th, kq) takes the latent dimensions
     //      [128 kq, +128) of the half th: A = probabilities (fp16), B = the rows, eight at a time transposed in the lane.
@@ -375,6 +433,7 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
             qv[k][0] = X.ld4(src);
             qv[k][1] = X.ld4(src + 4);
         }
+        float qf[NE][8];                                                // this thread's entries in fp32, for the new token's score
         float kn[2] = {0.f, 0.f};
         if (s == 0)                                                     // (uniform)
 #pragma unroll
@@ -389,11 +448,10 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
 #pragma unroll
         for (int k = 0; k < NE; ++k) {
             const int e = tid + NT * k, c2 = e & 15;
-            float v[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = c2 >= h0 && c2 < h1 ? qv[k][i >> 2][i & 3] * a.scale_log2e : 0.f;
+            for (int i = 0; i < 8; ++i) qf[k][i] = c2 >= h0 && c2 < h1 ? qv[k][i >> 2][i & 3] * a.scale_log2e : 0.f;
             h8 hi, lo;
-            split_hi_lo(v, hi, lo);
+            split_hi_lo(qf[k], hi, lo);
             if (e < kQops) {
                 qop_hi[e] = hi;
                 qop_lo[e] = lo;
@@ -486,14 +544,16 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
         }
         MLA_STAMP(11);          // rows consumed
         if (s == 0) {
-            // score of the new token (its row is not rounded): wavefront wv takes the operand steps wv, wv + 8, ...
+            // score of the new token (neither its row nor the query is rounded): wavefront wv takes the operand steps wv,
+            // wv + 8, ..., whose entries its lanes have built
             float d = 0.f;
-            for (int m = wv; m < kSteps; m += NW) {
-                const h8 hi = qop_hi[m * 64 + lane], lo = qop_lo[m * 64 + lane];
-                const f32x4 *kd = reinterpret_cast<const f32x4 *>(s_kn + score_dim(m, g));
 #pragma unroll
-                for (int i = 0; i < 8; ++i) d = fmaf((float)hi[i] + (float)lo[i], kd[i >> 2][i & 3], d);
-            }
+            for (int k = 0; k < NE; ++k)
+                if (wv + NW * k < kSteps) {                             // (uniform)
+                    const f32x4 *kd = reinterpret_cast<const f32x4 *>(s_kn + score_dim(wv + NW * k, g));
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) d = fmaf(qf[k][i], kd[i >> 2][i & 3], d);
+                }
             d += __shfl_xor(d, 16);
             d += __shfl_xor(d, 32);
             if (lane < HT) s_sn[wv * HT + c] = d;
@@ -615,8 +675,8 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
     MLA_STAMP(6);           // z posted
 
     // ---- E1: a_head = z W_Down[head] (contraction over 512: 64 rows per wavefront, added through LDS), then the rows of
-    //      W_O that belong to this head (contraction over v <= 128: wavefront (part, st) 32 rows, part: high or low half of
-    //      the fp16 pairs of a), column block j of the output
+    //      W_O that belong to this head (contraction over v <= 128: wavefront (part, st) 32 rows, part: first and third, or
+    //      second, of the fp16 parts of a), column block j of the output
     {
         float *s_a = smem, *s_red = smem + 16 * AS;                     // [16][AS], [NW][16][128]
         wait_flag(x, fD + head * TS + min(lane, TS - 1), lane < TS);
@@ -628,21 +688,30 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
         f32x4 acc[8];
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj) acc[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float v[2][8], vmax = 0.f;
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
-            float v[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = zv[st][i >> 2][i & 3];
-            h8 hi, lo, f8[8];
-            split_hi_lo(v, hi, lo);
+            for (int i = 0; i < 8; ++i) v[st][i] = zv[st][i >> 2][i & 3];
+            vmax = max_abs(v[st], vmax);
+        }
+        vmax = row_max(vmax);
+        const int ez = scale_exp(vmax);
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+            h8 f8[8];
+            const Split3 z = split3(v[st], ez, vmax);
             transpose8(wdn + 8 * st, f8);
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) {
-                acc[jj] = mfma16(hi, f8[jj], acc[jj]);
-                acc[jj] = mfma16(lo, f8[jj], acc[jj]);
+                acc[jj] = mfma16(z.hi, f8[jj], acc[jj]);
+                acc[jj] = mfma16(z.mid, f8[jj], acc[jj]);
+                acc[jj] = mfma16(z.lo, f8[jj], acc[jj]);
             }
         }
-        auto spill = [&]() {
+        // the wavefronts' partial products with the inverse of their rows' scales, and their sum
+        auto spill = [&](int e) {
+            if (lane < 16) s_f[lane * NW + wv] = __builtin_amdgcn_ldexpf(1.f, -e);
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) {
                 float *dst = s_red + (wv * 16 + 4 * g + rr) * 128 + 8 * c;
@@ -650,14 +719,16 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
                 *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{acc[4][rr], acc[5][rr], acc[6][rr], acc[7][rr]};
             }
         };
-        spill();
-        lds_sync();
-        for (int i = tid; i < 16 * 128; i += NT) {
+        auto total = [&](int i) {
+            const f32x4 f[2] = {*reinterpret_cast<const f32x4 *>(s_f + i / 128 * NW), *reinterpret_cast<const f32x4 *>(s_f + i / 128 * NW + 4)};
             float sum = 0.f;
 #pragma unroll
-            for (int w8 = 0; w8 < NW; ++w8) sum += s_red[w8 * 16 * 128 + i];
-            s_a[i / 128 * AS + i % 128] = sum;
-        }
+            for (int w8 = 0; w8 < NW; ++w8) sum = fmaf(s_red[w8 * 16 * 128 + i], f[w8 >> 2][w8 & 3], sum);
+            return sum;
+        };
+        spill(ez);
+        lds_sync();
+        for (int i = tid; i < 16 * 128; i += NT) s_a[i / 128 * AS + i % 128] = total(i);
         lds_sync();
         MLA_STAMP(8);           // a_head ready
         {
@@ -665,23 +736,22 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
             float v[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] = s_a[c * AS + 32 * st + 8 * g + i];
-            h8 hi, lo, f8[8];
-            split_hi_lo(v, hi, lo);
-            const h8 mine = wv < 4 ? hi : lo;
+            h8 f8[8];
+            const float m = row_max(max_abs(v, 0.f));
+            const int e = scale_exp(m);
+            const Split3 q = split3(v, e, m);
             transpose8(wor, f8);
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) acc[jj] = mfma16(mine, f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
+            for (int jj = 0; jj < 8; ++jj) acc[jj] = mfma16(wv < 4 ? q.hi : q.mid, f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
+            if (wv < 4)
+#pragma unroll
+                for (int jj = 0; jj < 8; ++jj) acc[jj] = mfma16(q.lo, f8[jj], acc[jj]);
+            spill(e);
         }
-        spill();
         lds_sync();
         for (int i = tid; i < B * 128; i += NT) {
             const int b = i / 128, cc = i % 128, col = j * pcsE * 8 + cc;
-            if (cc < 8 * pcsE && col < a.D) {
-                float sum = 0.f;
-#pragma unroll
-                for (int w8 = 0; w8 < NW; ++w8) sum += s_red[w8 * 16 * 128 + i];
-                cf::team::put(r, ((size_t)head * B + b) * a.D + col, sum, x.stamp);
-            }
+            if (cc < 8 * pcsE && col < a.D) cf::team::put(r, ((size_t)head * B + b) * a.D + col, total(i), x.stamp);
         }
     }
     MLA_STAMP(10);          // E1 done

@@ -240,3 +240,39 @@ def test_head_team_kernel_edges(heads, d_model, nope, v, kv_len):
     _log("heads %d d_model %d nope %d v %d L %d" % (heads, d_model, nope, v, kv_len))
     inp = cf_inputs.make_mla_inputs(shape, seed=heads + kv_len, batch=1, kv_len=kv_len)
     check(run(shape, inp, kv_len), oracle(shape, inp, kv_len), inp, kv_len, "heads %d L %d" % (heads, kv_len))
+
+
+# Operands of the small products far from one, their counterparts scaled the other way: q_nope (absorbed by W_Up), z and a
+# (multiplied by W_Down and W_O) at 1e-5 and below, q_nope and a above the fp16 range, x of subnormal fp16 values.
+# Powers of two on the inputs (nope / rope: the two parts of W_Q).
+MAGNITUDES = {
+    "small q_nope": dict(x=-9, nope=-8, rope=9, w_kv=9, w_up=13),
+    "large q_nope": dict(x=6, nope=12, rope=-6, w_kv=-12, w_up=-10, cache=-9, w_down=9),
+    "small a": dict(w_kv=-7, cache=-7, w_down=-8, w_o=12),
+    "large a": dict(nope=-8, rope=-8, w_kv=10, cache=10, w_down=11, w_o=-8),
+    "subnormal x": dict(x=-16, nope=15, rope=15, w_kv=15),
+}
+
+
+@pytest.mark.parametrize("batch", [1, 2, 16])
+@pytest.mark.parametrize("name", list(MAGNITUDES))
+def test_operands_of_any_magnitude(name, batch):
+    """q_lat is two fp32 sums in a row (512 and 128 terms), and nothing on its way is rounded to fewer bits: the error of a
+    sum of n terms grows as sqrt(n) * 2^-24, 1.4e-6 and 0.7e-6 of the result.  z and out: fp16 probabilities and an
+    fp16 result, 2^-12 each, judged as a relative RMS because the results are not of order one."""
+    shape, kv_len, s = cf_inputs.MlaShape("s", 512, 16, 128, 64, 512, 128, 10000.0, 0), 300, MAGNITUDES[name]
+    _log("%s batch %d" % (name, batch))
+    inp = cf_inputs.make_mla_inputs(shape, seed=400 + batch, batch=batch, kv_len=kv_len)
+    w_q = inp["w_q"].reshape(shape.d_model, shape.n_heads, -1)
+    w_q[:, :, :shape.nope_dim] *= np.float16(2.0 ** s.get("nope", 0))
+    w_q[:, :, shape.nope_dim:] *= np.float16(2.0 ** s.get("rope", 0))
+    for k in ("x", "w_kv", "w_up", "w_down", "w_o"):
+        inp[k] = (inp[k].astype(np.float32) * 2.0 ** s.get(k, 0)).astype(np.float16)
+    inp["kv_cache"] = (inp["kv_cache"].astype(np.float32) * 2.0 ** s.get("cache", 0)).astype(np.float16)
+    ref, got = oracle(shape, inp, kv_len), run(shape, inp, kv_len)
+    _log("   |q_nope W_Up| %.1e |z| %.1e |a| %.1e |out| %.1e" % tuple(np.abs(ref[k]).max() for k in ("q_lat", "z", "a", "out")))
+    for what, tol in (("q_lat", 2e-6), ("z", 1e-3), ("out", 1e-3)):
+        g = got[what].astype(np.float64)
+        rel = np.sqrt(np.mean((g - ref[what]) ** 2) / np.mean(ref[what] ** 2))
+        _log("   %s: relative RMS %.2e" % (what, rel))
+        assert np.isfinite(g).all() and rel < tol, what
