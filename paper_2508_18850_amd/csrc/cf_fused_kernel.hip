@@ -463,22 +463,44 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         c = i - b * P8;
         return i < npc && 8 * c < nrows;
     };
-    constexpr int XR = BT + 1;                                    // x values per thread kept in registers
-    const bool x_in_regs = !XV && BT * p.RPS <= XR * NT;
-    // (all of them unconditional: a load inside a branch would be waited for at the branch's end)
-    uint16_t xr[XR];
-    u32x2 xs2[XR];                                                // layer > 0: the stamped slots of the same values
-    bool xv[XR];
+    // The input of a stack (stamped slots, in its first layer x) value by value, XR per thread and round trip, the batch's own
+    // rows only; the first trip is requested here.  One trip for the whole
+    // slice or, past XR * 512 values, a wait for every value by itself took, us a layer of the one-launch stack:
+    // Llama-3-8B shape, 2048 rows, batch 2 / 4 / 16 31.3 / 34.1 / 57.9, Llama-2-70B shape, 1024 rows, batch 4 / 16 72.5 / 107.4;
+    // so they take 30.3 / 28.3 / 49.4 and 63.8 / 96.0.  (MFMA tiles with 17 / 16 / 14 values per trip: batch 16 49.6 / 49.4 /
+    // 48.9, Llama-2-7B shape, batch 8 59.2 / 59.2 / 58.2 against 57.0 with 9: the weights in flight leave few registers.)
+    constexpr int XR = MF ? 9 : BT + 1;
+    const int xn = p.B * p.RPS;
+    const float inv_rps = __builtin_amdgcn_rcpf((float)p.RPS);
+    auto x_at = [&](int i, int &b, int &r) {                      // value i: row b of the batch, row r of the slice
+        b = BT == 1 ? 0 : (int)(((float)i + 0.5f) * inv_rps);     // (exact: i < 2^18, the quotient is 0.5 / RPS away from an integer)
+        r = i - b * p.RPS;
+        return i < xn && r < nrows;
+    };
+    u32x2 xs2[XR];                                                // stamped slots, or the values as they are
     const bool from_slots = STACK && layer > 0;
     const Xbuf xsl(xin ? (const void *)xin : (const void *)p.p1);
-    // (the same number of loads on both paths, so that the waits behind this branch stay exact)
+    // (all of them unconditional: a load inside a branch would be waited for at the branch's end)
+    auto x_slots = [&](int i0) {
+        int i = i0 + tid;
+        asm volatile("" : "+v"(i));                               // (addresses are computed anew, not kept in registers)
 #pragma unroll
-    for (int q = 0; q < XR; ++q) {
-        const int i = tid + q * NT, b = BT == 1 ? 0 : i / p.RPS, r = i - b * p.RPS;
-        xv[q] = x_in_regs && i < BT * p.RPS && b < p.B && r < nrows;
-        xr[q] = 0;
-        xs2[q] = u32x2{0u, 0u};
-    }
+        for (int q = 0; q < XR; ++q) {
+            int b, r;
+            const bool in = x_at(i + q * NT, b, r);
+            xs2[q] = xsl.ld(in ? (size_t)b * p.D + r0 + r : 0);
+        }
+    };
+    auto x_values = [&](int i0) {
+        int i = i0 + tid;
+        asm volatile("" : "+v"(i));
+#pragma unroll
+        for (int q = 0; q < XR; ++q) {
+            int b, r;
+            const bool in = x_at(i + q * NT, b, r);
+            xs2[q].x = p.x[in ? (size_t)b * p.D + r0 + r : 0];
+        }
+    };
     if constexpr (XV) {
 #pragma unroll
         for (int q = 0; q < XP; ++q) {
@@ -486,42 +508,26 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             const bool in = piece_of(tid + q * NT, b, c);
             xp[q] = xg4[in ? ((size_t)b * p.D + r0) / 8 + c : 0];
         }
-    } else if (from_slots) {
-#pragma unroll
-        for (int q = 0; q < XR; ++q) {
-            const int i = tid + q * NT, b = BT == 1 ? 0 : i / p.RPS, r = i - b * p.RPS;
-            xs2[q] = xsl.ld(xv[q] ? (size_t)b * p.D + r0 + r : 0);
-        }
     } else {
+        // (the same number of loads on both paths, so that the waits behind this branch stay exact)
 #pragma unroll
-        for (int q = 0; q < XR; ++q) {
-            const int i = tid + q * NT, b = BT == 1 ? 0 : i / p.RPS, r = i - b * p.RPS;
-            xr[q] = p.x[xv[q] ? (size_t)b * p.D + r0 + r : 0];
-        }
+        for (int q = 0; q < XR; ++q) xs2[q] = u32x2{0u, 0u};
+        if (from_slots)
+            x_slots(0);
+        else
+            x_values(0);
     }
     // RMSNorm in front of the projection (when a weight vector is given): the projection is linear, so the
     // weights gamma go into the staged slice of x and the factor 1/sqrt(mean(x^2) + eps) of a row goes into
     // the partial sums when they are stored.  Every workgroup takes the mean square from the whole row
     // (D*2 bytes: one or two 16-byte loads per thread, issued here with the other small loads).
     const bool norm = kLayer && p.gamma != nullptr;
-    const uint16_t *gsrc = norm ? p.gamma : p.x;                  // any readable address when there is no weight
-    uint16_t gr[XR];
+    if (XV && norm) {       // (a wait behind this branch counts the loads of the path without it: nothing drains)
 #pragma unroll
-    for (int q = 0; q < XR; ++q) gr[q] = 0;
-    if (norm) {             // (a wait behind this branch counts the loads of the path without it: nothing drains)
-        if constexpr (XV) {
-#pragma unroll
-            for (int q = 0; q < XP; ++q) {
-                int b, c;
-                const bool in = piece_of(tid + q * NT, b, c);
-                gp[q] = gg4[in ? r0 / 8 + c : 0];
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < XR; ++q) {
-                const int i = tid + q * NT, b = BT == 1 ? 0 : i / p.RPS, r = i - b * p.RPS;
-                gr[q] = gsrc[xv[q] ? r0 + r : 0];
-            }
+        for (int q = 0; q < XP; ++q) {
+            int b, c;
+            const bool in = piece_of(tid + q * NT, b, c);
+            gp[q] = gg4[in ? r0 / 8 + c : 0];
         }
     }
     float *nrm = red + MAXI * NW * BT * HD;                       // [NW][BT] sums of squares, one per wavefront and row
@@ -594,29 +600,10 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         cnt0 = launches + 1ull;
     }
     const uint32_t stamp = stamp_of(cnt0, layer);
-    if (from_slots) {
-        // The slots carry the stamp of the previous layer.  A workgroup whose projection nobody waits for (no
-        // column block of its own) may arrive here after its sources have moved on and stamped newer values:
-        // any stamp from the previous layer's up to the last layer's of this launch is taken.
-        const uint32_t want = stamp_of(cnt0, layer - 1);
-        Spin spin;
-        for (;;) {
-            bool ok = true;
-#pragma unroll
-            for (int q = 0; q < XR; ++q) ok &= !xv[q] | ((uint32_t)(xs2[q].y - want) <= (uint32_t)n_layers);
-            if (ok || spin.expired(p)) break;
-#pragma unroll
-            for (int q = 0; q < XR; ++q) {
-                const int i = tid + q * NT, b = BT == 1 ? 0 : i / p.RPS, r = i - b * p.RPS;
-                xs2[q] = xsl.ld(xv[q] ? (size_t)b * p.D + r0 + r : 0);
-            }
-        }
-    }
     // MF: the value goes to row b, column r of the operand array as fp16; without RMSNorm that is x itself,
     // with it the product x * gamma is kept as high + low part, so that nothing is rounded away
-    auto stage = [&](int i, float v) {
+    auto stage = [&](int i, int b, int r, float v) {
         if constexpr (MF) {
-            const int b = i / p.RPS, r = i - b * p.RPS;
             const _Float16 hi = (_Float16)v;
             xh[b * XS + r] = hi;
             if (norm) xl[b * XS + r] = (_Float16)(v - (float)hi);
@@ -624,7 +611,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             xs[i] = v;
         }
     };
-    if (XV && xvec) {
+    if (xvec) {
         // (rows past the batch are left as they are: what they give lands in rows of the product nobody reads)
         auto stage_piece = [&](int b, int c, const uint4 &xw, const uint4 &gw, bool in) {
             const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -659,30 +646,44 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             const bool in = piece_of(i, b, c);
             stage_piece(b, c, xg4[in ? ((size_t)b * p.D + r0) / 8 + c : 0], gg4[in ? r0 / 8 + c : 0], in);
         }
-    } else if (x_in_regs) {
-#pragma unroll
-        for (int q = 0; q < XR; ++q) {
-            const int i = tid + q * NT;
-            const float xval = from_slots ? __builtin_bit_cast(float, xs2[q].x) : h2f(xr[q]);
-            if (i < BT * p.RPS) stage(i, xv[q] ? xval * (norm ? h2f(gr[q]) : 1.f) : 0.f);
-        }
-    } else {
+    } else if constexpr (STACK) {
+        // The slots carry the stamp of the previous layer.  A workgroup whose projection nobody waits for (no
+        // column block of its own) may arrive here after its sources have moved on and stamped newer values:
+        // any stamp from the previous layer's up to the last layer's of this launch is taken.
         const uint32_t want = stamp_of(cnt0, layer - 1);
-        for (int i = tid; i < BT * p.RPS; i += NT) {
-            const int b = i / p.RPS, r = i - b * p.RPS;
-            const bool in = b < p.B && r < nrows;
-            float xval = 0.f;
-            if (in && from_slots) {
+        for (int trip = 0; trip < xn; trip += XR * NT) {          // (uniform)
+            int i0 = trip;
+            asm volatile("" : "+s"(i0));                          // (the addresses of a trip are not kept for the next)
+            if (from_slots) {
+                if (i0 > 0) x_slots(i0);
                 Spin spin;
                 for (;;) {
-                    const u32x2 v = xsl.ld((size_t)b * p.D + r0 + r);
-                    xval = __builtin_bit_cast(float, v.x);
-                    if ((uint32_t)(v.y - want) <= (uint32_t)n_layers || spin.expired(p)) break;
+                    bool ok = true;
+#pragma unroll
+                    for (int q = 0; q < XR; ++q) {
+                        int b, r;
+                        ok &= !x_at(i0 + tid + q * NT, b, r) | ((uint32_t)(xs2[q].y - want) <= (uint32_t)n_layers);
+                    }
+                    if (ok || spin.expired(p)) break;
+                    x_slots(i0);
                 }
-            } else if (in) {
-                xval = h2f(p.x[(size_t)b * p.D + r0 + r]);
+            } else if (i0 > 0) {
+                x_values(i0);
             }
-            stage(i, in ? xval * (norm ? h2f(gsrc[r0 + r]) : 1.f) : 0.f);
+#pragma unroll
+            for (int q = 0; q < XR; ++q) {
+                int b, r;
+                const int i = i0 + tid + q * NT;
+                const bool in = x_at(i, b, r);
+                const float v = from_slots ? __builtin_bit_cast(float, xs2[q].x) : h2f((uint16_t)xs2[q].x);
+                if (i < xn) stage(i, b, r, in ? v : 0.f);
+            }
+        }
+    } else {
+        for (int i = tid; i < xn; i += NT) {                      // (slices that are no multiples of eight rows)
+            int b, r;
+            const bool in = x_at(i, b, r);
+            stage(i, b, r, in ? h2f(p.x[(size_t)b * p.D + r0 + r]) * (norm ? h2f(p.gamma[r0 + r]) : 1.f) : 0.f);
         }
     }
     if (MF && !xvec) {

@@ -254,3 +254,27 @@ def test_layer_with_uneven_slices(d_model, nq, nkv, hd, batch):
     gamma = gamma_for(shape, 9)
     res = run_layer(shape, batch, inp, kv_len, gamma, 1e-5, True, True)
     check(res, reference(shape, inp, kv_len, gamma, 1e-5, True), inp, kv_len, "uneven")
+
+
+# Slices of 33 rows, not a multiple of eight: x (and the norm's weights) staged value by value.
+@pytest.mark.parametrize("norm", [False, True])
+@pytest.mark.parametrize("hd,batch", [(128, 1), (128, 2), (128, 9), (128, 16), (64, 3), (64, 16)])
+def test_slices_that_are_no_multiple_of_eight_rows(hd, batch, norm, monkeypatch):
+    import paper_2508_18850_amd as cf
+
+    class Tuned(cf.DecodeBlock):
+        def __init__(self, *args, **kwargs):
+            super().__init__(*args, **kwargs)
+            self.set_tuning(k_splits=32)
+
+        def close(self):
+            assert self.plan()["rows_per_split"] == 33
+            super().close()
+
+    monkeypatch.setattr(cf, "DecodeBlock", Tuned)
+    shape, kv_len = cf_inputs.BlockShape("s", 1032, 8, 8, hd, 10000.0, 40), 40
+    _log("33-row slices, head_dim %d batch %d norm %s" % (hd, batch, norm))
+    inp = cf_inputs.make_inputs(shape, seed=31, batch=batch, kv_len=kv_len)
+    gamma = gamma_for(shape, 10) if norm else None
+    res = run_layer(shape, batch, inp, kv_len, gamma, 1e-5, norm, True)
+    check(res, reference(shape, inp, kv_len, gamma, 1e-5, norm), inp, kv_len, "33 rows")

@@ -326,3 +326,30 @@ M128_RAGGED = cf_inputs.BlockShape("mha128_ragged", 1000, 4, 4, 128, 10000.0, 0)
 @pytest.mark.parametrize("shape,batch", [(G4_RAGGED, 2), (M128_RAGGED, 1), (M128_RAGGED, 2)], ids=lambda v: getattr(v, "name", None))
 def test_stack_with_workgroups_that_own_no_output_column(shape, batch):
     test_stack_matches_single_calls_and_oracle(shape, False, 0, True, batch, 3, 150)
+
+
+# Slices of the input longer than what a thread has in flight at once (batch 2: more than 2560 values of the batch's rows,
+# batch 3 to 16: more than 4608), so that it arrives in several rounds, with slices forced and as the plan cuts them, and a
+# last slice that is shorter than the others.
+G4_LONG = cf_inputs.BlockShape("gqa4_long", 1536, 8, 2, 128, 10000.0, 0)
+G8_WIDE = cf_inputs.BlockShape("gqa8_wide", 1664, 64, 8, 128, 10000.0, 0)
+M128_SHORT_END = cf_inputs.BlockShape("mha128_short_end", 1304, 4, 4, 128, 10000.0, 0)
+
+
+@pytest.mark.parametrize("shape,batch,k_splits", [(G4_LONG, 2, 1), (G4, 16, 1), (M128_SHORT_END, 16, 2), (G8_WIDE, 16, 0)],
+                         ids=lambda v: getattr(v, "name", None))
+def test_stack_with_long_slices_of_the_input(shape, batch, k_splits, monkeypatch):
+    import paper_2508_18850_amd as cf
+
+    class Tuned(cf.DecodeBlock):
+        def __init__(self, *args):
+            super().__init__(*args)
+            self.set_tuning(k_splits=k_splits)
+
+        def close(self):
+            plan = self.plan()
+            assert batch * plan["rows_per_split"] > (2560 if batch == 2 else 4608), plan
+            super().close()
+
+    monkeypatch.setattr(cf, "DecodeBlock", Tuned)
+    test_stack_matches_single_calls_and_oracle(shape, False, 0, True, batch, 3, 70)
