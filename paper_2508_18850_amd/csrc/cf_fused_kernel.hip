@@ -1467,7 +1467,7 @@ __device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, in
     }
 }
 
-template <int HD, int BT>
+template <int HD, int BT, int MCW>
 __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, int tid0, int hq, int c3, int rs, uint32_t stamp, OutTile<HD> &tile,
                                         bool prefetched, float *smem)
 {
@@ -1607,8 +1607,8 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                 run(integral_constant<int, 2>{}, integral_constant<int, 4>{});
             else
                 run(integral_constant<int, 1>{}, integral_constant<int, 8>{});
-        } else if (p.NS * V > 4 * NT) {                                   // more than four splits per thread
-            run(integral_constant<int, 1>{}, integral_constant<int, 8>{});
+        } else if (MCW > 4 && p.NS * V > 4 * NT) {                        // more than four splits per thread
+            run(integral_constant<int, 1>{}, integral_constant<int, MCW>{});
         } else {
             run(integral_constant<int, 1>{}, integral_constant<int, 4>{});
         }
@@ -1788,6 +1788,14 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
     }
 }
 
+// Splits that the merge of phase 3 has in flight where a thread adds more than four (the sums and their order are the same).
+// Four in the one-launch stack with one batch row and up to two query heads per KV head: the next layer's weights fill the
+// registers there, and eight made the kernel spill 20 bytes per lane.
+template <int HD, int G, int BT, bool STACK>
+struct MergeWide {
+    static constexpr int n = STACK && BT == 1 && G <= 2 ? 4 : 8;
+};
+
 // One launch = n_layers decode steps in a row (1 for the plain entry points).  Layer l > 0 takes its weights and
 // caches from tab[l] and its input from the slots xslots, where the final reduction of layer l - 1 left its result;
 // the last layer writes `out`.  Nothing separates the layers but those slots: a workgroup goes on as soon as the
@@ -1923,7 +1931,7 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     for (int it = member; it < n3; it += p.TS) {
         int hq, c3, rs;
         p3_args(it, hq, c3, rs);
-        p3_item<HD, BT>(p, lp, tl, hq, c3, rs, stamp, tile, tile_ready && it == member, smem);
+        p3_item<HD, BT, MergeWide<HD, G, BT, STACK>::n>(p, lp, tl, hq, c3, rs, stamp, tile, tile_ready && it == member, smem);
     }
     CF_STAMP(4);
     // ---- phase 4 (sum over heads)
