@@ -466,8 +466,8 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     // The input of a stack (stamped slots, in its first layer x) value by value, XR per thread and round trip, the batch's own
     // rows only; the first trip is requested here.  One trip for the whole
     // slice or, past XR * 512 values, a wait for every value by itself took, us a layer of the one-launch stack:
-    // Llama-3-8B shape, 2048 rows, batch 2 / 4 / 16 31.3 / 34.1 / 57.9, Llama-2-70B shape, 1024 rows, batch 4 / 16 72.5 / 107.4;
-    // so they take 30.3 / 28.3 / 49.4 and 63.8 / 96.0.  (MFMA tiles with 17 / 16 / 14 values per trip: batch 16 49.6 / 49.4 /
+    // Llama-3-8B shape, 2048 rows, batch 2 / 4 / 16 31.0 / 33.8 / 57.6, Llama-2-70B shape, 1024 rows, batch 4 / 16 72.4 / 107.0;
+    // so they take 30.2 / 28.0 / 49.3 and 64.0 / 96.3.  (MFMA tiles with 17 / 16 / 14 values per trip: batch 16 49.6 / 49.4 /
     // 48.9, Llama-2-7B shape, batch 8 59.2 / 59.2 / 58.2 against 57.0 with 9: the weights in flight leave few registers.)
     constexpr int XR = MF ? 9 : BT + 1;
     const int xn = p.B * p.RPS;
@@ -651,11 +651,8 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         // column block of its own) may arrive here after its sources have moved on and stamped newer values:
         // any stamp from the previous layer's up to the last layer's of this launch is taken.
         const uint32_t want = stamp_of(cnt0, layer - 1);
-        for (int trip = 0; trip < xn; trip += XR * NT) {          // (uniform)
-            int i0 = trip;
-            asm volatile("" : "+s"(i0));                          // (the addresses of a trip are not kept for the next)
+        auto x_take = [&](int i0) {                               // waits for the trip that starts at value i0, and stages it
             if (from_slots) {
-                if (i0 > 0) x_slots(i0);
                 Spin spin;
                 for (;;) {
                     bool ok = true;
@@ -667,8 +664,6 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
                     if (ok || spin.expired(p)) break;
                     x_slots(i0);
                 }
-            } else if (i0 > 0) {
-                x_values(i0);
             }
 #pragma unroll
             for (int q = 0; q < XR; ++q) {
@@ -678,6 +673,17 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
                 const float v = from_slots ? __builtin_bit_cast(float, xs2[q].x) : h2f((uint16_t)xs2[q].x);
                 if (i < xn) stage(i, b, r, in ? v : 0.f);
             }
+        };
+        // (the first trip outside the loop: inside it, its addresses are computed once more, 0.2 - 0.9 us a layer at batch 1)
+        x_take(0);
+        for (int trip = XR * NT; trip < xn; trip += XR * NT) {    // (uniform)
+            int i0 = trip;
+            asm volatile("" : "+s"(i0));                          // (the addresses of a trip are not kept for the next)
+            if (from_slots)
+                x_slots(i0);
+            else
+                x_values(i0);
+            x_take(i0);
         }
     } else {
         for (int i = tid; i < xn; i += NT) {                      // (slices that are no multiples of eight rows)
