@@ -82,7 +82,6 @@ using cf::mfma::u32x4;
 struct MlaArgs {
     const uint16_t *x, *wq, *wkv, *wup, *wdown, *wo;
     uint16_t *cache, *out;
-    float *zdbg;                    // [B][nh][L]: the normalised latent vectors z of the call (for cf_mla_debug_export)
     uint64_t *slots;                // stamped slots of the last hand-over: [nh][B][D]
     float *data;                    // the other hand-overs' values, 4 bytes each
     uint32_t *flags;                // their flags: [4][256]
@@ -665,11 +664,7 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
             z[i] += __shfl_xor(z[i], 16);
             z[i] /= Ls;
         }
-        if (sq == 0 && b < B) {
-            const size_t at = ((size_t)b * a.nh + head) * L + LJ * j + 4 * d4;
-            X.st4(a.xz + at, z);
-            *reinterpret_cast<f32x4 *>(a.zdbg + at) = z;
-        }
+        if (sq == 0 && b < B) X.st4(a.xz + ((size_t)b * a.nh + head) * L + LJ * j + 4 * d4, z);
         post(fD + head * TS + j, x.stamp);
     }
     MLA_STAMP(6);           // z posted
@@ -799,7 +794,7 @@ struct cf_mla_s {
     uint64_t *slots = nullptr, *hslots = nullptr;    // stamped slots of the token-range kernel, of the head-team kernel
     float *data = nullptr;          // values of the token-range kernel's other hand-overs
     uint32_t *flags = nullptr;      // their flags
-    float *zdbg = nullptr, *qdbg = nullptr, *zpart = nullptr;
+    float *qdbg = nullptr, *zpart = nullptr;
     unsigned long long *counters = nullptr;
     uint32_t *err = nullptr;
     size_t x1 = 0, xq = 0, x3 = 0, xml = 0, xz = 0;
@@ -879,9 +874,9 @@ int cf_mla_create(const cf_mla_config *cfg, cf_mla *out)
     const size_t nslots = B * nh * c.d_model, nhslots = cf::mla::heads_layout(c, hfirst);
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t head_b = up(256 + (size_t)W * kCounterStride * sizeof(unsigned long long)), flag_b = 4 * 256 * sizeof(uint32_t);
-    const size_t slot_b = up(nslots * 8), hslot_b = up(nhslots * 8), data_b = up(ndata * 4), z_b = up(B * nh * L * 4), q_b = up(nh * LR * 4);
+    const size_t slot_b = up(nslots * 8), hslot_b = up(nhslots * 8), data_b = up(ndata * 4), q_b = up(nh * LR * 4);
     t->clear_bytes = head_b + flag_b + slot_b + hslot_b;
-    t->ws_bytes = t->clear_bytes + data_b + z_b + q_b + nh * TS * (2 + L) * sizeof(float);
+    t->ws_bytes = t->clear_bytes + data_b + q_b + nh * TS * (2 + L) * sizeof(float);
     if (slot_b > 0xfffffff0ull || data_b > 0xfffffff0ull) {
         delete t;
         return CF_EUNSUPPORTED;
@@ -901,8 +896,7 @@ int cf_mla_create(const cf_mla_config *cfg, cf_mla *out)
     t->slots = reinterpret_cast<uint64_t *>(cur += flag_b);
     t->hslots = reinterpret_cast<uint64_t *>(cur += slot_b);
     t->data = reinterpret_cast<float *>(cur += hslot_b);
-    t->zdbg = reinterpret_cast<float *>(cur += data_b);
-    t->qdbg = reinterpret_cast<float *>(cur += z_b);
+    t->qdbg = reinterpret_cast<float *>(cur += data_b);
     t->zpart = reinterpret_cast<float *>(cur += q_b);
     *out = t;
     return CF_OK;
@@ -965,7 +959,6 @@ int cf_mla_decode(cf_mla t, int32_t batch, const void *x, const void *W_q, const
     a.wo = static_cast<const uint16_t *>(W_o);
     a.cache = static_cast<uint16_t *>(kv_cache);
     a.out = static_cast<uint16_t *>(out);
-    a.zdbg = t->zdbg;
     a.slots = t->slots, a.data = t->data, a.flags = t->flags;
     a.counters = t->counters;
     a.err = t->err;
@@ -1039,7 +1032,8 @@ int cf_mla_debug_export(cf_mla t, int32_t what, void *host_dst, size_t bytes, vo
             for (int d = 0; d < L; ++d) dst[h * L + d] = (float)(z[d] / ls);
         }
     } else if (e == hipSuccess && what == 2) {
-        e = hipMemcpy(host_dst, t->zdbg, bytes, hipMemcpyDeviceToHost);
+        // z of the last call still sits in its exchange area, [b][head][L]
+        e = hipMemcpy(host_dst, t->data + t->xz, bytes, hipMemcpyDeviceToHost);
     }
     if (e == hipSuccess && what != 2 && t->last_heads) {
         std::vector<float> q(B * nh * LR);
