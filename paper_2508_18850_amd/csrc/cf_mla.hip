@@ -38,10 +38,8 @@
 #include "cf_team_device.h"
 
 #include <cmath>
-#include <cstdlib>
 #include <cstring>
 #include <new>
-#include <vector>
 
 namespace {
 
@@ -1013,43 +1011,33 @@ int cf_mla_debug_export(cf_mla t, int32_t what, void *host_dst, size_t bytes, vo
     const size_t per = what == 1 ? R : L;
     if (bytes != B * nh * per * sizeof(float)) return CF_EINVAL;
     hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
+    float *dst = static_cast<float *>(host_dst);
     if (e == hipSuccess && what == 2 && t->last_heads) {
-        // the head-team kernel merges behind W_Down: z is put together here from the members' partials
-        std::vector<float> part(nh * TS * (2 + L));
-        e = hipMemcpy(part.data(), t->zpart, part.size() * sizeof(float), hipMemcpyDeviceToHost);
-        float *dst = static_cast<float *>(host_dst);
+        // the head-team kernel merges behind W_Down: z is put together here from the members' partials, a head at a time (on
+        // the stack: nothing in here may throw)
+        float part[TS][2 + L];
         for (size_t h = 0; e == hipSuccess && h < nh; ++h) {
-            const float *p = part.data() + h * TS * (2 + L);
-            float M = p[0];
-            for (int s = 1; s < TS; ++s) M = std::fmax(M, p[s * (2 + L)]);
-            double ls = 0.0;
-            std::vector<double> z(L, 0.0);
+            e = hipMemcpy(part, t->zpart + h * TS * (2 + L), sizeof part, hipMemcpyDeviceToHost);
+            float M = part[0][0];
+            for (int s = 1; s < TS; ++s) M = std::fmax(M, part[s][0]);
+            double f[TS], ls = 0.0;
             for (int s = 0; s < TS; ++s) {
-                const double f = std::exp2((double)p[s * (2 + L)] - M);
-                ls += f * p[s * (2 + L) + 1];
-                for (int d = 0; d < L; ++d) z[d] += f * p[s * (2 + L) + 2 + d];
+                f[s] = std::exp2((double)part[s][0] - M);
+                ls += f[s] * part[s][1];
             }
-            for (int d = 0; d < L; ++d) dst[h * L + d] = (float)(z[d] / ls);
+            for (int d = 0; d < L; ++d) {
+                double z = 0.0;
+                for (int s = 0; s < TS; ++s) z += f[s] * part[s][2 + d];
+                dst[h * L + d] = (float)(z / ls);
+            }
         }
     } else if (e == hipSuccess && what == 2) {
         // z of the last call still sits in its exchange area, [b][head][L]
-        e = hipMemcpy(host_dst, t->data + t->xz, bytes, hipMemcpyDeviceToHost);
-    }
-    if (e == hipSuccess && what != 2 && t->last_heads) {
-        std::vector<float> q(B * nh * LR);
-        e = hipMemcpy(q.data(), t->qdbg, q.size() * sizeof(float), hipMemcpyDeviceToHost);
-        float *dst = static_cast<float *>(host_dst);
-        if (e == hipSuccess)
-            for (size_t i = 0; i < B * nh; ++i)
-                std::memcpy(dst + i * per, q.data() + i * LR + (what == 1 ? L : 0), per * sizeof(float));
-    } else if (e == hipSuccess && what != 2) {
-        // the query of the last call still sits in its exchange area: [b][head][L + R]
-        std::vector<float> q(B * nh * LR);
-        e = hipMemcpy(q.data(), t->data + t->xq, q.size() * sizeof(float), hipMemcpyDeviceToHost);
-        float *dst = static_cast<float *>(host_dst);
-        if (e == hipSuccess)
-            for (size_t i = 0; i < B * nh; ++i)
-                std::memcpy(dst + i * per, q.data() + i * LR + (what == 1 ? L : 0), per * sizeof(float));
+        e = hipMemcpy(dst, t->data + t->xz, bytes, hipMemcpyDeviceToHost);
+    } else if (e == hipSuccess) {
+        // the query: [b][head][L + R], of the token-range kernel still in its exchange area
+        const float *q = (t->last_heads ? t->qdbg : t->data + t->xq) + (what == 1 ? L : 0);
+        e = hipMemcpy2D(dst, per * sizeof(float), q, LR * sizeof(float), per * sizeof(float), B * nh, hipMemcpyDeviceToHost);
     }
     if (e != hipSuccess) {
         t->last_hip = (int)e;

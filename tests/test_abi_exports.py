@@ -34,3 +34,15 @@ def test_host_only_entry_points():
     # weights 128 MiB + KV 64 MiB + appended rows 16 KiB + x/out 16 KiB  (Llama-2-7B shape, L = 4096)
     assert pkg.algorithmic_bytes(cfg, 1, 4096) == 201326592 + 32 * 2 * 128 * 2 + 2 * 4096 * 2
     assert lib.cf_create(None, None) == -1
+
+
+def test_nothing_that_throws_is_linked_in():
+    """No exception may cross the C boundary: the host code uses neither the throwing operator new nor a container that
+    reports errors by exceptions, and has no frame that unwinds."""
+    import subprocess
+    import paper_2508_18850_amd as pkg
+    nm = subprocess.run(["nm", "-D", "--undefined-only", pkg.lib_path()], capture_output=True, text=True, check=True).stdout
+    names = [line.split()[-1].split("@")[0] for line in nm.splitlines()]
+    assert "_ZnwmRKSt9nothrow_t" in names
+    for name in names:
+        assert name not in ("_Znwm", "_Znam", "_Unwind_Resume", "__cxa_throw") and "__throw_" not in name, name
