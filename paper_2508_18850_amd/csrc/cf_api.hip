@@ -34,6 +34,7 @@ struct cf_handle_s {
     long long spin_ticks = 200000000LL;   // 2 s of the 100 MHz wall clock
     int wg_per_cu[6] = {0, 0, 0, 0, 0, 0};   // resident workgroups per CU for batch tiles 1, 4, 16 of the block kernel,
                                           // then of the layer kernel (0 = not probed)
+    size_t probed_lds[6] = {0, 0, 0, 0, 0, 0};   // LDS bytes per workgroup those were found for
     int last_batch = 0;
     int last_plan[10] = {0};
     int last_hip = 0;
@@ -231,16 +232,20 @@ int hip_fail(cf_handle_s *h, hipError_t e)
     return CF_EHIP;
 }
 
-// Check (once per batch tile) that the whole grid can be resident at the same time.
+// Check that the whole grid can be resident at the same time: once per batch tile, again for a call that needs more LDS
+// than was probed (the probe also raises the kernel's limit), and before a call that needs less is refused.
 int check_residency(cf_handle_s *h, const Params &p, int bt, size_t lds_bytes)
 {
     const bool layer = cf::wants_layer_kernel(p);
-    int &slot = h->wg_per_cu[tile_index(bt) + (layer ? 3 : 0)];
-    if (slot == 0) {
+    const int k = tile_index(bt) + (layer ? 3 : 0);
+    int &slot = h->wg_per_cu[k];
+    size_t &probed = h->probed_lds[k];
+    if (slot == 0 || lds_bytes > probed || (lds_bytes < probed && (long)slot * h->num_cu < p.W)) {
         int n = 0;
         hipError_t e = cf::max_workgroups_per_cu(h->cfg.head_dim, h->G, bt, lds_bytes, layer, &n);
         if (e != hipSuccess) return hip_fail(h, e);
         slot = n > 0 ? n : -1;
+        probed = lds_bytes;
     }
     if (slot < 0 || (long)slot * h->num_cu < p.W) return CF_EUNSUPPORTED;
     return CF_OK;
@@ -622,7 +627,8 @@ struct StaticDevice {
     int num_cu = 0;
     int last_w = 0;             // workgroups of the previous launch through this entry point on this GPU
     int wg_per_cu[6] = {0, 0, 0, 0, 0, 0};
-    unsigned long long occ_key = 0;   // (head_dim, group, LDS bytes) the residency figures above were taken for
+    size_t probed_lds[6] = {0, 0, 0, 0, 0, 0};
+    unsigned long long occ_key = 0;   // (head_dim, group) the residency figures above were taken for
 };
 StaticDevice g_static[kMaxDevices];
 
@@ -687,7 +693,10 @@ int cf_decode_block_static(const cf_config *cfg, int32_t batch, const void *x, c
     h.slot_area = sd.ptr + kScratchHeadBytes;
     h.slot_area_bytes = kScratchBytes - kScratchHeadBytes;
     const unsigned long long key = ((unsigned long long)cfg->head_dim << 40) ^ ((unsigned long long)h.G << 32);
-    if (sd.occ_key == key) std::memcpy(h.wg_per_cu, sd.wg_per_cu, sizeof h.wg_per_cu);
+    if (sd.occ_key == key) {
+        std::memcpy(h.wg_per_cu, sd.wg_per_cu, sizeof h.wg_per_cu);
+        std::memcpy(h.probed_lds, sd.probed_lds, sizeof h.probed_lds);
+    }
     const int w = default_workgroups(&h);
     if (w != sd.last_w) {
         // (a kernel, not a memset: the call may be recorded into a graph)
@@ -698,6 +707,7 @@ int cf_decode_block_static(const cf_config *cfg, int32_t batch, const void *x, c
     rc = decode_impl(&h, 0, batch, x, W_qkv, W_o, k_cache, v_cache, pos, out, stream);
     sd.occ_key = key;
     std::memcpy(sd.wg_per_cu, h.wg_per_cu, sizeof h.wg_per_cu);
+    std::memcpy(sd.probed_lds, h.probed_lds, sizeof h.probed_lds);
     return rc;
 }
 

@@ -79,3 +79,26 @@ def test_static_entry_point_refuses_what_does_not_fit():
     with pytest.raises(CfError) as e:      # bad shape: refused before anything else
         decode_block_static(CfConfig(1000, 8, 8, 100, 1, 64, 10000.0, 0), 1, p, p, p, p, p, 8, p, 0)
     assert e.value.code in (-1, -2)
+
+
+@pytest.mark.parametrize("batches", [(15, 16, 15), (16,)], ids=str)
+def test_static_entry_point_replans_at_the_scratch_limit(batches):
+    """120 heads over 15 KV heads of 64 values, 1864 columns: with batch 15 the plan cuts the projection into three slices
+    and its exchange slots fit the array; with batch 16 they do not (33.4 MB), and one slice is taken in place of three,
+    which needs twice the LDS."""
+    from paper_2508_18850_amd import CfConfig, decode_block_static
+    shape, kv_len = cf_inputs.BlockShape("static_limit", 1864, 120, 15, 64, 10000.0, 10), 10
+    dev = torch.device("cuda:0")
+    for batch in batches:
+        print("static entry point at the scratch limit: batch %d" % batch, flush=True)
+        inp = cf_inputs.make_inputs(shape, seed=14, batch=batch, kv_len=kv_len)
+        t = {k: torch.from_numpy(inp[k]).to(dev) for k in ("x", "w_qkv", "w_o", "k_cache", "v_cache")}
+        out = torch.full((batch, shape.d_model), float("nan"), dtype=torch.float16, device=dev)
+        cfg = CfConfig(shape.d_model, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, batch, inp["max_seq"], shape.rope_base, 0)
+        decode_block_static(cfg, batch, t["x"].data_ptr(), t["w_qkv"].data_ptr(), t["w_o"].data_ptr(), t["k_cache"].data_ptr(),
+                            t["v_cache"].data_ptr(), kv_len, out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        ref = orc.decode_block(inp["x"], inp["w_qkv"], inp["w_o"], inp["k_cache"], inp["v_cache"], kv_len, shape.n_q_heads,
+                               shape.n_kv_heads, shape.head_dim, shape.rope_base)
+        err = np.abs(out.cpu().numpy().astype(np.float64) - ref["out"]).max()
+        assert err <= 1e-2 * np.abs(ref["out"]).max() + 1e-3, (batch, err)
