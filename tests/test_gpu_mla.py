@@ -1,6 +1,6 @@
 """GPU parity of the fused MLA decode block (cf_mla_decode) with the CPU oracle (oracle/mla_block.py), through
-the C ABI.  cf_mla_decode has two kernels: up to batch 2 the head-team kernel, from batch 3 on (and whenever a limit
-on the token ranges is set) the token-range kernel on MFMA tiles; cases of batch 1 and 2 run both.
+the C ABI.  cf_mla_decode has two kernels: at batch 1 the head-team kernel, from batch 2 on (and whenever a limit
+on the token ranges is set) the token-range kernel on MFMA tiles; cases of batch 1 run both.
 
 Tolerance on the block output, as for the other block: max|err| <= 1e-2 * max|ref| + 1e-3 (fp16 storage, fp32
 accumulation), plus relative RMS < 5e-3; the appended cache row within one fp16 ulp plus the fp32 accumulation error
@@ -121,7 +121,7 @@ def test_edge_positions(pos):
 
 @pytest.mark.parametrize("max_splits,kv_len,batch", [(1, 700, 2), (3, 700, 2), (32, 700, 1), (5, 1000, 6), (1, 129, 16)])
 def test_forced_token_ranges(max_splits, kv_len, batch):
-    """One range with several tiles of 128 rows, ranges that end inside a tile, many short ranges, ranges of a 16-row batch."""
+    """One range with several tiles of 64 rows, ranges that end inside a tile, many short ranges, ranges of a 16-row batch."""
     shape = cf_inputs.MlaShape("s", 256, 4, 64, 64, 512, 64, 10000.0, 0)
     inp = cf_inputs.make_mla_inputs(shape, seed=90 + max_splits, batch=batch, kv_len=kv_len)
     check(run(shape, inp, kv_len, max_splits), oracle(shape, inp, kv_len), inp, kv_len,
@@ -276,3 +276,47 @@ def test_operands_of_any_magnitude(name, batch):
         rel = np.sqrt(np.mean((g - ref[what]) ** 2) / np.mean(ref[what] ** 2))
         _log("   %s: relative RMS %.2e" % (what, rel))
         assert np.isfinite(g).all() and rel < tol, what
+
+
+# The token-range kernel at the same edges: up-projection wavefronts that are partly or not live (nope 8, 72, 104), short value
+# blocks, members without output columns, heads that no power of two of groups divides, no cached row, one range and many.
+@pytest.mark.parametrize("heads,d_model,nope,v", [(1, 32, 8, 8), (3, 384, 128, 40), (8, 1024, 72, 128), (11, 1216, 104, 24),
+                                                  (16, 2048, 8, 128), (16, 96, 128, 8)])
+@pytest.mark.parametrize("batch,kv_len", [(2, 0), (2, 2049), (5, 1), (5, 700), (16, 0), (16, 17), (16, 1100)])
+def test_token_range_kernel_edges(heads, d_model, nope, v, batch, kv_len):
+    shape = cf_inputs.MlaShape("s", d_model, heads, nope, 64, 512, v, 10000.0, 0)
+    _log("heads %d d_model %d nope %d v %d batch %d L %d" % (heads, d_model, nope, v, batch, kv_len))
+    inp = cf_inputs.make_mla_inputs(shape, seed=heads + kv_len + batch, batch=batch, kv_len=kv_len)
+    check(run(shape, inp, kv_len), oracle(shape, inp, kv_len), inp, kv_len, "heads %d batch %d L %d" % (heads, batch, kv_len))
+
+
+@pytest.mark.parametrize("heads", [5, 16])
+def test_one_handle_for_changing_batches(heads):
+    """A handle for 16 rows called with 16, 1, 3, 1, 2 and 16: both kernels in turn over the same launch counters, flags and
+    exchange areas that the call before left behind under another plan, batches below the largest."""
+    from paper_2508_18850_amd import MlaBlock
+    shape = cf_inputs.MlaShape("s", 64 * heads, heads, 48, 64, 512, 64, 10000.0, 0)
+    dev = torch.device("cuda:0")
+    st = torch.cuda.current_stream().cuda_stream
+    cases = []
+    for k, (batch, kv_len) in enumerate([(16, 300), (1, 90), (3, 500), (1, 0), (2, 64), (16, 300)]):
+        inp = cf_inputs.make_mla_inputs(shape, seed=500 + k, batch=batch, kv_len=kv_len)
+        cases.append((batch, kv_len, inp, oracle(shape, inp, kv_len)))
+    blk = MlaBlock(shape.d_model, heads, shape.nope_dim, 64, 512, shape.v_head_dim, 16, max(c[2]["max_seq"] for c in cases),
+                   shape.rope_base)
+    for batch, kv_len, inp, ref in cases:
+        _log("heads %d batch %d L %d" % (heads, batch, kv_len))
+        cache = np.full((batch, max(c[2]["max_seq"] for c in cases), 576), np.float16(np.nan), dtype=np.float16)
+        cache[:, :inp["max_seq"]] = inp["kv_cache"]
+        inp = dict(inp, kv_cache=cache)
+        t = {k: torch.from_numpy(inp[k]).to(dev) for k in ("x", "w_q", "w_kv", "w_up", "w_down", "w_o", "kv_cache")}
+        out = torch.full((batch, shape.d_model), float("nan"), dtype=torch.float16, device=dev)
+        blk.decode(batch, t["x"].data_ptr(), t["w_q"].data_ptr(), t["w_kv"].data_ptr(), t["w_up"].data_ptr(),
+                   t["w_down"].data_ptr(), t["w_o"].data_ptr(), t["kv_cache"].data_ptr(), kv_len, out.data_ptr(), st)
+        blk.status(st)
+        res = {"out": out.cpu().numpy(), "kv_cache": t["kv_cache"].cpu().numpy()}
+        for what, (name, width) in enumerate((("q_lat", 512), ("q_rope", 64), ("z", 512))):
+            res[name] = np.empty((batch, heads, width), dtype=np.float32)
+            blk.debug_export(what, res[name], st)
+        check(res, ref, inp, kv_len, "batch %d" % batch)
+    blk.close()

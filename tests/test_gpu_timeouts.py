@@ -98,3 +98,46 @@ def test_mla_block_reports_a_timeout_and_recovers():
     err = np.abs(out.cpu().numpy().astype(np.float64) - ref).max()
     assert err <= 1e-2 * np.abs(ref).max() + 1e-3
     blk.close()
+
+
+@pytest.mark.parametrize("batch", [2, 4, 16])
+def test_mla_token_range_kernel_reports_a_timeout_and_recovers(batch):
+    """The same for the kernel of batch 2 to 16, whose hand-overs wait for flags: the status call clears them with the launch
+    counters.  A call at batch 1 (the head-team kernel, the same counters) lies between two of them."""
+    from paper_2508_18850_amd import MlaBlock, CfError
+    shape, kv_len = cf_inputs.MlaShape("s", 512, 16, 128, 64, 512, 128, 10000.0, 0), 1500
+    inp = cf_inputs.make_mla_inputs(shape, seed=92, batch=batch, kv_len=kv_len, poison=False)
+    dev = torch.device("cuda:0")
+    blk = MlaBlock(shape.d_model, shape.n_heads, shape.nope_dim, shape.rope_dim, shape.kv_lora_rank, shape.v_head_dim, batch,
+                   inp["max_seq"], shape.rope_base)
+    st = torch.cuda.current_stream().cuda_stream
+    t = {k: torch.from_numpy(inp[k]).to(dev) for k in ("x", "w_q", "w_kv", "w_up", "w_down", "w_o", "kv_cache")}
+    ref = morc.mla_decode_block(inp["x"], inp["w_q"], inp["w_kv"], inp["w_up"], inp["w_down"], inp["w_o"], inp["kv_cache"],
+                                kv_len, shape.n_heads, shape.nope_dim, shape.rope_dim, shape.kv_lora_rank, shape.v_head_dim,
+                                shape.rope_base)["out"]
+
+    def call(rows):
+        out = torch.full((rows, shape.d_model), float("nan"), dtype=torch.float16, device=dev)
+        blk.decode(rows, t["x"].data_ptr(), t["w_q"].data_ptr(), t["w_kv"].data_ptr(), t["w_up"].data_ptr(),
+                   t["w_down"].data_ptr(), t["w_o"].data_ptr(), t["kv_cache"].data_ptr(), kv_len, out.data_ptr(), st)
+        return out
+
+    def good(rows):
+        out = call(rows)
+        blk.status(st)
+        err = np.abs(out.cpu().numpy().astype(np.float64) - ref[:rows]).max()
+        assert err <= 1e-2 * np.abs(ref).max() + 1e-3, (rows, err)
+
+    good(batch)
+    for _ in range(2):
+        print("mla batch %d, wait limit 0" % batch, flush=True)
+        blk.set_spin_limit(0)
+        call(batch)
+        with pytest.raises(CfError) as e:
+            blk.status(st)
+        assert e.value.code == CF_ETIMEOUT
+        blk.set_spin_limit(2000000)
+        good(batch)
+        good(1)
+        good(batch)
+    blk.close()
