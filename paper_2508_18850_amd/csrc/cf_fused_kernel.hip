@@ -34,7 +34,6 @@
 #include "cf_rope_device.h"
 
 #include <cstddef>
-#include <cstdlib>
 #include <type_traits>
 
 namespace cf {
@@ -376,8 +375,8 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     const int nsteps = nsel * nb;
     auto sel_of = [&](int si) { return sel0 + si * dsel; };
     float *xs = smem;                       // [BT][RPS]
-    // MF: x as fp16 MFMA operands, [16][XS] halves (rows padded by 16 bytes: the sixteen lanes of an operand read
-    // then fall into different banks), followed by a second array with the low parts of x * gamma (RMSNorm)
+    // MF: x as fp16 MFMA operands, [16][XS] halves (rows of an odd number of 16-byte pieces: the sixteen lanes of an operand
+    // read then fall into different banks), followed by a second array with the low parts of x * gamma (RMSNorm)
     const int XS = xs16_stride(p.RPS);
     _Float16 *xh = reinterpret_cast<_Float16 *>(smem), *xl = xh + 16 * XS;
     float *red = smem + (MF ? 16 * XS : BT * p.RPS);   // [MAXI][NW][BT][HD]
@@ -693,7 +692,8 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         }
     }
     if (MF && !xvec) {
-        // columns RPS .. XS-1 of every row (an operand read may reach up to seven columns past the slice)
+        // columns RPS .. XS-1 of every row: an operand read that starts inside the slice may reach up to seven columns past it
+        // (with slices of 8 k rows it ends inside: nothing to clear when x came in pieces)
         const int nz = XS - p.RPS;
         for (int e = tid; e < 16 * nz; e += NT) {
             const int b = e / nz, r = p.RPS + (e - b * nz);
@@ -757,7 +757,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         if constexpr (MF) {
             // one step of 32 rows: operand A = x[batch row lane % 16][rows of this lane's group], operands B =
             // the eight columns of this lane.  Rows past the slice: their weights are zero (loads switched off)
-            // and x is zero up to column XS; a group that starts past the slice reads nothing.
+            // and x, where an operand reaches them, is zero; a group that starts past the slice reads nothing.
             const int r = NG * i0 + lrow;
             const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
             const int xo = (tid & 15) * XS + min(r, XS - 8);

@@ -103,7 +103,6 @@ hipError_t launch_fused_layer(const Params &p, int head_dim, int group, int batc
 hipError_t max_workgroups_per_cu_layer(int head_dim, int group, int batch_tile, size_t lds_bytes, int *out);
 // LDS floats needed by the three phases for the given plan.
 size_t lds_floats(const Params &p, int head_dim, int group, int batch_tile);
-// XCC id of every workgroup of a W-workgroup launch (host buffer of W ints).
 // Rearrange row-major weights into the packed layout (see cf_pack_weights in the public header).
 hipError_t launch_pack(const uint16_t *wqkv, const uint16_t *wo, uint16_t *wqkv_p, uint16_t *wo_p, int D, int nqkv,
                        int nq, int head_dim, hipStream_t stream);

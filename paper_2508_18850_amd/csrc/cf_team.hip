@@ -5,7 +5,6 @@
 #include "../../include/cfdecode.h"
 #include "cf_team_device.h"
 
-#include <cstdlib>
 #include <new>
 
 namespace {
