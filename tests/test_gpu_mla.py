@@ -320,3 +320,19 @@ def test_one_handle_for_changing_batches(heads):
             blk.debug_export(what, res[name], st)
         check(res, ref, inp, kv_len, "batch %d" % batch)
     blk.close()
+
+
+@pytest.mark.parametrize("batch", [2, 16])
+def test_an_infinite_input_stays_in_its_row(batch):
+    """One row of x holds an infinity: its output is not finite, every other row and its cache are what they are without it
+    (rows of a batch share matrix products, and the scale of an operand is taken per row)."""
+    shape, kv_len, bad = cf_inputs.MlaShape("s", 320, 5, 48, 64, 512, 64, 10000.0, 0), 100, 1
+    inp = cf_inputs.make_mla_inputs(shape, seed=600 + batch, batch=batch, kv_len=kv_len)
+    good = run(shape, inp, kv_len)
+    x = inp["x"].copy()
+    x[bad, 7] = np.float16(np.inf)
+    got = run(shape, dict(inp, x=x), kv_len)
+    rest = [b for b in range(batch) if b != bad]
+    assert not np.isfinite(got["out"][bad].astype(np.float64)).any()
+    for name in ("out", "kv_cache", "q_lat", "z"):
+        assert np.array_equal(got[name][rest], good[name][rest], equal_nan=True), name
