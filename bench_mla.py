@@ -22,8 +22,8 @@ if ROOT not in sys.path:
 # (profiles/fused_mla_deepseek_v2_lite_kv4096.md), DeepSeek-V2-Lite shape; None where no counter run exists
 MEASURED_TRAFFIC = {
     "b1_kv4096": 68172652,              # 32678.9, 1217.0
-    "b4_kv4096": 84325868,              # 36158.9, 10031.6
-    "b16_kv4096": 153228398,            # 63070.0, 23497.1
+    "b4_kv4096": 84097661,              # 36111.5, 9903.6
+    "b16_kv4096": 152710185,            # 63073.0, 22985.1
 }
 
 

@@ -310,7 +310,9 @@ int cf_team_set_spin_limit(cf_team t, int32_t spin_limit_us);
  * CF_EUNSUPPORTED otherwise.  cf_mla_status is cf_status for this handle.
  * Two kernels: at batch 1 every head scans the cached rows itself (16 workgroups per head, vector arithmetic);
  *   from batch 2 on the unit of work of the attention stage is a range of cached rows of one batch row, for a group of
- *   heads at once, as two products on MFMA tiles.
+ *   heads at once, as two products on MFMA tiles.  There the query q enters the scores of the cached rows as pairs of fp16
+ *   values, q * log2(e) / sqrt(nope_dim + rope_dim) in 22 bits and below 65504; q_nope, z
+ *   and a keep fp32's bits and range in their products.
  * cf_mla_set_splits: upper limit on the number of token ranges a batch row's cached rows are divided into; 0 = chosen
  *   by the library, at most 32.  A non-zero limit also selects the token-range kernel at batch 1.  For tests of
  *   the range logic and for measurements; CF_EINVAL outside 0..32.

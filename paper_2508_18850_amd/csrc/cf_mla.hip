@@ -26,10 +26,10 @@
 // polls, do not look into its caches.
 //
 // Measured (DeepSeek-V2-Lite shape, 4096 rows): 16 batch rows 63.8 -> 45.1 us, batch 2 / 4 / 8 36.6 / 44.1 / 52.6 ->
-// 32.9 / 33.7 / 37.7, against the kernel that sent everything through slots.  Time line at 16 rows, us from kernel
-// start, mean over the workgroups: A posted 4.5, up-projection 9.0, B posted 9.6, sources there 13.3, query operands
-// built 14.9, rows consumed 25.2 (7.3 TB/s), range posted 27.8, its sources there 32.1, z posted 34.4, a_i 38.3, partial
-// of out 39.6, end 42.0.  What bounds it is the chain of hand-overs, 2 to 4 us each.
+// 32.5 / 33.9 / 37.9, against the kernel that sent everything through slots.  Time line at 16 rows, us from kernel
+// start, mean over the workgroups: A posted 4.5, up-projection 9.7, B posted 10.3, sources there 14.0, query operands
+// built 15.5, rows consumed 26.5 (6.9 TB/s), range posted 29.1, its sources there 33.2, z posted 35.5, a_i 40.2, partial
+// of out 41.8, end 44.3.  What bounds it is the chain of hand-overs, 2 to 4 us each.
 // Each stage requests its weights (or cached rows) before it waits for its input.  All waits are bounded
 // (CF_ETIMEOUT), all workgroups have to be resident at once.
 #include "cf_mfma_device.h"
@@ -152,7 +152,7 @@ __device__ __forceinline__ void split_hi_lo(const float (&v)[8], h8 &hi, h8 &lo)
 // three fp16 parts of eleven bits.  Down to 2^-15 of the row's largest value the parts add up to the value exactly, below
 // that to 2^-38 of the largest one, whatever the row's magnitude (a pair without the scale: 2e-3 of a value at 1e-5, NaN
 // above 65504).  The scale is taken out where the wavefronts' partial products are added.  Three such products cost 0.65 us
-// of a step (batch 2 / 4 / 16: 32.4 / 33.5 / 44.6 us with unscaled pairs, 33.1 / 34.1 / 45.25 us); rounded parts, each with its
+// of a step (batch 2 / 4 / 16 on one box: 32.4 / 33.5 / 44.6 us with unscaled pairs, 33.1 / 34.1 / 45.25 us); rounded parts, each with its
 // conversion back, and a scale taken out of every accumulator cost 1.45 us.
 struct Split3 {
     h8 hi, mid, lo;
