@@ -30,6 +30,7 @@
 // workgroups of the launch must be resident (checked on the host), since
 // readers spin.  Spins are bounded: after spin_ticks a thread sets an error
 // flag and goes on, so the kernel always ends.
+#include "cf_lanes_device.h"
 #include "cf_params.h"
 #include "cf_rope_device.h"
 
@@ -132,11 +133,7 @@ __device__ __forceinline__ void split_hi_lo(const float (&v)[8], h8 &hi, h8 &lo)
 __device__ __forceinline__ float h2f(uint16_t bits) { return (float)__builtin_bit_cast(_Float16, bits); }
 __device__ __forceinline__ uint16_t f2h(float v) { return __builtin_bit_cast(uint16_t, (_Float16)v); }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
+using lanes::dpp_move;
 
 // Sum over the LPR (8 or 16) consecutive lanes that hold one row; every lane gets the total.
 template <int LPR>
@@ -806,19 +803,14 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             if (nbuf == 0) si_first = si;
             if (++nbuf == MAXI) flush();
         } else {
-            // last batch of this selector: row groups of a wavefront by shuffles; the wavefronts
-            // are added in flush(), in a fixed order
+            // last batch of this selector: the row groups of a wavefront here, the wavefronts in flush(), in a fixed order
 #pragma unroll
-            for (int off = LPR; off < 64; off <<= 1)
+            for (int b = 0; b < BT; ++b) {
+                float t[LPR / 8];
+                lanes::fold8<LPR>(acc[b], t);
+                float *dst = red + ((nbuf * NW + wv) * BT + b) * HD + lig * 8 + (tid & 63) / LPR * (LPR / 8);
 #pragma unroll
-                for (int b = 0; b < BT; ++b)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[b][j] += __shfl_xor(acc[b][j], off);
-            if ((tid & 63) < LPR) {
-#pragma unroll
-                for (int b = 0; b < BT; ++b)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) red[((nbuf * NW + wv) * BT + b) * HD + lig * 8 + j] = acc[b][j];
+                for (int j = 0; j < LPR / 8; ++j) dst[j] = t[j];
             }
 #pragma unroll
             for (int b = 0; b < BT; ++b)
@@ -1063,14 +1055,8 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
     float *kn = qs + G * HD;                // [HD] rotated new key
     float *vn = kn + HD;                    // [HD] new value
     float *snew = vn + HD;                  // [8]  scores of the new token, log2 domain
-    // Partials that are folded through LDS: one per wavefront (its row groups merged by shuffles first), or, for
-    // groups of 8 heads, one per row group: there the shuffle merge of 10 values per head and step runs on
-    // spilled registers and costs more than the larger fold (measured: 70B shape 111 -> 105 us; with 4 heads
-    // per group the shuffle merge is the faster one, 32.1 against 35.1 us).
-    constexpr int RGW = 64 / LPR;                               // row groups of a wavefront
-    constexpr bool MA = AttnMfma<HD, G>::on;                    // both products on MFMA tiles: one partial per wavefront
-    constexpr bool kFoldRowGroups = G >= 8 && !MA;
-    constexpr int NPART = kFoldRowGroups ? NW * RGW : NW;
+    constexpr bool MA = AttnMfma<HD, G>::on;                    // both products on MFMA tiles
+    constexpr int NPART = NW;               // partials that are folded through LDS: one per wavefront
     float *redm = snew + 8;                 // [G][NPART]
     float *redl = redm + G * NPART;         // [G][NPART]
     float *redacc = redl + G * NPART;       // [G][NPART][HD]
@@ -1310,47 +1296,22 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
     // store and the next phase's polls wait for every bulk load issued before them.)  The member with
     // the last split first polls for the new token's key/value sums, for the same reason.
     if (!last) issue_next(1);
-    if (kFoldRowGroups) {
-        // ---- every row group leaves its partial in LDS
-        const int part = wv * RGW + (lane / LPR);
+    // ---- merge the row groups of a wavefront
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            if (lig == 0) {
-                redm[g * NPART + part] = m[g];
-                redl[g * NPART + part] = l[g];
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) redacc[(g * NPART + part) * HD + lig * 8 + j] = acc[g][j];
+    for (int g = 0; g < G; ++g) {
+        const float mw = lanes::max_groups<LPR>(m[g]), f = __builtin_amdgcn_exp2f(m[g] - mw);
+        const float lw = lanes::sum_groups<LPR>(l[g] * f);
+        if (lane == 0) {
+            redm[g * NPART + wv] = mw;
+            redl[g * NPART + wv] = lw;
         }
-    } else {
-        // ---- merge the row groups of a wavefront
+        float t[LPR / 8];
 #pragma unroll
-        for (int off = LPR; off < 64; off <<= 1) {
+        for (int j = 0; j < 8; ++j) acc[g][j] *= f;
+        lanes::fold8<LPR>(acc[g], t);
+        float *dst = redacc + (g * NPART + wv) * HD + lig * 8 + lane / LPR * (LPR / 8);
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const float mo = __shfl_xor(m[g], off), lo = __shfl_xor(l[g], off);
-                const float mn = fmaxf(m[g], mo);
-                const float sa = __builtin_amdgcn_exp2f(m[g] - mn), sb = __builtin_amdgcn_exp2f(mo - mn);
-                l[g] = l[g] * sa + lo * sb;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float ao = __shfl_xor(acc[g][j], off);
-                    acc[g][j] = acc[g][j] * sa + ao * sb;
-                }
-                m[g] = mn;
-            }
-        }
-        if (lane < LPR) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (lane == 0) {
-                    redm[g * NPART + wv] = m[g];
-                    redl[g * NPART + wv] = l[g];
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) redacc[(g * NPART + wv) * HD + lig * 8 + j] = acc[g][j];
-            }
-        }
+        for (int j = 0; j < LPR / 8; ++j) dst[j] = t[j];
     }
     }   // !MA
     CF_STAMP(8);            // row groups of the wavefront merged
@@ -1426,7 +1387,7 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
 // ---------------------------------------------------------------------------
 template <int HD>
 struct OutTile {
-    static constexpr int MAXR = HD / NW;   // W_o rows per wavefront when a head is not split over rows
+    static constexpr int MAXR = HD / 8;    // 16-byte loads per thread when a head is not split over rows
     h8 w[MAXR];
 };
 
@@ -1445,13 +1406,15 @@ __device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, in
     const int nrows = HD / p.RS3;
     const int cbase = c3 * p.CW3 + ch * kOutChunk;
     const uint32_t rowb = (p.flags & kFlagPacked) ? (uint32_t)kOutChunk * 2 : (uint32_t)p.D * 2;
-    uint32_t voff = (cbase + lane * 8) < p.D ? (uint32_t)wv * rowb + lane * 16 : kNoLoad;
+    // vector tiles: wavefront wv takes 64 columns of the chunk, its eight row groups of eight lanes the rows r + 8 u
+    const int col = 64 * wv + 8 * (lane & 7);
+    uint32_t voff = (cbase + col) < p.D ? (uint32_t)(lane >> 3) * rowb + col * 2 : kNoLoad;
     // (opaque to the compiler: it otherwise computes the sixteen per-row offsets of all call sites once, far
     // ahead of the first one, and spills them)
     asm volatile("" : "+v"(voff));
     const uint32_t sbase = (p.flags & kFlagPacked) ? (uint32_t)((hq * NCH + cbase / kOutChunk) * HD + rs * nrows) * rowb
                                     : (uint32_t)(hq * HD + rs * nrows) * rowb + (uint32_t)cbase * 2;
-    const int iters = nrows / NW;
+    const int iters = nrows / 8;
     if constexpr (MF) {
         static_assert(OutTile<HD>::MAXR == 16, "two steps of eight rows per lane");
         const int lig = lane & 15, kg = lane >> 4, cb = wv & 3, kh = wv >> 2;
@@ -1469,7 +1432,7 @@ __device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, in
 #pragma unroll
     for (int u = 0; u < OutTile<HD>::MAXR; ++u) {
         const bool mine = part == 2 || (part == 0) == (u < OutTile<HD>::MAXR / 2);
-        if (mine) t.w[u] = Wo.ld(u < iters ? voff : kNoLoad, sbase + (uint32_t)(NW * u) * rowb);
+        if (mine) t.w[u] = Wo.ld(u < iters ? voff : kNoLoad, sbase + (uint32_t)(8 * u) * rowb);
     }
 }
 
@@ -1477,7 +1440,6 @@ template <int HD, int BT, int MCW>
 __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, int tid0, int hq, int c3, int rs, uint32_t stamp, OutTile<HD> &tile,
                                         bool prefetched, float *smem)
 {
-    constexpr int RB = BT < 4 ? BT : 4;
     constexpr int PS = HD + kP2Stride;
     // (the 16-row tile has no register to spare: the thread index is made opaque here, so that what this phase
     // derives from it is computed here and not kept from the start of the kernel)
@@ -1488,12 +1450,12 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
     // unpadded rows all of them from the same LDS banks (Llama-3-8B shape, batch 4: 1.8 us for a product of 0.3)
     constexpr int AP = mfma_tiles(HD, BT) ? 4 : 0;
     float *as = smem;
-    float *red = smem + BT * (HD + AP);      // [NW][RB][512]; also the sums of the merge
+    float *red = smem + BT * (HD + AP);      // the sums of the merge; MFMA tiles: [2][16][512]
     const Xbuf x2(p.p2), x3(p.p3);
 
     const int nrows = HD / p.RS3;
     const int rbeg = rs * nrows;
-    const int iters = nrows / NW;
+    const int iters = nrows / 8;
     const int slot = hq * p.RS3 + rs;
     const int nchunk = p.CW3 / kOutChunk;
 
@@ -1677,7 +1639,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
             // has a zero tile entry, its load was switched off, so it may be multiplied by any finite value
 #pragma unroll
             for (int u = 0; u < OutTile<HD>::MAXR; ++u) {
-                const int r = rbeg + wv + NW * min(u, iters - 1);
+                const int r = rbeg + (lane >> 3) + 8 * min(u, iters - 1);
                 float f[8];
                 unpack8(tile.w[u], f);
 #pragma unroll
@@ -1693,7 +1655,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 #pragma unroll
             for (int u = 0; u < OutTile<HD>::MAXR; ++u) {
                 if (u < iters) {
-                    const int r = rbeg + wv + NW * u;
+                    const int r = rbeg + (lane >> 3) + 8 * u;
                     float f[8];
                     unpack8(tile.w[u], f);
 #pragma unroll
@@ -1705,27 +1667,19 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                 }
             }
         }
-        // wavefronts -> one partial row per batch row, RB batch rows at a time
+        // The eight row groups of a wavefront hold the rows of the item, so their sum is the partial: it is folded in
+        // registers, a lane ends with one column, and nothing passes through LDS (rows dealt to the wavefronts, whose 512
+        // columns were then added through LDS between two barriers, took 0.6 - 1.2 us at batch 1).
+        const int cc = cbase + 64 * wv + 8 * (lane & 7) + (lane >> 3);
 #pragma unroll
-        for (int bb = 0; bb < BT; bb += RB) {
-#pragma unroll
-            for (int b = 0; b < RB; ++b)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) red[(wv * RB + b) * kOutChunk + lane * 8 + j] = acc[bb + b][j];
-            lds_barrier();
-            for (int e = tid; e < RB * kOutChunk; e += NT) {
-                const int b = e / kOutChunk, cc = e - b * kOutChunk;
-                if (bb + b < p.B && cbase + cc < p.D) {
-                    float sum = 0.f;
-#pragma unroll
-                    for (int w8 = 0; w8 < NW; ++w8) sum += red[(w8 * RB + b) * kOutChunk + cc];
-                    x3.st(((size_t)slot * p.B + bb + b) * p.D + cbase + cc, sum, stamp);
-                }
-            }
-            CF_STAMP(18);   // output partial stored
-            lds_barrier();
+        for (int b = 0; b < BT; ++b) {
+            float sum[1];
+            lanes::fold8<8>(acc[b], sum);
+            if (b < p.B && cc < p.D) x3.st(((size_t)slot * p.B + b) * p.D + cc, sum[0], stamp);
         }
+        CF_STAMP(18);       // output partial stored
     }
+    if constexpr (!MF) lds_barrier();         // the merged values have been read
 }
 
 // ---------------------------------------------------------------------------
@@ -1750,7 +1704,7 @@ __device__ __forceinline__ uint16_t residual_input(const Params &p, int tid0, in
 
 // xout != null (a layer of a stack that is not the last): the result, rounded to fp16 as `out` would hold it, goes to
 // the slots the next layer's projection reads its input from, not to `out`.
-template <class HookFn>
+template <bool FEW, class HookFn>
 __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t stamp, float *smem, uint64_t *xout, HookFn &&after_polls)
 {
     const int tid = tid0;
@@ -1769,10 +1723,15 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
         const int spt = min(NT / cb, nslots);        // slots read in parallel
         const int v = tid % cb, s0 = tid / cb;
         const int b = (v0 + v) / ncol, c = (v0 + v) - b * ncol;
-        // the residual input of the value this thread writes below (threads tid < cb have v == tid), on its
+        // the residual input of the value this thread writes below, on its
         // way while the partials are polled.  (Fetching it before phase 3 was tried: a load inside a branch
         // there makes every later wait for the output-projection tile drain the queue.)
-        const uint16_t xres = residual_input(p, tid0, v0);
+        // Up to 32 values: sixteen lanes add the sums of a value (one thread for up to 256 sums of two values took 0.9 us of
+        // the tiny shape, so 0.6); more: one thread each, at most sixteen sums.  (FEW: not in the 16-row kernels, which rarely
+        // have so few and lost 1 % to the code.)
+        const bool wide = FEW && cb <= NT / 16;
+        const int own = wide ? tid >> 4 : tid;       // the value whose sums this thread adds
+        const uint16_t xres = residual_input(p, own, v0);
         if (s0 < spt) {
             const int n = (nslots - s0 + spt - 1) / spt;
             const size_t base = (size_t)s0 * p.B * p.D + (size_t)b * p.D + c0 + c, stride = (size_t)spt * p.B * p.D;
@@ -1782,13 +1741,25 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
         CF_STAMP(19);           // head partials arrived
         lds_barrier();
         if (v0 == 0) after_polls();
-        if (tid < cb) {
-            float sum = kLayer && (p.flags & kFlagResidual) ? h2f(xres) : 0.f;
-            for (int k = 0; k < spt; ++k) sum += smem[k * cb + tid];
+        auto write = [&](int bo, int co, float sum) {
+            if (kLayer && (p.flags & kFlagResidual)) sum = h2f(xres) + sum;
             if (xout)
-                Xbuf(xout).st((size_t)b * p.D + c0 + c, h2f(f2h(sum)), stamp);
+                Xbuf(xout).st((size_t)bo * p.D + c0 + co, h2f(f2h(sum)), stamp);
             else
-                p.out[(size_t)b * p.D + c0 + c] = f2h(sum);
+                p.out[(size_t)bo * p.D + c0 + co] = f2h(sum);
+        };
+        if (wide) {
+            if (own < cb) {
+                float sum = 0.f;
+                for (int k = tid & 15; k < spt; k += 16) sum += smem[k * cb + own];
+                sum = row_sum<16>(sum);
+                const int bo = (v0 + own) / ncol;
+                if ((tid & 15) == 0) write(bo, (v0 + own) - bo * ncol, sum);
+            }
+        } else if (tid < cb) {
+            float sum = 0.f;
+            for (int k = 0; k < spt; ++k) sum += smem[k * cb + tid];
+            write(b, c, sum);
         }
         lds_barrier();
     }
@@ -1948,7 +1919,7 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // one already after the merge of the attention partials 37.7; none 37.6)
     if (AHEAD >= 1)
         p1_all<HD, G, BT, STACK, 1>(p, lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
-    final_reduce(p, tl, stamp, smem, more ? xslots : nullptr, [&]() {
+    final_reduce<(BT <= 4)>(p, tl, stamp, smem, more ? xslots : nullptr, [&]() {
         if (AHEAD >= 2)
             p1_all<HD, G, BT, STACK, 2>(p, lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
     });
@@ -2109,14 +2080,14 @@ bool wants_layer_kernel(const Params &p)
 
 size_t lds_floats(const Params &p, int hd, int g, int bt)
 {
-    const size_t rb = bt < 4 ? bt : 4;
     const size_t maxi = bt == 1 ? 4 : (bt <= 4 ? 2 : 1);
     const size_t f1 = x_lds_floats(hd, bt, p.RPS) + maxi * kWaves * bt * hd + (size_t)kWaves * bt;
     const bool ma = hd == 128 && g >= 4;                                          // attention on MFMA tiles: a K tile per wavefront
-    const size_t npart = (g >= 8 && !ma) ? (size_t)kWaves * (64 / (hd / 8)) : kWaves;      // attention partials folded through LDS
+    const size_t npart = kWaves;                                                  // attention partials folded through LDS
     const size_t f2 = (size_t)hd + (size_t)(g + 2) * hd + 8 + 2 * (size_t)g * npart + (size_t)g * npart * hd +
                       (ma ? (size_t)kWaves * 32 * (hd + 8) / 2 + 2 * 256 * 4 : 0);   // K tiles, q operands
-    const size_t f3 = (size_t)bt * (hd + (mfma_tiles(hd, bt) ? 4 : 0)) + (size_t)kWaves * rb * kOutChunk;
+    // merged attention rows, then the sums of the merge (one per thread) or, on MFMA tiles, the two halves of the product
+    const size_t f3 = mfma_tiles(hd, bt) ? (size_t)bt * (hd + 4) + (size_t)2 * bt * kOutChunk : (size_t)bt * hd + kThreads;
     size_t f = f1 > f2 ? f1 : f2;
     return f > f3 ? f : f3;
 }

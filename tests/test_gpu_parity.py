@@ -398,3 +398,18 @@ def test_merge_of_kv_splits(hd, batch, kv_splits):
         res = r.run(inp, pos, out_fill=float("nan"), packed=True)
         check(res, ref[pos], inp, pos, "splits %d pos %d" % (kv_splits, pos))
     r.blk.close()
+
+
+@pytest.mark.parametrize("d_model,nq,nkv,hd,batch", [
+    (256, 16, 2, 64, 1),      # one column per workgroup, 64 and more partials of it; eight query heads on the vector tile
+    (4096, 4, 4, 64, 2),      # 32 values per workgroup: the most that sixteen lanes each add
+    (4232, 2, 2, 128, 2),     # 34: one thread each
+    (776, 8, 1, 64, 4),       # four batch rows, column pieces that end inside a chunk
+])
+def test_sums_between_lanes(d_model, nq, nkv, hd, batch):
+    """Row groups of 8 and 16 lanes folded in registers (projection, attention, output projection), and the two forms of the
+    sum over heads on both sides of their border."""
+    shape = cf_inputs.BlockShape("s", d_model, nq, nkv, hd, 10000.0, 90)
+    inp = cf_inputs.make_inputs(shape, seed=5, batch=batch, kv_len=90)
+    r = Runner(shape, batch, inp["max_seq"])
+    check(r.run(inp, 90, out_fill=float("nan")), oracle(inp, shape, 90), inp, 90, "D=%d" % d_model)
