@@ -26,7 +26,7 @@ struct cf_handle_s {
     float *dbg_q = nullptr, *dbg_attn = nullptr;
     unsigned long long *dbg_t = nullptr;
     uint16_t *chain[2] = {nullptr, nullptr};   // hidden states between the layers of a stack, [max_batch, d_model] each
-    uint64_t *xslots = nullptr;                // the same between the layers of a one-launch stack: stamped fp32, [max_batch, d_model]
+    uint64_t *xslots = nullptr;                // the same between the layers of a one-launch stack: stamped pairs of values, [max_batch, d_model / 2]
     // tuning
     int tune_w = 0, tune_ks = 0, tune_ns = 0;
     int balance_rows = 0, balance_tokens = 32;   // half the length difference between even and odd splits (-1: off)
@@ -250,6 +250,21 @@ int check_residency(cf_handle_s *h, const Params &p, int bt, size_t lds_bytes)
     return CF_OK;
 }
 
+// Whether all layers of a stack go into one launch: at head_dim 128, where the slices of the projection are multiples of
+// eight rows (a layer's input is fetched in pieces of eight values).  With norm or residual every workgroup fetches the whole
+// rows of its input (it needs their mean squares), which pays at batch 1: us a layer, launch per layer / one launch,
+// Llama-3-8B shape 27.1 / 25.2, Llama-2-7B shape, 1024 rows 32.9 / 32.3, 1000 columns, 2 heads per group 20.2 / 18.7, but 8192 columns
+// 61.6 / 62.4 and, with more rows, Llama-2-7B shape, batch 2 37.6 / 39.4, 1024 columns, 1 head per group, batch 16 37.1 / 43.1,
+// Llama-3-8B shape, batch 2 / 4 / 8 / 16 32.1 / 31.8, 31.4 / 30.1, 35.5 / 35.6, 45.0 / 45.7.
+bool one_launch(const cf_handle_s *h, int batch, int pos, bool norm, bool residual)
+{
+    if (h->cfg.head_dim != 128 || h->slot_area || batch < 1 || batch > h->cfg.max_batch || pos < 0) return false;
+    if ((norm || residual) && (batch > 1 || h->cfg.d_model > 8 * cf::kThreads)) return false;
+    Params p;
+    std::memset(&p, 0, sizeof p);
+    return make_plan(h, batch, pos, &p) == CF_OK && ((p.RB | p.RD) & 7) == 0 && p.W <= h->num_cu;
+}
+
 }  // namespace
 
 extern "C" {
@@ -317,7 +332,7 @@ int cf_create(const cf_config *cfg, cf_handle *out)
     const size_t times_bytes = align_up((size_t)8 * h->num_cu * cf::kStamps * sizeof(unsigned long long), 256);
     h->exchange_bytes = h->counters_bytes + p1_bytes + p2_bytes + p3_bytes;
     const size_t chain_bytes = align_up(B * c.d_model * sizeof(uint16_t), 256);
-    const size_t xslot_bytes = align_up(B * c.d_model * sizeof(uint64_t), 256);
+    const size_t xslot_bytes = align_up(B * (c.d_model / 2) * sizeof(uint64_t), 256);
     h->exchange_bytes += xslot_bytes;
     h->ws_bytes = h->counters_bytes + p1_bytes + p2_bytes + p3_bytes + xslot_bytes + 2 * dbg_bytes + times_bytes +
                   2 * chain_bytes;
@@ -476,8 +491,8 @@ int cf_decode_stack(cf_handle h, int32_t n_layers, int32_t batch, const void *x,
         if (!aligned16(W_qkv[l]) || !aligned16(W_o[l]) || !aligned16(k_cache[l]) || !aligned16(v_cache[l]) ||
             (norm_weight && !aligned16(norm_weight[l])))
             return CF_EINVAL;
-    if (!norm_weight && !residual && h->cfg.head_dim == 128 && !h->slot_area) {
-        // The bare block: up to kMaxStackLayers layers per launch, the hidden state handed from layer to layer
+    if (one_launch(h, batch, pos, norm_weight != nullptr, residual != 0)) {
+        // Up to kMaxStackLayers layers per launch, the hidden state handed from layer to layer
         // inside the kernel; a deeper stack takes several such launches, chained through the two buffers.
         const void *in = x;
         int chunk_index = 0;
@@ -492,9 +507,10 @@ int cf_decode_stack(cf_handle h, int32_t n_layers, int32_t batch, const void *x,
                 a.tab[l].wo = static_cast<const uint16_t *>(W_o[l0 + l]);
                 a.tab[l].kc = static_cast<uint16_t *>(k_cache[l0 + l]);
                 a.tab[l].vc = static_cast<uint16_t *>(v_cache[l0 + l]);
+                a.tab[l].gamma = norm_weight ? static_cast<const uint16_t *>(norm_weight[l0 + l]) : nullptr;
             }
             const int rc = decode_impl(h, packed != 0, batch, in, W_qkv[l0], W_o[l0], k_cache[l0], v_cache[l0], pos, dst, stream,
-                                       nullptr, 0.f, 0, nullptr, &a);
+                                       norm_weight ? norm_weight[l0] : nullptr, eps, residual, nullptr, &a);
             if (rc != CF_OK) return rc;
             in = dst;
         }

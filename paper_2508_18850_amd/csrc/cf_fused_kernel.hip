@@ -159,9 +159,7 @@ __device__ __forceinline__ void lds_barrier()
 
 __device__ __forceinline__ float wave_sum(float v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    return lanes::sum_groups<16>(row_sum<16>(v));
 }
 
 // Maximum / sum over the wavefront, the same value in every lane: four data-parallel-primitive steps inside each row of
@@ -195,6 +193,11 @@ struct Xbuf {
     __device__ __forceinline__ u32x2 ld(size_t idx) const
     {
         return __builtin_amdgcn_raw_buffer_load_b64(r, (unsigned)(idx * 8), 0, 16);
+    }
+    // two neighbouring pairs (idx even): each half carries its own stamp, so nothing rests on the 16 bytes arriving together
+    __device__ __forceinline__ u32x4 ld2(size_t idx) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, (unsigned)(idx * 8), 0, 16);
     }
     __device__ __forceinline__ void st(size_t idx, float v, uint32_t stamp) const
     {
@@ -449,23 +452,22 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     // round trip per value for slices of more than 1024 rows).  The host makes the slices multiples of eight rows
     // wherever that leaves no slice empty; the others are staged value by value.
     constexpr bool XV = !STACK;
-    constexpr int XP = MF ? 4 : 2;
-    const bool xvec = XV && ((p.RB | p.RD) & 7) == 0;
+    constexpr bool ROW = STACK && kLayer;                         // the whole row is fetched (below)
+    static_assert(!ROW || BT == 1, "one row per launch");
+    constexpr int XP = MF && !STACK ? 4 : 2;
+    const bool xvec = STACK || ((p.RB | p.RD) & 7) == 0;          // (the host launches no stack otherwise)
     const int P8 = p.RPS >> 3, npc = xvec ? p.B * P8 : 0;         // pieces of a row's slice, of all rows
-    const uint4 *xg4 = reinterpret_cast<const uint4 *>(p.x), *gg4 = reinterpret_cast<const uint4 *>(p.gamma ? p.gamma : p.x);
+    const uint4 *xg4 = reinterpret_cast<const uint4 *>(p.x), *gg4 = reinterpret_cast<const uint4 *>(lp.gamma ? lp.gamma : p.x);
     uint4 xp[XV ? XP : 1], gp[XV ? XP : 1];
     auto piece_of = [&](int i, int &b, int &c) {                  // false: past the rows or past the slice
         b = BT == 1 ? 0 : qdiv(i, p.div_p8);
         c = i - b * P8;
         return i < npc && 8 * c < nrows;
     };
-    // The input of a stack (stamped slots, in its first layer x) value by value, XR per thread and round trip, the batch's own
-    // rows only; the first trip is requested here.  One trip for the whole
-    // slice or, past XR * 512 values, a wait for every value by itself took, us a layer of the one-launch stack:
-    // Llama-3-8B shape, 2048 rows, batch 2 / 4 / 16 31.0 / 33.8 / 57.6, Llama-2-70B shape, 1024 rows, batch 4 / 16 72.4 / 107.0;
-    // so they take 30.2 / 28.0 / 49.3 and 64.0 / 96.3.  (MFMA tiles with 17 / 16 / 14 values per trip: batch 16 49.6 / 49.4 /
-    // 48.9, Llama-2-7B shape, batch 8 59.2 / 59.2 / 58.2 against 57.0 with 9: the weights in flight leave few registers.)
-    constexpr int XR = MF ? 9 : BT + 1;
+    // The input of a stack comes from stamped slots, two fp16 values and the stamp in eight bytes; in its first layer from x.
+    // Without norm and residual a workgroup fetches its slice, in pieces like those above (two 16-byte loads each), XP per
+    // thread and round trip, the batch's own rows only; the first trip is requested here.  With norm (batch 1, d_model at most
+    // 8 NT) it fetches the whole row, a piece per thread, since it needs its mean square, and stages the pieces of its slice from it.
     const int xn = p.B * p.RPS;
     const float inv_rps = __builtin_amdgcn_rcpf((float)p.RPS);
     auto x_at = [&](int i, int &b, int &r) {                      // value i: row b of the batch, row r of the slice
@@ -473,28 +475,29 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         r = i - b * p.RPS;
         return i < xn && r < nrows;
     };
-    u32x2 xs2[XR];                                                // stamped slots, or the values as they are
     const bool from_slots = STACK && layer > 0;
     const Xbuf xsl(xin ? (const void *)xin : (const void *)p.p1);
-    // (all of them unconditional: a load inside a branch would be waited for at the branch's end)
-    auto x_slots = [&](int i0) {
-        int i = i0 + tid;
-        asm volatile("" : "+v"(i));                               // (addresses are computed anew, not kept in registers)
-#pragma unroll
-        for (int q = 0; q < XR; ++q) {
-            int b, r;
-            const bool in = x_at(i + q * NT, b, r);
-            xs2[q] = xsl.ld(in ? (size_t)b * p.D + r0 + r : 0);
-        }
-    };
-    auto x_values = [&](int i0) {
+    u32x4 sp[STACK ? XP : 1][2];                                  // pieces of the slice: {two values, stamp} x 4
+    auto piece_slots = [&](int i0) {
         int i = i0 + tid;
         asm volatile("" : "+v"(i));
 #pragma unroll
-        for (int q = 0; q < XR; ++q) {
-            int b, r;
-            const bool in = x_at(i + q * NT, b, r);
-            xs2[q].x = p.x[in ? (size_t)b * p.D + r0 + r : 0];
+        for (int q = 0; q < XP; ++q) {
+            int b, c;
+            const size_t at = piece_of(i + q * NT, b, c) ? ((size_t)b * p.D + r0) / 2 + 4 * c : 0;
+            sp[q][0] = xsl.ld2(at);
+            sp[q][1] = xsl.ld2(at + 2);
+        }
+    };
+    auto piece_values = [&](int i0) {
+        int i = i0 + tid;
+        asm volatile("" : "+v"(i));
+#pragma unroll
+        for (int q = 0; q < XP; ++q) {
+            int b, c;
+            const uint4 v = xg4[piece_of(i + q * NT, b, c) ? ((size_t)b * p.D + r0) / 8 + c : 0];
+            sp[q][0] = u32x4{v.x, 0u, v.y, 0u};
+            sp[q][1] = u32x4{v.z, 0u, v.w, 0u};
         }
     };
     if constexpr (XV) {
@@ -504,20 +507,17 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             const bool in = piece_of(tid + q * NT, b, c);
             xp[q] = xg4[in ? ((size_t)b * p.D + r0) / 8 + c : 0];
         }
-    } else {
-        // (the same number of loads on both paths, so that the waits behind this branch stay exact)
-#pragma unroll
-        for (int q = 0; q < XR; ++q) xs2[q] = u32x2{0u, 0u};
+    } else if constexpr (!ROW) {
         if (from_slots)
-            x_slots(0);
+            piece_slots(0);
         else
-            x_values(0);
+            piece_values(0);
     }
     // RMSNorm in front of the projection (when a weight vector is given): the projection is linear, so the
     // weights gamma go into the staged slice of x and the factor 1/sqrt(mean(x^2) + eps) of a row goes into
     // the partial sums when they are stored.  Every workgroup takes the mean square from the whole row
     // (D*2 bytes: one or two 16-byte loads per thread, issued here with the other small loads).
-    const bool norm = kLayer && p.gamma != nullptr;
+    const bool norm = kLayer && lp.gamma != nullptr;
     if (XV && norm) {       // (a wait behind this branch counts the loads of the path without it: nothing drains)
 #pragma unroll
         for (int q = 0; q < XP; ++q) {
@@ -530,12 +530,13 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     constexpr int RG = BT < 4 ? BT : (MF ? 8 : 4);                // rows whose loads are in flight together
     const int d8 = p.D >> 3;                                      // 16-byte pieces of a row
     const uint4 *x4 = reinterpret_cast<const uint4 *>(p.x);
-    uint4 xq[RG][2];                                              // rows b0 .. b0 + RG - 1; needs D <= 2 * 8 * NT
+    constexpr int KR = ROW ? 1 : 2;                               // pieces of a row per thread: needs D <= KR * 8 * NT
+    uint4 xq[RG][KR];                                             // rows b0 .. b0 + RG - 1
     auto load_rows = [&](int b0) {
 #pragma unroll
         for (int r = 0; r < RG; ++r)
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int k = 0; k < KR; ++k) {
                 const int c = tid + k * NT;
                 if (b0 + r < p.B && (k == 0 || d8 > NT))          // (uniform)
                     xq[r][k] = x4[c < d8 ? (size_t)(b0 + r) * d8 + c : 0];
@@ -547,7 +548,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             if (b0 + r >= p.B) break;                             // (uniform)
             float ss = 0.f;
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int k = 0; k < KR; ++k) {
                 float f[8];
                 unpack8(__builtin_bit_cast(h8, xq[r][k]), f);
                 float t = 0.f;
@@ -562,10 +563,25 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 #pragma unroll
     for (int r = 0; r < RG; ++r)
 #pragma unroll
-        for (int k = 0; k < 2; ++k) xq[r][k] = uint4{0u, 0u, 0u, 0u};
+        for (int k = 0; k < KR; ++k) xq[r][k] = uint4{0u, 0u, 0u, 0u};
     // (in front of the second weight batch: behind it the squares would wait for that batch; 16-row tile, 4 rows of
     // 4096: x staged at 10.3 us with the loads behind the batch)
-    if (norm) load_rows(0);
+    if (norm && !ROW) load_rows(0);
+    // the row that is the input of a stack with norm or residual, and the weights gamma that belong to it
+    u32x4 rsl[2];
+    uint4 grow;
+    auto row_slots = [&]() {
+        const size_t at = tid < d8 ? 4 * tid : 0;
+        rsl[0] = xsl.ld2(at);
+        rsl[1] = xsl.ld2(at + 2);
+    };
+    if constexpr (ROW) {
+        grow = gg4[norm && tid < d8 ? tid : 0];
+        if (from_slots)
+            row_slots();
+        else
+            load_rows(0);
+    }
     // for the RoPE tables, below: the frequency and the position of every table entry of this thread
     constexpr int NE = RopeRows<HD, BT>::NE;
     const bool own_pos = kLayer && p.row_pos != nullptr;
@@ -607,30 +623,49 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             xs[i] = v;
         }
     };
-    if (xvec) {
-        // (rows past the batch are left as they are: what they give lands in rows of the product nobody reads)
-        auto stage_piece = [&](int b, int c, const uint4 &xw, const uint4 &gw, bool in) {
-            const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-            h8 hi = in ? __builtin_bit_cast(h8, xw) : zero, lo = zero;
-            float f[8], g[8];
-            unpack8(hi, f);
-            if (norm) {
-                unpack8(__builtin_bit_cast(h8, gw), g);
+    // (rows past the batch are left as they are: what they give lands in rows of the product nobody reads)
+    auto stage_piece = [&](int b, int c, const uint4 &xw, const uint4 &gw, bool in) {
+        const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+        h8 hi = in ? __builtin_bit_cast(h8, xw) : zero, lo = zero;
+        float f[8], g[8];
+        unpack8(hi, f);
+        if (norm) {
+            unpack8(__builtin_bit_cast(h8, gw), g);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) f[j] = in ? f[j] * g[j] : 0.f;
+            for (int j = 0; j < 8; ++j) f[j] = in ? f[j] * g[j] : 0.f;
+        }
+        if constexpr (MF) {
+            if (norm) {
+                split_hi_lo(f, hi, lo);
+                *reinterpret_cast<h8 *>(xl + b * XS + 8 * c) = lo;
             }
-            if constexpr (MF) {
-                if (norm) {
-                    split_hi_lo(f, hi, lo);
-                    *reinterpret_cast<h8 *>(xl + b * XS + 8 * c) = lo;
-                }
-                *reinterpret_cast<h8 *>(xh + b * XS + 8 * c) = hi;
-            } else {
-                float *dst = xs + b * p.RPS + 8 * c;
-                *reinterpret_cast<f32x4 *>(dst) = f32x4{f[0], f[1], f[2], f[3]};
-                *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{f[4], f[5], f[6], f[7]};
+            *reinterpret_cast<h8 *>(xh + b * XS + 8 * c) = hi;
+        } else {
+            float *dst = xs + b * p.RPS + 8 * c;
+            *reinterpret_cast<f32x4 *>(dst) = f32x4{f[0], f[1], f[2], f[3]};
+            *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{f[4], f[5], f[6], f[7]};
+        }
+    };
+    // The slots carry the stamp of the previous layer.  A workgroup whose projection nobody waits for (no column block of its
+    // own) may arrive here after its sources have moved on and stamped newer values: any stamp from the previous layer's up
+    // to the last layer's of this launch is taken.
+    const uint32_t want = stamp_of(cnt0, layer - 1);
+    auto arrived = [&](uint32_t have) { return (uint32_t)(have - want) <= (uint32_t)n_layers; };
+    if constexpr (ROW) {
+        const int c = tid - (r0 >> 3), np = nrows >> 3;           // this thread's piece in the slice; pieces of the slice
+        if (from_slots) {
+            Spin spin;
+            while (!((tid >= d8) | (arrived(rsl[0].y) & arrived(rsl[0].w) & arrived(rsl[1].y) & arrived(rsl[1].w)))) {
+                if (spin.expired(p)) break;
+                row_slots();
             }
-        };
+            xq[0][0] = uint4{rsl[0].x, rsl[0].z, rsl[1].x, rsl[1].z};
+        }
+        if ((unsigned)c < (unsigned)np) stage_piece(0, c, xq[0][0], grow, true);
+        if (norm) square_rows(0);
+        const uint4 none = {0u, 0u, 0u, 0u};
+        for (int i = np + tid; i < P8; i += NT) stage_piece(0, i, none, none, false);     // the last slice may be shorter
+    } else if (XV && xvec) {
 #pragma unroll
         for (int q = 0; q < XP; ++q) {
             int b, c;
@@ -643,49 +678,46 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             stage_piece(b, c, xg4[in ? ((size_t)b * p.D + r0) / 8 + c : 0], gg4[in ? r0 / 8 + c : 0], in);
         }
     } else if constexpr (STACK) {
-        // The slots carry the stamp of the previous layer.  A workgroup whose projection nobody waits for (no
-        // column block of its own) may arrive here after its sources have moved on and stamped newer values:
-        // any stamp from the previous layer's up to the last layer's of this launch is taken.
-        const uint32_t want = stamp_of(cnt0, layer - 1);
-        auto x_take = [&](int i0) {                               // waits for the trip that starts at value i0, and stages it
+        auto take_pieces = [&](int i0) {                          // waits for the trip that starts at piece i0, and stages it
             if (from_slots) {
                 Spin spin;
                 for (;;) {
                     bool ok = true;
 #pragma unroll
-                    for (int q = 0; q < XR; ++q) {
-                        int b, r;
-                        ok &= !x_at(i0 + tid + q * NT, b, r) | ((uint32_t)(xs2[q].y - want) <= (uint32_t)n_layers);
+                    for (int q = 0; q < XP; ++q) {
+                        int b, c;
+                        ok &= !piece_of(i0 + tid + q * NT, b, c) |
+                              (arrived(sp[q][0].y) & arrived(sp[q][0].w) & arrived(sp[q][1].y) & arrived(sp[q][1].w));
                     }
                     if (ok || spin.expired(p)) break;
-                    x_slots(i0);
+                    piece_slots(i0);
                 }
             }
 #pragma unroll
-            for (int q = 0; q < XR; ++q) {
-                int b, r;
+            for (int q = 0; q < XP; ++q) {
+                int b, c;
                 const int i = i0 + tid + q * NT;
-                const bool in = x_at(i, b, r);
-                const float v = from_slots ? __builtin_bit_cast(float, xs2[q].x) : h2f((uint16_t)xs2[q].x);
-                if (i < xn) stage(i, b, r, in ? v : 0.f);
+                const bool in = piece_of(i, b, c);
+                const uint4 v = uint4{sp[q][0].x, sp[q][0].z, sp[q][1].x, sp[q][1].z};
+                if (i < npc) stage_piece(b, c, v, v, in);
             }
         };
         // (the first trip outside the loop: inside it, its addresses are computed once more, 0.2 - 0.9 us a layer at batch 1)
-        x_take(0);
-        for (int trip = XR * NT; trip < xn; trip += XR * NT) {    // (uniform)
+        take_pieces(0);
+        for (int trip = XP * NT; trip < npc; trip += XP * NT) {   // (uniform)
             int i0 = trip;
             asm volatile("" : "+s"(i0));                          // (the addresses of a trip are not kept for the next)
             if (from_slots)
-                x_slots(i0);
+                piece_slots(i0);
             else
-                x_values(i0);
-            x_take(i0);
+                piece_values(i0);
+            take_pieces(i0);
         }
     } else {
         for (int i = tid; i < xn; i += NT) {                      // (slices that are no multiples of eight rows)
             int b, r;
             const bool in = x_at(i, b, r);
-            stage(i, b, r, in ? h2f(p.x[(size_t)b * p.D + r0 + r]) * (norm ? h2f(p.gamma[r0 + r]) : 1.f) : 0.f);
+            stage(i, b, r, in ? h2f(p.x[(size_t)b * p.D + r0 + r]) * (norm ? h2f(lp.gamma[r0 + r]) : 1.f) : 0.f);
         }
     }
     if (MF && !xvec) {
@@ -698,7 +730,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             xl[b * XS + r] = (_Float16)0.f;
         }
     }
-    if (norm) {
+    if (norm && !ROW) {
         square_rows(0);
         for (int b0 = RG; b0 < p.B; b0 += RG) {       // large batches: the other rows
             load_rows(b0);
@@ -1687,30 +1719,40 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 // partials of those columns in slot order (the cross-head reduction that the paper
 // does with atomicAdd), then writes fp16.
 // ---------------------------------------------------------------------------
-// The residual input of output value v0 + threadIdx.x of this workgroup (0 when there is none).
-__device__ __forceinline__ uint16_t residual_input(const Params &p, int tid0, int v0)
+// Output columns a workgroup owns: an even number, since a stack hands its hidden state on in pairs of values.
+__device__ __forceinline__ int own_columns(const Params &p) { return ((p.D + p.W - 1) / p.W + 1) & ~1; }
+
+// The residual input of output value v0 + i of this workgroup (0 when there is none): from x, in a stack past its first layer
+// from the slots xin, where this workgroup itself has left it.
+__device__ __forceinline__ uint16_t residual_input(const Params &p, int i0, int v0, const uint64_t *xin)
 {
-    const int cpw = (p.D + p.W - 1) / p.W;
+    const int cpw = own_columns(p);
     const int c0 = blockIdx.x * cpw;
     const int ncol = min(cpw, p.D - c0);
-    const int i = v0 + tid0;
+    const int i = v0 + i0;
     uint16_t r = 0;
     if (kLayer && (p.flags & kFlagResidual) && ncol > 0 && i < ncol * p.B) {
         const int b = i / ncol, c = i - b * ncol;
-        r = p.x[(size_t)b * p.D + c0 + c];
+        const size_t at = (size_t)b * p.D + c0 + c;
+        if (xin) {
+            const uint32_t two = Xbuf(xin).ld(at >> 1).x;
+            r = (uint16_t)(at & 1 ? two >> 16 : two);
+        } else {
+            r = p.x[at];
+        }
     }
     return r;
 }
 
 // xout != null (a layer of a stack that is not the last): the result, rounded to fp16 as `out` would hold it, goes to
-// the slots the next layer's projection reads its input from, not to `out`.
-template <bool FEW, class HookFn>
-__device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t stamp, float *smem, uint64_t *xout, HookFn &&after_polls)
+// the slots the next layer's projection reads its input from, not to `out`.  xin: the slots this layer's input came from.
+template <bool FEW, bool STACK, class HookFn>
+__device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t stamp, float *smem, uint64_t *xout, const uint64_t *xin, HookFn &&after_polls)
 {
     const int tid = tid0;
     const Xbuf x3(p.p3);
     const int nslots = p.nq * p.RS3;
-    const int cpw = (p.D + p.W - 1) / p.W;
+    const int cpw = own_columns(p);
     const int c0 = blockIdx.x * cpw;
     const int ncol = min(cpw, p.D - c0);
     if (ncol <= 0) {                                 // no column of its own (W * cpw > D): the hook runs all the same, a
@@ -1731,7 +1773,7 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
         // have so few and lost 1 % to the code.)
         const bool wide = FEW && cb <= NT / 16;
         const int own = wide ? tid >> 4 : tid;       // the value whose sums this thread adds
-        const uint16_t xres = residual_input(p, own, v0);
+        const uint16_t xres = residual_input(p, own, v0, xin);
         if (s0 < spt) {
             const int n = (nslots - s0 + spt - 1) / spt;
             const size_t base = (size_t)s0 * p.B * p.D + (size_t)b * p.D + c0 + c, stride = (size_t)spt * p.B * p.D;
@@ -1741,25 +1783,28 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
         CF_STAMP(19);           // head partials arrived
         lds_barrier();
         if (v0 == 0) after_polls();
-        auto write = [&](int bo, int co, float sum) {
-            if (kLayer && (p.flags & kFlagResidual)) sum = h2f(xres) + sum;
-            if (xout)
-                Xbuf(xout).st((size_t)bo * p.D + c0 + co, h2f(f2h(sum)), stamp);
-            else
+        float sum = !wide && kLayer && (p.flags & kFlagResidual) ? h2f(xres) : 0.f;
+        if (own < cb)
+            for (int k = wide ? tid & 15 : 0; k < spt; k += wide ? 16 : 1) sum += smem[k * cb + own];
+        if (wide) sum = row_sum<16>(sum);
+        if (wide && kLayer && (p.flags & kFlagResidual)) sum = h2f(xres) + sum;
+        if (!STACK || !xout) {
+            if (own < cb && (!wide || (tid & 15) == 0)) {
+                const int bo = (v0 + own) / ncol, co = (v0 + own) - bo * ncol;
                 p.out[(size_t)bo * p.D + c0 + co] = f2h(sum);
-        };
-        if (wide) {
-            if (own < cb) {
-                float sum = 0.f;
-                for (int k = tid & 15; k < spt; k += 16) sum += smem[k * cb + own];
-                sum = row_sum<16>(sum);
-                const int bo = (v0 + own) / ncol;
-                if ((tid & 15) == 0) write(bo, (v0 + own) - bo * ncol, sum);
             }
-        } else if (tid < cb) {
-            float sum = 0.f;
-            for (int k = 0; k < spt; ++k) sum += smem[k * cb + tid];
-            write(b, c, sum);
+        } else {
+            // pairs of an even value and the one behind it, neighbours of one row (the workgroup's columns are an even number)
+            const uint32_t h = f2h(sum);
+            float a = __builtin_bit_cast(float, h), n = a;
+            if (wide)
+                lanes::swap16(a, n);                              // n: the value of the odd row of lanes beside this one
+            else
+                n = dpp_move<0xF5>(n);                            // quad_perm [1,1,3,3]
+            if (own < cb && (own & 1) == 0 && (!wide || (tid & 15) == 0)) {
+                const int bo = (v0 + own) / ncol, co = (v0 + own) - bo * ncol;
+                Xbuf(xout).st(((size_t)bo * p.D + c0 + co) >> 1, __builtin_bit_cast(float, h | __builtin_bit_cast(uint32_t, n) << 16), stamp);
+            }
         }
         lds_barrier();
     }
@@ -1840,7 +1885,8 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // weights and caches of this layer (layer 0, and the only layer of a plain call: those of the parameters);
     // a reference into the argument block either way, so that each pointer is fetched where it is used
     static_assert(offsetof(Params, wo) == offsetof(Params, wqkv) + 8 && offsetof(Params, kc) == offsetof(Params, wqkv) + 16 &&
-                      offsetof(Params, vc) == offsetof(Params, wqkv) + 24, "Params holds a LayerPtrs");
+                      offsetof(Params, vc) == offsetof(Params, wqkv) + 24 && offsetof(Params, gamma) == offsetof(Params, wqkv) + 32,
+                  "Params holds a LayerPtrs");
     const LayerPtrs &lp = (STACK && layer > 0) ? tab[layer] : *reinterpret_cast<const LayerPtrs *>(&p.wqkv);
     KvBuf<HD, G> kv;
     OutTile<HD> tile;
@@ -1919,7 +1965,7 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // one already after the merge of the attention partials 37.7; none 37.6)
     if (AHEAD >= 1)
         p1_all<HD, G, BT, STACK, 1>(p, lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
-    final_reduce<(BT <= 4)>(p, tl, stamp, smem, more ? xslots : nullptr, [&]() {
+    final_reduce<(BT <= 4), STACK>(p, tl, stamp, smem, more ? xslots : nullptr, layer > 0 ? xslots : nullptr, [&]() {
         if (AHEAD >= 2)
             p1_all<HD, G, BT, STACK, 2>(p, lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
     });
@@ -1940,14 +1986,17 @@ __global__ void __launch_bounds__(NT) CF_KERNEL(const Params p)
     decode_steps<HD, G, BT, false>(p, nullptr, 1, nullptr);
 }
 
-#if !CF_LAYER
 // A stack of layers in one launch: the argument block carries the table of per-layer pointers by value.
+#if CF_LAYER
+#define CF_STACK_KERNEL fused_layer_stack
+#else
+#define CF_STACK_KERNEL fused_decode_stack
+#endif
 template <int HD, int G, int BT>
-__global__ void __launch_bounds__(NT) fused_decode_stack(const StackArgs a)
+__global__ void __launch_bounds__(NT) CF_STACK_KERNEL(const StackArgs a)
 {
     decode_steps<HD, G, BT, true>(a.p, a.tab, a.n_layers, a.xslots);
 }
-#endif
 
 #if !CF_LAYER
 // One-time rearrangement of the weights into per-head contiguous blocks (16 bytes per thread step).
@@ -2010,18 +2059,17 @@ KernelFn pick(int hd, int g, int bt)
     return nullptr;
 }
 
-#if !CF_LAYER
 using StackFn = void (*)(const StackArgs);
 
 template <int G>
 StackFn pick_stack_bt(int bt)
 {
-    switch (bt) {
-    case 1: return fused_decode_stack<128, G, 1>;
-    case 4: return fused_decode_stack<128, G, 4>;
-    case 16: return fused_decode_stack<128, G, 16>;
-    default: return nullptr;
-    }
+    if (bt == 1) return CF_STACK_KERNEL<128, G, 1>;
+#if !CF_LAYER                                           // (with norm or residual: batch 1 only)
+    if (bt == 4) return CF_STACK_KERNEL<128, G, 4>;
+    if (bt == 16) return CF_STACK_KERNEL<128, G, 16>;
+#endif
+    return nullptr;
 }
 
 // (head_dim 128 only: the shapes whose stacks are worth one launch)
@@ -2036,7 +2084,6 @@ StackFn pick_stack(int hd, int g, int bt)
     default: return nullptr;
     }
 }
-#endif
 
 }  // namespace
 
@@ -2059,7 +2106,31 @@ static hipError_t launch_of(KernelFn fn, const Params &p, size_t lds_bytes, hipS
     return hipGetLastError();
 }
 
+static hipError_t launch_stack_of(StackFn fn, const StackArgs &a, size_t lds_bytes, hipStream_t stream)
+{
+    if (!fn || a.p.row_pos || a.n_layers < 1 || a.n_layers > kMaxStackLayers) return hipErrorInvalidDeviceFunction;
+    // all workgroups must be resident, as for the one-layer kernel
+    int per_cu = 0;
+    if (lds_bytes > 48 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        if (e != hipSuccess) return e;
+    }
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(fn), kThreads, lds_bytes);
+    if (e != hipSuccess) return e;
+    int dev = 0, cus = 0;
+    if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+    if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+    if ((long)per_cu * cus < a.p.W) return hipErrorLaunchOutOfResources;
+    hipLaunchKernelGGL(fn, dim3(a.p.W), dim3(kThreads), lds_bytes, stream, a);
+    return hipGetLastError();
+}
+
 #if CF_LAYER
+
+hipError_t launch_layer_stack(const StackArgs &a, int hd, int g, int bt, size_t lds_bytes, hipStream_t stream)
+{
+    return launch_stack_of(pick_stack(hd, g, bt), a, lds_bytes, stream);
+}
 
 hipError_t max_workgroups_per_cu_layer(int hd, int g, int bt, size_t lds_bytes, int *out)
 {
@@ -2110,22 +2181,8 @@ hipError_t launch_pack(const uint16_t *wqkv, const uint16_t *wo, uint16_t *wqkv_
 
 hipError_t launch_fused_stack(const StackArgs &a, int hd, int g, int bt, size_t lds_bytes, hipStream_t stream)
 {
-    StackFn fn = pick_stack(hd, g, bt);
-    if (!fn || wants_layer_kernel(a.p) || a.n_layers < 1 || a.n_layers > kMaxStackLayers) return hipErrorInvalidDeviceFunction;
-    // all workgroups must be resident, as for the one-layer kernel
-    int per_cu = 0;
-    if (lds_bytes > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
-    }
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(fn), kThreads, lds_bytes);
-    if (e != hipSuccess) return e;
-    int dev = 0, cus = 0;
-    if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-    if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-    if ((long)per_cu * cus < a.p.W) return hipErrorLaunchOutOfResources;
-    hipLaunchKernelGGL(fn, dim3(a.p.W), dim3(kThreads), lds_bytes, stream, a);
-    return hipGetLastError();
+    if (wants_layer_kernel(a.p)) return launch_layer_stack(a, hd, g, bt, lds_bytes, stream);
+    return launch_stack_of(pick_stack(hd, g, bt), a, lds_bytes, stream);
 }
 
 hipError_t launch_fused(const Params &p, int hd, int g, int bt, size_t lds_bytes, hipStream_t stream)

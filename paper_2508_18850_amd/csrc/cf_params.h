@@ -39,13 +39,14 @@ constexpr int kFlagResidual = 2;   // out = x + block output
 struct LayerPtrs {             // what differs from layer to layer of a stack
     const uint16_t *wqkv, *wo;
     uint16_t *kc, *vc;
+    const uint16_t *gamma;     // [D] RMSNorm weight applied to x in front of the projection, or null: x is used as it is
 };
 struct Params {
     const uint16_t *x;
-    const uint16_t *wqkv, *wo; // these four in the order of LayerPtrs: the kernel reads them as one
+    const uint16_t *wqkv, *wo; // these five in the order of LayerPtrs: the kernel reads them as one
     uint16_t *kc, *vc;
+    const uint16_t *gamma;
     const int32_t *row_pos;    // [B] tokens cached for each batch row (at most pos), or null: pos for every row
-    const uint16_t *gamma;     // [D] RMSNorm weight applied to x in front of the projection, or null: x is used as it is
     uint16_t *out;
     // workspace
     unsigned long long *done;  // [workgroups][kCounterStride]: launches that workgroup w has completed
@@ -74,12 +75,12 @@ struct Params {
     uint32_t spin_ticks;   // wait limit in 100 MHz ticks (at most 42 s)
 };
 
-// A stack of layers in one launch (cf_decode_stack without RMSNorm and residual): the pointers of every layer travel
-// by value in the kernel's argument block, behind the parameters of the first layer.
-constexpr int kMaxStackLayers = 88;        // 256 + 16 + 88 * 32 bytes = 3088 of the 4096 an argument block may have
+// A stack of layers in one launch: the pointers of every layer travel by value in the kernel's argument block, behind the
+// parameters of the first layer.
+constexpr int kMaxStackLayers = 88;        // 256 + 16 + 88 * 40 bytes = 3792 of the 4096 an argument block may have
 struct StackArgs {
     Params p;                  // everything of layer 0, and what all layers share
-    uint64_t *xslots;          // [B][D] stamped fp32: the hidden state between two layers
+    uint64_t *xslots;          // [B][D / 2] {two fp16 values, stamp}: the hidden state between two layers
     int n_layers, reserved;
     LayerPtrs tab[kMaxStackLayers];
 };
@@ -92,12 +93,14 @@ bool wants_layer_kernel(const Params &p);
 // Launch the variant for (head_dim, group size, batch tile).  Returns a hipError_t.
 hipError_t launch_fused(const Params &p, int head_dim, int group, int batch_tile, size_t lds_bytes,
                         hipStream_t stream);
-// The block kernel over a.n_layers layers in one launch (a.p must not ask for RMSNorm, residual or per-row positions).
+// The kernel over a.n_layers layers in one launch (a.p must not ask for per-row positions; with RMSNorm or residual the
+// slices of the projection have to be multiples of eight rows).
 hipError_t launch_fused_stack(const StackArgs &a, int head_dim, int group, int batch_tile, size_t lds_bytes,
                               hipStream_t stream);
 // Workgroups of that variant that fit on one CU with `lds_bytes` of LDS each (0 = variant missing).
 hipError_t max_workgroups_per_cu(int head_dim, int group, int batch_tile, size_t lds_bytes, bool layer, int *out);
-// the same two for the layer kernel (defined by the -DCF_LAYER=1 translation unit; called by the two above)
+// the same three for the layer kernel (defined by the -DCF_LAYER=1 translation unit; called by those above)
+hipError_t launch_layer_stack(const StackArgs &a, int head_dim, int group, int batch_tile, size_t lds_bytes, hipStream_t stream);
 hipError_t launch_fused_layer(const Params &p, int head_dim, int group, int batch_tile, size_t lds_bytes,
                               hipStream_t stream);
 hipError_t max_workgroups_per_cu_layer(int head_dim, int group, int batch_tile, size_t lds_bytes, int *out);

@@ -62,11 +62,12 @@ def check_layers(shape, layers, gammas, eps, residual, pos, hidden, caches):
 
 
 S64 = cf_inputs.BlockShape("s64", 512, 8, 4, 64, 10000.0, 0)
-# head_dim 128 without RMSNorm and residual: all layers in one launch
+# head_dim 128: all layers in one launch
 M128 = cf_inputs.BlockShape("mha128", 512, 4, 4, 128, 10000.0, 0)
 G2 = cf_inputs.BlockShape("gqa2", 512, 4, 2, 128, 10000.0, 0)
 G4 = cf_inputs.BlockShape("gqa4", 1024, 8, 2, 128, 500000.0, 0)
 G8 = cf_inputs.BlockShape("gqa8", 1024, 8, 1, 128, 10000.0, 0)
+ODD = cf_inputs.BlockShape("odd", 2056, 8, 2, 128, 10000.0, 0)
 
 
 @pytest.mark.parametrize("shape,norm,residual,packed,batch,n_layers,pos", [
@@ -75,7 +76,11 @@ G8 = cf_inputs.BlockShape("gqa8", 1024, 8, 1, 128, 10000.0, 0)
     (M128, False, 0, True, 1, 5, 150), (M128, False, 0, False, 3, 4, 97), (M128, False, 0, True, 9, 3, 150),
     (G2, False, 0, True, 1, 4, 300), (G2, False, 0, False, 4, 3, 31), (G4, False, 0, True, 1, 4, 333),
     (G4, False, 0, True, 2, 3, 0), (G4, False, 0, False, 16, 3, 70), (G8, False, 0, True, 1, 4, 257),
-    (G8, False, 0, True, 4, 3, 64), (M128, False, 0, True, 1, 1, 150)],
+    (G8, False, 0, True, 4, 3, 64), (M128, False, 0, True, 1, 1, 150),
+    # norm and residual: one launch at batch 1, one per layer otherwise; columns and slices that do not come out even
+    (M128, True, 1, True, 1, 4, 150), (M128, True, 0, False, 1, 3, 40), (G2, False, 1, True, 1, 3, 300), (G2, True, 1, True, 2, 3, 90),
+    (G4, True, 1, True, 2, 4, 77), (G4, False, 1, False, 3, 3, 33), (G8, True, 1, True, 1, 4, 64), (G4, True, 1, True, 1, 3, 0),
+    (ODD, True, 1, True, 1, 4, 60), (ODD, True, 1, False, 3, 3, 20), (ODD, False, 0, True, 2, 3, 60)],
     ids=lambda v: getattr(v, "name", None))
 def test_stack_matches_single_calls_and_oracle(shape, norm, residual, packed, batch, n_layers, pos):
     from paper_2508_18850_amd import DecodeBlock
