@@ -1428,7 +1428,8 @@ struct OutTile {
 // item; lane (l % 16, l / 16) loads eight adjacent columns of rows 32 s + 8 (l / 16) + 0..7 for the two steps s
 // (the same lane layout as in the projection: eight rows are transposed in the lane into MFMA operands).
 template <int HD, bool MF>
-__device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, int tid0, int hq, int c3, int rs, int ch, OutTile<HD> &t, int part = 2)
+__device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, int tid0, int hq, int c3, int rs, int ch, OutTile<HD> &t, int part = 2,
+                                        bool live = true)
 {
     const int lane = tid0 & 63, wv = tid0 >> 6;
     // row-major [nq*HD][D], or packed [nq][ceil(D/512)][HD][512] (one contiguous tile per head and chunk)
@@ -1440,7 +1441,7 @@ __device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, in
     const uint32_t rowb = (p.flags & kFlagPacked) ? (uint32_t)kOutChunk * 2 : (uint32_t)p.D * 2;
     // vector tiles: wavefront wv takes 64 columns of the chunk, its eight row groups of eight lanes the rows r + 8 u
     const int col = 64 * wv + 8 * (lane & 7);
-    uint32_t voff = (cbase + col) < p.D ? (uint32_t)(lane >> 3) * rowb + col * 2 : kNoLoad;
+    uint32_t voff = live && (cbase + col) < p.D ? (uint32_t)(lane >> 3) * rowb + col * 2 : kNoLoad;
     // (opaque to the compiler: it otherwise computes the sixteen per-row offsets of all call sites once, far
     // ahead of the first one, and spills them)
     asm volatile("" : "+v"(voff));
@@ -1450,7 +1451,7 @@ __device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, in
     if constexpr (MF) {
         static_assert(OutTile<HD>::MAXR == 16, "two steps of eight rows per lane");
         const int lig = lane & 15, kg = lane >> 4, cb = wv & 3, kh = wv >> 2;
-        uint32_t voffm = (cbase + 128 * cb + 8 * lig) < p.D ? (uint32_t)(8 * kg) * rowb + (uint32_t)(128 * cb + 8 * lig) * 2
+        uint32_t voffm = live && (cbase + 128 * cb + 8 * lig) < p.D ? (uint32_t)(8 * kg) * rowb + (uint32_t)(128 * cb + 8 * lig) * 2
                                                             : kNoLoad;
         asm volatile("" : "+v"(voffm));
 #pragma unroll
@@ -1810,6 +1811,18 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
     }
 }
 
+// Whether the first half of the output-projection tile is requested before the queries are waited for (the second behind the
+// cached rows) and not behind the cached rows (the second behind the stored partial): the memory pipe idles while the q
+// partials travel, and the merge finds less of the tile in front of its polls.  Per layer, us: Llama-2-7B shape, 100 / 4096 / 8000
+// rows 29.9 / 38.0 / 47.3 -> 28.9 / 37.2 / 46.6, one launch over the layers, 1024 rows 30.6 -> 29.7; D 2056, 14 heads of 64, batch 3
+// 20.0 -> 19.2.  With attention on MFMA tiles the registers decide: four heads per group, one or two rows gain at short caches only
+// (Llama-3-8B shape, 100 rows 25.0 -> 24.1, 32000 rows 41.7 -> 42.0; a choice at run time costs 1 us, the waits behind it are no
+// longer exact), eight heads (37.9 -> 38.8), the 16-row tile (35.2 -> 37.5, spills) and the one-launch stack (25.0 -> 25.4) lose.
+template <int HD, int G>
+struct EarlyTile {
+    static constexpr bool on = !AttnMfma<HD, G>::on;
+};
+
 // Splits that the merge of phase 3 has in flight where a thread adds more than four (the sums and their order are the same).
 // Four in the one-launch stack with one batch row and up to two query heads per KV head: the next layer's weights fill the
 // registers there, and eight made the kernel spill 20 bytes per lane.
@@ -1921,7 +1934,14 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
         c3 = rem / p.RS3;
         rs = rem % p.RS3;
     };
+    constexpr bool EARLY = EarlyTile<HD, G>::on;
     bool tile_ready = false;
+    if (EARLY) {
+        // (no branch around the loads, lanes off instead: the waits for the cached rows count them)
+        int hq, c3, rs;
+        p3_args(member < n3 ? member : 0, hq, c3, rs);
+        p3_load<HD, Mfma<HD, BT>::on>(p, lp, tl, hq, c3, rs, 0, tile, 0, member < n2 && member < n3);
+    }
     auto p3_prefetch = [&](int part) {
         if (member < n3) {
             int hq, c3, rs;
@@ -1938,10 +1958,10 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
             st2.prefetch(kv, 0);
             st2.prefetch(kv, 1);
         }
-        // stage 1: first half of the output-projection tile, stage 2: second half
+        // stage 1: first half of the output-projection tile, stage 2: second half (early: stage 1 the second half)
         p2_item<HD, G>(p, lp, tl, team, qdiv(it, p.div_ns), qmod(it, p.NS, p.div_ns), stamp, first, st2, kv, eq, smem,
                        s_rope + (kLayer && p.row_pos ? qdiv(it, p.div_ns) * HD : 0), [&](int stage) {
-            if (final_item) p3_prefetch(stage - 1);
+            if (final_item && (!EARLY || stage == 1)) p3_prefetch(EARLY ? 1 : stage - 1);
         });
     }
     if (member >= n2) p3_prefetch(2);
