@@ -65,6 +65,36 @@ __device__ __forceinline__ float max_groups(float v)
     return LPR == 8 ? fmaxf(v, xor8(v)) : v;
 }
 
+// Sum / maximum over a row of 16 lanes, and over a half wavefront, in every lane of it.
+__device__ __forceinline__ float sum_row(float v)
+{
+    v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]
+    v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
+    v += dpp_move<0x141>(v);   // row_half_mirror: lane i <-> 7-i within 8 lanes
+    return v + dpp_move<0x140>(v);   // row_mirror: lane i <-> 15-i within 16 lanes
+}
+__device__ __forceinline__ float max_row(float v)
+{
+    v = fmaxf(v, dpp_move<0xB1>(v));
+    v = fmaxf(v, dpp_move<0x4E>(v));
+    v = fmaxf(v, dpp_move<0x141>(v));
+    return fmaxf(v, dpp_move<0x140>(v));
+}
+// v of this lane plus v of the lane 16 further in the same half wavefront (i ^ 16)
+__device__ __forceinline__ float add16(float v)
+{
+    float p = v, q = v;
+    swap16(p, q);
+    return p + q;
+}
+__device__ __forceinline__ float sum_half(float v) { return add16(sum_row(v)); }
+__device__ __forceinline__ float max_half(float v)
+{
+    float p = max_row(v), q = p;
+    swap16(p, q);
+    return fmaxf(p, q);
+}
+
 // Eight values per lane, each summed over the row groups, the sums dealt out: afterwards the lane of row group r holds
 // those of values r * (LPR / 8) + j, j < LPR / 8.  A swap of halves between two values and an addition leave half as
 // many values, so that it takes 12 (16 lanes per row) or 14 instructions where a sum in every lane takes 32 or 48.

@@ -32,6 +32,7 @@
 // of out 41.8, end 44.3.  What bounds it is the chain of hand-overs, 2 to 4 us each.
 // Each stage requests its weights (or cached rows) before it waits for its input.  All waits are bounded
 // (CF_ETIMEOUT), all workgroups have to be resident at once.
+#include "cf_lanes_device.h"
 #include "cf_mfma_device.h"
 #include "cf_mla_internal.h"
 #include "cf_rope_device.h"
@@ -508,8 +509,7 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
                     mx = fmaxf(mx, sc[4 * e + i]);
                 }
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = cf::lanes::max_groups<16>(mx);
             const float Mn = fmaxf(M, mx);
             if (__any(Mn > M)) {                                        // a maximum has grown: rescale
                 const float f = __builtin_amdgcn_exp2f(M - Mn);
@@ -551,13 +551,11 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
 #pragma unroll
                     for (int i = 0; i < 8; ++i) d = fmaf(qf[k][i], kd[i >> 2][i & 3], d);
                 }
-            d += __shfl_xor(d, 16);
-            d += __shfl_xor(d, 32);
+            d = cf::lanes::sum_groups<16>(d);
             if (lane < HT) s_sn[wv * HT + c] = d;
         }
         // the two halves (and the new token) -> one partial (m, l, acc) per head
-        lw += __shfl_xor(lw, 16);
-        lw += __shfl_xor(lw, 32);
+        lw = cf::lanes::sum_groups<16>(lw);
         if (kq == 0 && lane < HT) {
             s_ml[th * 2 * HT + c] = M;
             s_ml[th * 2 * HT + HT + c] = lw;
@@ -643,12 +641,8 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
                 p[k] = X.ld4(a.x3 + ((it0 + (size_t)min(sq + 4 * k, a.NS - 1) * ngroups) * HT + head) * L + LJ * j + 4 * d4);
         }
         if (l5 >= a.NS) m = kNegBig, l = 0.f;
-        float M = m;
-#pragma unroll
-        for (int off = 1; off < 32; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
-        float f = l5 < a.NS ? __builtin_amdgcn_exp2f(m - M) : 0.f, Ls = l * f;
-#pragma unroll
-        for (int off = 1; off < 32; off <<= 1) Ls += __shfl_xor(Ls, off);
+        const float M = cf::lanes::max_half(m);
+        const float f = l5 < a.NS ? __builtin_amdgcn_exp2f(m - M) : 0.f, Ls = cf::lanes::sum_half(l * f);
         f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k = 0; k < kMaxSplits / 4; ++k) {
@@ -658,9 +652,7 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            z[i] += __shfl_xor(z[i], 8);
-            z[i] += __shfl_xor(z[i], 16);
-            z[i] /= Ls;
+            z[i] = cf::lanes::add16(z[i] + cf::lanes::xor8(z[i])) / Ls;
         }
         if (sq == 0 && b < B) X.st4(a.xz + ((size_t)b * a.nh + head) * L + LJ * j + 4 * d4, z);
         post(fD + head * TS + j, x.stamp);

@@ -27,6 +27,7 @@
 // is bound by what it loads (64 KB of A, 131 KB of W_Up, 295 KB of rows, 131 KB of W_Down): requesting W_Up or the rows
 // in front of the first hand-over moves the wait, not the end (21.2 - 21.9 us).
 // All waits are bounded (CF_ETIMEOUT), all workgroups have to be resident at once.
+#include "cf_lanes_device.h"
 #include "cf_mla_internal.h"
 #include "cf_rope_device.h"
 #include "cf_team_device.h"
@@ -54,11 +55,7 @@ typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint16_t f2h(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
+namespace lanes = cf::lanes;
 
 // Workgroup barrier that orders LDS accesses only (__syncthreads() would also wait until the write-through stores of
 // the last hand-over have reached memory); nothing here passes data between the threads of a workgroup through
@@ -91,15 +88,6 @@ __device__ __forceinline__ float take1(const Exchange &x, __amdgpu_buffer_rsrc_t
         if (q.y == x.stamp) return __builtin_bit_cast(float, q.x);
         if (cf::team::gave_up(x, t0)) return 0.f;
     }
-}
-
-// Sum over the lanes of a wavefront that agree modulo 8 (a rotation inside a row of 16 lanes, two shuffles).
-__device__ __forceinline__ float sum_mod8(float v)
-{
-    v += dpp_move<0x128>(v);               // row_ror:8
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
 }
 
 __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a)
@@ -158,11 +146,10 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc[c] = fmaf((float)xv[k], (float)wr[k][c], acc[c]);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[c] = sum_mod8(live ? acc[c] : 0.f);
-        if (lane < 8) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) s_part[wv * 64 + pl * 8 + c] = acc[c];
-        }
+        for (int c = 0; c < 8; ++c) acc[c] = live ? acc[c] : 0.f;
+        float fold[1];                                                // over the wavefront's rows; a lane keeps column lane / 8
+        lanes::fold8<8>(acc, fold);
+        s_part[wv * 64 + pl * 8 + (lane >> 3)] = fold[0];
         lds_sync();
         mycol = tid < 64 && sl < a.ksa && 64 * t + tid < P * 8;
         col = (size_t)sl * CQ + 64 * t + tid;
@@ -298,10 +285,7 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
         }
 #pragma unroll
         for (int u = 0; u < UR; ++u) {                                // sum over the 16 lanes of the row
-            d[u] += dpp_move<0xB1>(d[u]);
-            d[u] += dpp_move<0x4E>(d[u]);
-            d[u] += dpp_move<0x141>(d[u]);
-            d[u] += dpp_move<0x140>(d[u]);
+            d[u] = lanes::sum_row(d[u]);
         }
         float mn = m;
 #pragma unroll
@@ -349,35 +333,22 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
     // values of the wavefront.  The eight wavefronts' partials go through LDS (all 32 row groups through LDS, 64 KB written
     // and read back, took 0.5 us more).
     {
-        float mw = fmaxf(m, __shfl_xor(m, 16));
-        mw = fmaxf(mw, __shfl_xor(mw, 32));
+        const float mw = lanes::max_groups<16>(m);
         const float f = __builtin_amdgcn_exp2f(m - mw);
-        lsum *= f;
-        lsum += __shfl_xor(lsum, 16);
-        lsum += __shfl_xor(lsum, 32);
+        lsum = lanes::sum_groups<16>(lsum * f);
         float h[2][8], q8[8];
-        auto swap32 = [](float &p, float &q) {                        // p: lanes 32..63 <-> q: lanes 0..31
-            const auto t = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, p), __builtin_bit_cast(unsigned, q), false, false);
-            p = __builtin_bit_cast(float, (unsigned)t[0]);
-            q = __builtin_bit_cast(float, (unsigned)t[1]);
-        };
-        auto swap16 = [](float &p, float &q) {                        // odd rows of p <-> even rows of q
-            const auto t = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, p), __builtin_bit_cast(unsigned, q), false, false);
-            p = __builtin_bit_cast(float, (unsigned)t[0]);
-            q = __builtin_bit_cast(float, (unsigned)t[1]);
-        };
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 float p = acc[k][c] * f, q = acc[k + 2][c] * f;
-                swap32(p, q);                                         // lanes 0..31 sum acc[k], lanes 32..63 acc[k + 2]
+                lanes::swap32(p, q);                                         // lanes 0..31 sum acc[k], lanes 32..63 acc[k + 2]
                 h[k][c] = p + q;
             }
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             float p = h[0][c], q = h[1][c];
-            swap16(p, q);                                             // even rows of 16 lanes: h[0], odd rows: h[1]
+            lanes::swap16(p, q);                                             // even rows of 16 lanes: h[0], odd rows: h[1]
             q8[c] = p + q;
         }
         // lane (rg, li): latent dimensions 128 (2 (rg >> 1) + (rg & 1)) + 8 li .. + 8 = 128 rg + 8 li
@@ -398,10 +369,7 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
             for (int c = 0; c < 8; ++c) d = fmaf(ql[k][c], s_new[128 * k + 8 * li + c], d);
 #pragma unroll
         for (int c = 0; c < 4; ++c) d = fmaf(qr4[c], s_new[L + 4 * li + c], d);
-        d += dpp_move<0xB1>(d);
-        d += dpp_move<0x4E>(d);
-        d += dpp_move<0x141>(d);
-        d += dpp_move<0x140>(d);
+        d = lanes::sum_row(d);
         if (lane == 0) s_rope[R] = d;
     }
     lds_sync();
@@ -438,16 +406,9 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
 #pragma unroll
             for (int c = 0; c < 8; ++c) o[c] = fmaf(zv, (float)wdn[k][c], o[c]);
         }
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            o[c] += __shfl_xor(o[c], 16);
-            o[c] += __shfl_xor(o[c], 32);
-        }
-        if (lane < 16) {
-            float *dst = s_part + wv * 128 + pcD * 8;
-            *reinterpret_cast<float4 *>(dst) = make_float4(o[0], o[1], o[2], o[3]);
-            *reinterpret_cast<float4 *>(dst + 4) = make_float4(o[4], o[5], o[6], o[7]);
-        }
+        float t[2];
+        lanes::fold8<16>(o, t);
+        *reinterpret_cast<float2 *>(s_part + wv * 128 + pcD * 8 + 2 * rg) = make_float2(t[0], t[1]);
         lds_sync();
         if (tid < a.v + 2) {
             float sum = 0.f;
@@ -501,17 +462,17 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
             for (int k = 0; k < 4; ++k) ok &= qa[k].y == x.stamp;
             if (ok || cf::team::gave_up(x, tw)) break;
         }
-        const float ml = __builtin_bit_cast(float, qml.x), pm = __shfl(ml, lane & 15), pl = __shfl(ml, 16 + (lane & 15));
-        float Mx = pm;
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) Mx = fmaxf(Mx, __shfl_xor(Mx, off));
+        float pm = __builtin_bit_cast(float, qml.x), pl = pm;
+        lanes::swap16(pm, pl);                                         // even rows of 16 lanes hold maxima, odd ones sums
+        const float Mx = lanes::max_row(pm);
         const float fw = __builtin_amdgcn_exp2f(pm - Mx);              // of partial lane & 15
-        float Lx = pl * fw;
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) Lx += __shfl_xor(Lx, off);
+        const float Lx = lanes::sum_row(pl * fw);
+        const int first = __builtin_amdgcn_readfirstlane(4 * qtr);
         float av = 0.f;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) av = fmaf(__builtin_bit_cast(float, qa[k].x), __shfl(fw, 4 * qtr + k), av);
+        for (int k = 0; k < 4; ++k)
+            av = fmaf(__builtin_bit_cast(float, qa[k].x),
+                      __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, fw), first + k)), av);
         lds_sync();                                                    // s_part has been read
         s_part[tid] = av / Lx;
     }
@@ -528,16 +489,9 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
 #pragma unroll
             for (int c = 0; c < 8; ++c) o[c] = fmaf(av, (float)wor[k][c], o[c]);
         }
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            o[c] += __shfl_xor(o[c], 16);
-            o[c] += __shfl_xor(o[c], 32);
-        }
-        if (lane < 16) {
-            float *dst = s_part + 512 + wv * 128 + pcE * 8;
-            *reinterpret_cast<float4 *>(dst) = make_float4(o[0], o[1], o[2], o[3]);
-            *reinterpret_cast<float4 *>(dst + 4) = make_float4(o[4], o[5], o[6], o[7]);
-        }
+        float t[2];
+        lanes::fold8<16>(o, t);
+        *reinterpret_cast<float2 *>(s_part + 512 + wv * 128 + pcE * 8 + 2 * rg) = make_float2(t[0], t[1]);
         lds_sync();
         if (tid < 8 * pcsE && j * pcsE * 8 + tid < a.D) {
             float sum = 0.f;
