@@ -17,8 +17,11 @@ struct TeamArgs {
     const float *in;
     float *out;
     float *scratch;
-    uint64_t *slots;
-    unsigned long long *counters;    // [ranks][kCounterStride]
+    uint64_t *slots;                 // [ranks][cap]: pairs of the gather
+    uint32_t *boxes;                 // [2][ranks][kMaxRounds][box]: words of the reduce, in two sets
+    unsigned long long *counters;    // [ranks][kCounterStride]: launches of the gather, launches of the reduce, boxes and
+                                     // words per box the last reduce wrote
+    size_t set, box;                 // words of a set, of a box
     uint32_t *err;
     size_t cap, count;
     int N;
@@ -37,46 +40,138 @@ __device__ __forceinline__ uint32_t launch_stamp(const TeamArgs &a, unsigned lon
     return (uint32_t)(cnt + (cnt >> 32));
 }
 
-// E values per thread and chunk; the buffer is worked through chunk by chunk
+// The boxes of this launch of the reduce, and what it owes its predecessor.
+struct ReduceLaunch {
+    unsigned long long count, wrote;         // launches before this one; what the last one wrote: boxes << 32 | words per box
+    cf::team::Boxes x;
+    __device__ __forceinline__ explicit ReduceLaunch(const TeamArgs &a)
+    {
+        asm volatile("s_load_dwordx4 %0, %1, 0x8\n\ts_waitcnt lgkmcnt(0)"
+                     : "=s"(state)
+                     : "s"(a.counters + (size_t)blockIdx.x * kCounterStride)
+                     : "memory");
+        count = (unsigned long long)state.y << 32 | state.x;
+        wrote = (unsigned long long)state.w << 32 | state.z;
+        x.r = __builtin_amdgcn_make_buffer_rsrc(a.boxes + (count & 1 ? a.set : 0), 0, 0xfffffff0u, 0x00020000);
+        x.cap = a.box;
+        x.err = a.err;
+        x.spin_ticks = a.spin_ticks;
+    }
+    // kEmpty back into what the last launch wrote in the other set; the count of this launch and what it has written
+    __device__ __forceinline__ void finish(const TeamArgs &a, int boxes, size_t words) const
+    {
+        const __amdgpu_buffer_rsrc_t other = __builtin_amdgcn_make_buffer_rsrc(a.boxes + (count & 1 ? 0 : a.set), 0, 0xfffffff0u, 0x00020000);
+        const cf::team::words4 none = {cf::team::kEmpty, cf::team::kEmpty, cf::team::kEmpty, cf::team::kEmpty};
+        const int nb = (int)(wrote >> 32);
+        for (int s = 0; s < nb; ++s)
+            for (size_t i = 4 * threadIdx.x; i < (uint32_t)wrote; i += cf::team::kQuads)
+                __builtin_amdgcn_raw_buffer_store_b128(none, other, (unsigned)((x.at(blockIdx.x, s) + i) * 4), 0, 16);
+        if (threadIdx.x == 0) {
+            unsigned long long *c = a.counters + (size_t)blockIdx.x * kCounterStride;
+            c[1] = count + 1;
+            c[2] = (unsigned long long)boxes << 32 | (unsigned long long)words;
+        }
+    }
+
+private:
+    cf::team::words4 state;
+};
+
+// E 16-byte pieces per thread and chunk; the buffer is worked through chunk by chunk.  32 teams of 8, sum, us a call, with
+// 8-byte {value, stamp} pairs / now: XXX
 template <int E, int OP, bool DIRECT>
 __global__ void __launch_bounds__(kThreads) team_reduce_kernel(const TeamArgs a)
 {
+    using namespace cf::team;
     const int w = blockIdx.x, team = w / a.N, b = w % a.N, tid = threadIdx.x;
-    unsigned long long cnt;
-    const cf::team::Exchange x = {a.slots, a.cap, launch_stamp(a, cnt), a.err, a.spin_ticks};
     const float *src = a.in + (size_t)w * a.count;
     float *dst = a.out + (size_t)w * a.count;
-    for (size_t first = 0; first < a.count; first += (size_t)kThreads * E) {
-        float d[E];
+    f4_t d[E];
+    auto load = [&](size_t first) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const size_t i = first + tid + (size_t)kThreads * e;
-            d[e] = i < a.count ? src[i] : 0.f;
+        for (int e = 0; e < E; ++e) d[e] = load4(src, first + 4 * tid + (size_t)kQuads * e, a.count);
+    };
+    load(0);
+    const ReduceLaunch l(a);
+    int boxes = 1;
+    for (size_t first = 0; first < a.count; first += (size_t)kQuads * E) {
+        if (first) load(first);
+        if (DIRECT) {
+            post_box<E>(l.x, w, 0, first, a.count, d);
+            fold_team<E, OP>(l.x, team * a.N, a.N, b, first, a.count, d);
+        } else {
+            // Alg. 1: in round s rank b reads what rank b - 2^s holds (its own boxes are all a rank writes)
+            int s = 0;
+            for (int stride = 1; stride < a.N; stride <<= 1, ++s) {
+                post_box<E>(l.x, w, s, first, a.count, d);
+                fold_box<E, OP>(l.x, team * a.N + (b - stride + a.N) % a.N, s, first, a.count, d);
+            }
+            boxes = s;
         }
-        if (DIRECT)
-            cf::team::reduce_direct<E, OP>(x, team * a.N, a.N, b, first, a.count, d);
-        else
-            cf::team::reduce<E, OP>(x, team * a.N, a.N, b, first, a.count, d);
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const size_t i = first + tid + (size_t)kThreads * e;
-            if (i < a.count) dst[i] = d[e];
-        }
+        for (int e = 0; e < E; ++e) store4(dst, first + 4 * tid + (size_t)kQuads * e, a.count, d[e]);
     }
-    if (tid == 0) a.counters[(size_t)w * kCounterStride] = cnt;
+    l.finish(a, boxes, a.count);
 }
 
+// Two hops with the fewest bytes: rank b folds slice b of the buffer (in rank order) from the others' boxes 0, posts the
+// result in box 1, and reads the other slices from their owners.
 template <int OP>
 __global__ void __launch_bounds__(kThreads) team_reduce_two_hops_kernel(const TeamArgs a)
 {
+    using namespace cf::team;
+    constexpr int C = 8, E = 1;
     const int w = blockIdx.x, team = w / a.N, b = w % a.N;
-    unsigned long long cnt;
-    const cf::team::Exchange x = {a.slots, a.cap, launch_stamp(a, cnt), a.err, a.spin_ticks};
     const float *src = a.in + (size_t)w * a.count;
     float *dst = a.out + (size_t)w * a.count;
-    cf::team::reduce_two_hops<OP>(x, team * a.N, a.N, b, a.count, [&](size_t i) { return src[i]; },
-                                  [&](size_t i, float v) { dst[i] = v; });
-    if (threadIdx.x == 0) a.counters[(size_t)w * kCounterStride] = cnt;
+    const size_t t4 = 4 * threadIdx.x;
+    const ReduceLaunch l(a);
+    const Boxes &x = l.x;
+    const unsigned sl = (unsigned)(((a.count + a.N - 1) / a.N + 3) & ~(size_t)3);        // values of a slice: whole pieces
+    const size_t lo = min((size_t)b * sl, a.count), hi = min(lo + sl, a.count);
+    for (size_t i0 = 0; i0 < a.count; i0 += (size_t)kQuads * C) {          // post what the owners of the other slices need
+        f4_t v[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) v[k] = load4(src, i0 + t4 + (size_t)kQuads * k, a.count);
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const size_t i = i0 + t4 + (size_t)kQuads * k;
+            if (i < a.count && (i < lo || i >= hi)) x.put(x.at(w, 0) + i, v[k]);
+        }
+    }
+    for (size_t first = lo; first < hi; first += (size_t)kQuads * E) {     // fold the own slice, post it
+        f4_t d[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) d[e] = load4(src, first + t4 + (size_t)kQuads * e, a.count);
+        fold_team<E, OP>(x, team * a.N, a.N, b, first, hi, d);
+        post_box<E>(x, w, 1, first, hi, d);
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (first + t4 + (size_t)kQuads * e < hi) store4(dst, first + t4 + (size_t)kQuads * e, a.count, d[e]);
+    }
+    for (size_t i0 = 0; i0 < a.count; i0 += (size_t)kQuads * C) {          // the other slices, from their owners
+        words4 q[C];
+        long long t0 = 0;
+        for (;;) {
+            bool ok = true;
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const size_t i = i0 + t4 + (size_t)kQuads * k;
+                q[k] = words4{0u, 0u, 0u, 0u};
+                if (i < a.count && (i < lo || i >= hi)) q[k] = x.peek(x.at(team * a.N + (int)((unsigned)i / sl), 1) + i);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < C; ++k) ok &= Boxes::there(q[k]);
+            if (ok || x.gave_up(t0)) break;
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const size_t i = i0 + t4 + (size_t)kQuads * k;
+            if (i < a.count && (i < lo || i >= hi)) store4(dst, i, a.count, __builtin_bit_cast(f4_t, q[k]));
+        }
+    }
+    l.finish(a, 2, a.count);
 }
 
 // count = values of one segment; a rank's output has N segments
@@ -179,19 +274,14 @@ Kernel pick_reduce(int e)
     switch (e) {
     case 1: return team_reduce_kernel<1, OP, DIRECT>;
     case 2: return team_reduce_kernel<2, OP, DIRECT>;
-    case 4: return team_reduce_kernel<4, OP, DIRECT>;
-    case 8: return team_reduce_kernel<8, OP, DIRECT>;
     }
-    return team_reduce_kernel<16, OP, DIRECT>;
+    return team_reduce_kernel<4, OP, DIRECT>;
 }
 
-// values per thread and chunk: enough for the whole buffer in one chunk up to 16
-int values_per_thread(size_t values)
+// 16-byte pieces per thread and chunk: enough for the whole buffer in one chunk up to 4
+int pieces_per_thread(size_t values)
 {
-    const size_t need = (values + kThreads - 1) / kThreads;
-    for (int e = 1; e < 16; e *= 2)
-        if ((size_t)e >= need) return e;
-    return 16;
+    return values <= (size_t)cf::team::kQuads ? 1 : values <= (size_t)2 * cf::team::kQuads ? 2 : 4;
 }
 
 }  // namespace
@@ -201,8 +291,10 @@ struct cf_team_s {
     size_t cap = 0;
     int num_cu = 0;
     char *ws = nullptr;
-    size_t slots_bytes = 0, clear_bytes = 0;
+    size_t head_bytes = 0, slots_bytes = 0, boxes_bytes = 0;     // counters; pairs of the gather; words of the reduce
+    size_t box = 0;                         // words of a box
     uint64_t *slots = nullptr;
+    uint32_t *boxes = nullptr;
     unsigned long long *counters = nullptr;
     uint32_t *err = nullptr;
     float *scratch = nullptr;
@@ -233,14 +325,21 @@ int check_call(cf_team t, int32_t teams, int32_t team_size, const void *in, cons
     return CF_OK;
 }
 
+// Counters and pairs cleared, boxes emptied.
+hipError_t reset(cf_team t)
+{
+    hipError_t e = hipMemset(t->ws, 0, t->head_bytes + t->slots_bytes);
+    if (e == hipSuccess) e = hipMemset(t->boxes, 0xff, t->boxes_bytes);
+    return e == hipSuccess ? hipDeviceSynchronize() : e;
+}
+
 // Every workgroup counts its own launches and all of a launch must agree on the count: when the number of
 // workgroups changes, the counts (and with them all stamps) start together again.
 int same_grid(cf_team t, int ranks)
 {
     if (ranks == t->last_ranks) return CF_OK;
     hipError_t e = hipDeviceSynchronize();
-    if (e == hipSuccess) e = hipMemset(t->ws, 0, t->clear_bytes);
-    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = reset(t);
     if (e != hipSuccess) return fail(t, e);
     t->last_ranks = ranks;
     return CF_OK;
@@ -253,6 +352,9 @@ TeamArgs make_args(cf_team t, const float *in, float *out, size_t count, int n)
     a.out = out;
     a.scratch = t->scratch;
     a.slots = t->slots;
+    a.boxes = t->boxes;
+    a.set = (size_t)t->max_ranks * cf::team::kMaxRounds * t->box;
+    a.box = t->box;
     a.counters = t->counters;
     a.err = t->err;
     a.cap = t->cap;
@@ -281,25 +383,28 @@ int cf_team_create(int32_t max_ranks, size_t max_elems, cf_team *out)
     t->cap = max_elems;
     t->num_cu = prop.multiProcessorCount;
     const size_t head = 256 + (size_t)max_ranks * kCounterStride * sizeof(unsigned long long);
-    t->slots_bytes = (size_t)max_ranks * cf::team::kMaxRounds * max_elems * sizeof(uint64_t);
-    if (t->slots_bytes > 0xfffffff0ull) {            // slots are addressed with 32-bit byte offsets
+    // (what the exchange area of a handle took before there were two sets of words: the limit of a handle stays)
+    if ((size_t)max_ranks * cf::team::kMaxRounds * max_elems * sizeof(uint64_t) > 0xfffffff0ull) {
         delete t;
         return CF_EUNSUPPORTED;
     }
-    const size_t head_al = (head + 255) / 256 * 256;
+    auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+    t->head_bytes = up(head);
+    t->slots_bytes = up((size_t)max_ranks * max_elems * sizeof(uint64_t));
+    t->box = (max_elems + 3) & ~(size_t)3;
+    t->boxes_bytes = (size_t)2 * max_ranks * cf::team::kMaxRounds * t->box * sizeof(uint32_t);       // (a set: 32-bit byte offsets)
     const size_t scratch_bytes = (size_t)max_ranks * max_elems * sizeof(float);
-    t->clear_bytes = head_al + t->slots_bytes;
-    e = hipMalloc(reinterpret_cast<void **>(&t->ws), t->clear_bytes + scratch_bytes);
+    e = hipMalloc(reinterpret_cast<void **>(&t->ws), t->head_bytes + t->slots_bytes + t->boxes_bytes + scratch_bytes);
     if (e != hipSuccess) {
         delete t;
         return e == hipErrorOutOfMemory ? CF_ENOMEM : CF_EHIP;
     }
     t->err = reinterpret_cast<uint32_t *>(t->ws + 128);
     t->counters = reinterpret_cast<unsigned long long *>(t->ws + 256);
-    t->slots = reinterpret_cast<uint64_t *>(t->ws + head_al);
-    t->scratch = reinterpret_cast<float *>(t->ws + t->clear_bytes);
-    e = hipMemset(t->ws, 0, t->clear_bytes);
-    if (e == hipSuccess) e = hipDeviceSynchronize();
+    t->slots = reinterpret_cast<uint64_t *>(t->ws + t->head_bytes);
+    t->boxes = reinterpret_cast<uint32_t *>(t->ws + t->head_bytes + t->slots_bytes);
+    t->scratch = reinterpret_cast<float *>(t->ws + t->head_bytes + t->slots_bytes + t->boxes_bytes);
+    e = reset(t);
     if (e != hipSuccess) {
         (void)hipFree(t->ws);
         delete t;
@@ -334,7 +439,7 @@ int cf_team_reduce(cf_team t, int32_t teams, int32_t team_size, int32_t op, cons
         else
             hipLaunchKernelGGL(team_reduce_offchip_kernel<cf::team::kMax>, grid, block, 0, s, a);
     } else {
-        const int e = values_per_thread(elems);
+        const int e = pieces_per_thread(elems);
         Kernel k;
         if (mode == CF_TEAM_TWO_HOPS)
             k = op == CF_TEAM_SUM ? team_reduce_two_hops_kernel<cf::team::kSum> : team_reduce_two_hops_kernel<cf::team::kMax>;
@@ -379,8 +484,7 @@ int cf_team_status(cf_team t, void *stream)
     e = hipMemcpy(&flag, t->err, sizeof flag, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return fail(t, e);
     if (flag) {
-        e = hipMemset(t->ws, 0, t->clear_bytes);     // launch counters and all stamps start afresh
-        if (e == hipSuccess) e = hipDeviceSynchronize();
+        e = reset(t);                                // launch counters, stamps and boxes start afresh
         if (e != hipSuccess) return fail(t, e);
         return CF_ETIMEOUT;
     }

@@ -5,14 +5,16 @@
 // with one write-through store and polled by the receiver until the stamp is the current one.  No flag,
 // no fence, no atomic; a value is either the old pair or the new one.
 //
+// The all-reduce of whole buffers (cf_team_reduce) needs no stamps: see "four bytes per value" below.
+//
 // Two schedules.  The paper's: log2(N) rounds, in round s rank b sends to rank (b + 2^s) mod N and
 // receives from rank (b - 2^s) mod N.  And a direct one: every rank posts its data once and reads the
 // posts of its N - 1 peers, one hop in place of log2(N); a hop through memory costs microseconds here
 // where a hop through a cluster's shared memory costs a fraction of one, so the direct schedule is the one
 // the fused decode kernel uses.
 //
-// Buffers are worked through in chunks of kThreads x E values (E values per thread in registers), so that
-// the register use does not grow with the buffer.
+// Buffers are worked through in chunks (E values or 16-byte pieces per thread in registers), so that the register use does
+// not grow with the buffer.
 //
 // These are device functions to be called by all threads of a workgroup; every workgroup of the team
 // must be resident at the same time (the caller's launch has to guarantee that), because receivers spin.
@@ -32,8 +34,8 @@ constexpr int kMaxRounds = 4;      // N <= 16
 
 enum Op { kSum = 0, kMax = 1 };
 
-// Exchange area of one launch: inbox of rank r, round s = slots[(r * kMaxRounds + s) * cap ...] for the
-// reduce, slots[r * cap ...] for the gather (cap = capacity of one inbox in pairs).
+// Exchange area of one launch: rank r's slots = slots[r * kMaxRounds * cap ...] for the two-hop reduce of pairs,
+// slots[r * cap ...] for the gather (cap in pairs).
 struct Exchange {
     uint64_t *slots;     // device memory, cleared once when it is allocated
     size_t cap;          // pairs per inbox
@@ -73,66 +75,10 @@ __device__ __forceinline__ bool gave_up(const Exchange &x, long long &t0)
 
 constexpr int kPolls = 32;         // polls a thread keeps in flight: the receive rate is kPolls x 8 bytes per round trip
 
-// Wait for the pairs at base + first + tid + kThreads*e (e < E, first + ... < count) and hand each value to
-// use(e, value).  All polls of a batch are issued before the first one is looked at.
-template <int E, class Use>
-__device__ __forceinline__ void take(const Exchange &x, __amdgpu_buffer_rsrc_t r, size_t base, size_t first, size_t count,
-                                     Use &&use)
-{
-    constexpr int C = E < kPolls ? E : kPolls;
-    const size_t tid = threadIdx.x;
-#pragma unroll
-    for (int e0 = 0; e0 < E; e0 += C) {
-        long long t0 = 0;
-        pair_t q[C];
-        for (;;) {
-#pragma unroll
-            for (int k = 0; k < C; ++k) {
-                const size_t i = first + tid + (size_t)kThreads * (e0 + k);
-                q[k] = peek(r, base + (i < count ? i : 0));       // out of range: any valid slot, ignored
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            bool ok = true;
-#pragma unroll
-            for (int k = 0; k < C; ++k) {
-                const size_t i = first + tid + (size_t)kThreads * (e0 + k);
-                ok &= (i >= count) | (q[k].y == x.stamp);
-            }
-            if (ok || gave_up(x, t0)) break;
-        }
-#pragma unroll
-        for (int k = 0; k < C; ++k) use(e0 + k, __builtin_bit_cast(float, q[k].x));
-    }
-}
-
 template <int OP>
 __device__ __forceinline__ float fold(float a, float b)
 {
     return OP == kSum ? a + b : fmaxf(a, b);
-}
-
-// Alg. 1: all-reduce of the N ranks' buffers of `count` values, for the chunk that starts at value `first`:
-// rank b holds value first + tid + kThreads*e in d[e].  On return every rank holds the reduction of the
-// chunk.  fp32, folded in the order of the rounds.
-template <int E, int OP>
-__device__ __forceinline__ void reduce(const Exchange &x, int team_first_rank, int N, int b, size_t first, size_t count,
-                                       float (&d)[E])
-{
-    const __amdgpu_buffer_rsrc_t r = slots_rsrc(x);
-    const size_t tid = threadIdx.x;
-    int s = 0;
-    for (int stride = 1; stride < N; stride <<= 1, ++s) {
-        const int to = (b + stride) % N;
-        const size_t outbox = ((size_t)(team_first_rank + to) * kMaxRounds + s) * x.cap;
-        const size_t inbox = ((size_t)(team_first_rank + b) * kMaxRounds + s) * x.cap;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const size_t i = first + tid + (size_t)kThreads * e;
-            if (i < count) put(r, outbox + i, d[e], x.stamp);
-        }
-        // the whole chunk has been sent before any of it is overwritten (Alg. 1 sends D_b, then folds)
-        take<E>(x, r, inbox, first, count, [&](int e, float v) { d[e] = fold<OP>(d[e], v); });
-    }
 }
 
 // Fold what the N ranks of a team have posted at positions first + tid + kThreads*e (< end) of the area that
@@ -187,23 +133,6 @@ __device__ __forceinline__ void fold_posts(const Exchange &x, __amdgpu_buffer_rs
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) d[e] = acc[e];
-}
-
-// The all-reduce in one hop: every rank posts its chunk in its own slots and folds the N posts in rank order,
-// so that all ranks of a team end with the same bits.
-template <int E, int OP>
-__device__ __forceinline__ void reduce_direct(const Exchange &x, int team_first_rank, int N, int b, size_t first,
-                                              size_t count, float (&d)[E])
-{
-    const __amdgpu_buffer_rsrc_t r = slots_rsrc(x);
-    const size_t tid = threadIdx.x;
-    const size_t box = (size_t)kMaxRounds * x.cap;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const size_t i = first + tid + (size_t)kThreads * e;
-        if (i < count) put(r, (size_t)(team_first_rank + b) * box + i, d[e], x.stamp);
-    }
-    fold_posts<E, OP>(x, r, team_first_rank, N, b, 0, first, count, d);
 }
 
 // The all-reduce in two hops with the fewest bytes: rank b folds slice b of the buffer (count / N values, in
@@ -275,6 +204,148 @@ __device__ __forceinline__ void reduce_two_hops(const Exchange &x, int team_firs
             if (i < count && (i < lo || i >= hi)) use(i, __builtin_bit_cast(float, q[k].x));
         }
     }
+}
+
+// ---- all-reduce of whole buffers, four bytes per value ---------------------------------------------------------------
+//
+// The stamp of a pair doubles the bytes, and a pair is eight bytes at most: a rank's receive rate was that of 8-byte polls
+// (some 30 GB/s per workgroup).  Here a posted value is its own arrival mark: boxes are filled with kEmpty, a value is
+// there as soon as its word is anything else, and four words go in one 16-byte access, of which each is judged by itself.
+// There are two sets of boxes, used by launches in turn; a launch puts back kEmpty into what its predecessor has written in
+// the other set (nobody reads that any more: launches on one handle follow each other), so that the set is empty when the
+// next launch takes it.  A value whose bits are kEmpty, a NaN, is sent as the NaN next to it.
+typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));      // user buffers are 4-byte aligned
+
+constexpr uint32_t kEmpty = 0xffffffffu;
+constexpr int kQuads = kThreads * 4;       // values a workgroup handles with one 16-byte access per thread
+
+// Box s of rank r in the set of this launch = words[(r * kMaxRounds + s) * cap ...], cap a multiple of four.
+struct Boxes {
+    __amdgpu_buffer_rsrc_t r;
+    size_t cap;
+    uint32_t *err;
+    long long spin_ticks;
+    __device__ __forceinline__ size_t at(int rank, int s) const { return ((size_t)rank * kMaxRounds + s) * cap; }
+    __device__ __forceinline__ void put(size_t idx, const f4_t &v) const
+    {
+        words4 q = __builtin_bit_cast(words4, v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = q[k] == kEmpty ? kEmpty - 1 : q[k];
+        __builtin_amdgcn_raw_buffer_store_b128(q, r, (unsigned)(idx * 4), 0, 16);                    // sc1: through to memory
+    }
+    __device__ __forceinline__ words4 peek(size_t idx) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, (unsigned)(idx * 4), 0, 16);                 // sc1: not from a stale cache
+    }
+    static __device__ __forceinline__ bool there(const words4 &q)
+    {
+        return (q.x != kEmpty) & (q.y != kEmpty) & (q.z != kEmpty) & (q.w != kEmpty);
+    }
+    __device__ __forceinline__ bool gave_up(long long &t0) const
+    {
+        return team::gave_up(Exchange{nullptr, 0, 0, err, spin_ticks}, t0);
+    }
+};
+
+// Values i .. i + 3 of a user buffer of `count` values (zeros past its end), and the same stored.
+__device__ __forceinline__ f4_t load4(const float *src, size_t i, size_t count)
+{
+    if (i + 4 <= count) return *reinterpret_cast<const f4u_t *>(src + i);
+    f4_t v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (i + k < count) v[k] = src[i + k];
+    return v;
+}
+__device__ __forceinline__ void store4(float *dst, size_t i, size_t count, const f4_t &v)
+{
+    if (i + 4 <= count) {
+        *reinterpret_cast<f4u_t *>(dst + i) = v;
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (i + k < count) dst[i + k] = v[k];
+}
+
+template <int OP>
+__device__ __forceinline__ f4_t fold4(const f4_t &a, const f4_t &b)
+{
+    f4_t v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = fold<OP>(a[k], b[k]);
+    return v;
+}
+
+// Wait for box s of rank `from`, values first + 4 tid + kQuads e (e < E, < count), and fold them into d (Alg. 1: D_b op B_b).
+template <int E, int OP>
+__device__ __forceinline__ void fold_box(const Boxes &x, int from, int s, size_t first, size_t count, f4_t (&d)[E])
+{
+    const size_t base = x.at(from, s), i0 = first + 4 * threadIdx.x;
+    words4 q[E];
+    long long t0 = 0;
+    for (;;) {
+        bool ok = true;
+#pragma unroll
+        for (int e = 0; e < E; ++e) q[e] = x.peek(base + (i0 + (size_t)kQuads * e < count ? i0 + (size_t)kQuads * e : 0));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < E; ++e) ok &= (i0 + (size_t)kQuads * e >= count) | Boxes::there(q[e]);
+        if (ok || x.gave_up(t0)) break;
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) d[e] = fold4<OP>(d[e], __builtin_bit_cast(f4_t, q[e]));
+}
+
+// d = fold, in rank order, of box 0 of the N ranks of the team at the same values (own d at its place); kInFlight 16-byte
+// polls per thread go out before the first one is looked at.
+template <int E, int OP>
+__device__ __forceinline__ void fold_team(const Boxes &x, int team_first_rank, int N, int b, size_t first, size_t count, f4_t (&d)[E])
+{
+    constexpr int kInFlight = 16, P = kInFlight / E;                  // peers polled together
+    const size_t i0 = first + 4 * threadIdx.x;
+    f4_t acc[E];
+    for (int r0 = 0; r0 < N; r0 += P) {
+        words4 q[P][E];
+        long long t0 = 0;
+        for (;;) {
+            bool ok = true;
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                if (r0 + p < N && r0 + p != b)                        // (uniform)
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+                        q[p][e] = x.peek(x.at(team_first_rank + r0 + p, 0) + (i0 + (size_t)kQuads * e < count ? i0 + (size_t)kQuads * e : first));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                if (r0 + p < N && r0 + p != b)
+#pragma unroll
+                    for (int e = 0; e < E; ++e) ok &= (i0 + (size_t)kQuads * e >= count) | Boxes::there(q[p][e]);
+            if (ok || x.gave_up(t0)) break;
+        }
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            if (r0 + p < N)
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const f4_t v = r0 + p == b ? d[e] : __builtin_bit_cast(f4_t, q[p][e]);
+                    acc[e] = r0 + p == 0 ? v : fold4<OP>(acc[e], v);
+                }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) d[e] = acc[e];
+}
+
+template <int E>
+__device__ __forceinline__ void post_box(const Boxes &x, int rank, int s, size_t first, size_t count, const f4_t (&d)[E])
+{
+    const size_t base = x.at(rank, s), i0 = first + 4 * threadIdx.x;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (i0 + (size_t)kQuads * e < count) x.put(base + i0 + (size_t)kQuads * e, d[e]);
 }
 
 constexpr int kGatherBatch = 16;   // values per thread and step of the gathers
