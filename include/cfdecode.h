@@ -265,7 +265,7 @@ enum { CF_TEAM_ROUNDS = 0, CF_TEAM_TWO_KERNELS = 1, CF_TEAM_DIRECT = 2, CF_TEAM_
 
 /* max_ranks: most workgroups a launch may have; max_elems: most fp32 values a rank may hold in a reduce,
  * or receive in a gather (team_size * elems), at most 65536.  Allocates and clears the exchange area
- * (max_ranks * 4 * max_elems * 8 bytes) and a scratch buffer for the two-kernel versions.  Synchronous. */
+ * (max_ranks * 5 * max_elems * 8 bytes) and a scratch buffer for the two-kernel versions.  Synchronous. */
 int cf_team_create(int32_t max_ranks, size_t max_elems, cf_team *out);
 int cf_team_destroy(cf_team t);
 

@@ -78,7 +78,8 @@ private:
 };
 
 // E 16-byte pieces per thread and chunk; the buffer is worked through chunk by chunk.  32 teams of 8, sum, us a call, with
-// 8-byte {value, stamp} pairs / now: XXX
+// 8-byte {value, stamp} pairs / now: one hop, 16384 values 49.9 / 32.9, 16 teams of 16, 3001 values 14.0 / 10.0; rounds, 16 teams of
+// 16, 16001 values 100 / 75 (an eighth of that is the emptying of the other set); 1024 values 6.6 - 7, bound by the launch.
 template <int E, int OP, bool DIRECT>
 __global__ void __launch_bounds__(kThreads) team_reduce_kernel(const TeamArgs a)
 {

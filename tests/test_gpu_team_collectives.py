@@ -107,3 +107,44 @@ def test_bad_arguments_are_refused():
     big = TeamCollectives(1024, 16)
     assert big.reduce_rc(64, 8, TEAM_SUM, p, p, 16) == -2        # more workgroups than compute units: not resident
     big.close()
+
+
+def test_one_handle_for_changing_calls():
+    """The two sets of boxes in turn: calls of other sizes, modes and (last) another number of ranks on one handle, a gather in
+    between; what a call leaves behind must not be taken for a value of the next but one."""
+    tc = TeamCollectives(64, 20001)
+    st = torch.cuda.current_stream().cuda_stream
+    calls = [(8, 8, 20001, TEAM_DIRECT), (8, 8, 5, TEAM_ROUNDS), (8, 8, 2051, TEAM_TWO_HOPS), (8, 8, 20001, TEAM_ROUNDS),
+             (8, 8, 3, TEAM_TWO_HOPS), (8, 8, 20001, TEAM_TWO_HOPS), (8, 8, 4097, TEAM_DIRECT), (16, 4, 8193, TEAM_ROUNDS),
+             (16, 4, 1, TEAM_DIRECT), (2, 16, 6144, TEAM_DIRECT), (2, 16, 15, TEAM_TWO_HOPS)]
+    for k, (teams, n, elems, mode) in enumerate(calls):
+        _log("call %d: teams=%d N=%d elems=%d mode=%d" % (k, teams, n, elems, mode))
+        host = _data(teams, n, elems, seed=k)
+        src = torch.from_numpy(host).cuda()
+        dst = torch.full_like(src, float("nan"))
+        tc.reduce(teams, n, TEAM_MAX, src.data_ptr(), dst.data_ptr(), elems, mode, st)
+        if k % 3 == 1:
+            seg = min(elems, 20001 // n)
+            full = torch.empty((teams, n, n, seg), dtype=torch.float32, device="cuda")
+            tc.gather(teams, n, src.data_ptr(), full.data_ptr(), seg, TEAM_DIRECT, st)
+        tc.status(st)
+        assert np.array_equal(dst.cpu().numpy(), np.broadcast_to(host.max(axis=1, keepdims=True), host.shape))
+    tc.close()
+
+
+@pytest.mark.parametrize("mode", [TEAM_ROUNDS, TEAM_DIRECT, TEAM_TWO_HOPS])
+def test_a_nan_with_the_bits_of_an_empty_box_arrives(mode):
+    tc = TeamCollectives(8, 64)
+    st = torch.cuda.current_stream().cuda_stream
+    host = _data(1, 8, 64, seed=1)
+    host[0, 3, 7:9] = np.array([0xffffffff], dtype=np.uint32).view(np.float32)
+    src = torch.from_numpy(host).cuda()
+    dst = torch.zeros_like(src)
+    tc.reduce(1, 8, TEAM_SUM, src.data_ptr(), dst.data_ptr(), 64, mode, st)
+    tc.status(st)
+    got = dst.cpu().numpy()
+    assert np.isnan(got[:, :, 7:9]).all() and np.isfinite(np.delete(got, [7, 8], axis=2)).all()
+    tc.reduce(1, 8, TEAM_MAX, src.data_ptr(), dst.data_ptr(), 64, mode, st)
+    tc.status(st)
+    assert np.array_equal(dst.cpu().numpy(), np.broadcast_to(np.fmax.reduce(host, axis=1, keepdims=True), host.shape))
+    tc.close()
