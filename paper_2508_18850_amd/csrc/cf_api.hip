@@ -56,9 +56,10 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Register tile of the batch rows: 1, 4 (vector units) or 16 (MFMA).  The 16-row tile also wins at batch 3 and 4
 // (Llama-3-8B shape, batch 3 / 4: 52.2 / 46.9 against 54.9 / 48.3 us; Llama-2-7B shape, batch 4: 73.4 against 74.8 us).
-// Without MFMA tiles (head_dim 64) the 16-row tile is the vector variant with 128 accumulators per thread: there the
-// 4-row tile keeps batch 3 and 4.
-int batch_tile(int batch, int head_dim) { return batch <= 1 ? 1 : batch <= (cf::mfma_tiles(head_dim, 16) ? 2 : 4) ? 4 : 16; }
+// At head_dim 64 an operand holds two sets of rows, half of its product is thrown away, and the 4-row tile keeps batch 3 and 4:
+// D 2056, 14 heads, batch 3 19.2 against 19.8 us, 1024 columns, 32 heads, batch 4 21.7 against 23.1, tiny shape, batch 4 16.8 against 19.1;
+// from batch 5 on the vector tile loses: 64 heads over 8, batch 8 42.2 / 27.6 us, 32 heads, batch 12 40.0 / 30.4.
+int batch_tile(int batch, int head_dim) { return batch <= 1 ? 1 : batch <= (head_dim == 128 ? 2 : 4) ? 4 : 16; }
 int tile_index(int bt) { return bt == 1 ? 0 : bt == 4 ? 1 : 2; }
 
 constexpr int kMaxKS = 32;

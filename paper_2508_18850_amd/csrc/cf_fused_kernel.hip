@@ -84,7 +84,7 @@ __device__ __forceinline__ void unpack8(const h8 &u, float (&f)[8])
     for (int k = 0; k < 8; ++k) f[k] = (float)u[k];
 }
 
-// Batch tile 16 with head_dim 128: the two projections (Alg. 3 steps 2 and 8) are dense [16 x K] x [K x N]
+// Batch tile 16: the two projections (Alg. 3 steps 2 and 8) are dense [16 x K] x [K x N]
 // products and run on MFMA tiles (v_mfma_f32_16x16x32_f16: A is 16 x 32, B is 32 x 16, fp32 accumulators).
 // Operand layout of that instruction: lane l holds, of A, row l % 16 and eight consecutive values of the
 // contraction index for group l / 16; of B, column l % 16 and the same eight contraction values; of the
@@ -355,13 +355,16 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     // loads per thread and batch: the 16-row batch tile keeps 128 accumulators per thread, and anything above two
     // loads per batch spills (measured on the 8B shape, batch 16: 202 us with 8, 181 with 4, 177 with 2, 182 with 1);
     // the 4-row tile is best with 4 (8B shape, batch 4: 55.1 us with 8, 53.6 with 4, 53.7 with 2)
-    // With MFMA tiles (MF) a batch is eight rows per lane: one 32-row step of the contraction per wavefront.
+    // With MFMA tiles (MF) a batch is eight rows per lane: one step of the contraction, 32 RS rows, per wavefront.
     constexpr bool MF = P1Cfg<HD, BT>::MF;
     constexpr int U = P1Cfg<HD, BT>::U;
     constexpr int MAXI = BT == 1 ? 4 : (BT <= 4 ? 2 : 1);   // selectors whose wave partials are buffered in LDS
     const int tid = tid0, wv = tid >> 6, lig = tid % LPR, grp = tid / LPR;
     const int kg = (tid & 63) >> 4;                         // MF: contraction group of the lane (rows 8 kg .. 8 kg + 7 of a step)
-    const int lrow = 32 * wv + 8 * kg;                      // MF: first row of the lane inside a 256-row batch
+    // MF: the sixteen columns of an operand are LPR 16-byte pieces x RS sets of 32 rows (two sets at head_dim 64)
+    constexpr int RS = MF ? 16 / LPR : 1;
+    const int rs = tid / LPR % RS;
+    const int lrow = 32 * (RS * wv + rs) + 8 * kg;          // MF: first row of the lane inside a batch of 256 RS rows
     const int ks = qmod(member, p.KS, p.div_ks);
     const int sel0 = qdiv(member, p.div_ks), dsel = p.DSEL;
     // slices with an even index (workgroups on the faster dies, see the workgroup mapping in the
@@ -751,13 +754,15 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     CF_STAMP(2);            // x staged
 
     float acc[MF ? 1 : BT][8];              // FMA tiles: [batch row][column] of this lane's row group
-    f32x4 acc4[MF ? 8 : 1];                 // MFMA tiles: [column][batch rows 4 * (lane / 16) + 0..3]
+    // MFMA tiles: [row set][column][batch rows 4 * (lane / 16) + 0..3].  The columns of an operand share its rows of x, so every
+    // set of x rows gets a product of its own with all the weights; a lane's sum is the one of its own set, the others are junk.
+    f32x4 acc4[RS][MF ? 8 : 1];
 #pragma unroll
     for (int b = 0; b < (MF ? 1 : BT); ++b)
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[b][j] = 0.f;
 #pragma unroll
-    for (int c = 0; c < (MF ? 8 : 1); ++c) acc4[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < (MF ? 8 : 1) * RS; ++c) acc4[c % RS][c / RS] = f32x4{0.f, 0.f, 0.f, 0.f};
     int si_first = 0;                       // selector index of the first buffered item
     int nbuf = 0;
     auto flush = [&]() {
@@ -787,18 +792,21 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             // one step of 32 rows: operand A = x[batch row lane % 16][rows of this lane's group], operands B =
             // the eight columns of this lane.  Rows past the slice: their weights are zero (loads switched off)
             // and x, where an operand reaches them, is zero; a group that starts past the slice reads nothing.
-            const int r = NG * i0 + lrow;
             const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-            const int xo = (tid & 15) * XS + min(r, XS - 8);
-            const h8 ah = r < nrows ? *reinterpret_cast<const h8 *>(xh + xo) : zero;
             h8 f[8];
             transpose8(w, f);
 #pragma unroll
-            for (int c = 0; c < 8; ++c) acc4[c] = mfma16(ah, f[c], acc4[c]);
-            if (norm) {
-                const h8 al = r < nrows ? *reinterpret_cast<const h8 *>(xl + xo) : zero;
+            for (int h = 0; h < RS; ++h) {
+                const int r = NG * i0 + 32 * (RS * wv + h) + 8 * kg;
+                const int xo = (tid & 15) * XS + min(r, XS - 8);
+                const h8 ah = r < nrows ? *reinterpret_cast<const h8 *>(xh + xo) : zero;
 #pragma unroll
-                for (int c = 0; c < 8; ++c) acc4[c] = mfma16(al, f[c], acc4[c]);
+                for (int c = 0; c < 8; ++c) acc4[h][c] = mfma16(ah, f[c], acc4[h][c]);
+                if (norm) {
+                    const h8 al = r < nrows ? *reinterpret_cast<const h8 *>(xl + xo) : zero;
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) acc4[h][c] = mfma16(al, f[c], acc4[h][c]);
+                }
             }
         } else {
 #pragma unroll
@@ -826,12 +834,20 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             // the lane holds eight adjacent columns of batch rows 4 * kg + 0..3
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
+                float v[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    v[c] = RS == 2 && rs ? acc4[RS - 1][c][r] : acc4[0][c][r];
+                    if (RS == 2) v[c] += lanes::xor8(v[c]);             // the two row sets of a column
+                }
                 float *dst = red + ((nbuf * NW + wv) * BT + 4 * kg + r) * HD + lig * 8;
-                *reinterpret_cast<f32x4 *>(dst) = f32x4{acc4[0][r], acc4[1][r], acc4[2][r], acc4[3][r]};
-                *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{acc4[4][r], acc4[5][r], acc4[6][r], acc4[7][r]};
+                if (rs == 0) {
+                    *reinterpret_cast<f32x4 *>(dst) = f32x4{v[0], v[1], v[2], v[3]};
+                    *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{v[4], v[5], v[6], v[7]};
+                }
             }
 #pragma unroll
-            for (int c = 0; c < 8; ++c) acc4[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int c = 0; c < 8 * RS; ++c) acc4[c % RS][c / RS] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (nbuf == 0) si_first = si;
             if (++nbuf == MAXI) flush();
         } else {
@@ -868,7 +884,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         uint32_t v = voff0;
         if constexpr (MF) {
 #pragma unroll
-            for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(v) : "v"(acc4[c]));
+            for (int c = 0; c < 8 * RS; ++c) asm volatile("" : "+v"(v) : "v"(acc4[c % RS][c / RS]));
         } else {
 #pragma unroll
             for (int b = 0; b < BT; ++b)
@@ -1424,8 +1440,8 @@ struct OutTile {
 };
 
 // part: 0 = first half of the tile's loads, 1 = second half, 2 = all
-// MF (MFMA tiles): wavefront wv takes columns [128 (wv % 4), +128) of the chunk and rows [64 (wv / 4), +64) of the
-// item; lane (l % 16, l / 16) loads eight adjacent columns of rows 32 s + 8 (l / 16) + 0..7 for the two steps s
+// MF (MFMA tiles): wavefront wv takes columns [128 (wv % 4), +128) of the chunk and one half of the head's HD rows (wv / 4);
+// lane (l % 16, l / 16) loads eight adjacent columns of rows 32 s + 8 (l / 16) + 0..7 for the steps s (one or two)
 // (the same lane layout as in the projection: eight rows are transposed in the lane into MFMA operands).
 template <int HD, bool MF>
 __device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, int tid0, int hq, int c3, int rs, int ch, OutTile<HD> &t, int part = 2,
@@ -1449,15 +1465,15 @@ __device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, in
                                     : (uint32_t)(hq * HD + rs * nrows) * rowb + (uint32_t)cbase * 2;
     const int iters = nrows / 8;
     if constexpr (MF) {
-        static_assert(OutTile<HD>::MAXR == 16, "two steps of eight rows per lane");
+        constexpr int MAXR = OutTile<HD>::MAXR;                         // eight rows per lane and step
         const int lig = lane & 15, kg = lane >> 4, cb = wv & 3, kh = wv >> 2;
         uint32_t voffm = live && (cbase + 128 * cb + 8 * lig) < p.D ? (uint32_t)(8 * kg) * rowb + (uint32_t)(128 * cb + 8 * lig) * 2
                                                             : kNoLoad;
         asm volatile("" : "+v"(voffm));
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const bool mine = part == 2 || (part == 0) == (u < 8);
-            const int row = 64 * kh + 32 * (u >> 3) + (u & 7);          // + 8 kg: the lane's row inside the item
+        for (int u = 0; u < MAXR; ++u) {
+            const bool mine = part == 2 || (part == 0) == (u < MAXR / 2);
+            const int row = HD / 2 * kh + 32 * (u >> 3) + (u & 7);      // + 8 kg: the lane's row inside the item
             if (mine) t.w[u] = Wo.ld(row + 8 * kg < nrows ? voffm : kNoLoad, sbase + (uint32_t)row * rowb);
         }
         return;
@@ -1623,7 +1639,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
         if (cbase >= p.D) break;
         if (ch > 0) p3_load<HD, MF>(p, lp, tid, hq, c3, rs, ch, tile);
         if constexpr (MF) {
-            // [16 batch rows] x [rows of the item] x [128 columns of this wavefront]: two steps of 32 rows for each
+            // [16 batch rows] x [rows of the item] x [128 columns of this wavefront]: one or two steps of 32 rows for each
             // half of the rows; the attention output is split into a high and a low fp16 part (two products), so
             // that it enters with all its fp32 bits
             const int lig = lane & 15, kg = lane >> 4, cb = wv & 3, kh = wv >> 2;
@@ -1631,8 +1647,8 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc4[c] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int sstep = 0; sstep < 2; ++sstep) {
-                const int row = 64 * kh + 32 * sstep + 8 * kg;          // first of the lane's eight rows
+            for (int sstep = 0; sstep < HD / 64; ++sstep) {
+                const int row = HD / 2 * kh + 32 * sstep + 8 * kg;      // first of the lane's eight rows
                 float a[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) a[e] = row < nrows ? as[(lane & 15) * (HD + AP) + rbeg + row + e] : 0.f;

@@ -20,9 +20,9 @@ constexpr int kCounterStride = 16;   // 64-bit words between the launch counters
 constexpr int kMaxKSplits = 64;
 constexpr int kMaxKvSplits = 64;
 
-// Batch tile 16 with head_dim 128 runs both projections on MFMA tiles; x then sits in LDS as fp16 operands,
+// Batch tile 16 runs both projections on MFMA tiles; x then sits in LDS as fp16 operands,
 // [16][xs16_stride(rows of the longest split)] halves, twice (high parts, low parts of x * gamma).
-__host__ __device__ constexpr bool mfma_tiles(int head_dim, int batch_tile) { return batch_tile == 16 && head_dim == 128; }
+__host__ __device__ constexpr bool mfma_tiles(int head_dim, int batch_tile) { return batch_tile == 16 && head_dim > 0; }
 // (an odd number of 16-byte pieces: the sixteen lanes of an operand read, one per row, then fall into different banks;
 // with the 104 pieces of 824 rows and one of padding they met in two)
 __host__ __device__ constexpr int xs16_stride(int rps) { return (((rps + 7) >> 3) | 1) << 3; }

@@ -413,3 +413,16 @@ def test_sums_between_lanes(d_model, nq, nkv, hd, batch):
     inp = cf_inputs.make_inputs(shape, seed=5, batch=batch, kv_len=90)
     r = Runner(shape, batch, inp["max_seq"])
     check(r.run(inp, 90, out_fill=float("nan")), oracle(inp, shape, 90), inp, 90, "D=%d" % d_model)
+
+
+# Head dimension 64 on the 16-row MFMA tile (batch 5 to 16): two sets of rows per operand, batches of 512 rows.  Slices shorter
+# than a set, one row past a batch, several batches, few team members (long slices), one and two steps of the output projection.
+@pytest.mark.parametrize("d_model,nq,nkv,batch", [(40, 2, 2, 5), (520, 2, 1, 16), (1032, 24, 24, 7), (3080, 32, 32, 16), (2056, 64, 8, 9)])
+def test_head_dim_64_on_the_16_row_tile(d_model, nq, nkv, batch):
+    shape = cf_inputs.BlockShape("s", d_model, nq, nkv, 64, 10000.0, 70)
+    inp = cf_inputs.make_inputs(shape, seed=batch, batch=batch, kv_len=70)
+    ref = oracle(inp, shape, 70)
+    for packed in (False, True):
+        r = Runner(shape, batch, inp["max_seq"])
+        check(r.run(inp, 70, out_fill=float("nan"), packed=packed), ref, inp, 70, "D=%d packed=%s" % (d_model, packed))
+        r.blk.close()
