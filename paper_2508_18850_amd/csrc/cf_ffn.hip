@@ -19,6 +19,7 @@
 // The first rows of W3 are requested before the last pieces of stage A are consumed, so the memory pipe does not
 // drain at the stage boundary.  All waits are bounded (CF_ETIMEOUT); all workgroups have to be resident at once.
 #include "../../include/cfdecode.h"
+#include "cf_lanes_device.h"
 #include "cf_mfma_device.h"
 #include "cf_team_device.h"
 
@@ -79,20 +80,11 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-
 // Sum over the wavefront (the same value in every lane): four steps inside each row of 16 lanes, then the four row
 // totals are read out as scalars.
 __device__ __forceinline__ float wave_sum(float v)
 {
-    v += dpp_move<0xB1>(v);
-    v += dpp_move<0x4E>(v);
-    v += dpp_move<0x141>(v);
-    v += dpp_move<0x140>(v);
+    v = cf::lanes::sum_row(v);
     const int i = __builtin_bit_cast(int, v);
     const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, 0));
     const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, 16));
@@ -116,6 +108,14 @@ __device__ __forceinline__ float activate(float a, int act)
     return a / (1.0f + __expf(-a));                    // SiLU
 }
 
+// Launches this workgroup has completed: a scalar load that is waited for where the count is first used (waited for at once,
+// its trip to memory held up the first weights).  Written by an earlier launch, so the constant address space will do.
+__device__ __forceinline__ unsigned long long launches_before(const FfnArgs &a, int w)
+{
+    typedef const __attribute__((address_space(4))) unsigned long long *ScalarPtr;
+    return *(ScalarPtr)(uintptr_t)(a.counters + (size_t)w * kCounterStride);
+}
+
 template <int BT, int NCB>     // batch tile; column blocks of 4096 per thread (d_model <= 4096 NCB)
 __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
 {
@@ -132,12 +132,7 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
     float *part = smem + BT * Dp / 2;
     float *gl = part + 2 * BT * a.nrmax * NCK;
 
-    unsigned long long launches;
-    asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)"
-                 : "=s"(launches)
-                 : "s"(a.counters + (size_t)w * kCounterStride)
-                 : "memory");
-    const unsigned long long cnt = launches + 1ull;
+    const unsigned long long cnt = launches_before(a, w) + 1ull;
     const Exchange x = {a.slots, 0, (uint32_t)(cnt + (cnt >> 32)), a.err, a.spin_ticks};
     const __amdgpu_buffer_rsrc_t xr = cf::team::slots_rsrc(x);
 
@@ -341,10 +336,16 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
             smem[s0 * nv + v] = s;
         }
         lds_barrier();
-        if (tid < nv) {
-            float s = 0.f;
-            for (int k = 0; k < spt; ++k) s += smem[k * nv + tid];
-            a.out[(size_t)b * D + c0 + c] = __builtin_bit_cast(uint16_t, (_Float16)s);
+        // up to 32 values: sixteen lanes add the sums of a value; more: one thread each
+        const bool wide = nv <= NT / 16;
+        const int own = wide ? tid >> 4 : tid;
+        float s = 0.f;
+        if (own < nv)
+            for (int k = wide ? tid & 15 : 0; k < spt; k += wide ? 16 : 1) s += smem[k * nv + own];
+        if (wide) s = cf::lanes::sum_row(s);
+        if (own < nv && (!wide || (tid & 15) == 0)) {
+            const int bo = own / ncol;
+            a.out[(size_t)bo * D + c0 + own - bo * ncol] = __builtin_bit_cast(uint16_t, (_Float16)s);
         }
     }
     if (tid == 0) a.counters[(size_t)w * kCounterStride] = cnt;
@@ -397,12 +398,7 @@ __global__ void __launch_bounds__(NT) fused_ffn_tiles(const FfnArgs a)
 #endif
     FFN_STAMP(0);
 
-    unsigned long long launches;
-    asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)"
-                 : "=s"(launches)
-                 : "s"(a.counters + (size_t)w * kCounterStride)
-                 : "memory");
-    const unsigned long long cnt = launches + 1ull;
+    const unsigned long long cnt = launches_before(a, w) + 1ull;
     const Exchange x = {a.slots, 0, (uint32_t)(cnt + (cnt >> 32)), a.err, a.spin_ticks};
     const __amdgpu_buffer_rsrc_t xr = cf::team::slots_rsrc(x);
     const uint32_t wbytes = (uint32_t)((size_t)a.F * D * 2);
