@@ -378,9 +378,14 @@ __device__ unsigned long long g_ffn_ts[256 * kFfnStamps];
 //      the wavefronts of a column group are added through LDS; the partial goes to slots [NF][B][d_model]
 //   C  workgroup (fi, ci) adds the NF partials of 1/NF of the columns of slice ci, in slice order, and writes fp16.
 // Two hand-overs instead of one, NF partials per output value instead of W.
-template <int NTL>     // row tiles of 16 hidden units a workgroup owns at most (1..8)
+// SH == 4: up to two 512-column pieces in a row (d_model <= 1024) are shared by four wavefronts each, one for every half of the
+// columns and matrix; with one wavefront per piece the others had nothing to do in stage A.  Us a layer, SH 1 / 4: 600 x 1400,
+// batch 8 11.6 / 10.9, 512 x 20000, batch 8 27.9 / 26.1, 1000 x 28000, batch 2 43.7 / 41.8.  (Two wavefronts per piece up to 2048 columns:
+// 2000 x 3000, batch 16 18.1 / 18.4, 2048 x 6000, batch 3 20.0 / 19.9.)
+template <int NTL, int SH>     // row tiles of 16 hidden units a workgroup owns at most (1..8); wavefronts that share a piece
 __global__ void __launch_bounds__(NT) fused_ffn_tiles(const FfnArgs a)
 {
+    static_assert(SH == 1 || SH == 4, "wavefronts per piece");
     extern __shared__ __align__(16) float smem[];
     const int tid = threadIdx.x, lane = tid & 63, w = blockIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -417,18 +422,20 @@ __global__ void __launch_bounds__(NT) fused_ffn_tiles(const FfnArgs a)
         for (int t = 0; t < NTL; ++t) acc[t][0] = acc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
         _Float16 *stg = reinterpret_cast<_Float16 *>(smem) + (size_t)wv * 16 * kStageRow;      // [16][kStageRow]
         const int hi = lane >> 5, lp = lane & 31;
-        for (int piece = wv; piece < NCK; piece += NW) {          // (uniform per wavefront)
-            h8 zb[16];
+        const int own = wv / (NW / SH);
+        for (int piece = wv % (NW / SH); piece < NCK; piece += NW / SH) {         // (uniform per wavefront)
+            h8 zb[SH == 1 ? 16 : 8];
 #pragma unroll
-            for (int m = 0; m < 16; ++m) {
-                const int col = kChunk * piece + 32 * m + 8 * g;
+            for (int m = 0; m < (SH == 1 ? 16 : 8); ++m) {
+                const int col = kChunk * piece + (SH == 1 ? 0 : 256 * (own & 1)) + 32 * m + 8 * g;
                 uint4 v = {0u, 0u, 0u, 0u};
                 if (c < B && col < D) v = *reinterpret_cast<const uint4 *>(a.z + (size_t)c * D + col);
                 zb[m] = __builtin_bit_cast(h8, v);
             }
             // two tasks in flight; load k of a task: rows 2 k and 2 k + 1 of the tile, 32 lanes each
             auto request = [&](h8(&wr)[8], int task) {
-                const int t = task >> 2, mat = (task >> 1) & 1, half = task & 1;
+                // (task: of this wavefront; its tile is a constant, matrix and half may depend on the wavefront)
+                const int at = SH == 4 ? 4 * task + own : task, t = at >> 2, mat = (at >> 1) & 1, half = at & 1;
                 const bool colok = kChunk * piece + 256 * half + 8 * lp < D;
                 const uint32_t soff = 16 * t < nr ? (uint32_t)(((size_t)(r0 + 16 * t) * D + (size_t)kChunk * piece) * 2) : 0u;
 #pragma unroll
@@ -452,23 +459,25 @@ __global__ void __launch_bounds__(NT) fused_ffn_tiles(const FfnArgs a)
                 wave_sync();
             };
             auto consume = [&](int task) {
-                const int t = task >> 2, mat = (task >> 1) & 1, half = task & 1;
+                const int t = SH == 4 ? task : task >> 2, m = SH == 4 ? 0 : (task >> 1) & 1;      // (SH == 4: one matrix per wavefront)
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     const h8 wop = *reinterpret_cast<const h8 *>(stg + c * kStageRow + 32 * k + 8 * g);
-                    acc[t][mat] = mfma16(wop, zb[8 * half + k], acc[t][mat]);
+                    acc[t][m] = mfma16(wop, SH == 1 ? zb[8 * (task & 1) + k] : zb[k], acc[t][m]);
                 }
             };
             h8 wa[8], wb[8];
+            constexpr int NTASK = 4 * NTL / SH;
             request(wa, 0);
-            request(wb, 1);
+            if (NTASK > 1) request(wb, 1);
 #pragma unroll
-            for (int task = 0; task < 4 * NTL; task += 2) {
+            for (int task = 0; task < NTASK; task += 2) {
                 stage(wa);
-                if (task + 2 < 4 * NTL) request(wa, task + 2);
+                if (task + 2 < NTASK) request(wa, task + 2);
                 consume(task);
+                if (task + 1 == NTASK) break;
                 stage(wb);
-                if (task + 3 < 4 * NTL) request(wb, task + 3);
+                if (task + 3 < NTASK) request(wb, task + 3);
                 consume(task + 1);
             }
         }
@@ -479,7 +488,8 @@ __global__ void __launch_bounds__(NT) fused_ffn_tiles(const FfnArgs a)
         for (int t = 0; t < NTL; ++t)
 #pragma unroll
             for (int mat = 0; mat < 2; ++mat)
-                part[((wv * NTL + t) * 2 + mat) * 64 + lane] =
+                // (SH == 4: this wavefront's matrix is own / 2, its products are in acc[t][0], those of the other are acc[t][1], zero)
+                part[((wv * NTL + t) * 2 + (SH == 4 ? mat ^ own >> 1 : mat)) * 64 + lane] =
                     make_float4(acc[t][mat][0], acc[t][mat][1], acc[t][mat][2], acc[t][mat][3]);
         lds_barrier();
         for (int e = tid; e < nr * B; e += NT) {                  // consecutive threads, consecutive slots
@@ -637,11 +647,17 @@ KernelFn pick(int bt, int d_model)
 }
 int batch_tile(int b) { return b <= 1 ? 1 : b <= 2 ? 2 : 4; }
 int row_tiles(int nrmax) { return (nrmax + 15) / 16; }
-KernelFn pick_tiles(int nrmax)
+template <int SH>
+KernelFn pick_row_tiles(int n)
 {
-    static const KernelFn fn[8] = {fused_ffn_tiles<1>, fused_ffn_tiles<2>, fused_ffn_tiles<3>, fused_ffn_tiles<4>,
-                                   fused_ffn_tiles<5>, fused_ffn_tiles<6>, fused_ffn_tiles<7>, fused_ffn_tiles<8>};
-    return fn[row_tiles(nrmax) - 1];
+    static const KernelFn fn[8] = {fused_ffn_tiles<1, SH>, fused_ffn_tiles<2, SH>, fused_ffn_tiles<3, SH>, fused_ffn_tiles<4, SH>,
+                                   fused_ffn_tiles<5, SH>, fused_ffn_tiles<6, SH>, fused_ffn_tiles<7, SH>, fused_ffn_tiles<8, SH>};
+    return fn[n - 1];
+}
+KernelFn pick_tiles(int nrmax, int d_model)
+{
+    const int n = row_tiles(nrmax);
+    return d_model <= 2 * kChunk ? pick_row_tiles<4>(n) : pick_row_tiles<1>(n);
 }
 
 }  // namespace
@@ -712,9 +728,9 @@ int cf_ffn_create(const cf_ffn_config *cfg, cf_ffn *out)
         lds_tiles = lds_tiles > staging ? lds_tiles : staging;
         int per_cu = 0;
         if (lds_tiles > 160 * 1024 - 256 ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(pick_tiles(nrmax)), hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute(reinterpret_cast<const void *>(pick_tiles(nrmax, c.d_model)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds_tiles) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(pick_tiles(nrmax)), NT,
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(pick_tiles(nrmax, c.d_model)), NT,
                                                          lds_tiles) != hipSuccess ||
             per_cu < 1)
             return CF_EUNSUPPORTED;
@@ -783,7 +799,7 @@ int cf_ffn_decode(cf_ffn t, int32_t batch, const void *z, const void *W1, const 
     a.spin_ticks = t->spin_ticks;
     if (batch >= kTilesFrom && t->lds_tiles) {
         a.xg = t->xg, a.xp = t->xp, a.NF = t->NF, a.CW = t->CW, a.nRp = t->nRp;
-        hipLaunchKernelGGL(pick_tiles(t->nrmax), dim3(t->W), dim3(NT), t->lds_tiles, static_cast<hipStream_t>(stream), a);
+        hipLaunchKernelGGL(pick_tiles(t->nrmax, t->cfg.d_model), dim3(t->W), dim3(NT), t->lds_tiles, static_cast<hipStream_t>(stream), a);
     } else {
         const int bt = batch_tile(batch);
         hipLaunchKernelGGL(pick(bt, t->cfg.d_model), dim3(t->W), dim3(NT), lds_bytes_of(t->cfg, bt, t->nrmax),

@@ -184,3 +184,10 @@ def test_refused_arguments():
     assert blk.decode_rc(1, p + 2, p, p, p, p, 0) == -1
     assert blk.decode_rc(1, p, p, p, 0, p, 0) == -1
     blk.close()
+
+
+@pytest.mark.parametrize("d_model,d_ff,batch", [(1024, 4096, 2), (1032, 2000, 3), (8, 300, 16), (264, 32000, 5), (776, 4100, 16)])
+def test_wavefronts_that_share_a_piece_of_the_columns(d_model, d_ff, batch):
+    """Both sides of 1024 columns (four wavefronts per piece / one each); one piece, which leaves half of the wavefronts without
+    work; one to eight row tiles per workgroup."""
+    _run(cf_inputs.FfnShape("f_s", d_model, d_ff), batch, 0, seed=240 + batch, scale_rows=True)
