@@ -928,11 +928,11 @@ struct EarlyQ {
     u32x2 v[kEarly];
     bool issued = false;
     template <int HD, int G>
-    __device__ __forceinline__ void issue(const Params &p, int tid0, int team, int b)
+    __device__ __forceinline__ void issue(const Params &p, int tid0, int team, int b, int nsel)     // selectors to be summed
     {
         const Xbuf x1(p.p1);
         const int e = tid0;
-        if (e < G * HD) {
+        if (e < nsel * HD) {
             const int sel = e / HD, c = e - sel * HD;
             const size_t src = (size_t)b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c;
             // eight loads at a time on a straight-line path (slices past KS repeat the last one)
@@ -959,6 +959,17 @@ struct EarlyQ {
         out = s;
         return ok;
     }
+};
+
+// Selectors an attention item sums before it starts: its query heads, and for the item with the new token the new key and value
+// too, where the threads suffice for all of them in one trip.  (Behind the cached rows that trip and two barriers are the end of
+// the longest item.)  Us a layer, behind / first: tiny shape 13.9 / 13.4, 32 heads of 64, batch 12 30.4 / 30.0, Llama-2-7B shape 37.2 / 36.7; at
+// head_dim 128 with more rows or heads the queries wait for it: batch 2 / 8, 16 heads 21.6 / 21.8, 25.6 / 26.0, two heads per group,
+// batch 1 / 16 19.4 / 19.7, 37.0 / 37.9.
+template <int HD, int G, int BT>
+struct NewTokenFirst {
+    static constexpr bool on = (G + 2) * HD <= NT && (HD == 64 || (G == 1 && BT == 1));
+    static __device__ __forceinline__ int selectors(bool last) { return on && last ? G + 2 : G; }
 };
 
 template <int G>
@@ -1079,7 +1090,7 @@ struct P2Stream {
     }
 };
 
-template <int HD, int G, class TailFn>
+template <int HD, int G, int BT, class TailFn>
 __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, int tid0, int team, int b, int s, uint32_t stamp, bool first,
                                         const P2Stream<HD, G> &st, KvBuf<HD, G> &buf, const EarlyQ &eq, float *smem,
                                         const float *rope, TailFn &&issue_next)
@@ -1112,7 +1123,9 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
 
     // ---- sum the projection partials of the team (the gather of Alg. 3 step 3): q heads, and for
     //      the last split also the new key and value; then RoPE on q and the key
-    for (int e = tid; e < G * HD; e += NT) {
+    constexpr bool KVF = NewTokenFirst<HD, G, BT>::on;              // the new key and value beside the queries (kn and vn follow qs)
+    const int nsel = NewTokenFirst<HD, G, BT>::selectors(last);
+    for (int e = tid; e < nsel * HD; e += NT) {
         const int sel = e / HD, c = e - sel * HD;
         const size_t src = (size_t)b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c;
         float v;
@@ -1121,7 +1134,7 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
         qs[e] = v;
     }
     lds_barrier();
-    for (int e = tid; e < G * (HD / 2); e += NT) {
+    for (int e = tid; e < min(nsel, G + 1) * (HD / 2); e += NT) {          // (not the value)
         const int sel = e / (HD / 2), i = e - sel * (HD / 2);
         float *v = qs + sel * HD;
         const float lo = v[i], hi = v[i + HD / 2], c = cs[i], sgn = sn[i];
@@ -1342,8 +1355,8 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
     // streams while the partial is merged and stored; the other half follows the stored partial.
     // (Not all of it now: the vector memory path of a compute unit returns in order, so the stamped
     // store and the next phase's polls wait for every bulk load issued before them.)  The member with
-    // the last split first polls for the new token's key/value sums, for the same reason.
-    if (!last) issue_next(1);
+    // the last split first polls for the new token's key/value sums, for the same reason, where it has not done so yet.
+    if (!last || KVF) issue_next(1);
     // ---- merge the row groups of a wavefront
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -1366,19 +1379,21 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
     if (last) {
         // ---- the new token: sum its key/value partials (stored at the end of phase 1, long ago by
         //      now), rotate the key, append both (Sec. 2.1) and score the token
-        for (int e = tid; e < 2 * HD; e += NT) {
-            const int sel = G + e / HD, c = e % HD;
-            const size_t src = (size_t)b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c;
-            kn[e] = ll_sum(p, x1, src, (size_t)p.B * p.nqkv, p.KS, stamp);      // kn and vn are contiguous
+        if constexpr (!KVF) {
+            for (int e = tid; e < 2 * HD; e += NT) {
+                const int sel = G + e / HD, c = e % HD;
+                const size_t src = (size_t)b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c;
+                kn[e] = ll_sum(p, x1, src, (size_t)p.B * p.nqkv, p.KS, stamp);      // kn and vn are contiguous
+            }
+            issue_next(1);
+            lds_barrier();
+            if (tid < HD / 2) {
+                const float lo = kn[tid], hi = kn[tid + HD / 2], c = cs[tid], sgn = sn[tid];
+                kn[tid] = lo * c - hi * sgn;
+                kn[tid + HD / 2] = hi * c + lo * sgn;
+            }
+            lds_barrier();
         }
-        issue_next(1);
-        lds_barrier();
-        if (tid < HD / 2) {
-            const float lo = kn[tid], hi = kn[tid + HD / 2], c = cs[tid], sgn = sn[tid];
-            kn[tid] = lo * c - hi * sgn;
-            kn[tid + HD / 2] = hi * c + lo * sgn;
-        }
-        lds_barrier();
         const size_t row = st.head + (size_t)st.pos * HD;
         if (tid < HD)
             lp.kc[row + tid] = f2h(kn[tid]);
@@ -1940,7 +1955,7 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // a first look at the team's q partials (in a stack only for one batch row and attention on the vector ALU: no
     // registers are left for the sixteen pairs there, they would be spilled as they arrive)
     if (member < n2 && !(STACK && (AttnMfma<HD, G>::on || BT > 1)))
-        eq.issue<HD, G>(p, tl, team, qdiv(member, p.div_ns));
+        eq.issue<HD, G>(p, tl, team, qdiv(member, p.div_ns), NewTokenFirst<HD, G, BT>::selectors(s_first == p.NS - 1));
     st2.prefetch(kv, 1);
     CF_STAMP(1);
     // ---- phase 2 (attention); the last item already starts the W_o stream of phase 3
@@ -1975,7 +1990,7 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
             st2.prefetch(kv, 1);
         }
         // stage 1: first half of the output-projection tile, stage 2: second half (early: stage 1 the second half)
-        p2_item<HD, G>(p, lp, tl, team, qdiv(it, p.div_ns), qmod(it, p.NS, p.div_ns), stamp, first, st2, kv, eq, smem,
+        p2_item<HD, G, BT>(p, lp, tl, team, qdiv(it, p.div_ns), qmod(it, p.NS, p.div_ns), stamp, first, st2, kv, eq, smem,
                        s_rope + (kLayer && p.row_pos ? qdiv(it, p.div_ns) * HD : 0), [&](int stage) {
             if (final_item && (!EARLY || stage == 1)) p3_prefetch(EARLY ? 1 : stage - 1);
         });
