@@ -57,11 +57,11 @@ struct ReduceLaunch {
         x.err = a.err;
         x.spin_ticks = a.spin_ticks;
     }
-    // kEmpty back into what the last launch wrote in the other set; the count of this launch and what it has written
+    // What the last launch wrote in the other set is cleared; the count of this launch and what it has written
     __device__ __forceinline__ void finish(const TeamArgs &a, int boxes, size_t words) const
     {
         const __amdgpu_buffer_rsrc_t other = __builtin_amdgcn_make_buffer_rsrc(a.boxes + (count & 1 ? 0 : a.set), 0, 0xfffffff0u, 0x00020000);
-        const cf::team::words4 none = {cf::team::kEmpty, cf::team::kEmpty, cf::team::kEmpty, cf::team::kEmpty};
+        const cf::team::words4 none = {0u, 0u, 0u, 0u};
         const int nb = (int)(wrote >> 32);
         for (int s = 0; s < nb; ++s)
             for (size_t i = 4 * threadIdx.x; i < (uint32_t)wrote; i += cf::team::kQuads)
@@ -158,7 +158,7 @@ __global__ void __launch_bounds__(kThreads) team_reduce_two_hops_kernel(const Te
 #pragma unroll
             for (int k = 0; k < C; ++k) {
                 const size_t i = i0 + t4 + (size_t)kQuads * k;
-                q[k] = words4{0u, 0u, 0u, 0u};
+                q[k] = words4{1u, 1u, 1u, 1u};
                 if (i < a.count && (i < lo || i >= hi)) q[k] = x.peek(x.at(team * a.N + (int)((unsigned)i / sl), 1) + i);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -169,7 +169,7 @@ __global__ void __launch_bounds__(kThreads) team_reduce_two_hops_kernel(const Te
 #pragma unroll
         for (int k = 0; k < C; ++k) {
             const size_t i = i0 + t4 + (size_t)kQuads * k;
-            if (i < a.count && (i < lo || i >= hi)) store4(dst, i, a.count, __builtin_bit_cast(f4_t, q[k]));
+            if (i < a.count && (i < lo || i >= hi)) store4(dst, i, a.count, Boxes::values(q[k]));
         }
     }
     l.finish(a, 2, a.count);
@@ -326,11 +326,10 @@ int check_call(cf_team t, int32_t teams, int32_t team_size, const void *in, cons
     return CF_OK;
 }
 
-// Counters and pairs cleared, boxes emptied.
+// Counters, pairs and boxes cleared.
 hipError_t reset(cf_team t)
 {
-    hipError_t e = hipMemset(t->ws, 0, t->head_bytes + t->slots_bytes);
-    if (e == hipSuccess) e = hipMemset(t->boxes, 0xff, t->boxes_bytes);
+    const hipError_t e = hipMemset(t->ws, 0, t->head_bytes + t->slots_bytes + t->boxes_bytes);
     return e == hipSuccess ? hipDeviceSynchronize() : e;
 }
 

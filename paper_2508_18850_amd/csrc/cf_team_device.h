@@ -209,16 +209,15 @@ __device__ __forceinline__ void reduce_two_hops(const Exchange &x, int team_firs
 // ---- all-reduce of whole buffers, four bytes per value ---------------------------------------------------------------
 //
 // The stamp of a pair doubles the bytes, and a pair is eight bytes at most: a rank's receive rate was that of 8-byte polls
-// (some 30 GB/s per workgroup).  Here a posted value is its own arrival mark: boxes are filled with kEmpty, a value is
-// there as soon as its word is anything else, and four words go in one 16-byte access, of which each is judged by itself.
-// There are two sets of boxes, used by launches in turn; a launch puts back kEmpty into what its predecessor has written in
-// the other set (nobody reads that any more: launches on one handle follow each other), so that the set is empty when the
-// next launch takes it.  A value whose bits are kEmpty, a NaN, is sent as the NaN next to it.
+// (some 30 GB/s per workgroup).  Here a posted value is its own arrival mark: an empty box holds zeros, a value's bits are sent
+// inverted and are there as soon as the word is not zero, and four words go in one 16-byte access, of which each is judged by
+// itself.  There are two sets of boxes, used by launches in turn; a launch clears what its predecessor has written in the
+// other set (nobody reads that any more: launches on one handle follow each other), so that the set is empty when the
+// next launch takes it.  A value with all bits set, a NaN, is sent as the NaN next to it.
 typedef uint32_t words4 __attribute__((ext_vector_type(4)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));      // user buffers are 4-byte aligned
 
-constexpr uint32_t kEmpty = 0xffffffffu;
 constexpr int kQuads = kThreads * 4;       // values a workgroup handles with one 16-byte access per thread
 
 // Box s of rank r in the set of this launch = words[(r * kMaxRounds + s) * cap ...], cap a multiple of four.
@@ -230,9 +229,9 @@ struct Boxes {
     __device__ __forceinline__ size_t at(int rank, int s) const { return ((size_t)rank * kMaxRounds + s) * cap; }
     __device__ __forceinline__ void put(size_t idx, const f4_t &v) const
     {
-        words4 q = __builtin_bit_cast(words4, v);
+        words4 q = ~__builtin_bit_cast(words4, v);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) q[k] = q[k] == kEmpty ? kEmpty - 1 : q[k];
+        for (int k = 0; k < 4; ++k) q[k] = max(q[k], 1u);
         __builtin_amdgcn_raw_buffer_store_b128(q, r, (unsigned)(idx * 4), 0, 16);                    // sc1: through to memory
     }
     __device__ __forceinline__ words4 peek(size_t idx) const
@@ -241,8 +240,9 @@ struct Boxes {
     }
     static __device__ __forceinline__ bool there(const words4 &q)
     {
-        return (q.x != kEmpty) & (q.y != kEmpty) & (q.z != kEmpty) & (q.w != kEmpty);
+        return (q.x != 0u) & (q.y != 0u) & (q.z != 0u) & (q.w != 0u);
     }
+    static __device__ __forceinline__ f4_t values(const words4 &q) { return __builtin_bit_cast(f4_t, ~q); }
     __device__ __forceinline__ bool gave_up(long long &t0) const
     {
         return team::gave_up(Exchange{nullptr, 0, 0, err, spin_ticks}, t0);
@@ -296,7 +296,7 @@ __device__ __forceinline__ void fold_box(const Boxes &x, int from, int s, size_t
         if (ok || x.gave_up(t0)) break;
     }
 #pragma unroll
-    for (int e = 0; e < E; ++e) d[e] = fold4<OP>(d[e], __builtin_bit_cast(f4_t, q[e]));
+    for (int e = 0; e < E; ++e) d[e] = fold4<OP>(d[e], Boxes::values(q[e]));
 }
 
 // d = fold, in rank order, of box 0 of the N ranks of the team at the same values (own d at its place); kInFlight 16-byte
@@ -331,7 +331,7 @@ __device__ __forceinline__ void fold_team(const Boxes &x, int team_first_rank, i
             if (r0 + p < N)
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    const f4_t v = r0 + p == b ? d[e] : __builtin_bit_cast(f4_t, q[p][e]);
+                    const f4_t v = r0 + p == b ? d[e] : Boxes::values(q[p][e]);
                     acc[e] = r0 + p == 0 ? v : fold4<OP>(acc[e], v);
                 }
     }

@@ -133,7 +133,8 @@ def test_one_handle_for_changing_calls():
 
 
 @pytest.mark.parametrize("mode", [TEAM_ROUNDS, TEAM_DIRECT, TEAM_TWO_HOPS])
-def test_a_nan_with_the_bits_of_an_empty_box_arrives(mode):
+def test_a_nan_with_all_bits_set_arrives(mode):
+    """Values are sent inverted and an empty box holds zeros: this one is sent as the NaN next to it."""
     tc = TeamCollectives(8, 64)
     st = torch.cuda.current_stream().cuda_stream
     host = _data(1, 8, 64, seed=1)
