@@ -160,8 +160,8 @@ int cf_decode_layer(cf_handle h, int32_t batch, const void *x, const void *norm_
  * A stack of n_layers layers in one call: layer 0 reads x, layer l reads the hidden state layer l-1 wrote (two
  * buffers of the handle's workspace, used in turn), the last layer writes `out`.  Each layer is cf_decode_layer
  * with its own weights and caches and the common batch, pos, eps, residual and packed; the launch overhead the
- * paper compares in Sec. 4.2 is that of such a stack.  This version enqueues one launch of the fused kernel per
- * layer on `stream`.
+ * paper compares in Sec. 4.2 is that of such a stack.  Head dimension 128: one launch for all
+ * layers (up to 88), with norm or residual at batch 1 and d_model <= 4096; otherwise one launch per layer on `stream`.
  *   W_qkv, W_o, k_cache, v_cache: HOST arrays of n_layers DEVICE pointers (read during the call only), each as in
  *   cf_decode_layer; norm_weight: NULL (no RMSNorm in any layer) or a HOST array of n_layers DEVICE pointers.
  *   x and out must differ.  Errors as for cf_decode_layer; a pointer of any layer that is null or misaligned is

@@ -20,8 +20,9 @@
 //   -- hand-over: the heads' partials
 //   E2  sum over heads     every workgroup: 1/W of the output columns (the paper's atomicAdd)
 //
-// DeepSeek-V2-Lite shape, 4096 rows, weights and rows from memory: 22.6 us a step (27.9 with five hand-overs: partial
-// sums of the projections, latent query, partials, partial a_i, partial out); 100 rows 17.6 us.  Stages, us from kernel
+// DeepSeek-V2-Lite shape, 4096 rows, weights and rows from memory: 21.7 us a step (22.6 with shuffles between lanes instead
+// of permlane swaps; 27.9 with five hand-overs: partial
+// sums of the projections, latent query, partials, partial a_i, partial out); 100 rows 17.6 us.  Stages (with shuffles), us from kernel
 // start, mean over workgroups: projections posted 3.0, q arrived 6.4, latent query ready 8.9, rows used 11.5, partial
 // folded 13.9, D posted 15.0, a_i ready 17.6, partial out posted 18.4, end 19.9.  Between the hand-overs a compute unit
 // is bound by what it loads (64 KB of A, 131 KB of W_Up, 295 KB of rows, 131 KB of W_Down): requesting W_Up or the rows
