@@ -93,9 +93,11 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
         int best = 0, best_rows = 0;
         long best_cost = 0;
         const size_t maxi = bt == 1 ? 4 : (bt <= 4 ? 2 : 1);
+        bool low_parts = true;       // (the plan leaves room for them where it can: the same slices with and without RMSNorm)
         auto fits = [&](int rows) {
-            return (cf::x_lds_floats(hd, bt, rows) + maxi * cf::kWaves * bt * hd + (size_t)cf::kWaves * bt) * sizeof(float) <= kLdsLimit;
+            return (cf::x_lds_floats(hd, bt, rows, low_parts) + maxi * cf::kWaves * bt * hd + (size_t)cf::kWaves * bt) * sizeof(float) <= kLdsLimit;
         };
+        for (int pass = 0; pass < 2 && !best; ++pass, low_parts = cf::wants_layer_kernel(*p))
         for (int ks = 1; ks <= kMaxKS && ks <= TS; ++ks) {
             if (h->tune_ks > 0 && ks != h->tune_ks) continue;
             if ((h->tune_ks > 0 || even_slices) && TS % ks) continue;

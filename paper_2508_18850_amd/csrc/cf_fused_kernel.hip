@@ -382,7 +382,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     // read then fall into different banks), followed by a second array with the low parts of x * gamma (RMSNorm)
     const int XS = xs16_stride(p.RPS);
     _Float16 *xh = reinterpret_cast<_Float16 *>(smem), *xl = xh + 16 * XS;
-    float *red = smem + (MF ? 16 * XS : BT * p.RPS);   // [MAXI][NW][BT][HD]
+    float *red = smem + (MF ? (kLayer || HD == 128 ? 16 : 8) * XS : BT * p.RPS);   // [MAXI][NW][BT][HD]
     const Xbuf x1(p.p1);
     const uint32_t blkb = (uint32_t)p.D * HD * 2 + kQkvBlockPad;          // packed: bytes from one block to the next
     const Stream W(lp.wqkv, (p.flags & kFlagPacked) ? (uint32_t)(p.nqkv / HD) * blkb : (uint32_t)((size_t)p.D * p.nqkv * 2));
@@ -730,7 +730,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         for (int e = tid; e < 16 * nz; e += NT) {
             const int b = e / nz, r = p.RPS + (e - b * nz);
             xh[b * XS + r] = (_Float16)0.f;
-            xl[b * XS + r] = (_Float16)0.f;
+            if (kLayer || HD == 128) xl[b * XS + r] = (_Float16)0.f;
         }
     }
     if (norm && !ROW) {
@@ -2203,7 +2203,7 @@ bool wants_layer_kernel(const Params &p)
 size_t lds_floats(const Params &p, int hd, int g, int bt)
 {
     const size_t maxi = bt == 1 ? 4 : (bt <= 4 ? 2 : 1);
-    const size_t f1 = x_lds_floats(hd, bt, p.RPS) + maxi * kWaves * bt * hd + (size_t)kWaves * bt;
+    const size_t f1 = x_lds_floats(hd, bt, p.RPS, wants_layer_kernel(p)) + maxi * kWaves * bt * hd + (size_t)kWaves * bt;
     const bool ma = hd == 128 && g >= 4;                                          // attention on MFMA tiles: a K tile per wavefront
     const size_t npart = kWaves;                                                  // attention partials folded through LDS
     const size_t f2 = (size_t)hd + (size_t)(g + 2) * hd + 8 + 2 * (size_t)g * npart + (size_t)g * npart * hd +

@@ -26,10 +26,11 @@ __host__ __device__ constexpr bool mfma_tiles(int head_dim, int batch_tile) { re
 // (an odd number of 16-byte pieces: the sixteen lanes of an operand read, one per row, then fall into different banks;
 // with the 104 pieces of 824 rows and one of padding they met in two)
 __host__ __device__ constexpr int xs16_stride(int rps) { return (((rps + 7) >> 3) | 1) << 3; }
-// LDS floats that hold x in phase 1
-__host__ __device__ constexpr size_t x_lds_floats(int head_dim, int batch_tile, int rps)
+// LDS floats that hold x in phase 1.  `layer`: the kernel with RMSNorm; without it head_dim 64 keeps no low parts, which lets it
+// take slices of up to 4000 rows (a few shapes with hardly more workgroups than KV heads need more than 2024).
+__host__ __device__ constexpr size_t x_lds_floats(int head_dim, int batch_tile, int rps, bool layer)
 {
-    return mfma_tiles(head_dim, batch_tile) ? (size_t)16 * xs16_stride(rps) : (size_t)batch_tile * rps;
+    return mfma_tiles(head_dim, batch_tile) ? (size_t)(layer || head_dim == 128 ? 16 : 8) * xs16_stride(rps) : (size_t)batch_tile * rps;
 }
 
 constexpr int kFlagPacked = 1;     // weights are in the packed (per-head contiguous) layout of cf_pack_weights

@@ -426,3 +426,16 @@ def test_head_dim_64_on_the_16_row_tile(d_model, nq, nkv, batch):
         r = Runner(shape, batch, inp["max_seq"])
         check(r.run(inp, 70, out_fill=float("nan"), packed=packed), ref, inp, 70, "D=%d packed=%s" % (d_model, packed))
         r.blk.close()
+
+
+@pytest.mark.parametrize("d_model,batch,workgroups", [(2032, 5, 2), (4072, 16, 4), (4056, 9, 4)])
+def test_longest_slices_of_head_dim_64(d_model, batch, workgroups):
+    """As many workgroups as KV heads, or twice as many: slices of 2028 to 2036 rows, the longest that 16 rows of x in fp32 left
+    room for."""
+    shape = cf_inputs.BlockShape("s", d_model, 2, 2, 64, 10000.0, 40)
+    inp = cf_inputs.make_inputs(shape, seed=batch, batch=batch, kv_len=40)
+    r = Runner(shape, batch, inp["max_seq"])
+    r.blk.set_tuning(workgroups=workgroups)
+    check(r.run(inp, 40, out_fill=float("nan")), oracle(inp, shape, 40), inp, 40, "D=%d" % d_model)
+    _log("plan %s" % r.blk.plan())
+    r.blk.close()
