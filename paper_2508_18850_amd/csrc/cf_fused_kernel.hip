@@ -31,6 +31,7 @@
 // readers spin.  Spins are bounded: after spin_ticks a thread sets an error
 // flag and goes on, so the kernel always ends.
 #include "cf_lanes_device.h"
+#include "cf_mfma_device.h"
 #include "cf_params.h"
 #include "cf_rope_device.h"
 
@@ -120,7 +121,8 @@ __device__ __forceinline__ void transpose8(const h8 *w, h8 (&f)[8])
     }
 }
 
-// v = hi + lo with both parts fp16: the A operand of an MFMA product whose fp32 input must not lose bits
+// v = hi + lo with both parts fp16, for operands that enter a sum of exponents or weights of at most one: 22 bits of values
+// around one, an absolute step of 2^-24 below, no more than 65504.  Operands of the projections: mfma::split_scaled.
 __device__ __forceinline__ void split_hi_lo(const float (&v)[8], h8 &hi, h8 &lo)
 {
 #pragma unroll
@@ -172,6 +174,24 @@ __device__ __forceinline__ float wave_max(float v)
     v = fmaxf(v, dpp_move<0x141>(v));
     v = fmaxf(v, dpp_move<0x140>(v));
     return fmaxf(fmaxf(lane_of(v, 0), lane_of(v, 16)), fmaxf(lane_of(v, 32), lane_of(v, 48)));
+}
+// The bits of the largest magnitude over the wavefront, as a scalar, of up to four values per lane: the four are folded
+// into one register first (a row of 16 lanes each), so that they share the steps between lanes.
+template <int N>
+__device__ __forceinline__ void wave_max_bits(const float (&v)[N], int (&out)[N])
+{
+    static_assert(N == 1 || N == 2 || N == 4, "folds by halves");
+    float h[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        float p = v[2 * j % N], q = v[(2 * j + 1) % N];
+        lanes::swap32(p, q);
+        h[j] = fmaxf(fabsf(p), fabsf(q));            // lanes 0..31: value 2 j, lanes 32..63: value 2 j + 1
+    }
+    lanes::swap16(h[0], h[1]);
+    const int m = __builtin_bit_cast(int, lanes::max_row(fmaxf(h[0], h[1])));        // rows of lanes: values 0, 2, 1, 3
+#pragma unroll
+    for (int n = 0; n < N; ++n) out[n] = __builtin_amdgcn_readlane(m, 32 * (n & 1) + 16 * (n >> 1));
 }
 __device__ __forceinline__ float wave_total(float v)
 {
@@ -458,6 +478,10 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     constexpr bool ROW = STACK && kLayer;                         // the whole row is fetched (below)
     static_assert(!ROW || BT == 1, "one row per launch");
     constexpr int XP = MF && !STACK ? 4 : 2;
+    // MFMA tiles of the layer kernel: a row's pieces belong to one half wavefront (up to eight rows: one wavefront), since
+    // x * gamma is scaled by the largest value of the row's slice (stage_piece below), and the maximum is then one between lanes.
+    constexpr bool BYROW = MF && kLayer && !STACK;
+    const int lpr = p.B > 8 ? 32 : 64, brow = p.B > 8 ? tid >> 5 : wv, lane0 = tid & (lpr - 1);
     const bool xvec = STACK || ((p.RB | p.RD) & 7) == 0;          // (the host launches no stack otherwise)
     const int P8 = p.RPS >> 3, npc = xvec ? p.B * P8 : 0;         // pieces of a row's slice, of all rows
     const uint4 *xg4 = reinterpret_cast<const uint4 *>(p.x), *gg4 = reinterpret_cast<const uint4 *>(lp.gamma ? lp.gamma : p.x);
@@ -466,6 +490,12 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         b = BT == 1 ? 0 : qdiv(i, p.div_p8);
         c = i - b * P8;
         return i < npc && 8 * c < nrows;
+    };
+    auto own_piece = [&](int q, int &b, int &c) {                 // piece q of this thread
+        if constexpr (!BYROW) return piece_of(tid + q * NT, b, c);
+        b = brow;
+        c = lane0 + q * lpr;
+        return xvec && b < p.B && 8 * c < nrows;
     };
     // The input of a stack comes from stamped slots, two fp16 values and the stamp in eight bytes; in its first layer from x.
     // Without norm and residual a workgroup fetches its slice, in pieces like those above (two 16-byte loads each), XP per
@@ -507,7 +537,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 #pragma unroll
         for (int q = 0; q < XP; ++q) {
             int b, c;
-            const bool in = piece_of(tid + q * NT, b, c);
+            const bool in = own_piece(q, b, c);
             xp[q] = xg4[in ? ((size_t)b * p.D + r0) / 8 + c : 0];
         }
     } else if constexpr (!ROW) {
@@ -525,7 +555,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 #pragma unroll
         for (int q = 0; q < XP; ++q) {
             int b, c;
-            const bool in = piece_of(tid + q * NT, b, c);
+            const bool in = own_piece(q, b, c);
             gp[q] = gg4[in ? r0 / 8 + c : 0];
         }
     }
@@ -615,21 +645,22 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         cnt0 = launches + 1ull;
     }
     const uint32_t stamp = stamp_of(cnt0, layer);
-    // MF: the value goes to row b, column r of the operand array as fp16; without RMSNorm that is x itself,
-    // with it the product x * gamma is kept as high + low part, so that nothing is rounded away
+    // MF: the value goes to row b, column r of the operand array as fp16; without RMSNorm that is x itself, with it the product
+    // x * gamma (22 bits), scaled by 2^xe and cut into a high and a low part, so that nothing is rounded away; the scale is
+    // taken out with the row's factor.  (Without the scale the pair lost bits below one and was NaN above 65504: |x gamma|
+    // 1e-2 / 1e-4 to 2e-6 / 2e-4 of the projected value.)
+    int xe = 0;
+    float xmax = 0.f;
     auto stage = [&](int i, int b, int r, float v) {
-        if constexpr (MF) {
-            const _Float16 hi = (_Float16)v;
-            xh[b * XS + r] = hi;
-            if (norm) xl[b * XS + r] = (_Float16)(v - (float)hi);
-        } else {
+        if constexpr (MF)
+            xh[b * XS + r] = (_Float16)v;
+        else
             xs[i] = v;
-        }
     };
     // (rows past the batch are left as they are: what they give lands in rows of the product nobody reads)
     auto stage_piece = [&](int b, int c, const uint4 &xw, const uint4 &gw, bool in) {
         const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-        h8 hi = in ? __builtin_bit_cast(h8, xw) : zero, lo = zero;
+        h8 hi = in ? __builtin_bit_cast(h8, xw) : zero;
         float f[8], g[8];
         unpack8(hi, f);
         if (norm) {
@@ -639,8 +670,9 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         }
         if constexpr (MF) {
             if (norm) {
-                split_hi_lo(f, hi, lo);
-                *reinterpret_cast<h8 *>(xl + b * XS + 8 * c) = lo;
+                const mfma::Split<2> s = mfma::split_scaled<2>(f, xe, xmax);
+                hi = s.part[0];
+                *reinterpret_cast<h8 *>(xl + b * XS + 8 * c) = s.part[1];
             }
             *reinterpret_cast<h8 *>(xh + b * XS + 8 * c) = hi;
         } else {
@@ -668,6 +700,49 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         if (norm) square_rows(0);
         const uint4 none = {0u, 0u, 0u, 0u};
         for (int i = np + tid; i < P8; i += NT) stage_piece(0, i, none, none, false);     // the last slice may be shorter
+    } else if constexpr (BYROW) {
+        const bool live = brow < p.B, whole = xvec && P8 <= XP * lpr;     // (uniform: a row's pieces are all in registers)
+        auto row_scale = [&]() {
+            xmax = lpr == 32 ? lanes::max_half(xmax) : wave_max(xmax);
+            xe = mfma::scale_exp(xmax);
+        };
+        if (whole) {
+            if (norm) {
+#pragma unroll
+                for (int q = 0; q < XP; ++q) {
+                    if (q * lpr >= P8) break;                     // (uniform)
+                    int b, c;
+                    const bool in = own_piece(q, b, c);
+                    float f[8], g[8];
+                    unpack8(__builtin_bit_cast(h8, xp[q]), f);
+                    unpack8(__builtin_bit_cast(h8, gp[q]), g);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) f[j] *= g[j];
+                    const float m = mfma::max_abs(f, xmax);
+                    xmax = in ? m : xmax;
+                }
+                row_scale();
+            }
+#pragma unroll
+            for (int q = 0; q < XP; ++q) {
+                if (q * lpr >= P8) break;
+                int b, c;
+                const bool in = own_piece(q, b, c);
+                if (live && c < P8) stage_piece(b, c, xp[q], norm ? gp[q] : xp[q], in);
+            }
+        } else {
+            // slices of more than 1024 (up to eight rows: 2048) values, or of no multiple of eight: value by value
+            auto value = [&](int r) { return r < nrows ? h2f(p.x[(size_t)brow * p.D + r0 + r]) * (norm ? h2f(lp.gamma[r0 + r]) : 1.f) : 0.f; };
+            if (norm) {
+                for (int r = lane0; live && r < nrows; r += lpr) xmax = fmaxf(xmax, fabsf(value(r)));
+                row_scale();
+            }
+            for (int r = lane0; live && r < p.RPS; r += lpr) {
+                const float v = norm ? __builtin_amdgcn_ldexpf(value(r), xe) : value(r), hi = (float)__builtin_amdgcn_cvt_pkrtz(v, v)[0];
+                xh[brow * XS + r] = (_Float16)hi;
+                if (norm) xl[brow * XS + r] = (_Float16)(fabsf(v) <= 3.402823466e38f ? v - hi : 0.f);
+            }
+        }
     } else if (XV && xvec) {
 #pragma unroll
         for (int q = 0; q < XP; ++q) {
@@ -675,7 +750,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             const bool in = piece_of(tid + q * NT, b, c);
             if (tid + q * NT < npc) stage_piece(b, c, xp[q], norm ? gp[q] : xp[q], in);
         }
-        for (int i = tid + XP * NT; i < npc; i += NT) {           // (batch 16: slices of more than 1024 rows)
+        for (int i = tid + XP * NT; i < npc; i += NT) {           // (16 rows: slices of more than 1024 values, 4 rows: of more than 2048)
             int b, c;
             const bool in = piece_of(i, b, c);
             stage_piece(b, c, xg4[in ? ((size_t)b * p.D + r0) / 8 + c : 0], gg4[in ? r0 / 8 + c : 0], in);
@@ -765,7 +840,15 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     for (int c = 0; c < (MF ? 8 : 1) * RS; ++c) acc4[c % RS][c / RS] = f32x4{0.f, 0.f, 0.f, 0.f};
     int si_first = 0;                       // selector index of the first buffered item
     int nbuf = 0;
+    bool factors = false;
     auto flush = [&]() {
+        if (BYROW && norm && !factors && lane0 == 0 && brow < p.B) {          // the factor of a row, in the place of its first sum of squares
+            float ss = 0.f;
+#pragma unroll
+            for (int w8 = 0; w8 < NW; ++w8) ss += nrm[w8 * BT + brow];
+            nrm[brow] = __builtin_amdgcn_ldexpf(1.0f / sqrtf(ss / (float)p.D + p.eps), -xe);
+        }
+        factors = true;
         lds_barrier();
         for (int e = tid; e < nbuf * BT * HD; e += NT) {
             const int it = e / (BT * HD), rem = e - it * (BT * HD);
@@ -774,7 +857,9 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
                 float sum = 0.f, ss = 0.f;
 #pragma unroll
                 for (int w8 = 0; w8 < NW; ++w8) sum += red[((it * NW + w8) * BT + b) * HD + c];
-                if (norm) {
+                if (BYROW) {
+                    if (norm) sum *= nrm[b];
+                } else if (norm) {
 #pragma unroll
                     for (int w8 = 0; w8 < NW; ++w8) ss += nrm[w8 * BT + b];
                     sum *= 1.0f / sqrtf(ss / (float)p.D + p.eps);
@@ -1510,11 +1595,15 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
     int tid = tid0;
     if (Mfma<HD, BT>::on) asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wv = tid >> 6;
-    // merged, normalised attention output of head hq, [BT][HD + AP]; MFMA tiles read 32 bytes of every row at once, with
-    // unpadded rows all of them from the same LDS banks (Llama-3-8B shape, batch 4: 1.8 us for a product of 0.3)
-    constexpr int AP = mfma_tiles(HD, BT) ? 4 : 0;
+    // merged, normalised attention output of head hq, [BT][HD].  MFMA tiles: as operands, PARTS fp16 parts [16][AR] of every
+    // value, and what undoes their scale, [16][2] (64 columns each).  (Unpadded rows would be read from the same LDS
+    // banks: Llama-3-8B shape, batch 4, 1.8 us for a product of 0.3.)
+    constexpr bool MF = Mfma<HD, BT>::on;
+    constexpr int AR = HD + kOutPad, PARTS = out_parts(HD);
     float *as = smem;
-    float *red = smem + BT * (HD + AP);      // the sums of the merge; MFMA tiles: [2][16][512]
+    _Float16 *ap = reinterpret_cast<_Float16 *>(smem);
+    float *inv = smem + PARTS * 16 * AR / 2;
+    float *red = smem + (MF ? out_operand_floats(HD) : BT * HD);          // the sums of the merge; MFMA tiles: [2][16][512]
     const Xbuf x2(p.p2), x3(p.p3);
 
     const int nrows = HD / p.RS3;
@@ -1523,7 +1612,6 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
     const int slot = hq * p.RS3 + rs;
     const int nchunk = p.CW3 / kOutChunk;
 
-    constexpr bool MF = Mfma<HD, BT>::on;
     if (!prefetched) p3_load<HD, MF>(p, lp, tid, hq, c3, rs, 0, tile);     // independent of the attention result
 
     {
@@ -1536,6 +1624,27 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
         //      value they were two thirds of the loads: tiny shape 17.2 -> 15.5 us, Llama-3-8B shape at batch 8 67.4 -> 65.9 us, 3000
         //      columns at batch 5 29.1 -> 27.2 us; a branch around the loads past the last split costs more than they do.)
         const int V = p.B * HD;
+        // value vi of the wavefront's 64, neighbours in one row.  MFMA tiles: scaled by a power of two that brings the largest of
+        // them into [2^14, 2^15) and split into fp16 parts, so that they enter the product with the same bits whatever their
+        // magnitude (an unscaled pair: 1e-2 of the output at 1e-6)
+        constexpr int kNoScale = -114;                            // an infinity among them
+        auto scale_of = [&](int max_bits) { return min(141 - (max_bits >> 23), 126); };
+        auto keep = [&](int vi, float v, int e) {
+            const int b = vi / HD, c = vi - b * HD;
+            if constexpr (MF) {
+                float r = __builtin_amdgcn_ldexpf(v, e);
+#pragma unroll
+                for (int n = 0; n < PARTS; ++n) {
+                    const _Float16 t = (_Float16)r;
+                    ap[(n * 16 + b) * AR + c] = t;
+                    r = e == kNoScale ? 0.f : r - (float)t;       // (an infinity stays one, in the first part)
+                }
+                if (lane == 0) inv[2 * b + c / 64] = __builtin_bit_cast(float, (127 - e) << 23);
+            } else {
+                as[vi] = v;
+            }
+            if (p.dbg_attn && c3 == 0 && rs == 0) p.dbg_attn[((size_t)b * p.nq + hq) * HD + c] = v;
+        };
         auto run = [&](auto nv_c, auto mc_c) {
             constexpr int NV = decltype(nv_c)::value, MC = decltype(mc_c)::value;
             const bool wide = p.NS > 32;                                  // more splits than half a wavefront: two loads
@@ -1607,13 +1716,12 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                     if (NV == 1 && SG > 1) {
                         red[sg * cv + v] = at[0];
                     } else {
+                        int ex[NV] = {};
+                        if constexpr (MF) wave_max_bits(at, ex);
 #pragma unroll
                         for (int n = 0; n < NV; ++n) {
                             const int vi = v0 + v + n * NT;
-                            if (vi < V) {
-                                as[vi + AP * (vi / HD)] = at[n];
-                                if (p.dbg_attn && c3 == 0 && rs == 0) p.dbg_attn[((size_t)(vi / HD) * p.nq + hq) * HD + col[n]] = at[n];
-                            }
+                            if (vi < V) keep(vi, at[n], scale_of(ex[n]));
                         }
                     }
                 }
@@ -1622,11 +1730,9 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                     if (tid < cv) {
                         float a = red[tid];
                         for (int k = 1; k < SG; ++k) a += red[k * cv + tid];
-                        as[v0 + tid + AP * ((v0 + tid) / HD)] = a;
-                        if (p.dbg_attn && c3 == 0 && rs == 0) {
-                            const int b = (v0 + tid) / HD, c = (v0 + tid) - b * HD;
-                            p.dbg_attn[((size_t)b * p.nq + hq) * HD + c] = a;
-                        }
+                        int ex[1] = {};
+                        if constexpr (MF) wave_max_bits({a}, ex);
+                        keep(v0 + tid, a, scale_of(ex[0]));
                     }
                 }
             }
@@ -1644,7 +1750,8 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
         } else {
             run(integral_constant<int, 1>{}, integral_constant<int, 4>{});
         }
-        for (int e = V + tid; e < BT * HD; e += NT) as[e + AP * (e / HD)] = 0.f;
+        // (MFMA tiles: what rows past the batch hold lands in rows of the product nobody reads)
+        for (int e = V + tid; !MF && e < BT * HD; e += NT) as[e] = 0.f;
         lds_barrier();
     }
     CF_STAMP(11);           // attention merged
@@ -1655,8 +1762,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
         if (ch > 0) p3_load<HD, MF>(p, lp, tid, hq, c3, rs, ch, tile);
         if constexpr (MF) {
             // [16 batch rows] x [rows of the item] x [128 columns of this wavefront]: one or two steps of 32 rows for each
-            // half of the rows; the attention output is split into a high and a low fp16 part (two products), so
-            // that it enters with all its fp32 bits
+            // half of the rows, with every part of the attention output
             const int lig = lane & 15, kg = lane >> 4, cb = wv & 3, kh = wv >> 2;
             f32x4 acc4[8];
 #pragma unroll
@@ -1664,17 +1770,16 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 #pragma unroll
             for (int sstep = 0; sstep < HD / 64; ++sstep) {
                 const int row = HD / 2 * kh + 32 * sstep + 8 * kg;      // first of the lane's eight rows
-                float a[8];
+                const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+                h8 a[PARTS], f[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) a[e] = row < nrows ? as[(lane & 15) * (HD + AP) + rbeg + row + e] : 0.f;
-                h8 ahi, alo, f[8];
-                split_hi_lo(a, ahi, alo);
+                for (int n = 0; n < PARTS; ++n)
+                    a[n] = row < nrows ? *reinterpret_cast<const h8 *>(ap + (n * 16 + lig) * AR + rbeg + row) : zero;
                 transpose8(&tile.w[8 * sstep], f);
 #pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    acc4[c] = mfma16(ahi, f[c], acc4[c]);
-                    acc4[c] = mfma16(alo, f[c], acc4[c]);
-                }
+                for (int c = 0; c < 8; ++c)
+#pragma unroll
+                    for (int n = 0; n < PARTS; ++n) acc4[c] = mfma16(a[n], f[c], acc4[c]);
             }
             // the two halves of the rows -> one partial row per batch row
 #pragma unroll
@@ -1684,10 +1789,22 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                 *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{acc4[4][r], acc4[5][r], acc4[6][r], acc4[7][r]};
             }
             lds_barrier();
-            for (int e = tid; e < p.B * kOutChunk; e += NT) {
-                const int b = e / kOutChunk, cc = e - b * kOutChunk;
-                if (cbase + cc < p.D)
-                    x3.st(((size_t)slot * p.B + b) * p.D + cbase + cc, red[e] + red[16 * kOutChunk + e], stamp);
+            static_assert(kOutChunk == NT, "a thread adds one column of every row");
+            const float iv = inv[lane & 31];
+            const bool mine = cbase + tid < p.D, halves = HD == 128 && nrows > 64;      // (halves: with a factor each)
+            for (int b0 = 0; b0 < p.B; b0 += 4) {
+                float u[4], v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    u[k] = red[(b0 + k) * kOutChunk + tid];
+                    v[k] = red[(16 + b0 + k) * kOutChunk + tid];          // (rows HD / 2 and on of the item: zero if it has none)
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float f0 = lane_of(iv, 2 * (b0 + k) + rbeg / 64), f1 = lane_of(iv, 2 * (b0 + k) + 1);
+                    const float sum = fmaf(u[k], f0, v[k] * (halves ? f1 : f0));
+                    if (mine && b0 + k < p.B) x3.st(((size_t)slot * p.B + b0 + k) * p.D + cbase + tid, sum, stamp);
+                }
             }
             CF_STAMP(18);   // output partial stored
             lds_barrier();
@@ -2209,7 +2326,7 @@ size_t lds_floats(const Params &p, int hd, int g, int bt)
     const size_t f2 = (size_t)hd + (size_t)(g + 2) * hd + 8 + 2 * (size_t)g * npart + (size_t)g * npart * hd +
                       (ma ? (size_t)kWaves * 32 * (hd + 8) / 2 + 2 * 256 * 4 : 0);   // K tiles, q operands
     // merged attention rows, then the sums of the merge (one per thread) or, on MFMA tiles, the two halves of the product
-    const size_t f3 = mfma_tiles(hd, bt) ? (size_t)bt * (hd + 4) + (size_t)2 * bt * kOutChunk : (size_t)bt * hd + kThreads;
+    const size_t f3 = mfma_tiles(hd, bt) ? (size_t)out_operand_floats(hd) + (size_t)2 * bt * kOutChunk : (size_t)bt * hd + kThreads;
     size_t f = f1 > f2 ? f1 : f2;
     return f > f3 ? f : f3;
 }

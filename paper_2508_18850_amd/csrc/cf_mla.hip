@@ -148,56 +148,14 @@ __device__ __forceinline__ void split_hi_lo(const float (&v)[8], h8 &hi, h8 &lo)
     }
 }
 
-// An fp32 operand of a matrix product that has to count in full: every row of the operand (lane c of each contraction
-// group holds row c) is scaled by a power of two that brings its largest value into [2^14, 2^15) and each value is cut into
-// three fp16 parts of eleven bits.  Down to 2^-15 of the row's largest value the parts add up to the value exactly, below
-// that to 2^-38 of the largest one, whatever the row's magnitude (a pair without the scale: 2e-3 of a value at 1e-5, NaN
-// above 65504).  The scale is taken out where the wavefronts' partial products are added.  Three such products cost 0.65 us
-// of a step (batch 2 / 4 / 16 on one box: 32.4 / 33.5 / 44.6 us with unscaled pairs, 33.1 / 34.1 / 45.25 us); rounded parts, each with its
-// conversion back, and a scale taken out of every accumulator cost 1.45 us.
-struct Split3 {
-    h8 hi, mid, lo;
-};
-// largest magnitude of row c among this lane's values and those of the other contraction groups
-__device__ __forceinline__ float row_max(float m)
-{
-    const unsigned u = __builtin_bit_cast(unsigned, m);
-    const auto t = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    const unsigned v = __builtin_bit_cast(unsigned, fmaxf(__builtin_bit_cast(float, (unsigned)t[0]), __builtin_bit_cast(float, (unsigned)t[1])));
-    const auto q = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    return fmaxf(__builtin_bit_cast(float, (unsigned)q[0]), __builtin_bit_cast(float, (unsigned)q[1]));
-}
-__device__ __forceinline__ float max_abs(const float (&v)[8], float m)
-{
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(v[k]));
-    return m;
-}
-// exponent of the scale of a row from its largest magnitude (at most 126: the inverse is a normal number)
-__device__ __forceinline__ int scale_exp(float m) { return min(15 - (m <= 3.402823466e38f ? __builtin_amdgcn_frexp_expf(m) : 128), 126); }
-__device__ __forceinline__ Split3 split3(const float (&v)[8], int e, float m)
-{
-    u32x4 p[3];
-    float r[8], minus1 = -1.f;
-    asm("" : "+s"(minus1));                                               // (kept a product: one v_fma_mix_f32 in place of a conversion and a difference)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) r[k] = __builtin_amdgcn_ldexpf(v[k], e);
-#pragma unroll
-    for (int n = 0; n < 3; ++n)
-#pragma unroll
-        for (int k = 0; k < 8; k += 2) {
-            const auto t = __builtin_amdgcn_cvt_pkrtz(r[k], r[k + 1]);     // (cut off, not rounded: what is left keeps its sign)
-            p[n][k / 2] = __builtin_bit_cast(uint32_t, t);
-            r[k] = fmaf((float)t[0], minus1, r[k]);
-            r[k + 1] = fmaf((float)t[1], minus1, r[k + 1]);
-        }
-    Split3 s = {__builtin_bit_cast(h8, p[0]), __builtin_bit_cast(h8, p[1]), __builtin_bit_cast(h8, p[2])};
-    if (__any(!(m <= 3.402823466e38f)))                                   // an infinity stays one, in the first part
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (!(fabsf(v[k]) <= 3.402823466e38f)) s.mid[k] = s.lo[k] = (_Float16)0.f;
-    return s;
-}
+// Three fp16 parts of a scaled row (cf_mfma_device.h) cost 0.65 us of a step (batch 2 / 4 / 16: 32.4 / 33.5 / 44.6 us with
+// unscaled pairs, 33.1 / 34.1 / 45.25 us); rounded parts, each with its conversion back, and a scale taken out of every
+// accumulator cost 1.45 us.
+using cf::mfma::Split;
+using cf::mfma::max_abs;
+using cf::mfma::row_max;
+using cf::mfma::scale_exp;
+using cf::mfma::split_scaled;
 
 __device__ __forceinline__ float ror8_add(float v)     // v + the value of the lane 8 further in the row of 16 lanes
 {
@@ -333,15 +291,15 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
             h8 f8[8];
             const float m = row_max(max_abs(q8, 0.f));
             const int e = scale_exp(m);
-            const Split3 q = split3(q8, e, m);
+            const Split<3> q = split_scaled<3>(q8, e, m);
             if (lane < 16) s_f[lane * NW + wv] = __builtin_amdgcn_ldexpf(1.f, -e);
             transpose8(wup, f8);
             f32x4 acc[8];
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) {
-                acc[jj] = mfma16(q.hi, f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
-                acc[jj] = mfma16(q.mid, f8[jj], acc[jj]);
-                acc[jj] = mfma16(q.lo, f8[jj], acc[jj]);
+                acc[jj] = mfma16(q.part[0], f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
+                acc[jj] = mfma16(q.part[1], f8[jj], acc[jj]);
+                acc[jj] = mfma16(q.part[2], f8[jj], acc[jj]);
             }
             if (c < 4)
 #pragma unroll
@@ -685,13 +643,13 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
             h8 f8[8];
-            const Split3 z = split3(v[st], ez, vmax);
+            const Split<3> z = split_scaled<3>(v[st], ez, vmax);
             transpose8(wdn + 8 * st, f8);
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) {
-                acc[jj] = mfma16(z.hi, f8[jj], acc[jj]);
-                acc[jj] = mfma16(z.mid, f8[jj], acc[jj]);
-                acc[jj] = mfma16(z.lo, f8[jj], acc[jj]);
+                acc[jj] = mfma16(z.part[0], f8[jj], acc[jj]);
+                acc[jj] = mfma16(z.part[1], f8[jj], acc[jj]);
+                acc[jj] = mfma16(z.part[2], f8[jj], acc[jj]);
             }
         }
         // the wavefronts' partial products with the inverse of their rows' scales, and their sum
@@ -724,13 +682,13 @@ __global__ void __launch_bounds__(NT) fused_mla_decode(const MlaArgs a)
             h8 f8[8];
             const float m = row_max(max_abs(v, 0.f));
             const int e = scale_exp(m);
-            const Split3 q = split3(v, e, m);
+            const Split<3> q = split_scaled<3>(v, e, m);
             transpose8(wor, f8);
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) acc[jj] = mfma16(wv < 4 ? q.hi : q.mid, f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
+            for (int jj = 0; jj < 8; ++jj) acc[jj] = mfma16(wv < 4 ? q.part[0] : q.part[1], f8[jj], f32x4{0.f, 0.f, 0.f, 0.f});
             if (wv < 4)
 #pragma unroll
-                for (int jj = 0; jj < 8; ++jj) acc[jj] = mfma16(q.lo, f8[jj], acc[jj]);
+                for (int jj = 0; jj < 8; ++jj) acc[jj] = mfma16(q.part[2], f8[jj], acc[jj]);
             spill(e);
         }
         lds_sync();

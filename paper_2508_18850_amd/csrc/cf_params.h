@@ -33,6 +33,14 @@ __host__ __device__ constexpr size_t x_lds_floats(int head_dim, int batch_tile, 
     return mfma_tiles(head_dim, batch_tile) ? (size_t)(layer || head_dim == 128 ? 16 : 8) * xs16_stride(rps) : (size_t)batch_tile * rps;
 }
 
+// The attention output of a head as the operand of the output projection on MFMA tiles: fp16 parts of every value,
+// [parts][16][head_dim + kOutPad] halves (rows of an odd number of 16-byte pieces), and two factors per row.  Of a value scaled
+// as below, two parts hold 23 bits and three all 24.  Three at head_dim 64, where the vector tile before held fp32; the third costs
+// 128 columns 0.1 - 0.5 us (Llama-3-8B shape, 8192 rows, batch 16 107.5 / 107.7 us, Llama-2-7B shape, batch 8 55.4 / 55.9).
+constexpr int kOutPad = 8;
+__host__ __device__ constexpr int out_parts(int head_dim) { return head_dim == 64 ? 3 : 2; }
+__host__ __device__ constexpr int out_operand_floats(int head_dim) { return out_parts(head_dim) * 16 * (head_dim + kOutPad) / 2 + 32; }
+
 constexpr int kFlagPacked = 1;     // weights are in the packed (per-head contiguous) layout of cf_pack_weights
 constexpr int kFlagResidual = 2;   // out = x + block output
 

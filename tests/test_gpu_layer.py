@@ -278,3 +278,77 @@ def test_slices_that_are_no_multiple_of_eight_rows(hd, batch, norm, monkeypatch)
     gamma = gamma_for(shape, 10) if norm else None
     res = run_layer(shape, batch, inp, kv_len, gamma, 1e-5, norm, True)
     check(res, reference(shape, inp, kv_len, gamma, 1e-5, norm), inp, kv_len, "33 rows")
+
+
+# Operands of the two projections far from one, their counterparts scaled the other way (powers of two on the inputs): x * gamma
+# at 4e-6, up to 1e5 and up to 8e6 (fp16 ends at 65504), rows of one batch 2^16 apart, attention outputs at 1e-6.
+MAGNITUDES = {
+    "small x gamma": dict(x=-8, gamma=-10, w_qkv=10),
+    "large x gamma": dict(x=13, gamma=2, w_qkv=-2),
+    "largest x gamma": dict(x=13, gamma=8, w_qkv=-8),
+    "rows apart": dict(rows=True),
+    "small attention output": dict(w_v=-10, v_cache=-20, w_o=12),
+}
+
+
+@pytest.mark.parametrize("d_model,hd,batch,tuning", [
+    (520, 64, 1, {}), (520, 64, 5, {}), (520, 64, 16, {}), (520, 128, 1, {}), (520, 128, 5, {}), (520, 128, 16, {}),
+    (520, 64, 7, dict(k_splits=16)), (520, 128, 16, dict(k_splits=16)),         # slices of 33 rows, staged value by value
+    (1320, 64, 16, dict(workgroups=4)), (1320, 128, 9, dict(workgroups=4)),     # slices of 1320 rows: more than 32 x 4 pieces a row
+])
+@pytest.mark.parametrize("name", list(MAGNITUDES))
+def test_operands_of_any_magnitude(name, d_model, hd, batch, tuning, monkeypatch):
+    """The rotated queries are one fp32 sum of d_model terms whose operands are held in full: relative RMS about
+    sqrt(d_model) * 2^-24 at most, 1.5 of that allowed, at every magnitude and batch.  Appended rows and output end in fp16
+    (relative RMS 2^-12.5), attention is summed in fp32 over 300 rows (1e-4)."""
+    import paper_2508_18850_amd as cf
+
+    class Tuned(cf.DecodeBlock):
+        def __init__(self, *args, **kwargs):
+            super().__init__(*args, **kwargs)
+            if tuning:
+                self.set_tuning(**tuning)
+
+    monkeypatch.setattr(cf, "DecodeBlock", Tuned)
+    shape, kv_len, s = cf_inputs.BlockShape("s", d_model, 8, 4, hd, 10000.0, 300), 300, MAGNITUDES[name]
+    inp = cf_inputs.make_inputs(shape, seed=500 + batch, batch=batch, kv_len=kv_len)
+    gamma = gamma_for(shape, 11)
+
+    def scaled(a, e):
+        return (a.astype(np.float32) * np.float32(2.0) ** e).astype(np.float16)
+
+    for k in ("x", "w_qkv", "v_cache", "w_o"):
+        inp[k] = scaled(inp[k], s.get(k, 0))
+    gamma = scaled(gamma, s.get("gamma", 0))
+    first_v = (shape.n_q_heads + shape.n_kv_heads) * hd
+    inp["w_qkv"][:, first_v:] = scaled(inp["w_qkv"][:, first_v:], s.get("w_v", 0))
+    if s.get("rows"):
+        inp["x"] = scaled(inp["x"], np.array([(5 * b) % 17 - 8 for b in range(batch)], dtype=np.float32)[:, None])
+    for norm in (True, False) if "attention" in name else (True,):
+        res = run_layer(shape, batch, inp, kv_len, gamma if norm else None, 0.0, False, True)
+        ref = reference(shape, inp, kv_len, gamma if norm else None, 0.0, False)
+        _log("%s D %d head_dim %d batch %d norm %s: |x gamma| %.1e |attn| %.1e |out| %.1e" % (
+            name, d_model, hd, batch, norm, np.abs(inp["x"].astype(np.float64) * gamma.astype(np.float64)).max(),
+            np.abs(ref["attn"]).max(), np.abs(ref["out"]).max()))
+        for what, got, want, tol in (("q_rot", res["q_rot"], ref["q_rot"], 1.5 * np.sqrt(d_model) * 2.0 ** -24),
+                                     ("attn", res["attn"], ref["attn"], 1e-4), ("out", res["out"], ref["out"], 1e-3),
+                                     ("k", res["k_cache"][:, :, kv_len], ref["k_rot"], 1e-3),
+                                     ("v", res["v_cache"][:, :, kv_len], ref["v_new"], 1e-3)):
+            got = got.astype(np.float64)
+            rel = np.sqrt(np.mean((got - want) ** 2) / np.mean(want ** 2))
+            _log("   %s: relative RMS %.2e" % (what, rel))
+            assert np.isfinite(got).all() and rel < tol, what
+
+
+@pytest.mark.parametrize("hd,batch", [(64, 4), (64, 5), (128, 16)])
+def test_infinite_input_stays_in_its_row(hd, batch):
+    """Rows 1 and 2 hold an infinity and a NaN; every other row gives the bits it gives without them."""
+    shape, kv_len = cf_inputs.BlockShape("s", 520, 8, 4, hd, 10000.0, 50), 50
+    inp = cf_inputs.make_inputs(shape, seed=7, batch=batch, kv_len=kv_len)
+    gamma, rows = gamma_for(shape, 3), [b for b in range(batch) if b not in (1, 2)]
+    want = run_layer(shape, batch, inp, kv_len, gamma, 1e-5, True, True)
+    inp["x"][1, 77], inp["x"][2, 300] = np.inf, np.nan
+    got = run_layer(shape, batch, inp, kv_len, gamma, 1e-5, True, True)
+    for what in ("out", "k_cache", "v_cache"):
+        assert np.array_equal(got[what][rows].view(np.uint16), want[what][rows].view(np.uint16)), what
+    assert not np.isfinite(got["out"][1]).any() and not np.isfinite(got["out"][2]).any()
