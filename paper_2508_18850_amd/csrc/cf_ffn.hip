@@ -108,12 +108,13 @@ __device__ __forceinline__ float activate(float a, int act)
     return a / (1.0f + __expf(-a));                    // SiLU
 }
 
-// Launches this workgroup has completed: a scalar load that is waited for where the count is first used (waited for at once,
-// its trip to memory held up the first weights).  Written by an earlier launch, so the constant address space will do.
+// Launches this workgroup has completed: a uniform load in front of all stores, which the compiler makes a scalar load and
+// waits for where the count is first used (waited for at once, its trip to memory held up the first weights).  An ordinary load,
+// not one from the constant address space: thread 0 overwrites the word at the end of this very launch, and a wavefront that
+// loaded it again by then would wait for a stamp that nobody writes.
 __device__ __forceinline__ unsigned long long launches_before(const FfnArgs &a, int w)
 {
-    typedef const __attribute__((address_space(4))) unsigned long long *ScalarPtr;
-    return *(ScalarPtr)(uintptr_t)(a.counters + (size_t)w * kCounterStride);
+    return a.counters[(size_t)w * kCounterStride];
 }
 
 template <int BT, int NCB>     // batch tile; column blocks of 4096 per thread (d_model <= 4096 NCB)

@@ -56,3 +56,19 @@ def test_one_launch_stack_has_no_scratch_up_to_batch_4():
             mine = [v for k, v in all_kernels.items() if "fused_decode_stackILi128ELi%dELi%dEE" % (group, tile) in k]
             assert len(mine) == 1, (group, tile)
             assert mine[0][".private_segment_fixed_size"] == 0, (group, tile, mine[0][".private_segment_fixed_size"])
+
+
+def test_counters_are_not_read_as_constants(tmp_path):
+    """A launch counter is overwritten by the launch that reads it, so it may not be read through the constant address space:
+    such a load may be repeated by the compiler at any place, also behind the store.  (The kernel arguments are in that address
+    space from the start; nothing is cast to it.)"""
+    import re
+    import subprocess
+
+    from paper_2508_18850_amd import build
+    ir = tmp_path / "cf_ffn.ll"
+    subprocess.run([build._hipcc(), *build.HIPCC_FLAGS, "--cuda-device-only", "-S", "-emit-llvm", "-Xclang", "-disable-llvm-passes",
+                    "-o", str(ir), os.path.join(build.CSRC, "cf_ffn.hip")], check=True, capture_output=True)
+    text = ir.read_text()
+    assert "fused_ffn_tiles" in text
+    assert not re.findall(r"(?:inttoptr|addrspacecast) .* to ptr addrspace\(4\)", text)
