@@ -132,6 +132,23 @@ def test_one_handle_for_changing_calls():
     tc.close()
 
 
+def test_rounds_after_longer_rounds():
+    """Up to 4096 values a launch in rounds clears the other set box by box between its rounds: what a longer launch, or one of
+    more rounds, has left there must be gone when the set is used again (results of the next but one)."""
+    tc = TeamCollectives(64, 20001)
+    st = torch.cuda.current_stream().cuda_stream
+    for k, (teams, n, elems) in enumerate([(4, 16, 20001), (32, 2, 100), (4, 16, 20001), (16, 4, 4096), (4, 16, 4097), (8, 8, 5),
+                                           (4, 16, 4096), (64, 1, 7), (4, 16, 4096), (64, 1, 4097), (4, 16, 4097)]):
+        _log("call %d: teams=%d N=%d elems=%d" % (k, teams, n, elems))
+        host = _data(teams, n, elems, seed=k)
+        src = torch.from_numpy(host).cuda()
+        dst = torch.full_like(src, float("nan"))
+        tc.reduce(teams, n, TEAM_MAX, src.data_ptr(), dst.data_ptr(), elems, TEAM_ROUNDS, st)
+        tc.status(st)
+        assert np.array_equal(dst.cpu().numpy(), np.broadcast_to(host.max(axis=1, keepdims=True), host.shape))
+    tc.close()
+
+
 @pytest.mark.parametrize("mode", [TEAM_ROUNDS, TEAM_DIRECT, TEAM_TWO_HOPS])
 def test_a_nan_with_all_bits_set_arrives(mode):
     """Values are sent inverted and an empty box holds zeros: this one is sent as the NaN next to it."""
