@@ -97,24 +97,26 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
         auto fits = [&](int rows) {
             return (cf::x_lds_floats(hd, bt, rows, low_parts) + maxi * cf::kWaves * bt * hd + (size_t)cf::kWaves * bt) * sizeof(float) <= kLdsLimit;
         };
-        for (int pass = 0; pass < 2 && !best; ++pass, low_parts = cf::wants_layer_kernel(*p))
-        for (int ks = 1; ks <= kMaxKS && ks <= TS; ++ks) {
-            if (h->tune_ks > 0 && ks != h->tune_ks) continue;
-            if ((h->tune_ks > 0 || even_slices) && TS % ks) continue;
-            int rps = slice_rows(c.d_model, ks);
-            if (!fits(rps)) rps = ceil_div(c.d_model, ks);
-            if (rps < 8 && ks > 1) continue;
-            if ((long)(ks - 1) * rps >= c.d_model) continue;   // no empty slice
-            if (!fits(rps)) continue;
-            const int dsel = TS / ks;
-            // rows a member streams, plus what its consumers pay for every further slice: KS partial sums per projected
-            // value to fetch, for every batch row (weighed by measurements; the Llama-2-70B shape stays at 16 slices:
-            // 75.0 us, 76.3 us with 3, 76.8 us with 8)
-            const long cost = (long)ceil_div(G + 2, dsel) * rps + 12L * ks * (bt < 4 ? bt : 4);
-            if (!best || cost < best_cost) {
-                best = ks;
-                best_rows = rps;
-                best_cost = cost;
+        for (int pass = 0; pass < 2 && !best; ++pass) {
+            if (pass == 1) low_parts = cf::wants_layer_kernel(*p);
+            for (int ks = 1; ks <= kMaxKS && ks <= TS; ++ks) {
+                if (h->tune_ks > 0 && ks != h->tune_ks) continue;
+                if ((h->tune_ks > 0 || even_slices) && TS % ks) continue;
+                int rps = slice_rows(c.d_model, ks);
+                if (!fits(rps)) rps = ceil_div(c.d_model, ks);
+                if (rps < 8 && ks > 1) continue;
+                if ((long)(ks - 1) * rps >= c.d_model) continue;   // no empty slice
+                if (!fits(rps)) continue;
+                const int dsel = TS / ks;
+                // rows a member streams, plus what its consumers pay for every further slice: KS partial sums per projected
+                // value to fetch, for every batch row (weighed by measurements; the Llama-2-70B shape stays at 16 slices:
+                // 75.0 us, 76.3 us with 3, 76.8 us with 8)
+                const long cost = (long)ceil_div(G + 2, dsel) * rps + 12L * ks * (bt < 4 ? bt : 4);
+                if (!best || cost < best_cost) {
+                    best = ks;
+                    best_rows = rps;
+                    best_cost = cost;
+                }
             }
         }
         if (!best) return h->tune_ks > 0 ? CF_EINVAL : CF_EUNSUPPORTED;
