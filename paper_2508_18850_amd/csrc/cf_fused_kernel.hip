@@ -94,7 +94,7 @@ __device__ __forceinline__ void unpack8(const h8 &u, float (&f)[8])
 // into eight operands of one column each (transpose8); the sixteen batch rows are the A operand.
 template <int HD, int BT>
 struct Mfma {
-    static constexpr bool on = mfma_tiles(HD, BT);
+    static constexpr bool on = mfma_tiles(BT);
 };
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -346,7 +346,8 @@ __device__ __forceinline__ uint32_t stamp_of(unsigned long long cnt0, int layer)
 template <int HD, int BT>
 struct P1Cfg {
     static constexpr bool MF = Mfma<HD, BT>::on;
-    static constexpr int U = MF ? 8 : (BT > 4 ? 2 : (BT == 4 ? 4 : 8));     // loads per thread and batch
+    static_assert(MF || BT <= 4, "vector tiles of up to four rows");
+    static constexpr int U = BT == 4 ? 4 : 8;                               // loads per thread and batch
 };
 // How many of the two batches a stack requests ahead for its next layer: what the registers of the variant allow
 // (none with the 16-row tile, one where the attention or a second query head per KV head takes the room).
@@ -372,9 +373,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 {
     constexpr int LPR = HD / 8;
     constexpr int NG = NT / LPR;
-    // loads per thread and batch: the 16-row batch tile keeps 128 accumulators per thread, and anything above two
-    // loads per batch spills (measured on the 8B shape, batch 16: 202 us with 8, 181 with 4, 177 with 2, 182 with 1);
-    // the 4-row tile is best with 4 (8B shape, batch 4: 55.1 us with 8, 53.6 with 4, 53.7 with 2)
+    // loads per thread and batch: the 4-row tile is best with 4 (8B shape, batch 4: 55.1 us with 8, 53.6 with 4, 53.7 with 2).
     // With MFMA tiles (MF) a batch is eight rows per lane: one step of the contraction, 32 RS rows, per wavefront.
     constexpr bool MF = P1Cfg<HD, BT>::MF;
     constexpr int U = P1Cfg<HD, BT>::U;
@@ -1815,7 +1814,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
         for (int b = 0; b < BT; ++b)
 #pragma unroll
             for (int j = 0; j < 8; ++j) acc[b][j] = 0.f;
-        if (BT <= 4 && nchunk == 1) {
+        if (nchunk == 1) {
             // straight-line code (a branch per row would serialise the LDS reads): a row past the item
             // has a zero tile entry, its load was switched off, so it may be multiplied by any finite value
 #pragma unroll
@@ -1831,8 +1830,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                 }
             }
         } else {
-            // the 16-row batch tile has no registers to spare for reads hoisted across rows; with several
-            // chunks per item the tile was loaded just now, and row-by-row waits overlap its arrival
+            // with several chunks per item the tile was loaded just now, and row-by-row waits overlap its arrival
 #pragma unroll
             for (int u = 0; u < OutTile<HD>::MAXR; ++u) {
                 if (u < iters) {
@@ -1868,7 +1866,11 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 // partials of those columns in slot order (the cross-head reduction that the paper
 // does with atomicAdd), then writes fp16.
 // ---------------------------------------------------------------------------
-// Output columns a workgroup owns: an even number, since a stack hands its hidden state on in pairs of values.
+// Output columns a workgroup owns: an even number, since a stack hands its hidden state on in pairs of values.  Single launches
+// do the same: the bits of a stack are those of its layers one by one, and the sixteen bytes of two neighbouring partials are one
+// piece of a line (us a layer, exact / even number: 768 columns, 8 heads of 128, batch 4 / 16 20.9 / 19.5 and 30.3 / 26.0, 1280 columns,
+// 22.5 / 22.2 and 33.2 / 32.3, 2056 columns, 14 heads of 64, 19.9 / 19.6 and 25.1 / 24.4; 256 columns, one or two per workgroup: 4
+// heads of 64 14.6 / 14.6 and 19.4 / 21.0, 16 heads of 128 21.1 / 21.6 and 31.1 / 29.8).
 __device__ __forceinline__ int own_columns(const Params &p) { return ((p.D + p.W - 1) / p.W + 1) & ~1; }
 
 // The residual input of output value v0 + i of this workgroup (0 when there is none): from x, in a stack past its first layer
@@ -2326,7 +2328,7 @@ size_t lds_floats(const Params &p, int hd, int g, int bt)
     const size_t f2 = (size_t)hd + (size_t)(g + 2) * hd + 8 + 2 * (size_t)g * npart + (size_t)g * npart * hd +
                       (ma ? (size_t)kWaves * 32 * (hd + 8) / 2 + 2 * 256 * 4 : 0);   // K tiles, q operands
     // merged attention rows, then the sums of the merge (one per thread) or, on MFMA tiles, the two halves of the product
-    const size_t f3 = mfma_tiles(hd, bt) ? (size_t)out_operand_floats(hd) + (size_t)2 * bt * kOutChunk : (size_t)bt * hd + kThreads;
+    const size_t f3 = mfma_tiles(bt) ? (size_t)out_operand_floats(hd) + (size_t)2 * bt * kOutChunk : (size_t)bt * hd + kThreads;
     size_t f = f1 > f2 ? f1 : f2;
     return f > f3 ? f : f3;
 }

@@ -2,8 +2,7 @@
 // ds_bpermute: some hundred cycles until its result is there, and the LDS pipe of the compute unit shared by all wavefronts).
 //
 // In the decode block, with shuffles / with these (us a layer, single launches, D = d_model): tiny shape 15.5 / 14.2; D 2056,
-// 14 heads of 64, batch 3 22.9 / 20.2; Llama-2-7B shape 38.4 / 38.0; 64 heads of 64 over 8, D 2048, batch 1 / 8 28.8 / 23.0 and
-// 59.9 / 42.2; 16 heads of 64, D 1024, batch 16 53.3 / 33.7 (the shuffles of the 16-row vector tile had spilled 330 bytes per lane).
+// 14 heads of 64, batch 3 22.9 / 20.2; Llama-2-7B shape 38.4 / 38.0; 64 heads of 64 over 8, D 2048, batch 1 28.8 / 23.0.
 //
 // A wavefront is seen as row groups of LPR = 8 or 16 consecutive lanes (the lanes that hold one row of a weight or
 // cache tile); a value is reduced over the row groups, lane by lane.

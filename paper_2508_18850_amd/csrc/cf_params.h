@@ -22,7 +22,7 @@ constexpr int kMaxKvSplits = 64;
 
 // Batch tile 16 runs both projections on MFMA tiles; x then sits in LDS as fp16 operands,
 // [16][xs16_stride(rows of the longest split)] halves, twice (high parts, low parts of x * gamma).
-__host__ __device__ constexpr bool mfma_tiles(int head_dim, int batch_tile) { return batch_tile == 16 && head_dim > 0; }
+__host__ __device__ constexpr bool mfma_tiles(int batch_tile) { return batch_tile == 16; }
 // (an odd number of 16-byte pieces: the sixteen lanes of an operand read, one per row, then fall into different banks;
 // with the 104 pieces of 824 rows and one of padding they met in two)
 __host__ __device__ constexpr int xs16_stride(int rps) { return (((rps + 7) >> 3) | 1) << 3; }
@@ -30,7 +30,7 @@ __host__ __device__ constexpr int xs16_stride(int rps) { return (((rps + 7) >> 3
 // take slices of up to 4000 rows (a few shapes with hardly more workgroups than KV heads need more than 2024).
 __host__ __device__ constexpr size_t x_lds_floats(int head_dim, int batch_tile, int rps, bool layer)
 {
-    return mfma_tiles(head_dim, batch_tile) ? (size_t)(layer || head_dim == 128 ? 16 : 8) * xs16_stride(rps) : (size_t)batch_tile * rps;
+    return mfma_tiles(batch_tile) ? (size_t)(layer || head_dim == 128 ? 16 : 8) * xs16_stride(rps) : (size_t)batch_tile * rps;
 }
 
 // The attention output of a head as the operand of the output projection on MFMA tiles: fp16 parts of every value,
