@@ -1,8 +1,8 @@
 """cf_decode_stack through the C ABI: a stack of layers in one call, the hidden state handed from layer to layer.
 
 Checks: (1) the result and every appended cache row are bit-identical to the same layers enqueued one by one with
-cf_decode_layer (with RMSNorm or residual, or head_dim 64, the stack is the same launches with the library's buffers in
-between; the bare block with head_dim 128 runs all layers in ONE launch, the hidden state handed on inside the kernel);
+cf_decode_layer (with head_dim 64, or with RMSNorm or residual at batch 2 and more, the stack is the same launches with the library's buffers in
+between; head_dim 128, bare or at batch 1, runs all layers in ONE launch, the hidden state handed on inside the kernel);
 (2) every layer on its own: the oracle applied to the fp16 hidden state the GPU fed that layer, against what the GPU
 made of it, at the block tolerance max|err| <= 1e-2 * max|ref| + 1e-3 (not widened: both start from the same input);
 (3) bad arguments are refused before anything is enqueued.
@@ -190,6 +190,11 @@ def test_more_layers_than_one_launch_holds():
     blk.close()
 
 
+def test_more_layers_with_norm_than_one_launch_holds():
+    """RMSNorm and residual at batch 1: launches of 88 and 2 layers, the second with its own first row of the input."""
+    test_stack_matches_single_calls_and_oracle(G2, True, 1, False, 1, 90, 21)
+
+
 def test_bad_arguments_enqueue_nothing():
     from paper_2508_18850_amd import DecodeBlock
     shape = cf_inputs.SHAPES["tiny"]
@@ -333,10 +338,10 @@ def test_stack_with_workgroups_that_own_no_output_column(shape, batch):
     test_stack_matches_single_calls_and_oracle(shape, False, 0, True, batch, 3, 150)
 
 
-# Slices of the input longer than what a thread has in flight at once (batch 2: more than 2560 values of the batch's rows,
-# batch 3 to 16: more than 4608), so that it arrives in several rounds, with slices forced and as the plan cuts them, and a
+# Slices of the input longer than what the workgroup has in flight at once (two pieces of eight values per thread: 8192 values
+# of the batch's rows), so that it arrives in several rounds, with slices forced and as the plan cuts them, and a
 # last slice that is shorter than the others.
-G4_LONG = cf_inputs.BlockShape("gqa4_long", 1536, 8, 2, 128, 10000.0, 0)
+G4_LONG = cf_inputs.BlockShape("gqa4_long", 4224, 8, 2, 128, 10000.0, 0)
 G8_WIDE = cf_inputs.BlockShape("gqa8_wide", 1664, 64, 8, 128, 10000.0, 0)
 M128_SHORT_END = cf_inputs.BlockShape("mha128_short_end", 1304, 4, 4, 128, 10000.0, 0)
 
@@ -353,7 +358,7 @@ def test_stack_with_long_slices_of_the_input(shape, batch, k_splits, monkeypatch
 
         def close(self):
             plan = self.plan()
-            assert batch * plan["rows_per_split"] > (2560 if batch == 2 else 4608), plan
+            assert batch * plan["rows_per_split"] > 8192, plan
             super().close()
 
     monkeypatch.setattr(cf, "DecodeBlock", Tuned)
