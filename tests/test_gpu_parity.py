@@ -401,9 +401,9 @@ def test_merge_of_kv_splits(hd, batch, kv_splits):
 
 
 @pytest.mark.parametrize("d_model,nq,nkv,hd,batch", [
-    (256, 16, 2, 64, 1),      # one column per workgroup, 64 and more partials of it; eight query heads on the vector tile
+    (256, 16, 2, 64, 1),      # two columns for every other workgroup, 64 and more partials of them; eight query heads on the vector tile
     (4096, 4, 4, 64, 2),      # 32 values per workgroup: the most that sixteen lanes each add
-    (4232, 2, 2, 128, 2),     # 34: one thread each
+    (4232, 2, 2, 128, 2),     # 36 (18 columns, their number is even): one thread each
     (776, 8, 1, 64, 4),       # four batch rows, column pieces that end inside a chunk
 ])
 def test_sums_between_lanes(d_model, nq, nkv, hd, batch):

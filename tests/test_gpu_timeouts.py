@@ -48,6 +48,40 @@ def test_decode_block_reports_a_timeout_and_recovers():
     blk.close()
 
 
+def test_one_launch_stack_with_norm_reports_a_timeout_and_recovers():
+    """The waits for the whole row of a layer's input are bounded as well; the slots of the hidden state are cleared with the rest."""
+    from paper_2508_18850_amd import DecodeBlock, CfError
+    shape, kv_len, n_layers = cf_inputs.BlockShape("s", 1024, 16, 4, 128, 10000.0, 1500), 1500, 4
+    dev = torch.device("cuda:0")
+    st = torch.cuda.current_stream().cuda_stream
+    blk = DecodeBlock(shape.d_model, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, 1, cf_inputs.default_max_seq(kv_len), shape.rope_base)
+    host = [cf_inputs.make_inputs(shape, seed=95 + l, batch=1, kv_len=kv_len, poison=False) for l in range(n_layers)]
+    t = [{k: torch.from_numpy(inp[k]).to(dev) for k in ("w_qkv", "w_o", "k_cache", "v_cache")} for inp in host]
+    x = torch.from_numpy(host[0]["x"]).to(dev)
+    gamma = torch.ones(shape.d_model, dtype=torch.float16, device=dev)
+    out = torch.empty_like(x)
+
+    def call():
+        blk.decode_stack(1, x.data_ptr(), [gamma.data_ptr()] * n_layers, 1e-5, 1, 0, *([d[k].data_ptr() for d in t]
+                         for k in ("w_qkv", "w_o", "k_cache", "v_cache")), kv_len, out.data_ptr(), st)
+
+    call()
+    blk.status(st)
+    good = out.clone()
+    for _ in range(2):
+        print("stack, wait limit 0", flush=True)
+        blk.set_tuning(spin_limit_us=-1)
+        call()
+        with pytest.raises(CfError) as e:
+            blk.status(st)
+        assert e.value.code == CF_ETIMEOUT
+        blk.set_tuning(spin_limit_us=2000000)
+        call()
+        blk.status(st)
+        assert torch.equal(out, good)
+    blk.close()
+
+
 def test_team_collectives_report_a_timeout_and_recover():
     from paper_2508_18850_amd import TeamCollectives, TEAM_SUM, TEAM_ROUNDS, CfError
     tc = TeamCollectives(64, 65536)

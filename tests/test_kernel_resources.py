@@ -1,7 +1,7 @@
 """What the compiler made of the kernels: the metadata of the code objects in the built library.
 
-The one-launch stack keeps the next layer's weights in flight across all phases and fills the register file with one to
-four batch rows; scratch there means spills between a layer's first loads and their use.
+The one-launch stacks keep the next layer's weights in flight across all phases and fill the register file with one to
+four batch rows (with RMSNorm one); scratch there means spills between a layer's first loads and their use.
 """
 import os
 import struct
@@ -54,8 +54,20 @@ def test_one_launch_stack_has_no_scratch_up_to_batch_4():
     for group in (1, 2, 4, 8):
         for tile in (1, 4):
             mine = [v for k, v in all_kernels.items() if "fused_decode_stackILi128ELi%dELi%dEE" % (group, tile) in k]
-            assert len(mine) == 1, (group, tile)
-            assert mine[0][".private_segment_fixed_size"] == 0, (group, tile, mine[0][".private_segment_fixed_size"])
+            if tile == 1:
+                mine += [v for k, v in all_kernels.items() if "fused_layer_stackILi128ELi%dELi1EE" % group in k]
+            assert len(mine) == (2 if tile == 1 else 1), (group, tile)
+            for kernel in mine:
+                assert kernel[".private_segment_fixed_size"] == 0, (group, tile, kernel[".name"])
+
+
+def test_16_row_tile_has_no_scratch():
+    all_kernels = kernels()
+    for name in ("block", "layer"):
+        for hd in (64, 128):
+            for group in (1, 2, 4, 8):
+                mine = [v for k, v in all_kernels.items() if "fused_decode_%sILi%dELi%dELi16EE" % (name, hd, group) in k]
+                assert len(mine) == 1 and mine[0][".private_segment_fixed_size"] == 0, (name, hd, group)
 
 
 def test_counters_are_not_read_as_constants(tmp_path):
