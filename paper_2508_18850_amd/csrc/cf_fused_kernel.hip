@@ -700,28 +700,30 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         const uint4 none = {0u, 0u, 0u, 0u};
         for (int i = np + tid; i < P8; i += NT) stage_piece(0, i, none, none, false);     // the last slice may be shorter
     } else if constexpr (BYROW) {
-        const bool live = brow < p.B, whole = xvec && P8 <= XP * lpr;     // (uniform: a row's pieces are all in registers)
+        const bool live = brow < p.B;
         auto row_scale = [&]() {
             xmax = lpr == 32 ? lanes::max_half(xmax) : wave_max(xmax);
             xe = mfma::scale_exp(xmax);
         };
-        if (whole) {
-            if (norm) {
+        auto take_max = [&](const uint4 &xw, const uint4 &gw, bool in) {
+            float f[8], g[8];
+            unpack8(__builtin_bit_cast(h8, xw), f);
+            unpack8(__builtin_bit_cast(h8, gw), g);
 #pragma unroll
-                for (int q = 0; q < XP; ++q) {
-                    if (q * lpr >= P8) break;                     // (uniform)
-                    int b, c;
-                    const bool in = own_piece(q, b, c);
-                    float f[8], g[8];
-                    unpack8(__builtin_bit_cast(h8, xp[q]), f);
-                    unpack8(__builtin_bit_cast(h8, gp[q]), g);
+            for (int j = 0; j < 8; ++j) f[j] *= g[j];
+            const float m = mfma::max_abs(f, xmax);
+            xmax = in ? m : xmax;
+        };
+        auto max_of_registers = [&]() {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) f[j] *= g[j];
-                    const float m = mfma::max_abs(f, xmax);
-                    xmax = in ? m : xmax;
-                }
-                row_scale();
+            for (int q = 0; q < XP; ++q) {
+                if (q * lpr >= P8) break;                         // (uniform)
+                int b, c;
+                const bool in = own_piece(q, b, c);
+                take_max(xp[q], gp[q], in);
             }
+        };
+        auto stage_registers = [&]() {
 #pragma unroll
             for (int q = 0; q < XP; ++q) {
                 if (q * lpr >= P8) break;
@@ -729,8 +731,24 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
                 const bool in = own_piece(q, b, c);
                 if (live && c < P8) stage_piece(b, c, xp[q], norm ? gp[q] : xp[q], in);
             }
-        } else {
-            // slices of more than 1024 (up to eight rows: 2048) values, or of no multiple of eight: value by value
+        };
+        if (xvec && P8 <= XP * lpr) {                             // (uniform: all of a row's pieces are in registers)
+            if (norm) {
+                max_of_registers();
+                row_scale();
+            }
+            stage_registers();
+        } else if (xvec) {                                        // slices of more than 1024 (up to eight rows: 2048) values
+            auto fetch = [&](const uint4 *src, size_t at, int c) { return src[8 * c < nrows ? at + r0 / 8 + c : 0]; };
+            const size_t row8 = (size_t)brow * d8;
+            if (norm) {
+                max_of_registers();
+                for (int c = lane0 + XP * lpr; live && c < P8; c += lpr) take_max(fetch(xg4, row8, c), fetch(gg4, 0, c), 8 * c < nrows);
+                row_scale();
+            }
+            stage_registers();
+            for (int c = lane0 + XP * lpr; live && c < P8; c += lpr) stage_piece(brow, c, fetch(xg4, row8, c), fetch(gg4, 0, c), 8 * c < nrows);
+        } else {                                                  // slices that are no multiples of eight rows
             auto value = [&](int r) { return r < nrows ? h2f(p.x[(size_t)brow * p.D + r0 + r]) * (norm ? h2f(lp.gamma[r0 + r]) : 1.f) : 0.f; };
             if (norm) {
                 for (int r = lane0; live && r < nrows; r += lpr) xmax = fmaxf(xmax, fabsf(value(r)));

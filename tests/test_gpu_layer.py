@@ -340,6 +340,25 @@ def test_operands_of_any_magnitude(name, d_model, hd, batch, tuning, monkeypatch
             assert np.isfinite(got).all() and rel < tol, what
 
 
+@pytest.mark.parametrize("d_model,hd,batch", [(1976, 64, 5), (1976, 64, 16), (1392, 128, 3), (1392, 128, 16)])
+def test_longest_slices_of_the_layer(d_model, hd, batch, monkeypatch):
+    """As many workgroups as KV heads: one slice, about as long as LDS holds with the low parts of x * gamma beside it; a row has more pieces
+    than its lanes keep in registers at batch 16."""
+    import paper_2508_18850_amd as cf
+
+    class Tuned(cf.DecodeBlock):
+        def __init__(self, *args, **kwargs):
+            super().__init__(*args, **kwargs)
+            self.set_tuning(workgroups=2)
+
+    monkeypatch.setattr(cf, "DecodeBlock", Tuned)
+    shape, kv_len = cf_inputs.BlockShape("s", d_model, 2, 2, hd, 10000.0, 40), 40
+    inp = cf_inputs.make_inputs(shape, seed=batch, batch=batch, kv_len=kv_len)
+    gamma = gamma_for(shape, 12)
+    res = run_layer(shape, batch, inp, kv_len, gamma, 1e-5, True, True)
+    check(res, reference(shape, inp, kv_len, gamma, 1e-5, True), inp, kv_len, "one slice of %d" % d_model)
+
+
 @pytest.mark.parametrize("hd,batch", [(64, 4), (64, 5), (128, 16)])
 def test_infinite_input_stays_in_its_row(hd, batch):
     """Rows 1 and 2 hold an infinity and a NaN; every other row gives the bits it gives without them."""
