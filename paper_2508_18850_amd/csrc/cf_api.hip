@@ -29,7 +29,7 @@ struct cf_handle_s {
     uint64_t *xslots = nullptr;                // the same between the layers of a one-launch stack: stamped pairs of values, [max_batch, d_model / 2]
     // tuning
     int tune_w = 0, tune_ks = 0, tune_ns = 0;
-    int balance_rows = 0, balance_tokens = 32;   // half the length difference between even and odd splits (-1: off)
+    int balance_tokens = 32;   // half the length difference between even and odd splits of the cached rows
     long long spin_ticks = 200000000LL;   // 2 s of the 100 MHz wall clock
     int wg_per_cu[6] = {0, 0, 0, 0, 0, 0};   // resident workgroups per CU for batch tiles 1, 4, 16 of the block kernel,
                                           // then of the layer kernel (0 = not probed)
@@ -121,14 +121,8 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
         }
         if (!best) return h->tune_ks > 0 ? CF_EINVAL : CF_EUNSUPPORTED;
         p->KS = best;
-        p->RB = best_rows;
-        // uneven slices (see the kernel's workgroup mapping): only when member parity == slice parity
-        p->pairmap = (TS % 2 == 0 && W % 2 == 0 && h->balance_rows >= 0) ? 1 : 0;
-        p->RD = 0;
-        if (p->pairmap && TS % best == 0 && best % 2 == 0 && p->RB * best == c.d_model && p->RB >= 8 * h->balance_rows &&
-            fits(p->RB + h->balance_rows))
-            p->RD = h->balance_rows;
-        p->RPS = p->RB + p->RD;
+        p->RPS = best_rows;
+        p->pairmap = TS % 2 == 0 && W % 2 == 0 ? 1 : 0;
     }
     // attention: split the cached sequence so that B*NS items balance over TS members
     {
@@ -191,21 +185,31 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
             }
         }
         p->NC3 = best_nc;
-        p->RS3 = best_rs;
+        p->LRS3 = 0;
+        while ((1 << p->LRS3) < best_rs) ++p->LRS3;
         p->CW3 = ceil_div(nch, best_nc) * cf::kOutChunk;
         p->NC3 = ceil_div(nch * cf::kOutChunk, p->CW3);
     }
     p->DSEL = TS / p->KS;
-    auto divisor = [](int d) {                  // what the kernel's qdiv takes
-        for (uint32_t k = 0; k < 31; ++k)
-            if ((1 << k) == d) return k;
-        return (uint32_t)((0x100000000ull + d - 1) / d);
-    };
+    auto divisor = [](int d) { return (uint32_t)((0x80000000ull + d - 1) / d); };      // what the kernel's qdiv takes
     p->div_nkv = divisor(c.n_kv_heads);
     p->div_ks = divisor(p->KS);
     p->div_dsel = divisor(p->DSEL);
     p->div_ns = divisor(p->NS);
     p->div_p8 = divisor(p->RPS >= 8 ? p->RPS / 8 : 1);
+    p->div_n3 = divisor(p->NC3 << p->LRS3);
+    // Output columns a workgroup owns: an even number, since a stack hands its hidden state on in pairs of values.  Single launches
+    // do the same: the bits of a stack are those of its layers one by one, and the sixteen bytes of two neighbouring partials are one
+    // piece of a line (us a layer, exact / even number: 768 columns, 8 heads of 128, batch 4 / 16 20.9 / 19.5 and 30.3 / 26.0, 1280 columns,
+    // 22.5 / 22.2 and 33.2 / 32.3, 2056 columns, 14 heads of 64, 19.9 / 19.6 and 25.1 / 24.4; 256 columns, one or two per workgroup: 4
+    // heads of 64 14.6 / 14.6 and 19.4 / 21.0, 16 heads of 128 21.1 / 21.6 and 31.1 / 29.8).
+    p->CPW = (ceil_div(c.d_model, W) + 1) & ~1;
+    const bool packed = (p->flags & cf::kFlagPacked) != 0;
+    p->wrow = packed ? (uint32_t)hd * 2 : (uint32_t)h->nqkv * 2;
+    p->wblk = packed ? (uint32_t)c.d_model * hd * 2 + cf::kQkvBlockPad : (uint32_t)hd * 2;
+    p->orow = packed ? (uint32_t)cf::kOutChunk * 2 : (uint32_t)c.d_model * 2;
+    p->ohead = (packed ? (uint32_t)h->nch : 1u) * hd * p->orow;
+    p->ochunk = packed ? (uint32_t)hd * p->orow : (uint32_t)cf::kOutChunk * 2;
     return CF_OK;
 }
 
@@ -267,7 +271,7 @@ bool one_launch(const cf_handle_s *h, int batch, int pos, bool norm, bool residu
     if ((norm || residual) && (batch > 1 || h->cfg.d_model > 8 * cf::kThreads)) return false;
     Params p;
     std::memset(&p, 0, sizeof p);
-    return make_plan(h, batch, pos, &p) == CF_OK && ((p.RB | p.RD) & 7) == 0 && p.W <= h->num_cu;
+    return make_plan(h, batch, pos, &p) == CF_OK && (p.RPS & 7) == 0 && p.W <= h->num_cu;
 }
 
 }  // namespace
@@ -422,7 +426,7 @@ static int decode_impl(cf_handle h, int packed, int32_t batch, const void *x, co
         auto sizes = [&] {
             b1 = align_up((size_t)p.KS * batch * h->nqkv * sizeof(uint64_t), 256);
             b2 = align_up((size_t)batch * h->cfg.n_q_heads * p.NS * (h->cfg.head_dim + cf::kP2Stride) * sizeof(uint64_t), 256);
-            b3 = align_up((size_t)h->cfg.n_q_heads * p.RS3 * batch * h->cfg.d_model * sizeof(uint64_t), 256);
+            b3 = align_up(((size_t)h->cfg.n_q_heads << p.LRS3) * batch * h->cfg.d_model * sizeof(uint64_t), 256);
             return b1 + b2 + b3 <= h->slot_area_bytes;
         };
         if (!sizes()) {
@@ -440,7 +444,7 @@ static int decode_impl(cf_handle h, int packed, int32_t batch, const void *x, co
     if (lds > kLdsLimit) return CF_EUNSUPPORTED;
     rc = check_residency(h, p, bt, lds);
     if (rc != CF_OK) return rc;
-    const int plan[10] = {p.W, p.TS, p.KS, p.RB, p.NS, p.TPS, p.NC3, p.CW3, p.RS3, (int)lds};
+    const int plan[10] = {p.W, p.TS, p.KS, p.RPS, p.NS, p.TPS, p.NC3, p.CW3, 1 << p.LRS3, (int)lds};
     std::memcpy(h->last_plan, plan, sizeof plan);
     h->last_batch = batch;
     hipError_t e;

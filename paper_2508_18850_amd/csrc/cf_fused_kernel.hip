@@ -64,19 +64,23 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));   // eight fp16 values 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// A read-only tensor that is streamed once: raw buffer resource + 128-bit non-temporal loads.
-// The address of a load is base + voff (per lane) + soff (wave-uniform), so no 64-bit
-// address registers are needed per load; a lane with nothing to load passes kNoLoad,
-// which is beyond the buffer's size: the hardware then skips the access and returns zeros.
-constexpr uint32_t kNoLoad = 0x80000000u;
+// Part of a read-only tensor that is streamed once: raw buffer resource + 128-bit non-temporal loads.  The buffer ends where
+// the part ends (a slice of rows, a split of the cached rows; 0 bytes: nothing to load), so that a load past it costs no
+// comparison: the hardware skips the access and returns zeros.  The whole offset is per lane, since the range check covers it
+// then.  (A comparison and a select per load, and a wave-uniform offset beside them, were five instructions a load.)
+constexpr uint32_t kNoLoad = 0x80000000u;      // beyond the end of any part: for a lane with nothing to load
+// Base and size are the same in all lanes; they are read from the first one, or the compiler, where it cannot see that, puts
+// a loop over the lanes' values around every load.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, uint32_t bytes)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(base);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((uint64_t)hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
 struct Stream {
     __amdgpu_buffer_rsrc_t r;
-    __device__ __forceinline__ Stream(const void *base, uint32_t bytes)
-        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000)) {}
-    __device__ __forceinline__ h8 ld(uint32_t voff, uint32_t soff) const
-    {
-        return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 2));
-    }
+    __device__ __forceinline__ Stream(const void *base, uint32_t bytes) : r(buffer_of(base, bytes)) {}
+    __device__ __forceinline__ h8 ld(uint32_t off) const { return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 2)); }
 };
 
 __device__ __forceinline__ void unpack8(const h8 &u, float (&f)[8])
@@ -201,7 +205,8 @@ __device__ __forceinline__ float wave_total(float v)
 
 // Exchange slots (partials handed from one workgroup to another).  A slot is a 64-bit
 // {fp32 bits, stamp} pair written by ONE 8-byte write-through store (agent scope), so a
-// reader sees either the old pair or the new one; the stamp of a launch is its number.
+// reader sees either the old pair or the new one; the stamp of a launch is its number.  Indices are 32 bits (the host checks that
+// an area is smaller than 4 GiB).
 //
 // Scope: agent (sc1, through to memory), also for slots that only travel inside a team.  Keeping
 // those in the L2 of the team's die (workgroup-scope loads and stores) was tried: the per-CU cache
@@ -210,19 +215,19 @@ struct Xbuf {
     __amdgpu_buffer_rsrc_t r;
     __device__ __forceinline__ explicit Xbuf(const void *base)
         : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0xfffffff8u, 0x00020000)) {}
-    __device__ __forceinline__ u32x2 ld(size_t idx) const
+    __device__ __forceinline__ u32x2 ld(uint32_t idx) const
     {
-        return __builtin_amdgcn_raw_buffer_load_b64(r, (unsigned)(idx * 8), 0, 16);
+        return __builtin_amdgcn_raw_buffer_load_b64(r, idx * 8, 0, 16);
     }
     // two neighbouring pairs (idx even): each half carries its own stamp, so nothing rests on the 16 bytes arriving together
-    __device__ __forceinline__ u32x4 ld2(size_t idx) const
+    __device__ __forceinline__ u32x4 ld2(uint32_t idx) const
     {
-        return __builtin_amdgcn_raw_buffer_load_b128(r, (unsigned)(idx * 8), 0, 16);
+        return __builtin_amdgcn_raw_buffer_load_b128(r, idx * 8, 0, 16);
     }
-    __device__ __forceinline__ void st(size_t idx, float v, uint32_t stamp) const
+    __device__ __forceinline__ void st(uint32_t idx, float v, uint32_t stamp) const
     {
         u32x2 d = {__builtin_bit_cast(uint32_t, v), stamp};
-        __builtin_amdgcn_raw_buffer_store_b64(d, r, (unsigned)(idx * 8), 0, 16);
+        __builtin_amdgcn_raw_buffer_store_b64(d, r, idx * 8, 0, 16);
     }
 };
 
@@ -246,40 +251,42 @@ struct Spin {
 // Loads go out eight at a time (indices past n repeat the last slot and are ignored) and are consumed
 // only after all eight have been issued: written as one loop, each load was waited for on its own.
 template <int C = 8>
-__device__ __forceinline__ float ll_sum(const Params &p, const Xbuf &x, size_t base, size_t stride, int n,
+__device__ __forceinline__ float ll_sum(const Params &p, const Xbuf &x, uint32_t base, uint32_t stride, int n,
                                         uint32_t stamp)
 {
     Spin spin;
     for (;;) {
         float s = 0.f;
-        bool ok = true;
+        uint32_t stale = 0;                   // bits in which a stamp differs from the current one
         if (n == 1) {
             const u32x2 v = x.ld(base);
-            ok = (v.y == stamp);
+            stale = v.y ^ stamp;
             s = __builtin_bit_cast(float, v.x);
         } else {
             for (int k0 = 0; k0 < n; k0 += C) {
                 u32x2 v[C];
 #pragma unroll
-                for (int k = 0; k < C; ++k) v[k] = x.ld(base + (size_t)min(k0 + k, n - 1) * stride);
+                for (int k = 0; k < C; ++k) v[k] = x.ld(base + (uint32_t)min(k0 + k, n - 1) * stride);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int k = 0; k < C; ++k)
-                    if (k0 + k < n) {
-                        ok &= (v[k].y == stamp);
-                        s += __builtin_bit_cast(float, v[k].x);
-                    }
+                for (int k = 0; k < C; ++k) {
+                    stale |= v[k].y ^ stamp;
+                    s += k0 + k < n ? __builtin_bit_cast(float, v[k].x) : 0.f;
+                }
             }
         }
-        if (ok || spin.expired(p)) return s;
+        if (stale == 0 || spin.expired(p)) return s;
     }
 }
 
-// Division by a plan constant d: m < 32 is log2 of a power of two, any other m is ceil(2^32 / d), whose high product
-// with n is n / d for n * d < 2^32.  Integer division by a run-time value costs some thirty instructions, and a
-// handful of them sat between the start of the kernel and its first weight load (0.3 us).
-__device__ __forceinline__ int qdiv(int n, uint32_t m) { return m < 32u ? (int)((uint32_t)n >> m) : (int)__umulhi((uint32_t)n, m); }
+// Division by a plan constant d, m = ceil(2^31 / d): the high half of 2 n m is n / d for n d < 2^31.  Integer division by a
+// run-time value costs some thirty instructions.
+__device__ __forceinline__ int qdiv(int n, uint32_t m) { return (int)__umulhi((uint32_t)n + (uint32_t)n, m); }
 __device__ __forceinline__ int qmod(int n, int d, uint32_t m) { return n - qdiv(n, m) * d; }
+// n / d for a divisor of this workgroup, r = 1 / d to within an ulp or two: n + 1/2 is 0.5 / d away from a multiple, so the
+// quotient is exact for n < 2^20.
+__device__ __forceinline__ float reciprocal(int d) { return __builtin_amdgcn_rcpf((float)d); }
+__device__ __forceinline__ int fdiv(int n, float r) { return (int)(((float)n + 0.5f) * r); }
 
 // First weight column of selector `sel` for a team: sel < G query heads, G = key, G+1 = value.
 // Tokens cached for batch row b == index of the row's new token (b is uniform over the workgroup).
@@ -290,13 +297,13 @@ __device__ __forceinline__ int row_pos(const Params &p, int b)
     return p.pos;
 }
 
-template <int HD, int G>
-__device__ __forceinline__ int qkv_col0(const Params &p, int team, int sel)
+template <int G>
+__device__ __forceinline__ int qkv_block(const Params &p, int team, int sel)        // in blocks of head_dim columns
 {
-    if (sel < G) return (team * G + sel) * HD;
-    if (sel == G) return (p.nq + team) * HD;
-    return (p.nq + p.nkv + team) * HD;
+    return sel < G ? team * G + sel : p.nq + team + (sel - G) * p.nkv;
 }
+template <int HD, int G>
+__device__ __forceinline__ int qkv_col0(const Params &p, int team, int sel) { return qkv_block<G>(p, team, sel) * HD; }
 
 // The RoPE tables in LDS: [rows][HD] floats, per row HD/2 cosines then HD/2 sines of that row's position.
 // One row (the common position) unless the rows of the batch have positions of their own.
@@ -386,10 +393,8 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     const int lrow = 32 * (RS * wv + rs) + 8 * kg;          // MF: first row of the lane inside a batch of 256 RS rows
     const int ks = qmod(member, p.KS, p.div_ks);
     const int sel0 = qdiv(member, p.div_ks), dsel = p.DSEL;
-    // slices with an even index (workgroups on the faster dies, see the workgroup mapping in the
-    // kernel) are 2*RD rows longer than those with an odd index
-    const int r0 = ks * p.RB + ((ks & 1) ? p.RD : 0);
-    const int nrows = min(p.RB + ((ks & 1) ? -p.RD : p.RD), p.D - r0);   // > 0: the host never plans an empty slice
+    const int r0 = ks * p.RPS;
+    const int nrows = min(p.RPS, p.D - r0);                 // > 0: the host never plans an empty slice
     const int iters = (nrows + NG - 1) / NG;
     const int nb = (iters + U - 1) / U;                     // load batches per selector
     // selectors sel0, sel0 + dsel, ... of the team's G + 2 (the members past KS * DSEL have none)
@@ -403,50 +408,43 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     _Float16 *xh = reinterpret_cast<_Float16 *>(smem), *xl = xh + 16 * XS;
     float *red = smem + (MF ? (kLayer || HD == 128 ? 16 : 8) * XS : BT * p.RPS);   // [MAXI][NW][BT][HD]
     const Xbuf x1(p.p1);
-    const uint32_t blkb = (uint32_t)p.D * HD * 2 + kQkvBlockPad;          // packed: bytes from one block to the next
-    const Stream W(lp.wqkv, (p.flags & kFlagPacked) ? (uint32_t)(p.nqkv / HD) * blkb : (uint32_t)((size_t)p.D * p.nqkv * 2));
-    // row-major [D][Nqkv]: rows are Nqkv*2 bytes apart and a selector starts at column col0;
-    // packed [Nqkv/HD][D][HD] (+ pad): rows are HD*2 bytes apart and a selector is one contiguous block
-    const uint32_t rowb = (p.flags & kFlagPacked) ? (uint32_t)HD * 2 : (uint32_t)p.nqkv * 2;
+    // A selector is a block of head_dim columns, its rows p.wrow bytes apart (row-major: of a whole row; packed: of one
+    // contiguous block).  The buffer of a selector begins at the slice's first row and ends behind the block's part of its last.
+    const uint32_t rowb = p.wrow, lim = (uint32_t)(nrows - 1) * rowb + HD * 2;
     const uint32_t voff0 = (uint32_t)(MF ? lrow : grp) * rowb + lig * 16;
 
     // A step is (selector, batch of U row groups).  Steps are loaded and consumed strictly in order,
-    // so each side keeps a cursor that is advanced incrementally: no divisions, and the address
-    // of a load is one per-lane offset plus a wave-uniform offset that grows by a constant.
+    // so each side keeps a cursor that is advanced incrementally: no divisions.
     const uint32_t step_b = (uint32_t)NG * rowb;            // bytes between consecutive row groups
     struct Cursor {
         int si, i0;          // selector index, first row group of the batch
-        uint32_t sbase;      // uniform byte offset of that row group's first row
-    };
-    auto blk_base = [&](int si) {
-        const uint32_t col0 = (uint32_t)qkv_col0<HD, G>(p, team, sel_of(si));
-        return (uint32_t)r0 * rowb + ((p.flags & kFlagPacked) ? (col0 / HD) * blkb : col0 * 2);
+        uint32_t sbase;      // offset of that row group's first row
     };
     auto advance = [&](Cursor &c) {
-        c.i0 += U;
-        c.sbase += (uint32_t)U * step_b;
-        if (c.i0 >= iters) {
-            c.i0 = 0;
-            ++c.si;
-            c.sbase = blk_base(c.si);
-        }
+        const bool next = c.i0 + U >= iters;
+        c.sbase = next ? 0u : c.sbase + (uint32_t)U * step_b;
+        c.i0 = next ? 0 : c.i0 + U;
+        c.si += next;
     };
-    Cursor cc = {0, 0, nsteps > 0 ? blk_base(0) : 0u};      // next step to consume
+    Cursor cc = {0, 0, 0u};                                 // next step to consume
     Cursor lc = cc;                                         // next step to load
     constexpr int AHEAD = STACK ? P1Ahead<HD, G, BT>::n : 0;
     if (PART == 2 || (PART == 0 && primed && AHEAD > 0)) lc = Cursor{rg.si, rg.i0, rg.sbase};
     // Every call issues exactly U load instructions on one straight-line path, also for a step past
-    // the end (all lanes switched off through their offset).  The compiler derives each wait from
+    // the end (an empty buffer).  The compiler derives each wait from
     // the number of loads issued after the one it needs, taking the smallest over all paths of the
     // control flow, so a branch around loads would make every later wait drain the queue.
-    const int lim = nrows - (MF ? lrow : grp);              // row group i is inside the slice iff NG*i < lim (MF: row NG*i0 + u iff < lim)
     auto load = [&](h8(&w)[U], uint32_t voff) {
-        const bool live = lc.si < nsel;
-        const int g0 = live ? NG * lc.i0 : 0x40000000;      // uniform
+        const char *base = reinterpret_cast<const char *>(lp.wqkv) + (size_t)r0 * rowb +
+                           (size_t)(uint32_t)qkv_block<G>(p, team, sel_of(lc.si)) * p.wblk;
+        const Stream W(base, lc.si < nsel ? lim : 0u);
+        uint32_t off = voff + lc.sbase;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            w[u] = W.ld((g0 + (MF ? u : NG * u)) < lim ? voff : kNoLoad, lc.sbase + (uint32_t)u * (MF ? rowb : step_b));
-        if (live) advance(lc);
+        for (int u = 0; u < U; ++u) {
+            w[u] = W.ld(off);
+            off += MF ? rowb : step_b;
+        }
+        advance(lc);
     };
 
     CF_STAMP(20);           // phase 1 set up
@@ -456,7 +454,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     h8(&wa)[U] = rg.wa;
     h8(&wb)[U] = rg.wb;
     if (PART != 0) {
-        // (`primed` here means "there is a next layer"; without one the loads go out with every lane off: the
+        // (`primed` here means "there is a next layer"; without one the loads go out past the end of their buffer: the
         // registers are written either way, so that what they held does not stay alive through the caller's loop)
         load(PART == 1 ? wa : wb, primed ? voff0 : kNoLoad);
         rg.si = lc.si;
@@ -481,7 +479,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     // x * gamma is scaled by the largest value of the row's slice (stage_piece below), and the maximum is then one between lanes.
     constexpr bool BYROW = MF && kLayer && !STACK;
     const int lpr = p.B > 8 ? 32 : 64, brow = p.B > 8 ? tid >> 5 : wv, lane0 = tid & (lpr - 1);
-    const bool xvec = STACK || ((p.RB | p.RD) & 7) == 0;          // (the host launches no stack otherwise)
+    const bool xvec = STACK || (p.RPS & 7) == 0;          // (the host launches no stack otherwise)
     const int P8 = p.RPS >> 3, npc = xvec ? p.B * P8 : 0;         // pieces of a row's slice, of all rows
     const uint4 *xg4 = reinterpret_cast<const uint4 *>(p.x), *gg4 = reinterpret_cast<const uint4 *>(lp.gamma ? lp.gamma : p.x);
     uint4 xp[XV ? XP : 1], gp[XV ? XP : 1];
@@ -561,20 +559,24 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     float *nrm = red + MAXI * NW * BT * HD;                       // [NW][BT] sums of squares, one per wavefront and row
     constexpr int RG = BT < 4 ? BT : (MF ? 8 : 4);                // rows whose loads are in flight together
     const int d8 = p.D >> 3;                                      // 16-byte pieces of a row
-    const uint4 *x4 = reinterpret_cast<const uint4 *>(p.x);
-    constexpr int KR = ROW ? 1 : 2;                               // pieces of a row per thread: needs D <= KR * 8 * NT
+    // Pieces of a row per thread and round: a row has up to 16 NT values; on the 16-row tile the second half of longer rows takes a
+    // round of its own.  The loads are in no branch (a buffer that ends with the batch: rows past it and lanes past the row give zeros):
+    // behind branches their registers were copied where the paths met, which waited for the first weight batch (Llama-3-8B
+    // shape, 4 rows: x staged 1.5 us later).
+    constexpr int KR = MF || ROW ? 1 : 2;
+    const __amdgpu_buffer_rsrc_t xrows = buffer_of(p.x, norm || ROW ? (uint32_t)(p.B * p.D) * 2 : 0u);
     uint4 xq[RG][KR];                                             // rows b0 .. b0 + RG - 1
-    auto load_rows = [&](int b0) {
+    auto load_rows = [&](int b0, int k0) {
 #pragma unroll
         for (int r = 0; r < RG; ++r)
 #pragma unroll
             for (int k = 0; k < KR; ++k) {
-                const int c = tid + k * NT;
-                if (b0 + r < p.B && (k == 0 || d8 > NT))          // (uniform)
-                    xq[r][k] = x4[c < d8 ? (size_t)(b0 + r) * d8 + c : 0];
+                const int c = tid + (k0 + k) * NT;
+                xq[r][k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                         xrows, (c < d8 ? (uint32_t)c * 16 : kNoLoad) + (uint32_t)(b0 + r) * p.D * 2, 0, 0));
             }
     };
-    auto square_rows = [&](int b0) {
+    auto square_rows = [&](int b0, int k0) {
 #pragma unroll
         for (int r = 0; r < RG; ++r) {
             if (b0 + r >= p.B) break;                             // (uniform)
@@ -586,19 +588,15 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
                 float t = 0.f;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) t = fmaf(f[j], f[j], t);
-                ss += tid + k * NT < d8 ? t : 0.f;
+                ss += tid + (k0 + k) * NT < d8 ? t : 0.f;
             }
             ss = wave_sum(ss);
-            if ((tid & 63) == 0) nrm[wv * BT + b0 + r] = ss;
+            if ((tid & 63) == 0) nrm[wv * BT + b0 + r] = k0 > 0 ? nrm[wv * BT + b0 + r] + ss : ss;
         }
     };
-#pragma unroll
-    for (int r = 0; r < RG; ++r)
-#pragma unroll
-        for (int k = 0; k < KR; ++k) xq[r][k] = uint4{0u, 0u, 0u, 0u};
     // (in front of the second weight batch: behind it the squares would wait for that batch; 16-row tile, 4 rows of
     // 4096: x staged at 10.3 us with the loads behind the batch)
-    if (norm && !ROW) load_rows(0);
+    if (kLayer && !ROW) load_rows(0, 0);
     // the row that is the input of a stack with norm or residual, and the weights gamma that belong to it
     u32x4 rsl[2];
     uint4 grow;
@@ -612,7 +610,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         if (from_slots)
             row_slots();
         else
-            load_rows(0);
+            load_rows(0, 0);
     }
     // for the RoPE tables, below: the frequency and the position of every table entry of this thread
     constexpr int NE = RopeRows<HD, BT>::NE;
@@ -696,7 +694,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             xq[0][0] = uint4{rsl[0].x, rsl[0].z, rsl[1].x, rsl[1].z};
         }
         if ((unsigned)c < (unsigned)np) stage_piece(0, c, xq[0][0], grow, true);
-        if (norm) square_rows(0);
+        if (norm) square_rows(0, 0);
         const uint4 none = {0u, 0u, 0u, 0u};
         for (int i = np + tid; i < P8; i += NT) stage_piece(0, i, none, none, false);     // the last slice may be shorter
     } else if constexpr (BYROW) {
@@ -826,11 +824,12 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         }
     }
     if (norm && !ROW) {
-        square_rows(0);
-        for (int b0 = RG; b0 < p.B; b0 += RG) {       // large batches: the other rows
-            load_rows(b0);
-            square_rows(b0);
-        }
+        square_rows(0, 0);
+        for (int k0 = 0; k0 * NT < d8; k0 += KR)      // large batches: the other rows; long rows: their second half
+            for (int b0 = k0 > 0 ? 0 : RG; b0 < p.B; b0 += RG) {
+                load_rows(b0, k0);
+                square_rows(b0, k0);
+            }
     }
     // cos / sin of this position while the first weights are still on their way (the same for every layer of a stack)
 #pragma unroll
@@ -881,7 +880,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
                     for (int w8 = 0; w8 < NW; ++w8) ss += nrm[w8 * BT + b];
                     sum *= 1.0f / sqrtf(ss / (float)p.D + p.eps);
                 }
-                x1.st(((size_t)ks * p.B + b) * p.nqkv + qkv_col0<HD, G>(p, team, sel_of(si_first + it)) + c, sum,
+                x1.st((uint32_t)(ks * p.B + b) * p.nqkv + qkv_col0<HD, G>(p, team, sel_of(si_first + it)) + c, sum,
                       stamp);
             }
         }
@@ -892,7 +891,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         const int i0 = cc.i0;
         if constexpr (MF) {
             // one step of 32 rows: operand A = x[batch row lane % 16][rows of this lane's group], operands B =
-            // the eight columns of this lane.  Rows past the slice: their weights are zero (loads switched off)
+            // the eight columns of this lane.  Rows past the slice: their weights are zero (past the end of the buffer)
             // and x, where an operand reaches them, is zero; a group that starts past the slice reads nothing.
             const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
             h8 f[8];
@@ -913,7 +912,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         } else {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                // a row past the slice has zero weights (its load was switched off) and any finite x
+                // a row past the slice has zero weights (past the end of the buffer) and any finite x
                 const int r = min(grp + NG * (i0 + u), p.RPS - 1);
                 float f[8];
                 unpack8(w[u], f);
@@ -1010,8 +1009,10 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
     issue_next(0);
     consume(wa);
     finish();
-    consume(wb);
-    finish();
+    if (nsteps > 1) {       // (a padding step: small shapes have one step in all)
+        consume(wb);
+        finish();
+    }
     if (nbuf) flush();
     return stamp;
 }
@@ -1025,8 +1026,10 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 // (at the end of phase 1, before the second part of the K/V prefetch) and checked when q is needed:
 // where the other members were no later than this one, the sum costs no further round trip.  Covers
 // value e = threadIdx.x and the first kEarly k-slices; anything else takes the polling path.
-constexpr int kEarly = 16;
+// (eight in the one-launch stack, whose registers hold the next layer's weights too)
+template <int kEarly>
 struct EarlyQ {
+    static_assert(kEarly == 8 || kEarly == 16, "loads in groups of eight");
     u32x2 v[kEarly];
     bool issued = false;
     template <int HD, int G>
@@ -1036,13 +1039,14 @@ struct EarlyQ {
         const int e = tid0;
         if (e < nsel * HD) {
             const int sel = e / HD, c = e - sel * HD;
-            const size_t src = (size_t)b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c;
+            const uint32_t src = (uint32_t)(b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c);
             // eight loads at a time on a straight-line path (slices past KS repeat the last one)
+            const uint32_t stride = (uint32_t)(p.B * p.nqkv);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = x1.ld(src + (size_t)min(k, p.KS - 1) * p.B * p.nqkv);
-            if (p.KS > 8) {
+            for (int k = 0; k < 8; ++k) v[k] = x1.ld(src + (uint32_t)min(k, p.KS - 1) * stride);
+            if (kEarly > 8 && p.KS > 8) {
 #pragma unroll
-                for (int k = 8; k < kEarly; ++k) v[k] = x1.ld(src + (size_t)min(k, p.KS - 1) * p.B * p.nqkv);
+                for (int k = 8; k < kEarly; ++k) v[k] = x1.ld(src + (uint32_t)min(k, p.KS - 1) * stride);
             }
         }
         issued = true;
@@ -1050,16 +1054,25 @@ struct EarlyQ {
     // sum in slice order; false if a slot was not yet stamped or not covered
     __device__ __forceinline__ bool sum(const Params &p, uint32_t stamp, float &out) const
     {
-        bool ok = issued && p.KS <= kEarly;
+        // (opaque: the sixteen comparisons with it would otherwise be made in front of the loop over the items and be kept)
+        int n = p.KS;
+        asm volatile("" : "+s"(n));
+        uint32_t stale = issued && n <= kEarly ? 0u : 1u;
         float s = 0.f;
 #pragma unroll
-        for (int k = 0; k < kEarly; ++k)
-            if (k < p.KS) {
-                ok &= (v[k].y == stamp);
-                s += __builtin_bit_cast(float, v[k].x);
+        for (int k = 0; k < 8; ++k) {
+            stale |= v[k].y ^ stamp;
+            s += k < n ? __builtin_bit_cast(float, v[k].x) : 0.f;
+        }
+        if (kEarly > 8 && n > 8) {
+#pragma unroll
+            for (int k = 8; k < kEarly; ++k) {
+                stale |= v[k].y ^ stamp;
+                s += k < n ? __builtin_bit_cast(float, v[k].x) : 0.f;
             }
+        }
         out = s;
-        return ok;
+        return stale == 0;
     }
 };
 
@@ -1115,63 +1128,50 @@ struct P2Stream {
     static constexpr int U = P2Cfg<G>::U;
     static constexpr bool MA = AttnMfma<HD, G>::on;
     int t0, t1, iters, grp, pos, tid;
-    uint32_t voff0;
+    uint32_t voff0;          // of the lane's first row of the split
     size_t head;
     Stream K, V;
-    // `pos_b`: tokens cached for this batch row.  Rows >= pos_b are outside the buffers: they can never be
-    // read.  An inactive stream (a workgroup without an attention item) has an empty row range: its
-    // loads are issued with every lane off.  A row shorter than the longest one of the batch uses the
-    // same split boundaries: its splits past pos_b are empty.
+    // `pos_b`: tokens cached for this batch row.  The buffers end with the split: rows behind it, and so rows >= pos_b, are
+    // never read.  An inactive stream (a workgroup without an attention item) has an empty split.  A row shorter than the longest
+    // one of the batch uses the same split boundaries: its splits past pos_b are empty.
     __device__ __forceinline__ P2Stream(const Params &p, const LayerPtrs &lp, int tid0, int team, int b, int s, int pos_b,
                                         bool active = true)
-        : pos(pos_b), tid(tid0), head(((size_t)b * p.nkv + team) * p.max_seq * HD), K(lp.kc + head, (uint32_t)pos_b * HD * 2),
-          V(lp.vc + head, (uint32_t)pos_b * HD * 2)
+        : t0(s * p.TPS + ((s & 1) ? p.TD : 0)),                      // even splits are 2*TD tokens longer
+          t1(active ? min(t0 + p.TPS + ((s & 1) ? -p.TD : p.TD), pos_b) : 0), grp(tid0 / LPR), pos(pos_b), tid(tid0),
+          head(((size_t)b * p.nkv + team) * p.max_seq * HD), K(lp.kc + head, (uint32_t)t1 * HD * 2), V(lp.vc + head, (uint32_t)t1 * HD * 2)
     {
-        const int lig = tid0 % LPR;
-        grp = tid0 / LPR;
-        t0 = active ? s * p.TPS + ((s & 1) ? p.TD : 0) : 0;         // even splits are 2*TD tokens longer
-        t1 = active ? min(t0 + p.TPS + ((s & 1) ? -p.TD : p.TD), pos_b) : 0;
-        iters = t1 > t0 ? (t1 - t0 + NG - 1) / NG : 0;
-        voff0 = (uint32_t)(grp * HD + lig * 8) * 2;
-        if (MA) iters = t1 > t0 ? (t1 - t0 + 32 * NW - 1) / (32 * NW) : 0;   // rounds of one 32-token tile per wavefront
+        const int n = max(t1 - t0, 0);
+        iters = MA ? (n + 32 * NW - 1) / (32 * NW) : (n + NG - 1) / NG;   // MA: rounds of one 32-token tile per wavefront
+        voff0 = (uint32_t)(t0 + grp) * HD * 2 + tid % LPR * 16;
     }
     // MFMA tiles: round `it` gives wavefront wv the tokens t0 + 32 (8 it + wv) + 0..31.  K: load u brings rows
     // 4 u + (lane / 16); V: load u brings rows 16 (u / 4) + 4 (lane / 16) + u % 4 (the order in which the scores
-    // come out of the first product).  Eight load instructions each, lanes past the split switched off.
+    // come out of the first product).  Eight load instructions each.
     __device__ __forceinline__ void load_k(h8 (&kr)[8], int it, uint32_t dep) const
     {
         const int wv = tid >> 6, rg = (tid & 63) >> 4, lig = tid & 15;
-        const uint32_t voff = (uint32_t)((32 * wv + rg) * HD + lig * 8) * 2 + dep;
-        const int tb = t0 + 32 * NW * it;                       // uniform
-        const int lim = t1 - 32 * wv - rg;
+        const uint32_t off = (uint32_t)(t0 + 32 * (NW * it + wv) + rg) * HD * 2 + lig * 16 + dep;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) kr[u] = K.ld(tb + 4 * u < lim ? voff : kNoLoad, (uint32_t)(tb + 4 * u) * HD * 2);
+        for (int u = 0; u < 8; ++u) kr[u] = K.ld(off + 4 * u * HD * 2);
     }
     __device__ __forceinline__ void load_v(h8 (&vr)[8], int it, uint32_t dep) const
     {
         const int wv = tid >> 6, rg = (tid & 63) >> 4, lig = tid & 15;
-        const uint32_t voff = (uint32_t)((32 * wv + 4 * rg) * HD + lig * 8) * 2 + dep;
-        const int tb = t0 + 32 * NW * it;
-        const int lim = t1 - 32 * wv - 4 * rg;
+        const uint32_t off = (uint32_t)(t0 + 32 * (NW * it + wv) + 4 * rg) * HD * 2 + lig * 16 + dep;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int r = 16 * (u >> 2) + (u & 3);
-            vr[u] = V.ld(tb + r < lim ? voff : kNoLoad, (uint32_t)(tb + r) * HD * 2);
-        }
+        for (int u = 0; u < 8; ++u) vr[u] = V.ld(off + (16 * (u >> 2) + (u & 3)) * HD * 2);
     }
-    // Always 2*U load instructions on a straight-line path (rows past the split: lane switched off),
+    // Always 2*U load instructions on a straight-line path,
     // so that the compiler's wait counts for earlier loads stay exact.
-    __device__ __forceinline__ void load(h8 (&kr)[U], h8 (&vr)[U], int i0, uint32_t voff_on) const
+    __device__ __forceinline__ void load(h8 (&kr)[U], h8 (&vr)[U], int i0, uint32_t voff) const
     {
-        const int lim = t1 - t0 - grp;                         // row NG*i + grp is inside the split iff NG*i < lim
+        const uint32_t off = voff + (uint32_t)(NG * i0) * HD * 2;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + u;
-            const uint32_t soff = (uint32_t)(t0 + NG * i) * HD * 2;   // first row of this step (uniform)
-            const uint32_t voff = NG * i < lim ? voff_on : kNoLoad;
-            kr[u] = K.ld(voff, soff);
-            vr[u] = V.ld(voff, soff);
-        }
+        for (int u = 0; u < U; ++u) kr[u] = K.ld(off + (uint32_t)(NG * u) * HD * 2);
+#pragma unroll
+        for (int u = 0; u < U; ++u) vr[u] = V.ld(off + (uint32_t)(NG * u) * HD * 2);
+        // (the order of the batches is kept: where a later one is requested first, the loop waits for all of them)
+        __builtin_amdgcn_sched_barrier(0);
     }
     // the first NB batches do not depend on q: they are put in flight before q is needed; part 0
     // (two batches) before the last steps of phase 1, part 1 (the rest) once phase 1 has stored
@@ -1192,9 +1192,9 @@ struct P2Stream {
     }
 };
 
-template <int HD, int G, int BT, class TailFn>
+template <int HD, int G, int BT, class Early, class TailFn>
 __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, int tid0, int team, int b, int s, uint32_t stamp, bool first,
-                                        const P2Stream<HD, G> &st, KvBuf<HD, G> &buf, const EarlyQ &eq, float *smem,
+                                        const P2Stream<HD, G> &st, KvBuf<HD, G> &buf, const Early &eq, float *smem,
                                         const float *rope, TailFn &&issue_next)
 {
     constexpr int LPR = HD / 8;
@@ -1208,7 +1208,7 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
     if (AttnMfma<HD, G>::on) asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wv = tid >> 6, lig = tid % LPR, grp = tid / LPR;
     const bool last = (s == p.NS - 1);
-    const Xbuf x1(p.p1), x2(p.p2);
+    const Xbuf x1(p.p1);
 
     const float *cs = rope;                 // [HD/2] cos, filled at kernel start
     const float *sn = rope + HD / 2;        // [HD/2] sin
@@ -1229,10 +1229,10 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
     const int nsel = NewTokenFirst<HD, G, BT>::selectors(last);
     for (int e = tid; e < nsel * HD; e += NT) {
         const int sel = e / HD, c = e - sel * HD;
-        const size_t src = (size_t)b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c;
+        const uint32_t src = (uint32_t)(b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c);
         float v;
         if (!(first && e == tid && eq.sum(p, stamp, v)))
-            v = ll_sum(p, x1, src, (size_t)p.B * p.nqkv, p.KS, stamp);
+            v = ll_sum(p, x1, src, (uint32_t)(p.B * p.nqkv), p.KS, stamp);
         qs[e] = v;
     }
     lds_barrier();
@@ -1433,10 +1433,10 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
             }
         }
     };
-    // NB batches are in flight at the top of every iteration.  Consume and reload are unconditional
-    // (a batch past the split is all zeros with every row masked, its reload has every lane off), and
-    // the reload offset is made to depend on the state the batch was folded into: the reload then
-    // follows the last use of the registers it overwrites, so no copy and no drain is needed.
+    // NB batches are in flight at the top of every iteration.  The reload offset is made to depend on the state the batch was
+    // folded into: the reload then follows the last use of the registers it overwrites, so no copy and no drain is needed.  The
+    // last NB batches are folded behind the loop: a reload with nothing to load would still have to return, behind everything
+    // requested before it, before its registers can be used again, and a short split has one batch in all.
     auto after_consume = [&]() {
         uint32_t v = st.voff0;
 #pragma unroll
@@ -1445,13 +1445,18 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
                          "v"(acc[g][4]), "v"(acc[g][5]), "v"(acc[g][6]), "v"(acc[g][7]), "v"(l[g]), "v"(m[g]));
         return v;
     };
-    for (int i0 = 0; i0 < iters; i0 += NB * U) {
+    static_assert(NB == 2, "two batches behind the loop");
+    int i0 = 0;
+    for (; i0 + NB * U < iters; i0 += NB * U) {
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             consume(buf.k[j], buf.v[j], i0 + j * U);
+            __builtin_amdgcn_sched_barrier(0);
             st.load(buf.k[j], buf.v[j], i0 + (j + NB) * U, after_consume());
         }
     }
+    if (i0 < iters) consume(buf.k[0], buf.v[0], i0);
+    if (i0 + U < iters) consume(buf.k[1], buf.v[1], i0 + U);
     CF_STAMP(15);           // K/V consumed
     // Nothing of this phase is left to load.  Half of the next phase's first tile goes out now and
     // streams while the partial is merged and stored; the other half follows the stored partial.
@@ -1484,8 +1489,8 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
         if constexpr (!KVF) {
             for (int e = tid; e < 2 * HD; e += NT) {
                 const int sel = G + e / HD, c = e % HD;
-                const size_t src = (size_t)b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c;
-                kn[e] = ll_sum(p, x1, src, (size_t)p.B * p.nqkv, p.KS, stamp);      // kn and vn are contiguous
+                const uint32_t src = (uint32_t)(b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c);
+                kn[e] = ll_sum(p, x1, src, (uint32_t)(p.B * p.nqkv), p.KS, stamp);      // kn and vn are contiguous
             }
             issue_next(1);
             lds_barrier();
@@ -1515,6 +1520,7 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
     lds_barrier();
     CF_STAMP(9);            // new token handled, wavefronts in step
     // ---- the wavefronts and the new token -> one partial (m, l, acc) per query head
+    const Xbuf x2(p.p2);
     for (int e = tid; e < G * HD; e += NT) {
         const int g = e / HD, c = e - g * HD;
         float M = last ? snew[g] : kNegBig;
@@ -1532,7 +1538,7 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
             L += f;
             A = fmaf(vn[c], f, A);
         }
-        const size_t dst = (((size_t)b * p.nq + team * G + g) * p.NS + s) * PS;
+        const uint32_t dst = (uint32_t)(((b * p.nq + team * G + g) * p.NS + s) * PS);
         if (c == 0) {
             x2.st(dst, M, stamp);
             x2.st(dst + 1, L, stamp);
@@ -1556,61 +1562,52 @@ struct OutTile {
     h8 w[MAXR];
 };
 
-// part: 0 = first half of the tile's loads, 1 = second half, 2 = all
-// MF (MFMA tiles): wavefront wv takes columns [128 (wv % 4), +128) of the chunk and one half of the head's HD rows (wv / 4);
-// lane (l % 16, l / 16) loads eight adjacent columns of rows 32 s + 8 (l / 16) + 0..7 for the steps s (one or two)
-// (the same lane layout as in the projection: eight rows are transposed in the lane into MFMA operands).
+// Chunk `ch` of an item of the output projection: its rows of W_o as a buffer, and the lane's place in it.  Vector tiles:
+// wavefront wv takes 64 columns of the chunk, its eight row groups of eight lanes the rows r + 8 u.  MF (MFMA tiles): wavefront wv
+// takes columns [128 (wv % 4), +128) of the chunk and one half of the head's HD rows (wv / 4); lane (l % 16, l / 16) loads eight
+// adjacent columns of rows 32 s + 8 (l / 16) + 0..7 for the steps s (one or two; the same lane layout as in the projection: eight
+// rows are transposed in the lane into MFMA operands).  Lanes past the last column load nothing.
 template <int HD, bool MF>
-__device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, int tid0, int hq, int c3, int rs, int ch, OutTile<HD> &t, int part = 2,
+struct OutRows {
+    Stream W;
+    uint32_t off, rowb;
+    __device__ __forceinline__ OutRows(const Params &p, const LayerPtrs &lp, int tid, int hq, int c3, int rs, int ch, bool live)
+        : W(reinterpret_cast<const char *>(lp.wo) + (size_t)(uint32_t)hq * p.ohead +
+                (size_t)(uint32_t)((HD >> p.LRS3) * rs * p.orow + ((c3 * p.CW3 + ch * kOutChunk) / kOutChunk) * p.ochunk),
+            live ? (uint32_t)((HD >> p.LRS3) - 1) * p.orow + min(kOutChunk, p.D - c3 * p.CW3 - ch * kOutChunk) * 2u : 0u),
+          rowb(p.orow)
+    {
+        const int lane = tid & 63, wv = tid >> 6;
+        const int row = MF ? HD / 2 * (wv >> 2) + 8 * (lane >> 4) : lane >> 3, col = MF ? 128 * (wv & 3) + 8 * (lane & 15) : 64 * wv + 8 * (lane & 7);
+        off = c3 * p.CW3 + ch * kOutChunk + col < p.D ? (uint32_t)row * rowb + col * 2 : kNoLoad;
+        // (opaque to the compiler: it otherwise computes the sixteen per-row offsets of all call sites once, far
+        // ahead of the first one, and spills them)
+        asm volatile("" : "+v"(off));
+    }
+    __device__ __forceinline__ h8 row(int u, uint32_t at) const { return W.ld(at + (uint32_t)(MF ? 32 * (u >> 3) + (u & 7) : 8 * u) * rowb); }
+};
+
+// part: 0 = first half of the tile's loads, 1 = second half, 2 = all
+template <int HD, bool MF>
+__device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, int tid, int hq, int c3, int rs, int ch, OutTile<HD> &t, int part = 2,
                                         bool live = true)
 {
-    const int lane = tid0 & 63, wv = tid0 >> 6;
-    // row-major [nq*HD][D], or packed [nq][ceil(D/512)][HD][512] (one contiguous tile per head and chunk)
-    const int NCH = (p.D + kOutChunk - 1) / kOutChunk;        // 512-column chunks of the output
-    const Stream Wo(lp.wo, (p.flags & kFlagPacked) ? (uint32_t)((size_t)p.nq * NCH * HD * kOutChunk * 2)
-                                   : (uint32_t)((size_t)p.nq * HD * p.D * 2));
-    const int nrows = HD / p.RS3;
-    const int cbase = c3 * p.CW3 + ch * kOutChunk;
-    const uint32_t rowb = (p.flags & kFlagPacked) ? (uint32_t)kOutChunk * 2 : (uint32_t)p.D * 2;
-    // vector tiles: wavefront wv takes 64 columns of the chunk, its eight row groups of eight lanes the rows r + 8 u
-    const int col = 64 * wv + 8 * (lane & 7);
-    uint32_t voff = live && (cbase + col) < p.D ? (uint32_t)(lane >> 3) * rowb + col * 2 : kNoLoad;
-    // (opaque to the compiler: it otherwise computes the sixteen per-row offsets of all call sites once, far
-    // ahead of the first one, and spills them)
-    asm volatile("" : "+v"(voff));
-    const uint32_t sbase = (p.flags & kFlagPacked) ? (uint32_t)((hq * NCH + cbase / kOutChunk) * HD + rs * nrows) * rowb
-                                    : (uint32_t)(hq * HD + rs * nrows) * rowb + (uint32_t)cbase * 2;
-    const int iters = nrows / 8;
-    if constexpr (MF) {
-        constexpr int MAXR = OutTile<HD>::MAXR;                         // eight rows per lane and step
-        const int lig = lane & 15, kg = lane >> 4, cb = wv & 3, kh = wv >> 2;
-        uint32_t voffm = live && (cbase + 128 * cb + 8 * lig) < p.D ? (uint32_t)(8 * kg) * rowb + (uint32_t)(128 * cb + 8 * lig) * 2
-                                                            : kNoLoad;
-        asm volatile("" : "+v"(voffm));
-#pragma unroll
-        for (int u = 0; u < MAXR; ++u) {
-            const bool mine = part == 2 || (part == 0) == (u < MAXR / 2);
-            const int row = HD / 2 * kh + 32 * (u >> 3) + (u & 7);      // + 8 kg: the lane's row inside the item
-            if (mine) t.w[u] = Wo.ld(row + 8 * kg < nrows ? voffm : kNoLoad, sbase + (uint32_t)row * rowb);
-        }
-        return;
-    }
+    const OutRows<HD, MF> o(p, lp, tid, hq, c3, rs, ch, live);
 #pragma unroll
     for (int u = 0; u < OutTile<HD>::MAXR; ++u) {
-        const bool mine = part == 2 || (part == 0) == (u < OutTile<HD>::MAXR / 2);
-        if (mine) t.w[u] = Wo.ld(u < iters ? voff : kNoLoad, sbase + (uint32_t)(8 * u) * rowb);
+        if (part == 2 || (part == 0) == (u < OutTile<HD>::MAXR / 2)) t.w[u] = o.row(u, o.off);
     }
 }
 
 template <int HD, int BT, int MCW>
 __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, int tid0, int hq, int c3, int rs, uint32_t stamp, OutTile<HD> &tile,
-                                        bool prefetched, float *smem)
+                                        float *smem)
 {
     constexpr int PS = HD + kP2Stride;
-    // (the 16-row tile has no register to spare: the thread index is made opaque here, so that what this phase
-    // derives from it is computed here and not kept from the start of the kernel)
+    // (the thread index is made opaque here, so that what this phase derives from it is computed here and not kept from the start
+    // of the kernel or, in front of the loop over the items, for all of them)
     int tid = tid0;
-    if (Mfma<HD, BT>::on) asm volatile("" : "+v"(tid));
+    asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wv = tid >> 6;
     // merged, normalised attention output of head hq, [BT][HD].  MFMA tiles: as operands, PARTS fp16 parts [16][AR] of every
     // value, and what undoes their scale, [16][2] (64 columns each).  (Unpadded rows would be read from the same LDS
@@ -1623,13 +1620,11 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
     float *red = smem + (MF ? out_operand_floats(HD) : BT * HD);          // the sums of the merge; MFMA tiles: [2][16][512]
     const Xbuf x2(p.p2), x3(p.p3);
 
-    const int nrows = HD / p.RS3;
+    const int nrows = HD >> p.LRS3;
     const int rbeg = rs * nrows;
     const int iters = nrows / 8;
-    const int slot = hq * p.RS3 + rs;
+    const int slot = (hq << p.LRS3) + rs;
     const int nchunk = p.CW3 / kOutChunk;
-
-    if (!prefetched) p3_load<HD, MF>(p, lp, tid, hq, c3, rs, 0, tile);     // independent of the attention result
 
     {
         // ---- merge of the split-KV partials (Alg. 3 steps 5-7).  A pass handles up to NV * 512 values v = (batch row,
@@ -1667,11 +1662,12 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
             const bool wide = p.NS > 32;                                  // more splits than half a wavefront: two loads
             for (int v0 = 0; v0 < V; v0 += NT * NV) {
                 const int cv = min(NT * NV, V - v0);                      // a multiple of 64
-                const int SG = NV == 1 ? max(1, min(NT / cv, p.NS)) : 1;
-                const int sg = NV == 1 ? __builtin_amdgcn_readfirstlane(tid / cv) : 0, v = tid - sg * cv;
+                const float rcv = reciprocal(cv);
+                const int SG = NV == 1 ? max(1, min(__builtin_amdgcn_readfirstlane(fdiv(NT, rcv)), p.NS)) : 1;
+                const int sg = NV == 1 ? __builtin_amdgcn_readfirstlane(fdiv(tid, rcv)) : 0, v = tid - sg * cv;
                 if (sg < SG) {
                     float at[NV], wgt[NV];
-                    size_t src[NV];
+                    uint32_t src[NV];
                     int col[NV];
 #pragma unroll
                     for (int n = 0; n < NV; ++n) {
@@ -1680,7 +1676,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                         const int vi = min(v0 + v + n * NT, V - 1);        // a value past the end repeats the last one
                         const int b = vi / HD;
                         col[n] = vi - b * HD;
-                        src[n] = ((size_t)b * p.nq + hq) * p.NS * PS;
+                        src[n] = (uint32_t)((b * p.nq + hq) * p.NS * PS);
                     }
                     for (int sb = sg; sb < p.NS; sb += MC * SG) {
                         const bool head = sb == sg;                       // the first round
@@ -1690,7 +1686,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 #pragma unroll
                             for (int n = 0; n < NV; ++n) {
                                 if (head) {
-                                    const size_t o = src[n] + (size_t)min(wide ? lane : lane & 31, p.NS - 1) * PS;
+                                    const uint32_t o = src[n] + (uint32_t)min(wide ? lane : lane & 31, p.NS - 1) * PS;
                                     vm[n] = x2.ld(o + (wide ? 0 : lane >> 5));
                                     vl[n] = vm[n];
                                     if (wide) vl[n] = x2.ld(o + 1);
@@ -1698,18 +1694,18 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 #pragma unroll
                                 for (int k = 0; k < MC; ++k) {
                                     const int s = sb + k * SG;            // (a load past the splits repeats one)
-                                    va[n][k] = x2.ld(src[n] + (size_t)(s < p.NS ? s : sb) * PS + kP2Stride + col[n]);
+                                    va[n][k] = x2.ld(src[n] + (uint32_t)(s < p.NS ? s : sb) * PS + kP2Stride + col[n]);
                                 }
                             }
                             __builtin_amdgcn_sched_barrier(0);
-                            bool ok = true;
+                            uint32_t stale = 0;
 #pragma unroll
                             for (int n = 0; n < NV; ++n) {
-                                if (head) ok &= (vm[n].y == stamp) & (vl[n].y == stamp);
+                                if (head) stale |= (vm[n].y ^ stamp) | (vl[n].y ^ stamp);
 #pragma unroll
-                                for (int k = 0; k < MC; ++k) ok &= va[n][k].y == stamp;
+                                for (int k = 0; k < MC; ++k) stale |= va[n][k].y ^ stamp;
                             }
-                            if (ok || spin.expired(p)) break;
+                            if (stale == 0 || spin.expired(p)) break;
                         }
                         if (head) {
 #pragma unroll
@@ -1773,7 +1769,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
     }
     CF_STAMP(11);           // attention merged
 
-    for (int ch = 0; ch < nchunk; ++ch) {
+    for (int ch = 0; MF && ch < nchunk; ++ch) {
         const int cbase = c3 * p.CW3 + ch * kOutChunk;
         if (cbase >= p.D) break;
         if (ch > 0) p3_load<HD, MF>(p, lp, tid, hq, c3, rs, ch, tile);
@@ -1820,61 +1816,94 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                 for (int k = 0; k < 4; ++k) {
                     const float f0 = lane_of(iv, 2 * (b0 + k) + rbeg / 64), f1 = lane_of(iv, 2 * (b0 + k) + 1);
                     const float sum = fmaf(u[k], f0, v[k] * (halves ? f1 : f0));
-                    if (mine && b0 + k < p.B) x3.st(((size_t)slot * p.B + b0 + k) * p.D + cbase + tid, sum, stamp);
+                    if (mine && b0 + k < p.B) x3.st((uint32_t)(slot * p.B + b0 + k) * p.D + cbase + tid, sum, stamp);
                 }
             }
             CF_STAMP(18);   // output partial stored
             lds_barrier();
-            continue;
         }
+    }
+    if constexpr (!MF) {
         float acc[BT][8];
+        auto clear = [&]() {
 #pragma unroll
-        for (int b = 0; b < BT; ++b)
+            for (int b = 0; b < BT; ++b)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[b][j] = 0.f;
-        if (nchunk == 1) {
-            // straight-line code (a branch per row would serialise the LDS reads): a row past the item
-            // has a zero tile entry, its load was switched off, so it may be multiplied by any finite value
+                for (int j = 0; j < 8; ++j) acc[b][j] = 0.f;
+        };
+        // (straight-line code: a branch per row would serialise the LDS reads; a row past the item has a zero tile entry, its
+        // is past the end of its buffer, so it may be multiplied by any finite value)
+        auto use_row = [&](int u) {
+            const int r = rbeg + (lane >> 3) + 8 * min(u, iters - 1);
+            float f[8];
+            unpack8(tile.w[u], f);
 #pragma unroll
-            for (int u = 0; u < OutTile<HD>::MAXR; ++u) {
-                const int r = rbeg + (lane >> 3) + 8 * min(u, iters - 1);
-                float f[8];
-                unpack8(tile.w[u], f);
+            for (int b = 0; b < BT; ++b) {
+                const float av = as[b * HD + r];
 #pragma unroll
-                for (int b = 0; b < BT; ++b) {
-                    const float av = as[b * HD + r];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[b][j] = fmaf(av, f[j], acc[b][j]);
-                }
+                for (int j = 0; j < 8; ++j) acc[b][j] = fmaf(av, f[j], acc[b][j]);
             }
-        } else {
-            // with several chunks per item the tile was loaded just now, and row-by-row waits overlap its arrival
-#pragma unroll
-            for (int u = 0; u < OutTile<HD>::MAXR; ++u) {
-                if (u < iters) {
-                    const int r = rbeg + (lane >> 3) + 8 * u;
-                    float f[8];
-                    unpack8(tile.w[u], f);
-#pragma unroll
-                    for (int b = 0; b < BT; ++b) {
-                        const float av = as[b * HD + r];
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) acc[b][j] = fmaf(av, f[j], acc[b][j]);
-                    }
-                }
-            }
-        }
+        };
         // The eight row groups of a wavefront hold the rows of the item, so their sum is the partial: it is folded in
         // registers, a lane ends with one column, and nothing passes through LDS (rows dealt to the wavefronts, whose 512
         // columns were then added through LDS between two barriers, took 0.6 - 1.2 us at batch 1).
-        const int cc = cbase + 64 * wv + 8 * (lane & 7) + (lane >> 3);
+        auto publish = [&](int ch) {
+            const int cc = c3 * p.CW3 + ch * kOutChunk + 64 * wv + 8 * (lane & 7) + (lane >> 3);
 #pragma unroll
-        for (int b = 0; b < BT; ++b) {
-            float sum[1];
-            lanes::fold8<8>(acc[b], sum);
-            if (b < p.B && cc < p.D) x3.st(((size_t)slot * p.B + b) * p.D + cc, sum[0], stamp);
+            for (int b = 0; b < BT; ++b) {
+                float sum[1];
+                lanes::fold8<8>(acc[b], sum);
+                if (b < p.B && cc < p.D) x3.st((uint32_t)(slot * p.B + b) * p.D + cc, sum[0], stamp);
+            }
+            CF_STAMP(18);       // output partial stored
+        };
+        auto use_tile = [&]() {
+#pragma unroll
+            for (int u = 0; u < OutTile<HD>::MAXR; ++u) {
+                use_row(u);
+                // (the sums of all batch rows are made here, a few rows of the tile at a time: left alone, the compiler moves those
+                // of a batch row to where they are published and keeps the whole tile as fp32 values until the last one)
+                if (BT > 1 && u % 4 == 3) {
+#pragma unroll
+                    for (int b = 0; b < BT; ++b)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(acc[b][j]));
+                }
+            }
+        };
+        const int n = min(nchunk, (p.D - c3 * p.CW3 + kOutChunk - 1) / kOutChunk);
+        if constexpr (BT == 1) {
+            if (n == 1) {
+                clear();
+                use_tile();
+                publish(0);
+            } else {
+                // Several chunks per item: every register of the tile is requested again, for the next chunk, as soon as it has
+                // been used, so that the stream of W_o does not stop between two chunks (the offset depends on the sums the
+                // register went into: the request stays behind its last use).  Behind the last chunk there is nothing to load.
+                for (int ch = 0; ch < n; ++ch) {
+                    const OutRows<HD, false> next(p, lp, tid, hq, c3, rs, ch + 1, ch + 1 < n);
+                    clear();
+#pragma unroll
+                    for (int u = 0; u < OutTile<HD>::MAXR; ++u) {
+                        use_row(u);
+                        uint32_t off = next.off;
+                        asm volatile("" : "+v"(off) : "v"(acc[0][0]), "v"(acc[0][1]), "v"(acc[0][2]), "v"(acc[0][3]), "v"(acc[0][4]),
+                                     "v"(acc[0][5]), "v"(acc[0][6]), "v"(acc[0][7]));
+                        tile.w[u] = next.row(u, off);
+                    }
+                    publish(ch);
+                }
+            }
+        } else {
+            for (int ch = 0;;) {
+                clear();
+                use_tile();
+                publish(ch);
+                if (++ch >= n) break;
+                p3_load<HD, MF>(p, lp, tid, hq, c3, rs, ch, tile);
+            }
         }
-        CF_STAMP(18);       // output partial stored
     }
     if constexpr (!MF) lds_barrier();         // the merged values have been read
 }
@@ -1884,24 +1913,13 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 // partials of those columns in slot order (the cross-head reduction that the paper
 // does with atomicAdd), then writes fp16.
 // ---------------------------------------------------------------------------
-// Output columns a workgroup owns: an even number, since a stack hands its hidden state on in pairs of values.  Single launches
-// do the same: the bits of a stack are those of its layers one by one, and the sixteen bytes of two neighbouring partials are one
-// piece of a line (us a layer, exact / even number: 768 columns, 8 heads of 128, batch 4 / 16 20.9 / 19.5 and 30.3 / 26.0, 1280 columns,
-// 22.5 / 22.2 and 33.2 / 32.3, 2056 columns, 14 heads of 64, 19.9 / 19.6 and 25.1 / 24.4; 256 columns, one or two per workgroup: 4
-// heads of 64 14.6 / 14.6 and 19.4 / 21.0, 16 heads of 128 21.1 / 21.6 and 31.1 / 29.8).
-__device__ __forceinline__ int own_columns(const Params &p) { return ((p.D + p.W - 1) / p.W + 1) & ~1; }
-
-// The residual input of output value v0 + i of this workgroup (0 when there is none): from x, in a stack past its first layer
+// The residual input of output value i of this workgroup, which owns the columns [c0, c0 + ncol) (0 when there is none): from x, in a stack past its first layer
 // from the slots xin, where this workgroup itself has left it.
-__device__ __forceinline__ uint16_t residual_input(const Params &p, int i0, int v0, const uint64_t *xin)
+__device__ __forceinline__ uint16_t residual_input(const Params &p, int i, int c0, int ncol, float rncol, const uint64_t *xin)
 {
-    const int cpw = own_columns(p);
-    const int c0 = blockIdx.x * cpw;
-    const int ncol = min(cpw, p.D - c0);
-    const int i = v0 + i0;
     uint16_t r = 0;
-    if (kLayer && (p.flags & kFlagResidual) && ncol > 0 && i < ncol * p.B) {
-        const int b = i / ncol, c = i - b * ncol;
+    if (kLayer && (p.flags & kFlagResidual) && i < ncol * p.B) {
+        const int b = fdiv(i, rncol), c = i - b * ncol;
         const size_t at = (size_t)b * p.D + c0 + c;
         if (xin) {
             const uint32_t two = Xbuf(xin).ld(at >> 1).x;
@@ -1920,38 +1938,39 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
 {
     const int tid = tid0;
     const Xbuf x3(p.p3);
-    const int nslots = p.nq * p.RS3;
-    const int cpw = own_columns(p);
-    const int c0 = blockIdx.x * cpw;
-    const int ncol = min(cpw, p.D - c0);
-    if (ncol <= 0) {                                 // no column of its own (W * cpw > D): the hook runs all the same, a
-        after_polls();                               // stack's next layer counts on what it requests
-        return;
-    }
-    const int nv = ncol * p.B;                       // values this workgroup produces
-    for (int v0 = 0; v0 < nv; v0 += NT) {
-        const int cb = min(NT, nv - v0);
-        const int spt = min(NT / cb, nslots);        // slots read in parallel
-        const int v = tid % cb, s0 = tid / cb;
-        const int b = (v0 + v) / ncol, c = (v0 + v) - b * ncol;
+    const int nslots = p.nq << p.LRS3;
+    const int c0 = blockIdx.x * p.CPW;
+    const int ncol = min(p.CPW, p.D - c0);
+    const int nv = max(ncol, 0) * p.B;               // values this workgroup produces (none where W * CPW > D)
+    const float rncol = reciprocal(ncol);
+    int cb, spt, own;
+    bool wide;
+    uint16_t xres;
+    auto fetch = [&](int v0) {                       // the partials of the values v0 .. v0 + cb - 1, added up by slots s0, s0 + spt, ..., to LDS
+        cb = min(NT, nv - v0);
+        const float rcb = reciprocal(cb);
+        spt = min(__builtin_amdgcn_readfirstlane(fdiv(NT, rcb)), nslots);        // slots read in parallel
+        const int s0 = fdiv(tid, rcb), v = tid - s0 * cb;
+        const int b = fdiv(v0 + v, rncol), c = (v0 + v) - b * ncol;
         // the residual input of the value this thread writes below, on its
         // way while the partials are polled.  (Fetching it before phase 3 was tried: a load inside a branch
         // there makes every later wait for the output-projection tile drain the queue.)
         // Up to 32 values: sixteen lanes add the sums of a value (one thread for up to 256 sums of two values took 0.9 us of
         // the tiny shape, so 0.6); more: one thread each, at most sixteen sums.  (FEW: not in the 16-row kernels, which rarely
         // have so few and lost 1 % to the code.)
-        const bool wide = FEW && cb <= NT / 16;
-        const int own = wide ? tid >> 4 : tid;       // the value whose sums this thread adds
-        const uint16_t xres = residual_input(p, own, v0, xin);
+        wide = FEW && cb <= NT / 16;
+        own = wide ? tid >> 4 : tid;                 // the value whose sums this thread adds
+        xres = residual_input(p, v0 + own, c0, ncol, rncol, xin);
         if (s0 < spt) {
-            const int n = (nslots - s0 + spt - 1) / spt;
-            const size_t base = (size_t)s0 * p.B * p.D + (size_t)b * p.D + c0 + c, stride = (size_t)spt * p.B * p.D;
+            const int n = fdiv(nslots - s0 + spt - 1, reciprocal(spt));
+            const uint32_t base = (uint32_t)(s0 * p.B + b) * p.D + c0 + c, stride = (uint32_t)(spt * p.B) * p.D;
             // (more than eight slots per thread: sixteen polls in flight, one round trip instead of two)
             smem[s0 * cb + v] = nslots > 8 * spt ? ll_sum<16>(p, x3, base, stride, n, stamp) : ll_sum<8>(p, x3, base, stride, n, stamp);
         }
         CF_STAMP(19);           // head partials arrived
         lds_barrier();
-        if (v0 == 0) after_polls();
+    };
+    auto finish = [&](int v0) {
         float sum = !wide && kLayer && (p.flags & kFlagResidual) ? h2f(xres) : 0.f;
         if (own < cb)
             for (int k = wide ? tid & 15 : 0; k < spt; k += wide ? 16 : 1) sum += smem[k * cb + own];
@@ -1959,7 +1978,7 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
         if (wide && kLayer && (p.flags & kFlagResidual)) sum = h2f(xres) + sum;
         if (!STACK || !xout) {
             if (own < cb && (!wide || (tid & 15) == 0)) {
-                const int bo = (v0 + own) / ncol, co = (v0 + own) - bo * ncol;
+                const int bo = fdiv(v0 + own, rncol), co = (v0 + own) - bo * ncol;
                 p.out[(size_t)bo * p.D + c0 + co] = f2h(sum);
             }
         } else {
@@ -1971,11 +1990,18 @@ __device__ __forceinline__ void final_reduce(const Params &p, int tid0, uint32_t
             else
                 n = dpp_move<0xF5>(n);                            // quad_perm [1,1,3,3]
             if (own < cb && (own & 1) == 0 && (!wide || (tid & 15) == 0)) {
-                const int bo = (v0 + own) / ncol, co = (v0 + own) - bo * ncol;
-                Xbuf(xout).st(((size_t)bo * p.D + c0 + co) >> 1, __builtin_bit_cast(float, h | __builtin_bit_cast(uint32_t, n) << 16), stamp);
+                const int bo = fdiv(v0 + own, rncol), co = (v0 + own) - bo * ncol;
+                Xbuf(xout).st((uint32_t)(bo * p.D + c0 + co) >> 1, __builtin_bit_cast(float, h | __builtin_bit_cast(uint32_t, n) << 16), stamp);
             }
         }
         lds_barrier();
+    };
+    if (nv > 0) fetch(0);
+    after_polls();          // (in one place and in no branch: a stack's next layer counts on what it requests, and the registers that takes hold nothing before)
+    if (nv > 0) finish(0);
+    for (int v0 = NT; v0 < nv; v0 += NT) {
+        fetch(v0);
+        finish(v0);
     }
 }
 
@@ -2005,6 +2031,22 @@ struct MergeWide {
 // rows of the input it needs have arrived.  The exchange areas need no second set: a workgroup can post values of
 // layer l + 1 only after it has taken in that layer's input, which exists only when every workgroup has finished
 // reading what layer l exchanged.
+// The kernel's arguments, through a pointer the compiler cannot connect with an earlier one (see decode_steps).
+//
+// At small shapes the time between two hand-overs is the time to issue the instructions in between (one every four to eight
+// clocks and wavefront; 1300 a wavefront at the tiny shape, half of them scalar).  Us a layer, before / after: the arguments by
+// phase, loads that end with their buffer, divisions by reciprocals, no copies of loaded registers where paths meet:
+// tiny shape 13.7 / 11.6, D 2056, 14 heads of 64, batch 3 19.4 / 16.3, 1024 columns, 8 heads of 128, batch 1 15.4 / 12.9,
+// 16 heads of 64 over 8, batch 5, norm 26.3 / 21.4, Llama-3-8B shape, norm, 1000 rows, batch 1 / 16 26.8 / 24.0 and 46.8 / 42.7,
+// one launch, norm, 2048 rows 24.9 / 23.5, Llama-2-7B shape 36.4 / 35.1, Llama-2-70B shape 75.1 / 73.4 (of which 0.5 the stream of W_o).
+__device__ __forceinline__ const Params &kernarg_params()
+{
+    typedef const __attribute__((address_space(4))) Params *KernargParams;
+    KernargParams pk = (KernargParams)__builtin_amdgcn_kernarg_segment_ptr();      // (StackArgs begins with Params)
+    asm volatile("" : "+s"(pk));
+    return *(const Params *)pk;
+}
+
 template <int HD, int G, int BT, bool STACK>
 __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *tab, int n_layers_in, uint64_t *xslots)
 {
@@ -2014,12 +2056,12 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
         // The compiler loads each kernel argument shortly before its first use: several dependent
         // round trips to cold memory in a row at the start of every launch.  One word of every 64-byte
         // line of the argument block is read here, all at once, so the later reads hit the scalar cache.
-        static_assert(sizeof(Params) == 256, "one load per 64-byte line of the argument block below");
+        static_assert(sizeof(Params) == 320, "one load per 64-byte line of the argument block below");
         auto ka = __builtin_amdgcn_kernarg_segment_ptr();
-        uint32_t t0, t1, t2, t3;
-        asm volatile("s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\t"
-                     "s_load_dword %3, %4, 0xc0\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3)
+        uint32_t t0, t1, t2, t3, t4;
+        asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\t"
+                     "s_load_dword %3, %5, 0xc0\n\ts_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4)
                      : "s"(ka));
     }
     __shared__ float s_rope[RopeRows<HD, BT>::ROWS * HD];    // cos / sin of the RoPE angles, per row if the rows differ
@@ -2051,18 +2093,18 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // layer (as are the thread and workgroup index below): whatever depends only on them is loop-invariant, and
     // the compiler would otherwise compute all of it once in front of the loop over the layers and keep it in
     // registers, hundreds of values, across every phase.
-    typedef const __attribute__((address_space(4))) Params *KernargParams;
-    KernargParams pk = (KernargParams)__builtin_amdgcn_kernarg_segment_ptr();      // StackArgs begins with Params
-    if (STACK) asm volatile("" : "+s"(pk));
-    const Params &p = STACK ? *(const Params *)pk : p0;
+    // The same at the start of every phase: what a phase takes from the arguments, it fetches itself (hits in the scalar cache)
+    // and does not keep beyond its end.  With one reference for all phases more scalars were alive than there are registers,
+    // and every one moved to a vector register's lane and back is an instruction each way, hundreds of them.
+    const Params &p = kernarg_params();
     const int n2 = p.B * p.NS;                       // attention items of the team
-    const int n3 = G * p.NC3 * p.RS3;                // output-projection items of the team
+    const int n3 = G * (p.NC3 << p.LRS3);            // output-projection items of the team
     // (in a stack the thread index is made opaque per layer: everything derived from it would otherwise be computed
     // once in front of the loop over the layers and be kept in registers across all phases)
     int tl = threadIdx.x, w = blockIdx.x;
     if (STACK) asm volatile("" : "+v"(tl), "+s"(w));
-    const int team = p.pairmap ? qmod(w >> 1, p.nkv, p.div_nkv) : qmod(w, p.nkv, p.div_nkv);
-    const int member = p.pairmap ? qdiv(w >> 1, p.div_nkv) * 2 + (w & 1) : qdiv(w, p.div_nkv);
+    const int team_round = qdiv(w >> p.pairmap, p.div_nkv);
+    const int team = (w >> p.pairmap) - team_round * p.nkv, member = (team_round << p.pairmap) | (w & p.pairmap);
     // weights and caches of this layer (layer 0, and the only layer of a plain call: those of the parameters);
     // a reference into the argument block either way, so that each pointer is fetched where it is used
     static_assert(offsetof(Params, wo) == offsetof(Params, wqkv) + 8 && offsetof(Params, kc) == offsetof(Params, wqkv) + 16 &&
@@ -2073,14 +2115,14 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     OutTile<HD> tile;
     const int b_first = member < n2 ? qdiv(member, p.div_ns) : 0;     // batch row of the first attention item
     const int pos_first = row_pos(p, b_first);
-    const int s_first = member < n2 ? qmod(member, p.NS, p.div_ns) : 0;
+    const int s_first = member < n2 ? member - b_first * p.NS : 0;
     // (with positions per row the stream is set up only where phase 1 first needs it: the position comes from
     // memory, and waiting for it here would hold up the first weight loads)
     const bool own_pos = kLayer && p.row_pos != nullptr;
     P2Stream<HD, G> st2(p, lp, tl, team, b_first, s_first, own_pos ? 0 : p.pos, member < n2 && !own_pos);
 
     // ---- phase 1 (projection); its last step already starts the K/V stream of phase 2
-    EarlyQ eq;
+    EarlyQ<STACK ? 8 : 16> eq;
     // (without batches requested ahead the registers of the two batches belong to this layer alone)
     P1Regs<HD, BT> rg_layer;
     P1Regs<HD, BT> &rgu = (STACK && P1Ahead<HD, G, BT>::n > 0) ? rg : rg_layer;
@@ -2092,57 +2134,77 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // a first look at the team's q partials (in a stack only for one batch row and attention on the vector ALU: no
     // registers are left for the sixteen pairs there, they would be spilled as they arrive)
     if (member < n2 && !(STACK && (AttnMfma<HD, G>::on || BT > 1)))
-        eq.issue<HD, G>(p, tl, team, qdiv(member, p.div_ns), NewTokenFirst<HD, G, BT>::selectors(s_first == p.NS - 1));
+        eq.template issue<HD, G>(p, tl, team, qdiv(member, p.div_ns), NewTokenFirst<HD, G, BT>::selectors(s_first == p.NS - 1));
     st2.prefetch(kv, 1);
     CF_STAMP(1);
     // ---- phase 2 (attention); the last item already starts the W_o stream of phase 3
-    auto p3_args = [&](int it, int &hq, int &c3, int &rs) {
-        const int g = it / (p.NC3 * p.RS3), rem = it - g * (p.NC3 * p.RS3);
+    auto p3_args = [&](const Params &q, int it, int &hq, int &c3, int &rs) {
+        const int g = qdiv(it, q.div_n3), rem = it - g * (q.NC3 << q.LRS3);
         hq = team * G + g;
-        c3 = rem / p.RS3;
-        rs = rem % p.RS3;
+        c3 = rem >> q.LRS3;
+        rs = rem & ((1 << q.LRS3) - 1);
+    };
+    auto layer_ptrs = [&](const Params &q) -> const LayerPtrs & {
+        return (STACK && layer > 0) ? tab[layer] : *reinterpret_cast<const LayerPtrs *>(&q.wqkv);
     };
     constexpr bool EARLY = EarlyTile<HD, G>::on;
-    bool tile_ready = false;
     if (EARLY) {
-        // (no branch around the loads, lanes off instead: the waits for the cached rows count them)
+        // (no branch around the loads, an empty buffer instead: the waits for the cached rows count them)
+        const Params &q = kernarg_params();
         int hq, c3, rs;
-        p3_args(member < n3 ? member : 0, hq, c3, rs);
-        p3_load<HD, Mfma<HD, BT>::on>(p, lp, tl, hq, c3, rs, 0, tile, 0, member < n2 && member < n3);
+        p3_args(q, member < n3 ? member : 0, hq, c3, rs);
+        p3_load<HD, Mfma<HD, BT>::on>(q, layer_ptrs(q), tl, hq, c3, rs, 0, tile, 0, member < n2 && member < n3);
     }
     auto p3_prefetch = [&](int part) {
         if (member < n3) {
+            const Params &q = kernarg_params();
             int hq, c3, rs;
-            p3_args(member, hq, c3, rs);
-            p3_load<HD, Mfma<HD, BT>::on>(p, lp, tl, hq, c3, rs, 0, tile, part);
-            tile_ready = true;
+            p3_args(q, member, hq, c3, rs);
+            p3_load<HD, Mfma<HD, BT>::on>(q, layer_ptrs(q), tl, hq, c3, rs, 0, tile, part);
         }
     };
-    for (int it = member; it < n2; it += p.TS) {
-        const bool first = (it == member), final_item = (it + p.TS >= n2);
-        if (!first) {
-            const int b_it = qdiv(it, p.div_ns);
-            st2 = P2Stream<HD, G>(p, lp, tl, team, b_it, qmod(it, p.NS, p.div_ns), row_pos(p, b_it));
+    if (member < n2) {
+        for (int it = member;;) {
+            const Params &q = kernarg_params();
+            const int b_it = qdiv(it, q.div_ns), next = it + q.TS;
+            const bool more_items = next < n2;
+            // stage 1: first half of the output-projection tile, stage 2: second half (early: stage 1 the second half)
+            p2_item<HD, G, BT>(q, layer_ptrs(q), tl, team, b_it, it - b_it * q.NS, stamp, it == member, st2, kv, eq, smem,
+                               s_rope + (kLayer && q.row_pos ? b_it * HD : 0), [&](int stage) {
+                if (!more_items && (!EARLY || stage == 1)) p3_prefetch(EARLY ? 1 : stage - 1);
+            });
+            if (!more_items) break;
+            it = next;
+            const Params &qn = kernarg_params();
+            const int b_next = qdiv(it, qn.div_ns);
+            st2 = P2Stream<HD, G>(qn, layer_ptrs(qn), tl, team, b_next, it - b_next * qn.NS, row_pos(qn, b_next));
             st2.prefetch(kv, 0);
             st2.prefetch(kv, 1);
         }
-        // stage 1: first half of the output-projection tile, stage 2: second half (early: stage 1 the second half)
-        p2_item<HD, G, BT>(p, lp, tl, team, qdiv(it, p.div_ns), qmod(it, p.NS, p.div_ns), stamp, first, st2, kv, eq, smem,
-                       s_rope + (kLayer && p.row_pos ? qdiv(it, p.div_ns) * HD : 0), [&](int stage) {
-            if (final_item && (!EARLY || stage == 1)) p3_prefetch(EARLY ? 1 : stage - 1);
-        });
+    } else {
+        p3_prefetch(2);
     }
-    if (member >= n2) p3_prefetch(2);
     CF_STAMP(3);
     const bool more = STACK && layer + 1 < n_layers;
     auto no_next = [](int) {};
     const LayerPtrs &lpn = STACK ? tab[more ? layer + 1 : layer] : lp;
     constexpr int AHEAD = STACK ? P1Ahead<HD, G, BT>::n : 0;
     // ---- phase 3 (output projection, per-head partials)
-    for (int it = member; it < n3; it += p.TS) {
-        int hq, c3, rs;
-        p3_args(it, hq, c3, rs);
-        p3_item<HD, BT, MergeWide<HD, G, BT, STACK>::n>(p, lp, tl, hq, c3, rs, stamp, tile, tile_ready && it == member, smem);
+    // (The tile of the first item is on its way, that of a further one is requested when the item before is done.  A load in front
+    // of the merge for the items that need it is a second source of the tile's registers there: they were copied, and the copy
+    // waited for the whole tile before the first poll went out.)
+    if (member < n3) {
+        for (int it = member;;) {
+            const Params &q = kernarg_params();
+            int hq, c3, rs;
+            p3_args(q, it, hq, c3, rs);
+            p3_item<HD, BT, MergeWide<HD, G, BT, STACK>::n>(q, layer_ptrs(q), tl, hq, c3, rs, stamp, tile, smem);
+            it += q.TS;
+            if (it >= n3) break;
+            const Params &qn = kernarg_params();
+            p3_args(qn, it, hq, c3, rs);
+            p3_load<HD, Mfma<HD, BT>::on>(qn, layer_ptrs(qn), tl, hq, c3, rs, 0, tile);
+        }
     }
     CF_STAMP(4);
     // ---- phase 4 (sum over heads)
@@ -2152,10 +2214,10 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // (measured on the 7B shape, us per layer: this placement 36.5; both batches before the wait 37.6; the first
     // one already after the merge of the attention partials 37.7; none 37.6)
     if (AHEAD >= 1)
-        p1_all<HD, G, BT, STACK, 1>(p, lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
-    final_reduce<(BT <= 4), STACK>(p, tl, stamp, smem, more ? xslots : nullptr, layer > 0 ? xslots : nullptr, [&]() {
+        p1_all<HD, G, BT, STACK, 1>(kernarg_params(), lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
+    final_reduce<(BT <= 4), STACK>(kernarg_params(), tl, stamp, smem, more ? xslots : nullptr, layer > 0 ? xslots : nullptr, [&]() {
         if (AHEAD >= 2)
-            p1_all<HD, G, BT, STACK, 2>(p, lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
+            p1_all<HD, G, BT, STACK, 2>(kernarg_params(), lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
     });
     primed = more;
     CF_STAMP(5);

@@ -44,7 +44,9 @@ __host__ __device__ constexpr int out_operand_floats(int head_dim) { return out_
 constexpr int kFlagPacked = 1;     // weights are in the packed (per-head contiguous) layout of cf_pack_weights
 constexpr int kFlagResidual = 2;   // out = x + block output
 
-// Everything the fused kernel needs, passed by value (256 bytes: four 64-byte lines, fetched together at kernel start).
+// Everything the fused kernel needs, passed by value (320 bytes: five 64-byte lines, fetched together at kernel start).  What
+// can be computed once per call is computed by the host: a wavefront issues an instruction every four to eight clocks, and
+// at small shapes the instructions between two hand-overs are most of the time.
 struct LayerPtrs {             // what differs from layer to layer of a stack
     const uint16_t *wqkv, *wo;
     uint16_t *kc, *vc;
@@ -69,24 +71,29 @@ struct Params {
     unsigned long long *dbg_t; // [W][kStamps] wall-clock stamps at phase boundaries, or null
     int D, nq, nkv, B, pos, max_seq, nqkv;
     int W, TS;             // workgroups, workgroups per team (team = one KV head)
-    int KS, RPS;           // projection: splits of the reduction dimension, rows of the longest split (LDS stride)
-    int RB, RD;            // rows of a split are RB + RD (even split index) or RB - RD (odd)
+    int KS, RPS;           // projection: splits of the reduction dimension, rows of a split (the last one may be shorter)
     int TD;                // attention: tokens of a split are TPS + TD (even split index) or TPS - TD (odd)
     int DSEL;              // TS / KS: selectors advance by this much from one step of a member to the next
-    uint32_t div_nkv, div_ks, div_dsel, div_ns;   // for divisions by nkv, KS, DSEL, NS: log2 of a power of two, else ceil(2^32 / d)
+    uint32_t div_nkv, div_ks, div_dsel, div_ns;   // for divisions by nkv, KS, DSEL, NS: ceil(2^31 / d)
     int pairmap;           // workgroup -> (team, member) keeps the parity of the workgroup id in the member id
     int NS, TPS;           // attention: splits of the cached sequence, tokens per split
-    int NC3, CW3, RS3;     // output projection: column blocks, columns per block, row splits per head
+    int NC3, CW3, LRS3;    // output projection: column blocks, columns per block, log2 of the row splits per head
+    int CPW;               // output columns a workgroup adds up and writes (an even number)
     uint32_t div_p8;       // the same for RPS / 8
+    uint32_t div_n3;       // and for NC3 << LRS3
+    // the two layouts of the weights (row-major, packed) as strides in bytes: W_qkv: row, block of head_dim columns; W_o: row,
+    // head, chunk of kOutChunk columns
+    uint32_t wrow, wblk, orow, ohead, ochunk;
     int flags;             // kFlagPacked, kFlagResidual
     float qk_scale_log2e;  // log2(e)/sqrt(head_dim)
     float eps;             // RMSNorm: added to the mean square
     uint32_t spin_ticks;   // wait limit in 100 MHz ticks (at most 42 s)
+    int reserved[10];
 };
 
 // A stack of layers in one launch: the pointers of every layer travel by value in the kernel's argument block, behind the
 // parameters of the first layer.
-constexpr int kMaxStackLayers = 88;        // 256 + 16 + 88 * 40 bytes = 3792 of the 4096 an argument block may have
+constexpr int kMaxStackLayers = 88;        // 320 + 16 + 88 * 40 bytes = 3856 of the 4096 an argument block may have
 struct StackArgs {
     Params p;                  // everything of layer 0, and what all layers share
     uint64_t *xslots;          // [B][D / 2] {two fp16 values, stamp}: the hidden state between two layers
