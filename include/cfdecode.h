@@ -179,7 +179,8 @@ int cf_decode_stack(cf_handle h, int32_t n_layers, int32_t batch, const void *x,
  *   row_pos  DEVICE [batch] int32, 4-byte aligned, read by the kernel (it may be written by earlier work on
  *            `stream`); 0 <= row_pos[b] <= max_pos.  Entries outside that range are clamped into it.
  *   max_pos  HOST value, an upper bound of the entries, 0 <= max_pos < max_seq: the work is split as for a batch
- *            with max_pos cached tokens in every row (shorter rows leave their last splits empty).
+ *            with max_pos cached tokens in every row (shorter rows leave their last splits empty), except where the
+ *            lengths are so different that the kernel deals the cached rows by them.
  * norm_weight may be NULL and residual 0: then this is the bare block with per-row positions.
  */
 int cf_decode_layer_rows(cf_handle h, int32_t batch, const void *x, const void *norm_weight, float eps,

@@ -190,6 +190,10 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
         p->CW3 = ceil_div(nch, best_nc) * cf::kOutChunk;
         p->NC3 = ceil_div(nch * cf::kOutChunk, p->CW3);
     }
+    // Rows of different lengths: NS splits of the longest one for every row leave the members of the short rows' last splits idle
+    // (four rows of 5120 to 8192 tokens, 32 members: 7 without a token, the others 1024 each where 832 would do).  Where every member
+    // has at most one item, the kernel deals the items by the rows' lengths instead.
+    p->ragged = p->row_pos && batch <= TS && h->tune_ns == 0 && p->TPS >= 4 * cf::ragged_gain(hd) ? 1 : 0;
     p->DSEL = TS / p->KS;
     auto divisor = [](int d) { return (uint32_t)((0x80000000ull + d - 1) / d); };      // what the kernel's qdiv takes
     p->div_nkv = divisor(c.n_kv_heads);

@@ -297,6 +297,68 @@ __device__ __forceinline__ int row_pos(const Params &p, int b)
     return p.pos;
 }
 
+// The attention item of a member where the batch rows have lengths of their own (Params::ragged): row b is cut into ns_b splits of
+// about the same number of tokens in all rows, at most one item per member, and the items are numbered row by row.
+constexpr int kMaxRows = 16;
+struct RowItem {
+    int b = 0, s = 0, ns = 1, pos = 0;      // row, split, splits of the row, its cached tokens
+    int first = 0;                          // number of the row's first item
+    int t0 = 0, t1 = 0;
+    int table = 0;                          // lane b: first item of row b (lanes past the batch: number of items)
+    int items = 0;                          // 0: the plan's items
+};
+// `len`: cached tokens of row `lane % 16` (0 past the batch).  All wavefronts of all workgroups come to the same result.
+template <int CTRL>
+__device__ __forceinline__ int dpp_int(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
+template <int HD>
+__device__ __forceinline__ RowItem deal_rows(const Params &p, int lane, int len, int member, RowItem it)         // it: the plan's item
+{
+    int total = len, longest = len;                               // over the 16 lanes of a row
+    total += dpp_int<0xB1>(total), longest = max(longest, dpp_int<0xB1>(longest));       // quad_perm [1,0,3,2]
+    total += dpp_int<0x4E>(total), longest = max(longest, dpp_int<0x4E>(longest));       // quad_perm [2,3,0,1]
+    total += dpp_int<0x141>(total), longest = max(longest, dpp_int<0x141>(longest));     // row_half_mirror
+    total += dpp_int<0x140>(total), longest = max(longest, dpp_int<0x140>(longest));     // row_mirror
+    total = __builtin_amdgcn_readfirstlane(total), longest = __builtin_amdgcn_readfirstlane(longest);
+    // Tokens per split: the fewest of 64 candidates that need at most TS items (and 64 splits of a row), one candidate per lane
+    // between what a perfect division would take and what is certain to suffice (an item more than it for every row); no fewer
+    // than 64, below which a split costs more than it saves.
+    auto up = [](int n, int d) { return fdiv(n + d - 1, reciprocal(d)); };        // (nothing rests on the last bit for huge lengths)
+    const int lo = max(max(up(total, p.TS), up(longest, kMaxKvSplits)), 64);
+    if (p.TPS - lo < ragged_gain(HD)) return it;
+    const int hi = p.TS > p.B ? max(up(total, p.TS - p.B), lo) : max(longest, lo);
+    const int cand = lane == 63 ? hi : lo + (int)((float)(hi - lo) * ((float)lane * (1.f / 63.f)));
+    const float rc = reciprocal(cand);
+    int need = 0;
+    for (int b = 0; b < p.B; ++b) need += max(fdiv(__builtin_amdgcn_readlane(len, b) + cand - 1, rc), 1);
+    const unsigned long long fit = __ballot(need <= p.TS);
+    const int size = fit ? __builtin_amdgcn_readlane(cand, __builtin_ctzll(fit)) : longest;
+    if (p.TPS - size < ragged_gain(HD)) return it;
+    const int row = lane & 15;
+    const int mine = row < p.B ? min(max(fdiv(len + size - 1, reciprocal(size)), 1), kMaxKvSplits) : 0;       // splits of the lane's row
+    int incl = mine;                                              // ... and of those before it
+    incl += dpp_int<0x111>(incl);                                 // row_shr 1, 2, 4, 8
+    incl += dpp_int<0x112>(incl);
+    incl += dpp_int<0x114>(incl);
+    incl += dpp_int<0x118>(incl);
+    it.items = __builtin_amdgcn_readlane(incl, 15);
+    it.table = lane < 16 ? incl - mine : it.items;
+    it.b = max(__builtin_popcountll(__ballot(lane < p.B && it.table <= member)) - 1, 0);
+    it.first = __builtin_amdgcn_readlane(it.table, it.b);
+    it.ns = __builtin_amdgcn_readlane(mine, it.b);
+    it.pos = __builtin_amdgcn_readlane(len, it.b);
+    it.s = member - it.first;
+    if (member < it.items) {
+        // (the split with the new token is shorter, by about what the token costs)
+        int t = up(it.pos + (it.ns > 1 ? 64 : 0), it.ns);
+        if (t * (it.ns - 1) > it.pos) t = up(it.pos, it.ns);
+        // (an item of an odd member, on a slower die, is 2 TD shorter than its neighbours: a boundary in front of one is TD further)
+        const int td = p.pairmap && t >= 256 ? 32 : 0;
+        it.t0 = it.s == 0 ? 0 : min(it.s * t + (member & 1 ? td : 0), it.pos);
+        it.t1 = it.s == it.ns - 1 ? it.pos : min(it.s * t + t + (member & 1 ? 0 : td), it.pos);
+    }
+    return it;
+}
+
 template <int G>
 __device__ __forceinline__ int qkv_block(const Params &p, int team, int sel)        // in blocks of head_dim columns
 {
@@ -376,7 +438,7 @@ struct P1Regs {
 template <int HD, int G, int BT, bool STACK, int PART, class NextFn>
 __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp, int tid0, int team, int member, float *smem,
                                            float *rope, int layer, const uint64_t *xin, int n_layers,
-                                           unsigned long long &cnt0, P1Regs<HD, BT> &rg, bool primed, NextFn &&issue_next)
+                                           unsigned long long &cnt0, P1Regs<HD, BT> &rg, bool primed, int &lens, NextFn &&issue_next)
 {
     constexpr int LPR = HD / 8;
     constexpr int NG = NT / LPR;
@@ -622,6 +684,7 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
         const int e = tid + k * NT, eb = e / (HD / 2);
         epos[k] = psrc[own_pos && eb < p.B ? eb : 0];
     }
+    if constexpr (kLayer && !STACK) lens = psrc[own_pos && (tid & 15) < p.B ? tid & 15 : 0];        // of row `lane % 16`, for deal_rows
     __builtin_amdgcn_sched_barrier(0);
     if (!(AHEAD >= 2 && primed)) load(wb, voff0);
     __builtin_amdgcn_sched_barrier(0);
@@ -1131,18 +1194,22 @@ struct P2Stream {
     uint32_t voff0;          // of the lane's first row of the split
     size_t head;
     Stream K, V;
-    // `pos_b`: tokens cached for this batch row.  The buffers end with the split: rows behind it, and so rows >= pos_b, are
-    // never read.  An inactive stream (a workgroup without an attention item) has an empty split.  A row shorter than the longest
-    // one of the batch uses the same split boundaries: its splits past pos_b are empty.
-    __device__ __forceinline__ P2Stream(const Params &p, const LayerPtrs &lp, int tid0, int team, int b, int s, int pos_b,
-                                        bool active = true)
-        : t0(s * p.TPS + ((s & 1) ? p.TD : 0)),                      // even splits are 2*TD tokens longer
-          t1(active ? min(t0 + p.TPS + ((s & 1) ? -p.TD : p.TD), pos_b) : 0), grp(tid0 / LPR), pos(pos_b), tid(tid0),
-          head(((size_t)b * p.nkv + team) * p.max_seq * HD), K(lp.kc + head, (uint32_t)t1 * HD * 2), V(lp.vc + head, (uint32_t)t1 * HD * 2)
+    // `pos_b`: tokens cached for this batch row, [t0, t1) the split.  The buffers end with the split: rows behind it, and so rows
+    // >= pos_b, are never read.
+    __device__ __forceinline__ P2Stream(const Params &p, const LayerPtrs &lp, int tid0, int team, int b, int t0_, int t1_, int pos_b)
+        : t0(t0_), t1(t1_), grp(tid0 / LPR), pos(pos_b), tid(tid0), head(((size_t)b * p.nkv + team) * p.max_seq * HD),
+          K(lp.kc + head, (uint32_t)t1 * HD * 2), V(lp.vc + head, (uint32_t)t1 * HD * 2)
     {
         const int n = max(t1 - t0, 0);
         iters = MA ? (n + 32 * NW - 1) / (32 * NW) : (n + NG - 1) / NG;   // MA: rounds of one 32-token tile per wavefront
         voff0 = (uint32_t)(t0 + grp) * HD * 2 + tid % LPR * 16;
+    }
+    // Split s of the plan.  An inactive stream (a workgroup without an attention item) has an empty split; a row shorter than the
+    // longest one of the batch uses the same split boundaries: its splits past pos_b are empty.
+    static __device__ __forceinline__ P2Stream planned(const Params &p, const LayerPtrs &lp, int tid0, int team, int b, int s, int pos_b, bool active = true)
+    {
+        const int first = s * p.TPS + ((s & 1) ? p.TD : 0);               // even splits are 2*TD tokens longer
+        return P2Stream(p, lp, tid0, team, b, first, active ? min(first + p.TPS + ((s & 1) ? -p.TD : p.TD), pos_b) : 0, pos_b);
     }
     // MFMA tiles: round `it` gives wavefront wv the tokens t0 + 32 (8 it + wv) + 0..31.  K: load u brings rows
     // 4 u + (lane / 16); V: load u brings rows 16 (u / 4) + 4 (lane / 16) + u % 4 (the order in which the scores
@@ -1193,7 +1260,7 @@ struct P2Stream {
 };
 
 template <int HD, int G, int BT, class Early, class TailFn>
-__device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, int tid0, int team, int b, int s, uint32_t stamp, bool first,
+__device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, int tid0, int team, int b, int s, int ns, int row_item, uint32_t stamp, bool first,
                                         const P2Stream<HD, G> &st, KvBuf<HD, G> &buf, const Early &eq, float *smem,
                                         const float *rope, TailFn &&issue_next)
 {
@@ -1207,7 +1274,7 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
     int tid = tid0;
     if (AttnMfma<HD, G>::on) asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wv = tid >> 6, lig = tid % LPR, grp = tid / LPR;
-    const bool last = (s == p.NS - 1);
+    const bool last = (s == ns - 1);             // of the row's ns splits, whose first is item `row_item`
     const Xbuf x1(p.p1);
 
     const float *cs = rope;                 // [HD/2] cos, filled at kernel start
@@ -1538,7 +1605,7 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
             L += f;
             A = fmaf(vn[c], f, A);
         }
-        const uint32_t dst = (uint32_t)(((b * p.nq + team * G + g) * p.NS + s) * PS);
+        const uint32_t dst = (uint32_t)((row_item * p.nq + (team * G + g) * ns + s) * PS);
         if (c == 0) {
             x2.st(dst, M, stamp);
             x2.st(dst + 1, L, stamp);
@@ -1601,7 +1668,7 @@ __device__ __forceinline__ void p3_load(const Params &p, const LayerPtrs &lp, in
 
 template <int HD, int BT, int MCW>
 __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, int tid0, int hq, int c3, int rs, uint32_t stamp, OutTile<HD> &tile,
-                                        float *smem)
+                                        float *smem, const int *row_items)
 {
     constexpr int PS = HD + kP2Stride;
     // (the thread index is made opaque here, so that what this phase derives from it is computed here and not kept from the start
@@ -1657,18 +1724,18 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
             }
             if (p.dbg_attn && c3 == 0 && rs == 0) p.dbg_attn[((size_t)b * p.nq + hq) * HD + c] = v;
         };
-        auto run = [&](auto nv_c, auto mc_c) {
+        auto run = [&](auto nv_c, auto mc_c, auto ragged_c) {
             constexpr int NV = decltype(nv_c)::value, MC = decltype(mc_c)::value;
-            const bool wide = p.NS > 32;                                  // more splits than half a wavefront: two loads
+            constexpr bool ragged = decltype(ragged_c)::value;            // the rows' splits by the table (an instance of its own: 0.3 us a layer)
             for (int v0 = 0; v0 < V; v0 += NT * NV) {
                 const int cv = min(NT * NV, V - v0);                      // a multiple of 64
                 const float rcv = reciprocal(cv);
-                const int SG = NV == 1 ? max(1, min(__builtin_amdgcn_readfirstlane(fdiv(NT, rcv)), p.NS)) : 1;
+                const int SG = NV == 1 ? max(1, min(__builtin_amdgcn_readfirstlane(fdiv(NT, rcv)), ragged ? p.TS : p.NS)) : 1;
                 const int sg = NV == 1 ? __builtin_amdgcn_readfirstlane(fdiv(tid, rcv)) : 0, v = tid - sg * cv;
                 if (sg < SG) {
                     float at[NV], wgt[NV];
                     uint32_t src[NV];
-                    int col[NV];
+                    int col[NV], ns[NV], most = ragged ? 1 : p.NS;    // splits of the value's row; most of them
 #pragma unroll
                     for (int n = 0; n < NV; ++n) {
                         at[n] = 0.f;
@@ -1676,9 +1743,17 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                         const int vi = min(v0 + v + n * NT, V - 1);        // a value past the end repeats the last one
                         const int b = vi / HD;
                         col[n] = vi - b * HD;
-                        src[n] = (uint32_t)((b * p.nq + hq) * p.NS * PS);
+                        ns[n] = p.NS;
+                        int row_item = b * p.NS;
+                        if constexpr (ragged) {
+                            row_item = __builtin_amdgcn_readfirstlane(row_items[b]);
+                            ns[n] = __builtin_amdgcn_readfirstlane(row_items[b + 1]) - row_item;
+                        }
+                        if (ragged) most = max(most, ns[n]);
+                        src[n] = (uint32_t)((row_item * p.nq + hq * ns[n]) * PS);
                     }
-                    for (int sb = sg; sb < p.NS; sb += MC * SG) {
+                    const bool wide = most > 32;                          // more splits than half a wavefront: two loads
+                    for (int sb = sg; sb < most; sb += MC * SG) {
                         const bool head = sb == sg;                       // the first round
                         Spin spin;
                         u32x2 vm[NV], vl[NV], va[NV][MC];
@@ -1686,7 +1761,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 #pragma unroll
                             for (int n = 0; n < NV; ++n) {
                                 if (head) {
-                                    const uint32_t o = src[n] + (uint32_t)min(wide ? lane : lane & 31, p.NS - 1) * PS;
+                                    const uint32_t o = src[n] + (uint32_t)min(wide ? lane : lane & 31, ns[n] - 1) * PS;
                                     vm[n] = x2.ld(o + (wide ? 0 : lane >> 5));
                                     vl[n] = vm[n];
                                     if (wide) vl[n] = x2.ld(o + 1);
@@ -1694,7 +1769,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 #pragma unroll
                                 for (int k = 0; k < MC; ++k) {
                                     const int s = sb + k * SG;            // (a load past the splits repeats one)
-                                    va[n][k] = x2.ld(src[n] + (uint32_t)(s < p.NS ? s : sb) * PS + kP2Stride + col[n]);
+                                    va[n][k] = x2.ld(src[n] + (uint32_t)(ragged ? min(s, ns[n] - 1) : s < ns[n] ? s : sb) * PS + kP2Stride + col[n]);
                                 }
                             }
                             __builtin_amdgcn_sched_barrier(0);
@@ -1712,7 +1787,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                             for (int n = 0; n < NV; ++n) {
                                 const float m = __builtin_bit_cast(float, vm[n].x);
                                 const float l = wide ? __builtin_bit_cast(float, vl[n].x) : __shfl(m, 32 + (lane & 31));
-                                const bool mine = lane < p.NS;            // (NS <= 32: lanes 32..63 hold sums)
+                                const bool mine = lane < ns[n];           // (up to 32 splits: lanes 32..63 hold sums)
                                 const float f = mine ? __builtin_amdgcn_exp2f(m - wave_max(mine ? m : kNegBig)) : 0.f;
                                 wgt[n] = f / wave_total(mine ? l * f : 0.f);
                             }
@@ -1723,7 +1798,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
                             for (int k = 0; k < MC; ++k) {
                                 const int s = sb + k * SG;                // (uniform)
                                 const float w = lane_of(wgt[n], s & 63);
-                                if (s < p.NS) at[n] = fmaf(__builtin_bit_cast(float, va[n][k].x), w, at[n]);
+                                if (s < ns[n]) at[n] = fmaf(__builtin_bit_cast(float, va[n][k].x), w, at[n]);
                             }
                     }
                     if (NV == 1 && SG > 1) {
@@ -1751,18 +1826,25 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
             }
         };
         using std::integral_constant;
-        if constexpr (BT > 4) {
-            if (V > 2 * NT)
-                run(integral_constant<int, 4>{}, integral_constant<int, 2>{});
-            else if (V > NT)
-                run(integral_constant<int, 2>{}, integral_constant<int, 4>{});
-            else
-                run(integral_constant<int, 1>{}, integral_constant<int, 8>{});
-        } else if (MCW > 4 && p.NS * V > 4 * NT) {                        // more than four splits per thread
-            run(integral_constant<int, 1>{}, integral_constant<int, MCW>{});
-        } else {
-            run(integral_constant<int, 1>{}, integral_constant<int, 4>{});
-        }
+        auto merge = [&](auto ragged_c) {
+            constexpr bool ragged = decltype(ragged_c)::value;
+            if constexpr (BT > 4) {
+                if (V > 2 * NT)
+                    run(integral_constant<int, 4>{}, integral_constant<int, 2>{}, ragged_c);
+                else if (V > NT)
+                    run(integral_constant<int, 2>{}, integral_constant<int, 4>{}, ragged_c);
+                else
+                    run(integral_constant<int, 1>{}, integral_constant<int, 8>{}, ragged_c);
+            } else if (MCW > 4 && (ragged ? row_items[p.B] * HD : p.NS * V) > 4 * NT) {      // more than four splits per thread
+                run(integral_constant<int, 1>{}, integral_constant<int, MCW>{}, ragged_c);
+            } else {
+                run(integral_constant<int, 1>{}, integral_constant<int, 4>{}, ragged_c);
+            }
+        };
+        if (kLayer && row_items)
+            merge(integral_constant<bool, kLayer>{});
+        else
+            merge(integral_constant<bool, false>{});
         // (MFMA tiles: what rows past the batch hold lands in rows of the product nobody reads)
         for (int e = V + tid; !MF && e < BT * HD; e += NT) as[e] = 0.f;
         lds_barrier();
@@ -2025,6 +2107,21 @@ struct MergeWide {
     static constexpr int n = STACK && BT == 1 && G <= 2 ? 4 : 8;
 };
 
+// LDS floats of phases 2 and 3: the same expressions as in lds_floats, where the host adds the table of the rows' first items.
+constexpr size_t p2_lds_floats(int hd, int g)
+{
+    const bool ma = hd == 128 && g >= 4;                                          // attention on MFMA tiles: a K tile per wavefront
+    return (size_t)hd + (size_t)(g + 2) * hd + 8 + 2 * (size_t)g * kWaves + (size_t)g * kWaves * hd +          // partials folded through LDS
+           (ma ? (size_t)kWaves * 32 * (hd + 8) / 2 + 2 * 256 * 4 : 0);           // K tiles, q operands
+}
+// merged attention rows, then the sums of the merge (one per thread) or, on MFMA tiles, the two halves of the product
+constexpr size_t p3_lds_floats(int hd, int bt)
+{
+    return mfma_tiles(bt) ? (size_t)out_operand_floats(hd) + (size_t)2 * bt * kOutChunk : (size_t)bt * hd + kThreads;
+}
+template <int HD, int G, int BT>
+constexpr size_t kRowTable = p2_lds_floats(HD, G) > p3_lds_floats(HD, BT) ? p2_lds_floats(HD, G) : p3_lds_floats(HD, BT);
+
 // One launch = n_layers decode steps in a row (1 for the plain entry points).  Layer l > 0 takes its weights and
 // caches from tab[l] and its input from the slots xslots, where the final reduction of layer l - 1 left its result;
 // the last layer writes `out`.  Nothing separates the layers but those slots: a workgroup goes on as soon as the
@@ -2097,7 +2194,7 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // and does not keep beyond its end.  With one reference for all phases more scalars were alive than there are registers,
     // and every one moved to a vector register's lane and back is an instruction each way, hundreds of them.
     const Params &p = kernarg_params();
-    const int n2 = p.B * p.NS;                       // attention items of the team
+    int n2 = p.B * p.NS;                             // attention items of the team
     const int n3 = G * (p.NC3 << p.LRS3);            // output-projection items of the team
     // (in a stack the thread index is made opaque per layer: everything derived from it would otherwise be computed
     // once in front of the loop over the layers and be kept in registers across all phases)
@@ -2113,13 +2210,17 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     const LayerPtrs &lp = (STACK && layer > 0) ? tab[layer] : *reinterpret_cast<const LayerPtrs *>(&p.wqkv);
     KvBuf<HD, G> kv;
     OutTile<HD> tile;
-    const int b_first = member < n2 ? qdiv(member, p.div_ns) : 0;     // batch row of the first attention item
-    const int pos_first = row_pos(p, b_first);
-    const int s_first = member < n2 ? member - b_first * p.NS : 0;
-    // (with positions per row the stream is set up only where phase 1 first needs it: the position comes from
-    // memory, and waiting for it here would hold up the first weight loads)
+    // the first attention item.  With positions per row the stream is set up only where phase 1 first needs it: the positions come from
+    // memory, and waiting for them here would hold up the first weight loads.
     const bool own_pos = kLayer && p.row_pos != nullptr;
-    P2Stream<HD, G> st2(p, lp, tl, team, b_first, s_first, own_pos ? 0 : p.pos, member < n2 && !own_pos);
+    int lens = 0;
+    RowItem ri;
+    ri.b = member < n2 ? qdiv(member, p.div_ns) : 0;
+    ri.s = member < n2 ? member - ri.b * p.NS : 0;
+    ri.ns = p.NS;
+    ri.first = ri.b * p.NS;
+    const int pos_first = row_pos(p, ri.b);
+    P2Stream<HD, G> st2 = P2Stream<HD, G>::planned(p, lp, tl, team, ri.b, ri.s, own_pos ? 0 : p.pos, member < n2 && !own_pos);
 
     // ---- phase 1 (projection); its last step already starts the K/V stream of phase 2
     EarlyQ<STACK ? 8 : 16> eq;
@@ -2127,14 +2228,27 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     P1Regs<HD, BT> rg_layer;
     P1Regs<HD, BT> &rgu = (STACK && P1Ahead<HD, G, BT>::n > 0) ? rg : rg_layer;
     const uint32_t stamp = p1_all<HD, G, BT, STACK, 0>(p, lp, tl, team, member, smem, s_rope, STACK ? layer : 0, xslots, n_layers, cnt0,
-                                             rgu, primed, [&](int stage) {
-                                                 if (own_pos) st2 = P2Stream<HD, G>(p, lp, tl, team, b_first, s_first, pos_first, member < n2);
+                                             rgu, primed, lens, [&](int stage) {
+                                                 // (here, where two batches of weights are in flight: in front of the first one it
+                                                 // delayed the second, 0.8 us with 16 rows)
+                                                 if (kLayer && !STACK && p.ragged)
+                                                     ri = deal_rows<HD>(p, tl & 63, (tl & 15) < p.B ? min(max(lens, 0), p.pos) : 0, member, ri);
+                                                 if (kLayer && !STACK && ri.items)
+                                                     st2 = P2Stream<HD, G>(p, lp, tl, team, ri.b, ri.t0, ri.t1, ri.pos);
+                                                 else if (own_pos)
+                                                     st2 = P2Stream<HD, G>::planned(p, lp, tl, team, ri.b, ri.s, pos_first, member < n2);
                                                  st2.prefetch(kv, 0);
                                              });
+    const bool ragged = kLayer && !STACK && ri.items != 0;
+    if (ragged) n2 = ri.items;
+    // first items of the rows for the merge of phase 3, behind what the phases up to there hold in LDS (phase 1 is over in this
+    // workgroup: whoever took part in it has passed its last barrier)
+    int *row_items = reinterpret_cast<int *>(smem + kRowTable<HD, G, BT>);
+    if (ragged && tl <= kMaxRows) row_items[tl] = ri.table;
     // a first look at the team's q partials (in a stack only for one batch row and attention on the vector ALU: no
     // registers are left for the sixteen pairs there, they would be spilled as they arrive)
     if (member < n2 && !(STACK && (AttnMfma<HD, G>::on || BT > 1)))
-        eq.template issue<HD, G>(p, tl, team, qdiv(member, p.div_ns), NewTokenFirst<HD, G, BT>::selectors(s_first == p.NS - 1));
+        eq.template issue<HD, G>(p, tl, team, ri.b, NewTokenFirst<HD, G, BT>::selectors(ri.s == ri.ns - 1));
     st2.prefetch(kv, 1);
     CF_STAMP(1);
     // ---- phase 2 (attention); the last item already starts the W_o stream of phase 3
@@ -2166,18 +2280,20 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     if (member < n2) {
         for (int it = member;;) {
             const Params &q = kernarg_params();
-            const int b_it = qdiv(it, q.div_ns), next = it + q.TS;
+            const int next = it + q.TS;
             const bool more_items = next < n2;
             // stage 1: first half of the output-projection tile, stage 2: second half (early: stage 1 the second half)
-            p2_item<HD, G, BT>(q, layer_ptrs(q), tl, team, b_it, it - b_it * q.NS, stamp, it == member, st2, kv, eq, smem,
-                               s_rope + (kLayer && q.row_pos ? b_it * HD : 0), [&](int stage) {
+            p2_item<HD, G, BT>(q, layer_ptrs(q), tl, team, ri.b, ri.s, ri.ns, ri.first, stamp, it == member, st2, kv, eq, smem,
+                               s_rope + (kLayer && q.row_pos ? ri.b * HD : 0), [&](int stage) {
                 if (!more_items && (!EARLY || stage == 1)) p3_prefetch(EARLY ? 1 : stage - 1);
             });
             if (!more_items) break;
             it = next;
             const Params &qn = kernarg_params();
-            const int b_next = qdiv(it, qn.div_ns);
-            st2 = P2Stream<HD, G>(qn, layer_ptrs(qn), tl, team, b_next, it - b_next * qn.NS, row_pos(qn, b_next));
+            ri.b = qdiv(it, qn.div_ns);
+            ri.first = ri.b * qn.NS;
+            ri.s = it - ri.first;
+            st2 = P2Stream<HD, G>::planned(qn, layer_ptrs(qn), tl, team, ri.b, ri.s, row_pos(qn, ri.b));
             st2.prefetch(kv, 0);
             st2.prefetch(kv, 1);
         }
@@ -2193,12 +2309,13 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // (The tile of the first item is on its way, that of a further one is requested when the item before is done.  A load in front
     // of the merge for the items that need it is a second source of the tile's registers there: they were copied, and the copy
     // waited for the whole tile before the first poll went out.)
+    if (ragged) lds_barrier();               // (a member without an attention item has passed no barrier since its table)
     if (member < n3) {
         for (int it = member;;) {
             const Params &q = kernarg_params();
             int hq, c3, rs;
             p3_args(q, it, hq, c3, rs);
-            p3_item<HD, BT, MergeWide<HD, G, BT, STACK>::n>(q, layer_ptrs(q), tl, hq, c3, rs, stamp, tile, smem);
+            p3_item<HD, BT, MergeWide<HD, G, BT, STACK>::n>(q, layer_ptrs(q), tl, hq, c3, rs, stamp, tile, smem, ragged ? row_items : nullptr);
             it += q.TS;
             if (it >= n3) break;
             const Params &qn = kernarg_params();
@@ -2214,10 +2331,10 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     // (measured on the 7B shape, us per layer: this placement 36.5; both batches before the wait 37.6; the first
     // one already after the merge of the attention partials 37.7; none 37.6)
     if (AHEAD >= 1)
-        p1_all<HD, G, BT, STACK, 1>(kernarg_params(), lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
+        p1_all<HD, G, BT, STACK, 1>(kernarg_params(), lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, lens, no_next);
     final_reduce<(BT <= 4), STACK>(kernarg_params(), tl, stamp, smem, more ? xslots : nullptr, layer > 0 ? xslots : nullptr, [&]() {
         if (AHEAD >= 2)
-            p1_all<HD, G, BT, STACK, 2>(kernarg_params(), lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, no_next);
+            p1_all<HD, G, BT, STACK, 2>(kernarg_params(), lpn, tl, team, member, smem, s_rope, 0, nullptr, n_layers, cnt0, rg, more, lens, no_next);
     });
     primed = more;
     CF_STAMP(5);
@@ -2403,12 +2520,8 @@ size_t lds_floats(const Params &p, int hd, int g, int bt)
 {
     const size_t maxi = bt == 1 ? 4 : (bt <= 4 ? 2 : 1);
     const size_t f1 = x_lds_floats(hd, bt, p.RPS, wants_layer_kernel(p)) + maxi * kWaves * bt * hd + (size_t)kWaves * bt;
-    const bool ma = hd == 128 && g >= 4;                                          // attention on MFMA tiles: a K tile per wavefront
-    const size_t npart = kWaves;                                                  // attention partials folded through LDS
-    const size_t f2 = (size_t)hd + (size_t)(g + 2) * hd + 8 + 2 * (size_t)g * npart + (size_t)g * npart * hd +
-                      (ma ? (size_t)kWaves * 32 * (hd + 8) / 2 + 2 * 256 * 4 : 0);   // K tiles, q operands
-    // merged attention rows, then the sums of the merge (one per thread) or, on MFMA tiles, the two halves of the product
-    const size_t f3 = mfma_tiles(bt) ? (size_t)out_operand_floats(hd) + (size_t)2 * bt * kOutChunk : (size_t)bt * hd + kThreads;
+    const size_t table = p.ragged ? kMaxRows + 1 : 0;
+    const size_t f2 = p2_lds_floats(hd, g) + table, f3 = p3_lds_floats(hd, bt) + table;
     size_t f = f1 > f2 ? f1 : f2;
     return f > f3 ? f : f3;
 }

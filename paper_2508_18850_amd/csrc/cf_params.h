@@ -88,8 +88,16 @@ struct Params {
     float qk_scale_log2e;  // log2(e)/sqrt(head_dim)
     float eps;             // RMSNorm: added to the mean square
     uint32_t spin_ticks;   // wait limit in 100 MHz ticks (at most 42 s)
-    int reserved[10];
+    int ragged;            // rows of different lengths, at most one attention item per member: the kernel deals the items itself
+    int reserved[9];
 };
+
+// Tokens that the longest attention item has to get shorter by for the items to be dealt by the rows' lengths: 48 KB of keys and
+// values, what a compute unit streams in 1.5 us; dealing and a merge with splits of their own number cost up to 1 us.  The kernel looks
+// for it where a split of the plan is four times that long (finding out takes 0.2 us).  Us a layer, plan / dealt: Llama-3-8B shape, batch
+// 4, 5120 to 8192 tokens (1024 against 864 a member) 40.9 / 39.7, 8192 and three of 170 36.1 / 31.4; 16 heads of 64 over 8, batch 6,
+// 9000 and five of 190 29.9 / 24.4.  Dealt where it gains less: Llama-3-8B shape, batch 2, 6144 and 8192 (516 against 456) 33.9 / 34.3.
+constexpr int ragged_gain(int head_dim) { return 48 * 1024 / (4 * head_dim); }
 
 // A stack of layers in one launch: the pointers of every layer travel by value in the kernel's argument block, behind the
 // parameters of the first layer.

@@ -200,6 +200,42 @@ def test_rows_with_own_positions_match_oracle(name, shape, row_pos, packed, laye
     check_rows(res, ref, inp, row_pos, name)
 
 
+# Lengths so far apart that the kernel deals the attention items by them: every batch tile and width of the merge (values per
+# thread), more than 32 splits of a row, rows without a token, all rows shorter than the bound, as many members as rows and one more.
+DEALT = [
+    ("d128_g4_b4", cf_inputs.BlockShape("s", 512, 8, 2, 128, 10000.0, 52000), [3000, 5, 0, 700]),
+    ("d128_g1_b1", cf_inputs.BlockShape("s", 256, 32, 32, 128, 10000.0, 9000), [1000]),
+    ("d128_g2_b2", cf_inputs.BlockShape("s", 264, 2, 1, 128, 10000.0, 25000), [6000, 40]),
+    ("d128_g1_b9", cf_inputs.BlockShape("s", 512, 8, 8, 128, 500000.0, 2100), [2100, 1, 2, 3, 400, 0, 31, 32, 33]),
+    ("d128_g8_b16", cf_inputs.BlockShape("s", 264, 32, 4, 128, 10000.0, 2000), [2000] + [17 * b for b in range(15)]),
+    ("d128_g1_b16_17_members", cf_inputs.BlockShape("s", 264, 15, 15, 128, 10000.0, 1500), [40] * 15 + [1500]),
+    ("d64_g1_b5", cf_inputs.BlockShape("s", 520, 16, 16, 64, 10000.0, 4000), [4000, 10, 20, 30, 3999]),
+    ("d64_g2_b3", cf_inputs.BlockShape("s", 520, 16, 8, 64, 10000.0, 6500), [64, 6500, 65]),
+    ("d64_g8_b2", cf_inputs.BlockShape("s", 520, 16, 2, 64, 10000.0, 60000), [0, 0]),
+]
+
+
+@pytest.mark.parametrize("name,shape,row_pos", DEALT)
+def test_rows_of_very_different_lengths(name, shape, row_pos):
+    _log("dealt rows case %s pos=%s" % (name, row_pos))
+    batch, max_pos = len(row_pos), shape.kv_len
+    inp = cf_inputs.make_inputs(shape, seed=33, batch=batch, kv_len=max(row_pos))
+    for b, pos in enumerate(row_pos):                       # rows at and beyond a row's position are never read
+        inp["k_cache"][b, :, pos:] = np.nan
+        inp["v_cache"][b, :, pos:] = np.nan
+    # the bound is an argument of the plan; the caches have to hold it
+    grow = max_pos + 1 - inp["max_seq"]
+    if grow > 0:
+        for c in ("k_cache", "v_cache"):
+            inp[c] = np.concatenate([inp[c], np.full(inp[c].shape[:2] + (grow, shape.head_dim), np.nan, dtype=np.float16)], axis=2)
+        inp["max_seq"] = max_pos + 1
+    gamma = gamma_for(shape, 11)
+    res = run_rows(shape, batch, inp, row_pos, max_pos, gamma, 1e-5, True, True)
+    ref = orc.decode_rows(inp["x"], gamma, 1e-5, inp["w_qkv"], inp["w_o"], inp["k_cache"], inp["v_cache"], row_pos,
+                          shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.rope_base)
+    check_rows(res, ref, inp, row_pos, name)
+
+
 def test_rows_when_a_workgroup_handles_several_rows():
     """More (row, split) items than workgroups in a team: a workgroup goes from one row to another and has to
     rebuild its RoPE table for the other row's position."""
