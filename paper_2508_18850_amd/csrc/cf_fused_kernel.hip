@@ -34,6 +34,7 @@
 #include "cf_mfma_device.h"
 #include "cf_params.h"
 #include "cf_rope_device.h"
+#include "cf_stream_device.h"
 
 #include <cstddef>
 #include <type_traits>
@@ -60,28 +61,10 @@ constexpr float kNegBig = -1.0e30f;   // stands for "no score yet"; finite so th
 #endif
 constexpr bool kPrefetchNextLayer = CF_PREFETCH_NEXT_LAYER != 0;   // stack kernel: next layer's first weights during the tail
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));   // eight fp16 values = one 128-bit load
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Part of a read-only tensor that is streamed once: raw buffer resource + 128-bit non-temporal loads.  The buffer ends where
-// the part ends (a slice of rows, a split of the cached rows; 0 bytes: nothing to load), so that a load past it costs no
-// comparison: the hardware skips the access and returns zeros.  The whole offset is per lane, since the range check covers it
-// then.  (A comparison and a select per load, and a wave-uniform offset beside them, were five instructions a load.)
-constexpr uint32_t kNoLoad = 0x80000000u;      // beyond the end of any part: for a lane with nothing to load
-// Base and size are the same in all lanes; they are read from the first one, or the compiler, where it cannot see that, puts
-// a loop over the lanes' values around every load.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, uint32_t bytes)
-{
-    const uint64_t a = reinterpret_cast<uint64_t>(base);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>((uint64_t)hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
-}
-struct Stream {
-    __amdgpu_buffer_rsrc_t r;
-    __device__ __forceinline__ Stream(const void *base, uint32_t bytes) : r(buffer_of(base, bytes)) {}
-    __device__ __forceinline__ h8 ld(uint32_t off) const { return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 2)); }
-};
+using Stream = Part<2>;
 
 __device__ __forceinline__ void unpack8(const h8 &u, float (&f)[8])
 {
@@ -278,15 +261,6 @@ __device__ __forceinline__ float ll_sum(const Params &p, const Xbuf &x, uint32_t
         if (stale == 0 || spin.expired(p)) return s;
     }
 }
-
-// Division by a plan constant d, m = ceil(2^31 / d): the high half of 2 n m is n / d for n d < 2^31.  Integer division by a
-// run-time value costs some thirty instructions.
-__device__ __forceinline__ int qdiv(int n, uint32_t m) { return (int)__umulhi((uint32_t)n + (uint32_t)n, m); }
-__device__ __forceinline__ int qmod(int n, int d, uint32_t m) { return n - qdiv(n, m) * d; }
-// n / d for a divisor of this workgroup, r = 1 / d to within an ulp or two: n + 1/2 is 0.5 / d away from a multiple, so the
-// quotient is exact for n < 2^20.
-__device__ __forceinline__ float reciprocal(int d) { return __builtin_amdgcn_rcpf((float)d); }
-__device__ __forceinline__ int fdiv(int n, float r) { return (int)(((float)n + 0.5f) * r); }
 
 // First weight column of selector `sel` for a team: sel < G query heads, G = key, G+1 = value.
 // Tokens cached for batch row b == index of the row's new token (b is uniform over the workgroup).
@@ -741,6 +715,16 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{f[4], f[5], f[6], f[7]};
         }
     };
+    // cos / sin of this position while x is still on its way (the same for every layer of a stack)
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        const int e = tid + k * NT, eb = e / (HD / 2), i = e % (HD / 2);
+        if (!STACK && eb < (own_pos ? p.B : 1)) {      // (a stack builds the table once, in front of its layers)
+            const int pos_e = own_pos ? min(max(epos[k], 0), p.pos) : p.pos;
+            // (the frequency is computed here: a table in memory was one more cold page in front of the first wait)
+            rope_cos_sin(pos_e, rope_inv_freq(i, HD, p.rope_log2_base), rope[eb * HD + i], rope[eb * HD + HD / 2 + i]);
+        }
+    }
     // The slots carry the stamp of the previous layer.  A workgroup whose projection nobody waits for (no column block of its
     // own) may arrive here after its sources have moved on and stamped newer values: any stamp from the previous layer's up
     // to the last layer's of this launch is taken.
@@ -893,16 +877,6 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
                 load_rows(b0, k0);
                 square_rows(b0, k0);
             }
-    }
-    // cos / sin of this position while the first weights are still on their way (the same for every layer of a stack)
-#pragma unroll
-    for (int k = 0; k < NE; ++k) {
-        const int e = tid + k * NT, eb = e / (HD / 2), i = e % (HD / 2);
-        if (!STACK && eb < (own_pos ? p.B : 1)) {      // (a stack builds the table once, in front of its layers)
-            const int pos_e = own_pos ? min(max(epos[k], 0), p.pos) : p.pos;
-            // (the frequency is computed here: a table in memory was one more cold page in front of the first wait)
-            rope_cos_sin(pos_e, rope_inv_freq(i, HD, p.rope_log2_base), rope[eb * HD + i], rope[eb * HD + HD / 2 + i]);
-        }
     }
     lds_barrier();
     CF_STAMP(2);            // x staged

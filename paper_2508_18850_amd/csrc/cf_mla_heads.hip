@@ -20,9 +20,11 @@
 //   -- hand-over: the heads' partials
 //   E2  sum over heads     every workgroup: 1/W of the output columns (the paper's atomicAdd)
 //
-// DeepSeek-V2-Lite shape, 4096 rows, weights and rows from memory: 21.7 us a step (22.6 with shuffles between lanes instead
+// DeepSeek-V2-Lite shape, 4096 rows, weights and rows from memory: 21.1 us a step (21.9 with conditions around loads, which waited
+// for the first load of a group before the next went out, and with both batches of rows requested in front of the product that
+// needs W_Up: a wavefront stands still while its loads are accepted; 22.6 with shuffles between lanes instead
 // of permlane swaps; 27.9 with five hand-overs: partial
-// sums of the projections, latent query, partials, partial a_i, partial out); 100 rows 17.6 us.  Stages (with shuffles), us from kernel
+// sums of the projections, latent query, partials, partial a_i, partial out); 100 rows 17.5 us (18.6), 16000 rows 35.4 (46.7).  Stages (with shuffles), us from kernel
 // start, mean over workgroups: projections posted 3.0, q arrived 6.4, latent query ready 8.9, rows used 11.5, partial
 // folded 13.9, D posted 15.0, a_i ready 17.6, partial out posted 18.4, end 19.9.  Between the hand-overs a compute unit
 // is bound by what it loads (64 KB of A, 131 KB of W_Up, 295 KB of rows, 131 KB of W_Down): requesting W_Up or the rows
@@ -31,6 +33,7 @@
 #include "cf_lanes_device.h"
 #include "cf_mla_internal.h"
 #include "cf_rope_device.h"
+#include "cf_stream_device.h"
 #include "cf_team_device.h"
 
 namespace {
@@ -50,7 +53,9 @@ constexpr int PSTR = L + 8;         // floats of a wavefront's attention partial
 constexpr size_t kDynLds = (size_t)NW * PSTR * sizeof(float);   // also [NW][L] sums of B, [NW][128] of D, 512 + [NW][128] of E1
 constexpr float kNegBig = -1.0e30f;
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+using cf::h8;
+using cf::kNoLoad;
+using Weights = cf::Part<0>;
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 
 
@@ -119,18 +124,23 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
     size_t col = 0;
     unsigned long long launches;
     {
-        const int qv = CQq / 8, P = qv + LR / 8, T = (P + 7) / 8;
-        const int t = w % T, sl = w / T;
-        const int pl = tid & 7, row = sl * a.rows + (tid >> 3) * 8;   // piece of the tile; first of the thread's eight rows
-        const int piece = 8 * t + pl;
-        const bool live = sl < a.ksa && piece < P && (tid >> 3) * 8 < a.rows && row < a.D;     // (rows, D: multiples of eight)
-        const bool isq = piece < qv;
-        const size_t ld = isq ? qv : LR / 8;                          // row stride in pieces
-        const h8 *wp = reinterpret_cast<const h8 *>(isq ? a.wq : a.wkv) + (live ? (size_t)row * ld + (isq ? piece : piece - qv) : 0);
-        const h8 xv = *reinterpret_cast<const h8 *>(a.x + (live ? row : 0));
+        // tiles of W_Q first, then the nine of W_KV, each matrix with whole tiles of its own
+        const int sl = cf::qdiv(w, a.div_t), t = w - sl * a.tiles;
+        const bool isq = t < a.tiles - LR / 64;
+        const int tk = isq ? t : t - (a.tiles - LR / 64), cols = isq ? CQq : LR;    // tile and width of the matrix
+        const int pl = tid & 7, rl = (tid >> 3) * 8;                  // piece of the tile; first of the thread's eight rows of the slice
+        const int nrows = sl < a.ksa ? min(a.rows, a.D - sl * a.rows) : 0;          // (rows, D: multiples of eight)
+        const uint32_t ld = (uint32_t)cols * 2;
+        const Weights W((isq ? a.wq : a.wkv) + (size_t)(sl * a.rows) * cols, (uint32_t)nrows * ld), X(a.x + sl * a.rows, (uint32_t)nrows * 2);
+        uint32_t off = 64 * tk + 8 * pl < cols ? (uint32_t)rl * ld + (64 * tk + 8 * pl) * 2 : kNoLoad;
+        const h8 xv = X.ld(rl * 2);
         h8 wr[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) wr[k] = wp[live ? k * ld : 0];
+        for (int k = 0; k < 8; ++k) {
+            wr[k] = W.ld(off);
+            off += ld;
+        }
+        __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)"
                      : "=s"(launches)
                      : "s"(a.counters + (size_t)w * kCounterStride)
@@ -146,14 +156,12 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
         for (int k = 0; k < 8; ++k)
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc[c] = fmaf((float)xv[k], (float)wr[k][c], acc[c]);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[c] = live ? acc[c] : 0.f;
         float fold[1];                                                // over the wavefront's rows; a lane keeps column lane / 8
         lanes::fold8<8>(acc, fold);
         s_part[wv * 64 + pl * 8 + (lane >> 3)] = fold[0];
         lds_sync();
-        mycol = tid < 64 && sl < a.ksa && 64 * t + tid < P * 8;
-        col = (size_t)sl * CQ + 64 * t + tid;
+        mycol = tid < 64 && sl < a.ksa && 64 * tk + tid < cols;
+        col = (size_t)sl * CQ + (isq ? 0 : CQq) + 64 * tk + tid;
         if (mycol)
 #pragma unroll
             for (int w8 = 0; w8 < NW; ++w8) colsum += s_part[w8 * 64 + tid];
@@ -165,18 +173,17 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
     MLA_STAMP(1);           // A done
 
     // ---- B: the whole of W_Up[head] (row = nope dimension): thread = 16-byte piece `lane` of the rows wv, wv + 8, ...
-    //      The weights and the first cached rows do not wait for the query: they are requested behind the put.
+    //      The weights do not wait for the query: they are requested behind the put.
     h8 wup[16];
+    {
+        const Weights W(a.wup + (size_t)head * a.n * L, (uint32_t)a.n * L * 2);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int row = wv + 8 * k;
-        wup[k] = row < a.n ? *reinterpret_cast<const h8 *>(a.wup + ((size_t)head * a.n + row) * L + lane * 8) : h8{0, 0, 0, 0, 0, 0, 0, 0};
+        for (int k = 0; k < 16; ++k) wup[k] = W.ld((uint32_t)(wv + 8 * k) * L * 2 + lane * 16);
     }
     // Cached rows of this member.  A row is handled by 16 lanes (a wavefront takes four rows at a time): lane li of a row
     // group owns the latent dimensions 128 k + 8 li .. + 8 (k < 4) and the rotary dimensions 4 li .. + 4, so a row's score
     // needs only the four in-row steps of a cross-lane sum and one exponential serves 36 multiply-adds.  UR rows per row
-    // group and batch, two batches in flight; rows past the member's range are read from its last row (finite data) and
-    // count for nothing.
+    // group and batch, two batches in flight; rows past the member's range are zeros and count for nothing.
     constexpr int UR = 4, RPB = NW * 4;                               // rows of the workgroup per step of a batch
     constexpr int step = RPB * UR;
     const int tps = (a.pos + TS - 1) / TS;
@@ -185,15 +192,17 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
     h8 kl[2][UR][4];
     h4 kr[2][UR];
     auto request = [&](int buf, int t) {
+        __builtin_amdgcn_sched_barrier(0);                            // (behind the last use of the registers)
+        const Weights rows(a.cache + (size_t)t * LR, (uint32_t)min(max(t1 - t, 0), step) * LR * 2);
 #pragma unroll
         for (int u = 0; u < UR; ++u) {
-            const uint16_t *row = a.cache + (size_t)max(min(t + myrow + u * RPB, t1 - 1), 0) * LR;
+            const uint32_t off = (uint32_t)(myrow + u * RPB) * LR * 2;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) kl[buf][u][k] = *reinterpret_cast<const h8 *>(row + 128 * k + 8 * li);
-            kr[buf][u] = *reinterpret_cast<const h4 *>(row + L + 4 * li);
+            for (int k = 0; k < 4; ++k) kl[buf][u][k] = rows.ld(off + 256 * k + 16 * li);
+            kr[buf][u] = __builtin_bit_cast(h4, __builtin_amdgcn_raw_buffer_load_b64(rows.r, off + 2 * L + 8 * li, 0, 0));
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
-    request(0, t0);
     {
         const int cnt1 = nr + (last ? LR : 0);                        // q of this head; the last member: the new row too
         for (int i = tid; i < cnt1; i += NT) {
@@ -218,6 +227,7 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
                 s_new[i - nr] = v;
         }
     }
+    request(0, t0);
     lds_sync();
     MLA_STAMP(2);           // q arrived
     {
@@ -230,7 +240,6 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc[c] = fmaf(qn, (float)wup[k][c], acc[c]);
         }
-        request(1, t0 + step);                                        // the registers of W_Up are free
         float *dst = s_part + wv * L + lane * 8;
         *reinterpret_cast<float4 *>(dst) = make_float4(acc[0], acc[1], acc[2], acc[3]);
         *reinterpret_cast<float4 *>(dst + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
@@ -252,6 +261,7 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
         s_q[tid] = sum;
         lds_sync();
     }
+    request(1, t0 + step);                                            // the registers of W_Up are free
     MLA_STAMP(3);           // query ready
     if (j == 0)                                                       // for cf_mla_debug_export: (q_lat | q_rope) of this head
         for (int i = tid; i < LR; i += NT) a.qdbg[(size_t)head * LR + i] = s_q[i];
@@ -312,7 +322,7 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
         }
     };
     int tt = t0;
-    if (t1 > t0) use(0, tt);                                          // (uniform; an empty range has read a row that may hold anything)
+    if (t1 > t0) use(0, tt);                                          // (uniform)
     for (; tt + 2 * step < t1; tt += 2 * step) {                      // uniform over the workgroup
         request(0, tt + 2 * step);
         use(1, tt + step);
@@ -323,10 +333,16 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
     //      piece tid % 16 of the rows tid / 16, + 32, ...
     const int pcD = tid % 16, rowD = tid / 16;
     h8 wdn[16];
+    {
+        const Weights W(a.wdown + (size_t)head * L * a.v, (uint32_t)L * a.v * 2);
+        uint32_t off = 8 * pcD < a.v ? (uint32_t)rowD * a.v * 2 + pcD * 16 : kNoLoad;
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
-        wdn[k] = pcD < a.v / 8 ? *reinterpret_cast<const h8 *>(a.wdown + ((size_t)head * L + rowD + 32 * k) * a.v + pcD * 8)
-                               : h8{0, 0, 0, 0, 0, 0, 0, 0};
+        for (int k = 0; k < 16; ++k) {
+            wdn[k] = W.ld(off);
+            off += 64 * a.v;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
     if (tt + step < t1) use(1, tt + step);
     MLA_STAMP(4);           // rows consumed
     // The four row groups of a wavefront are merged in registers: a swap of half-wavefronts (then of rows of 16 lanes)
@@ -429,11 +445,12 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
     const int pcE = tid % 16, rgE = tid / 16, pieceE = j * pcsE + pcE;  // 32 row groups
     const bool liveE = pcE < pcsE && pieceE < dpE;
     h8 wor[4];
+    {
+        const Weights W(a.wo + (size_t)head * a.v * a.D, (uint32_t)a.v * a.D * 2);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {                                      // v <= 128: at most four rows per thread
-        const int row = rgE + 32 * k;
-        wor[k] = (liveE && row < a.v) ? *reinterpret_cast<const h8 *>(a.wo + ((size_t)head * a.v + row) * a.D + pieceE * 8)
-                                      : h8{0, 0, 0, 0, 0, 0, 0, 0};
+        for (int k = 0; k < 4; ++k)                                    // v <= 128: at most four rows per thread
+            wor[k] = W.ld(liveE ? (uint32_t)(rgE + 32 * k) * a.D * 2 + pieceE * 16 : kNoLoad);
+        __builtin_amdgcn_sched_barrier(0);
     }
     // For cf_mla_debug_export: the member's partial in the latent space, 2 KB on its way while the others' partials arrive.
     // (It costs no time here: without it 22.8 us a step, behind the last poll 22.9, here 22.6 - the polls start a little later
@@ -506,8 +523,8 @@ __global__ void __launch_bounds__(NT) fused_mla_heads(const cf::mla::HeadsArgs a
     // ---- E2: sum over the heads (what the paper does with atomicAdd), columns [CW*w, +CW) of the output: thread = (head,
     //      column), one poll each; the heads of a column are added in order by one thread
     {
-        const int CW = (a.D + a.W - 1) / a.W;                          // <= 8
-        const int h = tid / CW, c = CW * w + tid % CW;
+        const int CW = a.CW;                                           // <= 8
+        const int h = cf::qdiv(tid, a.div_cw), c = CW * w + tid - h * CW;
         if (h < a.nh && c < a.D) s_in[tid] = take1(x, r, a.x6 + (size_t)h * a.D + c);
         lds_sync();
         if (h == 0 && c < a.D) {

@@ -22,6 +22,8 @@ struct HeadsArgs {
     size_t x1, x3, x6;              // first slot of each exchange area
     int D, nh, n, v, pos, W;
     int ksa, rows;                  // row slices of the projections, rows per slice (a multiple of eight)
+    int tiles, CW;                  // 64-column tiles of W_Q and W_KV, output columns per workgroup
+    uint32_t div_t, div_cw;         // ceil(2^31 / d) of both
     float scale_log2e;              // log2(e) / sqrt(nope_dim + rope_dim)
     double log2_base;
     long long spin_ticks;
