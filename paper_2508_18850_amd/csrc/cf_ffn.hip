@@ -7,9 +7,9 @@
 // the counterpart of the decode block's sum over heads.
 //
 // All three matrices are stored [d_ff, d_model] (row f = hidden unit f), so hidden unit f is one contiguous row in
-// each of them.  Workgroup w owns the hidden units [w F / W, (w + 1) F / W):
+// each of them.  Workgroup w owns about F / W hidden units in a row (first_unit):
 //   A  h_f = W1[f] . z, u_f = W2[f] . z for its units: a row is read in 512-column pieces, one piece per wavefront
-//      step (64 lanes x 16 bytes, contiguous), the pieces of all rows dealt round-robin to the eight wavefronts;
+//      step (64 lanes x 16 bytes, contiguous), the pieces of all rows taken by the eight wavefronts as they come to them;
 //      fp16 x fp16 products accumulated in fp32 (v_dot2_f32_f16), summed over the wavefront and, through LDS,
 //      over the pieces of a row in a fixed order;  g_f = sigma(h_f) u_f
 //   B  partial out = sum over its units of g_f W3[f]: thread t owns eight columns (and eight more per further
@@ -17,10 +17,15 @@
 //      workgroup is needed
 //   C  every workgroup adds, in workgroup order, the partials of its own d_model / W output columns and writes fp16.
 // The first rows of W3 are requested before the last pieces of stage A are consumed, so the memory pipe does not
-// drain at the stage boundary.  All waits are bounded (CF_ETIMEOUT); all workgroups have to be resident at once.
+// drain at the stage boundary.  What bounds it is memory: of 45.4 us a layer at 4096 x 11008 (270.5 MB, 5.95 TB/s) the first 5 pass until
+// the first batch is there, the last 5 go to the hand-over.  More in flight is no faster: W3 rows requested by wavefronts that are
+// done early hold up the others' pieces (two batches of 4 / 2 rows 45.2 / 45.7; in an earlier order of the
+// pieces two of 4 / two of 8 / four of 8 46.4 / 46.8 / 48.4).
+// All waits are bounded (CF_ETIMEOUT); all workgroups have to be resident at once.
 #include "../../include/cfdecode.h"
 #include "cf_lanes_device.h"
 #include "cf_mfma_device.h"
+#include "cf_stream_device.h"
 #include "cf_team_device.h"
 
 #include <cmath>
@@ -39,9 +44,10 @@ constexpr int kMaxBatch = 16;          // the batch of Appendix C
 constexpr int kVectorBatch = 4;        // the largest batch of the vector-unit kernel
 constexpr int kTilesFrom = 2;          // from this batch on the MFMA kernel runs where the shape allows it (measured:
                                        // Llama-2-7B shape, batch 1 / 2 / 4: 46.5 / 52.3 / 75.2 us against 47.8 / 47.8 / 49.0)
+constexpr size_t kLdsLimit = 160 * 1024 - 256;
 constexpr int kNC = 16;                // MFMA kernel: column slices of the output (workgroups per slice of hidden units)
 constexpr int kStageRow = 256 + 8;     // MFMA kernel: row stride (fp16 values) of a wavefront's staging area in LDS
-constexpr uint32_t kNoLoad = 0x80000000u;
+using cf::kNoLoad;
 
 using cf::mfma::f32x4;
 using cf::mfma::h8;
@@ -57,11 +63,25 @@ struct FfnArgs {
     uint32_t *err;
     int D, F, B, W, act;
     int nrmax;                         // most hidden units a workgroup owns
+    int uneven;                        // workgroups of odd index own fewer units (first_unit)
+    uint32_t div_nck;                  // pieces of a row as a divisor (cf::qdiv)
     long long spin_ticks;
     // MFMA kernel only
     size_t xg, xp;                     // first slot of g [d_ff][B] and of the partial outputs [NF][B][D]
     int NF, CW, nRp;                   // slices of hidden units; columns per column slice; units of a slice, padded to 32
 };
+
+// First hidden unit of workgroup w (vector kernel).  Workgroup w runs on die w % 8, and the odd dies get 3 to 10 % less memory
+// bandwidth than the even ones: of the units of two neighbours the even one takes 524 of 1024.  Us a layer, even share 50.0 / 51.2 /
+// 52.4 %: 4096 x 11008 46.2 / 45.75 / 46.0, 4096 x 14336 57.1 / 57.0 / 57.5, 8192 x 28672 211.3 / 209.6 / 209.7.
+constexpr int kEvenShare = 524;
+__host__ __device__ inline int even_units(int pair) { return (pair * kEvenShare + 512) >> 10; }
+__host__ __device__ inline int first_unit(int w, int F, int W, int uneven)
+{
+    if (!uneven) return (int)((long long)w * F / W);
+    const int p0 = (int)((long long)(w & ~1) * F / W);
+    return w & 1 ? p0 + even_units((int)((long long)(w + 1) * F / W) - p0) : p0;
+}
 
 struct Stream {
     __amdgpu_buffer_rsrc_t r;
@@ -117,6 +137,18 @@ __device__ __forceinline__ unsigned long long launches_before(const FfnArgs &a, 
     return a.counters[(size_t)w * kCounterStride];
 }
 
+// Stage time stamps of every workgroup, only in builds with -DCF_STAMPS=1 (the profiling library).
+#ifndef CF_STAMPS
+#define CF_STAMPS 0
+#endif
+#if CF_STAMPS
+constexpr int kFfnStamps = 16;
+__device__ unsigned long long g_ffn_ts[256 * kFfnStamps];
+#define FFN_STAMP(k) do { if (threadIdx.x == 0) s_ts[k] = wall_clock64(); } while (0)
+#else
+#define FFN_STAMP(k)
+#endif
+
 template <int BT, int NCB>     // batch tile; column blocks of 4096 per thread (d_model <= 4096 NCB)
 __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
 {
@@ -124,9 +156,14 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
     const int tid = threadIdx.x, lane = tid & 63, w = blockIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int D = a.D, B = a.B;
+#if CF_STAMPS
+    __shared__ unsigned long long s_ts[kFfnStamps];
+    if (tid < kFfnStamps) s_ts[tid] = 0;
+#endif
+    FFN_STAMP(0);
     const int NCK = (D + kChunk - 1) / kChunk;                    // pieces of a row
     const int Dp = NCK * kChunk;
-    const int r0 = (int)((long long)w * a.F / a.W), r1 = (int)((long long)(w + 1) * a.F / a.W), nr = r1 - r0;
+    const int r0 = first_unit(w, a.F, a.W, a.uneven), nr = first_unit(w + 1, a.F, a.W, a.uneven) - r0;
     const int NU = nr * NCK;                                      // (row, piece) units of this workgroup, per matrix
     // LDS: z as fp16 [BT][Dp]; partial dot products [2][BT][nrmax][NCK]; g [BT][nrmax]
     _Float16 *z16 = reinterpret_cast<_Float16 *>(smem);
@@ -140,24 +177,35 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
     const uint32_t wbytes = (uint32_t)((size_t)a.F * D * 2);
     const Stream W1(a.w1, wbytes), W2(a.w2, wbytes), W3(a.w3, wbytes);
 
-    // ---- stage A.  Units q = wv, wv + 8, ... of this wavefront; unit q is piece q % NCK of row q / NCK.
+    // ---- stage A.  Unit q is piece q % NCK of row q / NCK.  A batch is U units, every eighth: the batches a workgroup has in flight
+    //      then cover adjacent pieces (U adjacent pieces per wavefront: 0.5 % slower).  The wavefronts take the batches as they come
+    //      to them, from a counter in LDS: dealt beforehand, the first wavefront was done 6 us before the last, since the memory pipe
+    //      serves the oldest one first.  Every (row, piece) has a place of its own for its sum, so who takes it changes no bit.
     constexpr int U = 4;                                          // units per batch of loads (two loads each)
+    __shared__ int s_next;
+    const int NB = (NU + NW * U - 1) / (NW * U) * NW;
     struct Cursor {
         int r, c;                                                 // row (local), piece
     };
-    // a wavefront's next unit is eight units on: branch-free (loads inside branches would make every later
-    // wait for a load drain the queue)
-    const int dr = NW / NCK, dc = NW % NCK;
-    auto advance = [&](Cursor &k) {
+    auto cursor = [&](int batch) {
+        const int q = batch / NW * (NW * U) + batch % NW, r = cf::qdiv(q, a.div_nck);
+        return Cursor{r, q - r * NCK};
+    };
+    const int dr = cf::qdiv(NW, a.div_nck), dc = NW - dr * NCK;
+    auto advance = [&](Cursor &k) {                               // eight units on, branch-free
         k.c += dc;
         k.r += dr;
         const bool wrap = k.c >= NCK;
         k.c -= wrap ? NCK : 0;
         k.r += wrap ? 1 : 0;
     };
-    Cursor lc = {wv / NCK, wv % NCK};
-    Cursor cc = lc;
-    auto load = [&](h8(&p1)[U], h8(&p2)[U], uint32_t dep) {
+    auto grab = [&]() {
+        int t = 0;
+        if (lane == 0) t = __hip_atomic_fetch_add(&s_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return __builtin_amdgcn_readfirstlane(t);
+    };
+    auto load = [&](h8(&p1)[U], h8(&p2)[U], int batch, uint32_t dep) {
+        Cursor lc = cursor(batch);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool live = lc.r < nr && lc.c * kChunk + lane * 8 < D;
@@ -169,7 +217,9 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
         }
     };
     h8 a1[U], a2[U], b1[U], b2[U];
-    load(a1, a2, 0u);
+    int ta = wv, tb = wv + NW;                                    // the batches in flight
+    load(a1, a2, ta, 0u);
+    if (tid == 0) s_next = 2 * NW;
     // z of every batch row -> LDS as it is (fp16), zero past d_model and past the batch
     for (int i = tid; i < BT * Dp / 8; i += NT) {
         const int b = i / (Dp / 8), c8 = i - b * (Dp / 8);
@@ -177,10 +227,11 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
         if (b < B && c8 * 8 < D) v = *reinterpret_cast<const uint4 *>(a.z + (size_t)b * D + c8 * 8);
         *reinterpret_cast<uint4 *>(z16 + (size_t)b * Dp + c8 * 8) = v;
     }
-    load(b1, b2, 0u);
+    load(b1, b2, tb, 0u);
     lds_barrier();
 
-    auto consume = [&](const h8(&p1)[U], const h8(&p2)[U]) -> uint32_t {
+    auto consume = [&](const h8(&p1)[U], const h8(&p2)[U], int batch) -> uint32_t {
+        Cursor cc = cursor(batch);
         float keep = 0.f;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -205,7 +256,7 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
     };
 
     // ---- stage B set-up: thread t owns columns 8 t + 4096 cb
-    constexpr int UB = 8;                                         // rows of W3 per batch of loads
+    constexpr int UB = 4;                                         // rows of W3 per batch of loads
     auto load3 = [&](h8(&p3)[NCB][UB], int row0, uint32_t dep) {
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
@@ -218,18 +269,21 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
     };
     h8 t3a[NCB][UB], t3b[NCB][UB];
 
-    const int nsteps = (NU + NW * U - 1) / (NW * U);             // batches of this wavefront (the same for all)
-    const int nsteps2 = max(2, (nsteps + 1) & ~1);
-    for (int k = 0; k + 2 < nsteps2; k += 2) {
-        const uint32_t d0 = consume(a1, a2);
-        load(a1, a2, d0);
-        const uint32_t d1 = consume(b1, b2);
-        load(b1, b2, d1);
+    for (int k = 0;; ++k) {
+        const int na = grab();                                        // (ascending: from the first one past the end on all are)
+        const uint32_t d0 = consume(a1, a2, ta);
+        if (k == 0) FFN_STAMP(1);                                 // first batch consumed
+        if (na >= NB) break;
+        load(a1, a2, na, d0);
+        const int nb = grab();
+        const uint32_t d1 = consume(b1, b2, tb);
+        load(b1, b2, nb, d1);
+        ta = na, tb = nb;
     }
     load3(t3a, 0, 0u);                                            // the first rows of W3, before the tail of stage A
-    consume(a1, a2);
+    consume(b1, b2, tb);
     load3(t3b, UB, 0u);
-    consume(b1, b2);
+    FFN_STAMP(2);           // products of stage A done (this wavefront)
     lds_barrier();
     // pieces of a row in piece order; activation; g
     for (int e = tid; e < BT * nr; e += NT) {
@@ -242,6 +296,7 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
         gl[b * a.nrmax + r] = b < B ? activate(h, a.act) * u : 0.f;
     }
     lds_barrier();
+    FFN_STAMP(3);           // g ready
 
     // ---- stage B
     float acc[BT][NCB][8];
@@ -283,6 +338,7 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
         const uint32_t d1 = consume3(t3b, row0 + UB);
         load3(t3b, row0 + 3 * UB, d1);
     }
+    FFN_STAMP(4);           // products of stage B done (this wavefront)
     // ---- the partial output of this workgroup.  A thread holds eight adjacent columns; stored from there, one store
     //      instruction would touch 64 lines with 8 bytes each.  The values pass through LDS (4096 columns at a time) so
     //      that consecutive lanes write consecutive slots.
@@ -303,6 +359,7 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
             }
         }
 
+    FFN_STAMP(5);           // partial output published
     lds_barrier();              // stage C reuses the front of LDS
     // ---- stage C: columns [c0, c0 + ncol) of every batch row, summed over the workgroups in workgroup order
     const int cpw = (D + a.W - 1) / a.W;
@@ -350,19 +407,12 @@ __global__ void __launch_bounds__(NT) fused_ffn(const FfnArgs a)
         }
     }
     if (tid == 0) a.counters[(size_t)w * kCounterStride] = cnt;
-}
-
-// Stage time stamps of every workgroup, only in builds with -DCF_STAMPS=1 (the profiling library).
-#ifndef CF_STAMPS
-#define CF_STAMPS 0
-#endif
+    FFN_STAMP(6);
 #if CF_STAMPS
-constexpr int kFfnStamps = 16;
-__device__ unsigned long long g_ffn_ts[256 * kFfnStamps];
-#define FFN_STAMP(k) do { if (threadIdx.x == 0) s_ts[k] = wall_clock64(); } while (0)
-#else
-#define FFN_STAMP(k)
+    lds_barrier();
+    if (tid < kFfnStamps && w < 256) g_ffn_ts[w * kFfnStamps + tid] = s_ts[tid];
 #endif
+}
 
 // ---------------------------------------------------------------------------------------------------------------------
 // Batch 2..16: the same block on matrix cores, with the work cut in two directions.  One partial output per workgroup
@@ -666,6 +716,7 @@ KernelFn pick_tiles(int nrmax, int d_model)
 struct cf_ffn_s {
     cf_ffn_config cfg;
     int W = 0, nrmax = 0;
+    int uneven = 0, nrmax_v = 0;       // vector kernel: first_unit, most units of a workgroup
     int NF = 0, CW = 0, nRp = 0;       // MFMA kernel (max_batch >= 2)
     size_t xg = 0, xp = 0, lds_tiles = 0;
     char *ws = nullptr;
@@ -705,10 +756,19 @@ int cf_ffn_create(const cf_ffn_config *cfg, cf_ffn *out)
     const int cpw = (c.d_model + W - 1) / W;
     const int vbatch = c.max_batch < kVectorBatch ? c.max_batch : kVectorBatch;
     if ((size_t)cpw * vbatch > (size_t)NT) return CF_EUNSUPPORTED;            // stage C: one thread per output value
+    // (uneven shares where workgroups come in whole rounds of the dies and the larger share still fits LDS)
+    int uneven = W % 8 == 0, nrmax_v = nrmax;
+    if (uneven) {
+        nrmax_v = even_units((c.d_ff + W / 2 - 1) / (W / 2));
+        nrmax_v = nrmax_v > nrmax ? nrmax_v : nrmax;
+        int top = 1;
+        while (top < vbatch) top *= 2;
+        if (lds_bytes_of(c, top, nrmax_v) > kLdsLimit) uneven = 0, nrmax_v = nrmax;
+    }
     for (int bt = 1; bt <= kVectorBatch; bt *= 2) {
         if (bt / 2 >= c.max_batch) break;
-        const size_t lds = lds_bytes_of(c, bt, nrmax);
-        if (lds > 160 * 1024 - 256) return CF_EUNSUPPORTED;
+        const size_t lds = lds_bytes_of(c, bt, nrmax_v);
+        if (lds > kLdsLimit) return CF_EUNSUPPORTED;
         int per_cu = 0;
         if ((lds > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(pick(bt, c.d_model)),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) ||
@@ -728,7 +788,7 @@ int cf_ffn_create(const cf_ffn_config *cfg, cf_ffn *out)
         const size_t staging = (size_t)NW * 16 * kStageRow * sizeof(uint16_t);
         lds_tiles = lds_tiles > staging ? lds_tiles : staging;
         int per_cu = 0;
-        if (lds_tiles > 160 * 1024 - 256 ||
+        if (lds_tiles > kLdsLimit ||
             hipFuncSetAttribute(reinterpret_cast<const void *>(pick_tiles(nrmax, c.d_model)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds_tiles) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(pick_tiles(nrmax, c.d_model)), NT,
@@ -741,6 +801,7 @@ int cf_ffn_create(const cf_ffn_config *cfg, cf_ffn *out)
     t->cfg = c;
     t->W = W;
     t->nrmax = nrmax;
+    t->uneven = uneven, t->nrmax_v = nrmax_v;
     t->NF = NF, t->CW = CW, t->nRp = nRp, t->lds_tiles = lds_tiles;
     t->xg = 0;
     t->xp = (size_t)c.d_ff * c.max_batch;
@@ -797,13 +858,16 @@ int cf_ffn_decode(cf_ffn t, int32_t batch, const void *z, const void *W1, const 
     a.err = t->err;
     a.D = t->cfg.d_model, a.F = t->cfg.d_ff, a.B = batch, a.W = t->W, a.act = t->cfg.activation;
     a.nrmax = t->nrmax;
+    const int nck = (t->cfg.d_model + kChunk - 1) / kChunk;
+    a.div_nck = (uint32_t)((0x80000000ull + nck - 1) / nck);
     a.spin_ticks = t->spin_ticks;
     if (batch >= kTilesFrom && t->lds_tiles) {
         a.xg = t->xg, a.xp = t->xp, a.NF = t->NF, a.CW = t->CW, a.nRp = t->nRp;
         hipLaunchKernelGGL(pick_tiles(t->nrmax, t->cfg.d_model), dim3(t->W), dim3(NT), t->lds_tiles, static_cast<hipStream_t>(stream), a);
     } else {
         const int bt = batch_tile(batch);
-        hipLaunchKernelGGL(pick(bt, t->cfg.d_model), dim3(t->W), dim3(NT), lds_bytes_of(t->cfg, bt, t->nrmax),
+        a.nrmax = t->nrmax_v, a.uneven = t->uneven;
+        hipLaunchKernelGGL(pick(bt, t->cfg.d_model), dim3(t->W), dim3(NT), lds_bytes_of(t->cfg, bt, t->nrmax_v),
                            static_cast<hipStream_t>(stream), a);
     }
     hipError_t e = hipGetLastError();

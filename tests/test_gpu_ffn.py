@@ -191,3 +191,24 @@ def test_wavefronts_that_share_a_piece_of_the_columns(d_model, d_ff, batch):
     """Both sides of 1024 columns (four wavefronts per piece / one each); one piece, which leaves half of the wavefronts without
     work; one to eight row tiles per workgroup."""
     _run(cf_inputs.FfnShape("f_s", d_model, d_ff), batch, 0, seed=240 + batch, scale_rows=True)
+
+
+@pytest.mark.parametrize("d_model,d_ff,batch", [(512, 255, 1), (8, 256, 1), (1544, 264, 1), (4096, 777, 1), (4104, 1032, 1), (7688, 513, 1),
+                                                (64, 200, 3), (264, 40000, 2)])
+def test_pieces_taken_from_a_counter(d_model, d_ff, batch):
+    """The vector kernel: one to sixteen pieces a row, fewer batches than wavefronts and a last one that is partly empty, workgroups
+    with one unit, pairs of workgroups with an odd number of units, workgroups that are no multiple of eight (equal shares).
+    The sums have places of their own, so two calls give the same bits."""
+    from paper_2508_18850_amd import FfnBlock
+    shape = cf_inputs.FfnShape("counter", d_model, d_ff)
+    _run(shape, batch, 0, seed=400 + d_ff, scale_rows=batch > 1, calls=2)
+    inp = cf_inputs.make_ffn_inputs(shape, seed=7, batch=batch)
+    t = {k: torch.from_numpy(inp[k]).to("cuda:0") for k in ("z", "w1", "w2", "w3")}
+    outs = [torch.full((batch, d_model), float("nan"), dtype=torch.float16, device="cuda:0") for _ in range(4)]
+    blk = FfnBlock(d_model, d_ff, batch, 0)
+    stream = torch.cuda.current_stream().cuda_stream
+    for out in outs:
+        blk.decode(batch, t["z"].data_ptr(), t["w1"].data_ptr(), t["w2"].data_ptr(), t["w3"].data_ptr(), out.data_ptr(), stream)
+    blk.status(stream)
+    blk.close()
+    assert all(torch.equal(out, outs[0]) for out in outs[1:])

@@ -25,3 +25,24 @@ def test_fdiv(d):
             rr = np.nextafter(rr, np.float32(np.inf if ulps > 0 else 0), dtype=np.float32)
         got = ((k.astype(np.float32) + np.float32(0.5)) * rr).astype(np.int64)
         assert np.array_equal(got, k // d), ulps
+
+
+def test_uneven_shares_of_the_hidden_units():
+    """FFN kernels: what neighbours own covers every unit once, the even one owns as many as the odd one or more, nobody owns none
+    or more than the host makes room for."""
+    def even_units(pair):
+        return (pair * 524 + 512) >> 10
+
+    def first_unit(w, F, W):
+        p0 = (w & ~1) * F // W
+        return p0 + even_units((w + 1) * F // W - p0) if w & 1 else p0
+
+    for W in (8, 16, 200, 256, 304):
+        for F in list(range(W, 3 * W + 1)) + [10 * W + 7, 11008, 14336, 28672, 40001]:
+            if F < W:
+                continue
+            first = [first_unit(w, F, W) for w in range(W + 1)]
+            share = [b - a for a, b in zip(first, first[1:])]
+            most = max(even_units((F + W // 2 - 1) // (W // 2)), -(-F // W))
+            assert first[0] == 0 and first[-1] == F and min(share) >= 1 and max(share) <= most
+            assert all(share[w] >= share[w + 1] for w in range(0, W, 2))
