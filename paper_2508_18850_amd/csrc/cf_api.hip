@@ -155,13 +155,23 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
         if (tps * (best - 1) > pos) tps = ceil_div(pos, best);
         p->TPS = tps > 0 ? tps : 1;
         p->TD = 0;
-        if (p->pairmap && best % 2 == 0 && TS % best == 0 && p->TPS >= 8 * h->balance_tokens) p->TD = h->balance_tokens;
+        // Splits of odd members, on the slower dies, are shorter: by 32 tokens to either side; by three in 64 where the cached rows are most
+        // of the work, splits of eight batches or more for every member.  Us a pass, half difference 0 / 32 / 64 / 96 / 128 / 192 /
+        // 256: 4096 tokens (Llama-3-8B shape, batch 16, 8192 rows) 105.1 / 104.5 / 104.2 / 104.2 / 104.1 / 103.6 / 104.0, 2048 (batch 8, two
+        // layers) 123.9 / 122.7 / 122.6 / 122.9 / 123.6, (Llama-2-7B shape, 16384 rows, two layers) 127.0 / 126.3 / 126.2 / 125.6 / 125.7.
+        // Not where members are without an item (batch 12, 0 / 192: 86.6 / 87.6) and not at head dimension 64 (4096 tokens 61.7 / 61.8, 16
+        // heads 52.9 / 53.1).
+        const bool uneven = p->pairmap && best % 2 == 0 && TS % best == 0;
+        auto is_long = [&](int t) { return uneven && hd == 128 && batch * best % TS == 0 && t >= 8 * 8 * rows_per_step; };
+        auto long_difference = [](int t) { return t / 64 * 3 / 32 * 32; };
+        if (uneven && p->TPS >= 8 * h->balance_tokens) p->TD = is_long(p->TPS) ? long_difference(p->TPS) : h->balance_tokens;
         // A workgroup walks its split in batches of 8 * rows_per_step cached rows.  When the rows divide into whole
         // batches per split, equal splits keep every workgroup at the same number of batches; the discount and the
-        // even/odd difference would push half of them into one more (measured: 0.2 - 0.6 us per step).
+        // even/odd difference would push half of them into one more (measured: 0.2 - 0.6 us per step; a half difference of 32 at 1024
+        // tokens, Llama-3-8B shape, batch 1, 32768 rows, six layers 236.4 -> 239.1 us).  A long split gains more from the difference.
         if (pos > 0 && pos % (best * 8 * rows_per_step) == 0) {
             p->TPS = pos / best;
-            p->TD = 0;
+            p->TD = is_long(p->TPS) ? long_difference(p->TPS) : 0;
         }
     }
     // output projection: G heads x NC3 column blocks x RS3 row splits per team.  A member walks its items chunk by chunk

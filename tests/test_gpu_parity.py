@@ -439,3 +439,16 @@ def test_longest_slices_of_head_dim_64(d_model, batch, workgroups):
     check(r.run(inp, 40, out_fill=float("nan")), oracle(inp, shape, 40), inp, 40, "D=%d" % d_model)
     _log("plan %s" % r.blk.plan())
     r.blk.close()
+
+
+# Splits of eight batches (2048 rows) or more at head dimension 128, one per member: the even ones are longer by three in 64.  Lengths that
+# divide into whole batches and that do not, the last length with the common difference, attention on the vector and the matrix units.
+@pytest.mark.parametrize("nq,batch,workgroups,kv_len", [(2, 1, 4, 4096), (8, 1, 4, 4096), (8, 2, 8, 4133), (2, 2, 8, 4030), (16, 5, 20, 6144)])
+def test_long_splits_of_different_length(nq, batch, workgroups, kv_len):
+    shape = cf_inputs.BlockShape("s", 264, nq, 2, 128, 10000.0, kv_len)
+    inp = cf_inputs.make_inputs(shape, seed=kv_len, batch=batch, kv_len=kv_len)
+    r = Runner(shape, batch, inp["max_seq"])
+    r.blk.set_tuning(workgroups=workgroups, kv_splits=2)
+    check(r.run(inp, kv_len, out_fill=float("nan")), oracle(inp, shape, kv_len), inp, kv_len, "heads %d batch %d" % (nq, batch))
+    _log("plan %s" % r.blk.plan())
+    r.blk.close()
