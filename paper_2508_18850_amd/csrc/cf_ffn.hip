@@ -43,7 +43,7 @@ constexpr int kCounterStride = 16;
 constexpr int kMaxBatch = 16;          // the batch of Appendix C
 constexpr int kVectorBatch = 4;        // the largest batch of the vector-unit kernel
 constexpr int kTilesFrom = 2;          // from this batch on the MFMA kernel runs where the shape allows it (measured:
-                                       // Llama-2-7B shape, batch 1 / 2 / 4: 46.5 / 52.3 / 75.2 us against 47.8 / 47.8 / 49.0)
+                                       // Llama-2-7B shape, batch 1 / 2 / 4: 46.5 / 52.3 / 75.2 us, batch 1 now 45.5, against 47.8 / 47.8 / 49.0)
 constexpr size_t kLdsLimit = 160 * 1024 - 256;
 constexpr int kNC = 16;                // MFMA kernel: column slices of the output (workgroups per slice of hidden units)
 constexpr int kStageRow = 256 + 8;     // MFMA kernel: row stride (fp16 values) of a wavefront's staging area in LDS
