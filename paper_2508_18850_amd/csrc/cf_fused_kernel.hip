@@ -271,15 +271,26 @@ __device__ __forceinline__ int row_pos(const Params &p, int b)
     return p.pos;
 }
 
-// The attention item of a member where the batch rows have lengths of their own (Params::ragged): row b is cut into ns_b splits of
-// about the same number of tokens in all rows, at most one item per member, and the items are numbered row by row.
-constexpr int kMaxRows = 16;
+// The attention item of a member where the batch rows have lengths of their own (Params::ragged).
 struct RowItem {
     int b = 0, s = 0, ns = 1, pos = 0;      // row, split, splits of the row, its cached tokens
     int first = 0;                          // number of the row's first item
     int t0 = 0, t1 = 0;
     int table = 0;                          // lane b: first item of row b (lanes past the batch: number of items)
     int items = 0;                          // 0: the plan's items
+};
+// The lanes of a wavefront as dealt_size wants them: the length of row `lane % 16` and one candidate each.
+struct DealWave {
+    int lane, own;
+    __device__ __forceinline__ float reciprocal(int d) const { return cf::reciprocal(d); }
+    __device__ __forceinline__ int len(int b) const { return __builtin_amdgcn_readlane(own, b); }
+    template <class Candidate, class Fits>
+    __device__ __forceinline__ int first_of(Candidate &&candidate, Fits &&fits) const
+    {
+        const int c = candidate(lane);
+        const unsigned long long m = __ballot(fits(c));
+        return m ? __builtin_amdgcn_readlane(c, __builtin_ctzll(m)) : 0;
+    }
 };
 // `len`: cached tokens of row `lane % 16` (0 past the batch).  All wavefronts of all workgroups come to the same result.
 template <int CTRL>
@@ -293,22 +304,11 @@ __device__ __forceinline__ RowItem deal_rows(const Params &p, int lane, int len,
     total += dpp_int<0x141>(total), longest = max(longest, dpp_int<0x141>(longest));     // row_half_mirror
     total += dpp_int<0x140>(total), longest = max(longest, dpp_int<0x140>(longest));     // row_mirror
     total = __builtin_amdgcn_readfirstlane(total), longest = __builtin_amdgcn_readfirstlane(longest);
-    // Tokens per split: the fewest of 64 candidates that need at most TS items (and 64 splits of a row), one candidate per lane
-    // between what a perfect division would take and what is certain to suffice (an item more than it for every row); no fewer
-    // than 64, below which a split costs more than it saves.
-    auto up = [](int n, int d) { return fdiv(n + d - 1, reciprocal(d)); };        // (nothing rests on the last bit for huge lengths)
-    const int lo = max(max(up(total, p.TS), up(longest, kMaxKvSplits)), 64);
-    if (p.TPS - lo < ragged_gain(HD)) return it;
-    const int hi = p.TS > p.B ? max(up(total, p.TS - p.B), lo) : max(longest, lo);
-    const int cand = lane == 63 ? hi : lo + (int)((float)(hi - lo) * ((float)lane * (1.f / 63.f)));
-    const float rc = reciprocal(cand);
-    int need = 0;
-    for (int b = 0; b < p.B; ++b) need += max(fdiv(__builtin_amdgcn_readlane(len, b) + cand - 1, rc), 1);
-    const unsigned long long fit = __ballot(need <= p.TS);
-    const int size = fit ? __builtin_amdgcn_readlane(cand, __builtin_ctzll(fit)) : longest;
-    if (p.TPS - size < ragged_gain(HD)) return it;
+    const DealWave wave = {lane, len};
+    const int size = dealt_size(wave, total, longest, p.B, p.TS, p.TPS, ragged_gain(HD));
+    if (size == 0) return it;
     const int row = lane & 15;
-    const int mine = row < p.B ? min(max(fdiv(len + size - 1, reciprocal(size)), 1), kMaxKvSplits) : 0;       // splits of the lane's row
+    const int mine = row < p.B ? dealt_splits(len, size, reciprocal(size)) : 0;          // splits of the lane's row
     int incl = mine;                                              // ... and of those before it
     incl += dpp_int<0x111>(incl);                                 // row_shr 1, 2, 4, 8
     incl += dpp_int<0x112>(incl);
@@ -322,13 +322,8 @@ __device__ __forceinline__ RowItem deal_rows(const Params &p, int lane, int len,
     it.pos = __builtin_amdgcn_readlane(len, it.b);
     it.s = member - it.first;
     if (member < it.items) {
-        // (the split with the new token is shorter, by about what the token costs)
-        int t = up(it.pos + (it.ns > 1 ? 64 : 0), it.ns);
-        if (t * (it.ns - 1) > it.pos) t = up(it.pos, it.ns);
-        // (an item of an odd member, on a slower die, is 2 TD shorter than its neighbours: a boundary in front of one is TD further)
-        const int td = p.pairmap && t >= 256 ? 32 : 0;
-        it.t0 = it.s == 0 ? 0 : min(it.s * t + (member & 1 ? td : 0), it.pos);
-        it.t1 = it.s == it.ns - 1 ? it.pos : min(it.s * t + t + (member & 1 ? 0 : td), it.pos);
+        const TokenRange r = dealt_range(wave, it.pos, it.s, it.ns, member, p.pairmap);
+        it.t0 = r.t0, it.t1 = r.t1;
     }
     return it;
 }

@@ -2,6 +2,8 @@
 // side (cf_api.hip) and the device side (cf_fused_kernel.hip) of libcfdecode.
 #pragma once
 
+#include "cf_plan_arith.h"
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -18,7 +20,6 @@ constexpr int kStamps = 24;                // debug time stamps per workgroup
 constexpr int kQkvBlockPad = 256;
 constexpr int kCounterStride = 16;   // 64-bit words between the launch counters of two workgroups (one 128-byte line each)
 constexpr int kMaxKSplits = 64;
-constexpr int kMaxKvSplits = 64;
 
 // Batch tile 16 runs both projections on MFMA tiles; x then sits in LDS as fp16 operands,
 // [16][xs16_stride(rows of the longest split)] halves, twice (high parts, low parts of x * gamma).
@@ -91,13 +92,6 @@ struct Params {
     int ragged;            // rows of different lengths, at most one attention item per member: the kernel deals the items itself
     int reserved[9];
 };
-
-// Tokens that the longest attention item has to get shorter by for the items to be dealt by the rows' lengths: 48 KB of keys and
-// values, what a compute unit streams in 1.5 us; dealing and a merge with splits of their own number cost up to 1 us.  The kernel looks
-// for it where a split of the plan is four times that long (finding out takes 0.2 us).  Us a layer, plan / dealt: Llama-3-8B shape, batch
-// 4, 5120 to 8192 tokens (1024 against 864 a member) 40.9 / 39.7, 8192 and three of 170 36.1 / 31.4; 16 heads of 64 over 8, batch 6,
-// 9000 and five of 190 29.9 / 24.4.  Dealt where it gains less: Llama-3-8B shape, batch 2, 6144 and 8192 (516 against 456) 33.9 / 34.3.
-constexpr int ragged_gain(int head_dim) { return 48 * 1024 / (4 * head_dim); }
 
 // A stack of layers in one launch: the pointers of every layer travel by value in the kernel's argument block, behind the
 // parameters of the first layer.

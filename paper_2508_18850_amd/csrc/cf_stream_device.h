@@ -2,6 +2,8 @@
 #ifndef CF_STREAM_DEVICE_H
 #define CF_STREAM_DEVICE_H
 
+#include "cf_plan_arith.h"
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -34,10 +36,8 @@ struct Part {
 // run-time value costs some thirty instructions.
 __device__ __forceinline__ int qdiv(int n, uint32_t m) { return (int)__umulhi((uint32_t)n + (uint32_t)n, m); }
 __device__ __forceinline__ int qmod(int n, int d, uint32_t m) { return n - qdiv(n, m) * d; }
-// n / d for a divisor of this workgroup, r = 1 / d to within an ulp or two: n + 1/2 is 0.5 / d away from a multiple, so the
-// quotient is exact for n < 2^20.
+// What fdiv takes for a divisor of this workgroup.
 __device__ __forceinline__ float reciprocal(int d) { return __builtin_amdgcn_rcpf((float)d); }
-__device__ __forceinline__ int fdiv(int n, float r) { return (int)(((float)n + 0.5f) * r); }
 
 }  // namespace cf
 

@@ -212,6 +212,8 @@ DEALT = [
     ("d64_g1_b5", cf_inputs.BlockShape("s", 520, 16, 16, 64, 10000.0, 4000), [4000, 10, 20, 30, 3999]),
     ("d64_g2_b3", cf_inputs.BlockShape("s", 520, 16, 8, 64, 10000.0, 6500), [64, 6500, 65]),
     ("d64_g8_b2", cf_inputs.BlockShape("s", 520, 16, 2, 64, 10000.0, 60000), [0, 0]),
+    ("d64_g1_b16_16_members", cf_inputs.BlockShape("s", 520, 16, 16, 64, 10000.0, 2000), [1000] + [60 * b for b in range(15)]),
+    ("d128_g1_b8_8_members", cf_inputs.BlockShape("s", 256, 32, 32, 128, 10000.0, 1500), [700, 0, 3, 699, 500, 31, 257, 1]),
 ]
 
 
