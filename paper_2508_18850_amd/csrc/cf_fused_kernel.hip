@@ -1057,8 +1057,11 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 // The loads of the team's q partials are put in flight right behind this workgroup's own partial sums
 // (at the end of phase 1, before the second part of the K/V prefetch) and checked when q is needed:
 // where the other members were no later than this one, the sum costs no further round trip.  Covers
-// value e = threadIdx.x and the first kEarly k-slices; anything else takes the polling path.
-// (eight in the one-launch stack, whose registers hold the next layer's weights too)
+// value e = threadIdx.x of up to kEarly k-slices; anything else takes the polling path.
+// (Eight in the one-launch stack, whose registers hold the next layer's weights too.  Of more slices nothing is requested: eight
+// of ten cost a stack 1.2 - 3 % and could not be used; us a pass, eight requested / none: eight layers, 4096 columns, 8 heads, 512
+// rows, 10 slices 123.4 / 121.1, 8 heads over 4, 2048 rows, 16 slices 143.7 / 139.3; sixteen of 21 in a single launch, 8192 columns, 4
+// heads, two layers 34.6 / 32.8.)
 template <int kEarly>
 struct EarlyQ {
     static_assert(kEarly == 8 || kEarly == 16, "loads in groups of eight");
@@ -1069,6 +1072,7 @@ struct EarlyQ {
     {
         const Xbuf x1(p.p1);
         const int e = tid0;
+        if (p.KS > kEarly) return;                        // (uniform)
         if (e < nsel * HD) {
             const int sel = e / HD, c = e - sel * HD;
             const uint32_t src = (uint32_t)(b * p.nqkv + qkv_col0<HD, G>(p, team, sel) + c);
@@ -1089,7 +1093,7 @@ struct EarlyQ {
         // (opaque: the sixteen comparisons with it would otherwise be made in front of the loop over the items and be kept)
         int n = p.KS;
         asm volatile("" : "+s"(n));
-        uint32_t stale = issued && n <= kEarly ? 0u : 1u;
+        uint32_t stale = issued ? 0u : 1u;
         float s = 0.f;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {

@@ -363,3 +363,22 @@ def test_stack_with_long_slices_of_the_input(shape, batch, k_splits, monkeypatch
 
     monkeypatch.setattr(cf, "DecodeBlock", Tuned)
     test_stack_matches_single_calls_and_oracle(shape, False, 0, True, batch, 3, 70)
+
+
+# More slices of the projection than a member's early look at the queries covers (eight here, sixteen in the single launches) take the polling path.
+@pytest.mark.parametrize("shape,norm,k_splits", [(M128, False, 8), (M128, True, 16), (G2, False, 16), (M128, False, 32), (G2, True, 32)],
+                         ids=lambda v: getattr(v, "name", None))
+def test_stack_with_many_slices_of_the_projection(shape, norm, k_splits, monkeypatch):
+    import paper_2508_18850_amd as cf
+
+    class Tuned(cf.DecodeBlock):
+        def __init__(self, *args):
+            super().__init__(*args)
+            self.set_tuning(k_splits=k_splits)
+
+        def close(self):
+            assert self.plan()["k_splits"] == k_splits
+            super().close()
+
+    monkeypatch.setattr(cf, "DecodeBlock", Tuned)
+    test_stack_matches_single_calls_and_oracle(shape, norm, int(norm), True, 1, 4, 150)
