@@ -181,6 +181,8 @@ int cf_decode_stack(cf_handle h, int32_t n_layers, int32_t batch, const void *x,
  *   max_pos  HOST value, an upper bound of the entries, 0 <= max_pos < max_seq: the work is split as for a batch
  *            with max_pos cached tokens in every row (shorter rows leave their last splits empty), except where the
  *            lengths are so different that the kernel deals the cached rows by them.
+ * The last bits of a row's result may depend on the other entries of row_pos, since they decide where its cached rows are cut;
+ * the same row_pos gives the same bits.
  * norm_weight may be NULL and residual 0: then this is the bare block with per-row positions.
  */
 int cf_decode_layer_rows(cf_handle h, int32_t batch, const void *x, const void *norm_weight, float eps,
@@ -224,7 +226,8 @@ int cf_debug_export(cf_handle h, int32_t what, void *host_dst, size_t bytes, voi
  */
 int cf_set_tuning(cf_handle h, int32_t workgroups, int32_t k_splits, int32_t kv_splits, int32_t spin_limit_us);
 
-/* Plan of the most recent call, for reports: fills up to n ints
+/* Plan of the most recent call, for reports (of cf_decode_layer_rows: the split for max_pos, also where the kernel has dealt
+ * the cached rows by the lengths instead): fills up to n ints
  * {workgroups, team_size, k_splits, rows_per_split, kv_splits, tokens_per_split,
  *  out_col_blocks, out_cols_per_block, out_row_splits, lds_bytes}. */
 int cf_get_plan(cf_handle h, int32_t *dst, int32_t n);

@@ -47,3 +47,12 @@ def test_items_of_any_lengths(ulps):
         d = check(lens, team_size, max(1, -(-top // splits)), plan_arith.ragged_gain(rng.choice([64, 128])), rng.randint(0, 1), ulps)
         dealt += d.items > 0
     assert dealt > 500
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_dealt_from_the_gain_on(head_dim):
+    gain = plan_arith.ragged_gain(head_dim)
+    lens = [8192, 170, 170, 170]
+    size = plan_arith.deal(lens, 32, 10 ** 6, gain).size
+    assert size > 0 and check(lens, 32, size + gain, gain, 1, 0).size == size
+    assert check(lens, 32, size + gain - 1, gain, 1, 0).items == 0

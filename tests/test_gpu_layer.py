@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import cf_inputs
+import plan_arith
 from oracle import decode_block as orc
 from oracle import c_oracle
 from test_gpu_parity import check, _log
@@ -217,25 +218,63 @@ DEALT = [
 ]
 
 
-@pytest.mark.parametrize("name,shape,row_pos", DEALT)
-def test_rows_of_very_different_lengths(name, shape, row_pos):
-    _log("dealt rows case %s pos=%s" % (name, row_pos))
-    batch, max_pos = len(row_pos), shape.kv_len
-    inp = cf_inputs.make_inputs(shape, seed=33, batch=batch, kv_len=max(row_pos))
+def dealt_inputs(shape, row_pos):
+    inp = cf_inputs.make_inputs(shape, seed=33, batch=len(row_pos), kv_len=max(row_pos))
     for b, pos in enumerate(row_pos):                       # rows at and beyond a row's position are never read
         inp["k_cache"][b, :, pos:] = np.nan
         inp["v_cache"][b, :, pos:] = np.nan
     # the bound is an argument of the plan; the caches have to hold it
-    grow = max_pos + 1 - inp["max_seq"]
+    grow = shape.kv_len + 1 - inp["max_seq"]
     if grow > 0:
         for c in ("k_cache", "v_cache"):
             inp[c] = np.concatenate([inp[c], np.full(inp[c].shape[:2] + (grow, shape.head_dim), np.nan, dtype=np.float16)], axis=2)
-        inp["max_seq"] = max_pos + 1
+        inp["max_seq"] = shape.kv_len + 1
+    return inp
+
+
+@pytest.mark.parametrize("name,shape,row_pos", DEALT)
+def test_rows_of_very_different_lengths(name, shape, row_pos):
+    _log("dealt rows case %s pos=%s" % (name, row_pos))
+    batch, max_pos = len(row_pos), shape.kv_len
+    inp = dealt_inputs(shape, row_pos)
     gamma = gamma_for(shape, 11)
     res = run_rows(shape, batch, inp, row_pos, max_pos, gamma, 1e-5, True, True)
     ref = orc.decode_rows(inp["x"], gamma, 1e-5, inp["w_qkv"], inp["w_o"], inp["k_cache"], inp["v_cache"], row_pos,
                           shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.rope_base)
     check_rows(res, ref, inp, row_pos, name)
+
+
+# Both sides of the gain from which items are dealt: two rows of 6000 and 4800 tokens over eight members take 1500 tokens a member,
+# the plan for a bound of 6316 / 6320 tokens 1595 / 1596, and the gain asked for is 96.
+NEARLY = [("d128_g1_b2_%s" % ("dealt" if bound == 6320 else "planned"), cf_inputs.BlockShape("s", 256, 32, 32, 128, 10000.0, bound), [6000, 4800])
+          for bound in (6316, 6320)]
+
+
+@pytest.mark.parametrize("name,shape,row_pos", DEALT + NEARLY)
+def test_dealt_items_are_the_ones_that_run(name, shape, row_pos):
+    """Which items ran shows in the bits of the attention result, since the partials of other splits add up to other bits: with items
+    dealt into two and more splits of a row they are not those of the plan's splits (which a call with tuned splits takes), otherwise they
+    are.  Two calls with the same lengths give the same bits."""
+    _log("dealt items case %s pos=%s" % (name, row_pos))
+    inp = dealt_inputs(shape, row_pos)
+    gamma = gamma_for(shape, 11)
+    args = (shape, len(row_pos), inp, row_pos, shape.kv_len, gamma, 1e-5, True, True)
+    res, again = run_rows(*args), run_rows(*args)
+    for key in ("attn", "q_rot", "out", "k_cache", "v_cache"):
+        assert res[key].tobytes() == again[key].tobytes(), key
+    plan, gain = res["plan"], plan_arith.ragged_gain(shape.head_dim)
+    assert plan["tokens_per_split"] >= 4 * gain, plan
+    d = plan_arith.deal(row_pos, plan["team_size"], plan["tokens_per_split"], gain,
+                        int(plan["team_size"] % 2 == 0 and plan["workgroups"] % 2 == 0))
+    assert (d.items > 0) == (not name.endswith("planned")), (plan, d)
+    planned = run_rows(*args, kv_splits=plan["kv_splits"])
+    assert all(planned["plan"][k] == plan[k] for k in ("kv_splits", "tokens_per_split", "team_size")), planned["plan"]
+    same = planned["attn"].tobytes() == res["attn"].tobytes()
+    _log("   %d items of %d tokens, splits %s, same bits as the plan's: %s" % (d.items, d.size, d.splits, same))
+    if d.items == 0:
+        assert same
+    elif max(d.splits) > 1:
+        assert not same
 
 
 def test_rows_when_a_workgroup_handles_several_rows():
