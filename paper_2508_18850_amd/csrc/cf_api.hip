@@ -63,7 +63,8 @@ int batch_tile(int batch, int head_dim) { return batch <= 1 ? 1 : batch <= (head
 int tile_index(int bt) { return bt == 1 ? 0 : bt == 4 ? 1 : 2; }
 
 constexpr int kMaxKS = 32;
-constexpr size_t kLdsLimit = 160 * 1024 - 256;   // LDS per workgroup on gfx950, minus the static flags
+using cf::divisor;
+using cf::kLdsLimit;
 
 bool aligned16(const void *p) { return p && (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -205,7 +206,6 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
     // has at most one item, the kernel deals the items by the rows' lengths instead.
     p->ragged = p->row_pos && batch <= TS && h->tune_ns == 0 && p->TPS >= 4 * cf::ragged_gain(hd) ? 1 : 0;
     p->DSEL = TS / p->KS;
-    auto divisor = [](int d) { return (uint32_t)((0x80000000ull + d - 1) / d); };      // what the kernel's qdiv takes
     p->div_nkv = divisor(c.n_kv_heads);
     p->div_ks = divisor(p->KS);
     p->div_dsel = divisor(p->DSEL);

@@ -25,6 +25,7 @@
 #include "../../include/cfdecode.h"
 #include "cf_lanes_device.h"
 #include "cf_mfma_device.h"
+#include "cf_plan_arith.h"
 #include "cf_stream_device.h"
 #include "cf_team_device.h"
 
@@ -36,15 +37,19 @@ namespace {
 
 using cf::team::Exchange;
 using cf::team::pair_t;
-constexpr int NT = 512;
+using cf::kLdsLimit;
+using cf::ffn::first_unit;
+using cf::ffn::lds_bytes;
+using cf::ffn::most_units;
+using cf::ffn::uneven_shares;
+constexpr int NT = cf::ffn::kThreads;
 constexpr int NW = NT / 64;
-constexpr int kChunk = 512;            // columns of one wavefront load: 64 lanes x 8 values
+constexpr int kChunk = cf::ffn::kPiece;            // columns of one wavefront load: 64 lanes x 8 values
 constexpr int kCounterStride = 16;
 constexpr int kMaxBatch = 16;          // the batch of Appendix C
 constexpr int kVectorBatch = 4;        // the largest batch of the vector-unit kernel
 constexpr int kTilesFrom = 2;          // from this batch on the MFMA kernel runs where the shape allows it (measured:
                                        // Llama-2-7B shape, batch 1 / 2 / 4: 46.5 / 52.3 / 75.2 us, batch 1 now 45.5, against 47.8 / 47.8 / 49.0)
-constexpr size_t kLdsLimit = 160 * 1024 - 256;
 constexpr int kNC = 16;                // MFMA kernel: column slices of the output (workgroups per slice of hidden units)
 constexpr int kStageRow = 256 + 8;     // MFMA kernel: row stride (fp16 values) of a wavefront's staging area in LDS
 using cf::kNoLoad;
@@ -70,18 +75,6 @@ struct FfnArgs {
     size_t xg, xp;                     // first slot of g [d_ff][B] and of the partial outputs [NF][B][D]
     int NF, CW, nRp;                   // slices of hidden units; columns per column slice; units of a slice, padded to 32
 };
-
-// First hidden unit of workgroup w (vector kernel).  Workgroup w runs on die w % 8, and the odd dies get 3 to 10 % less memory
-// bandwidth than the even ones: of the units of two neighbours the even one takes 524 of 1024.  Us a layer, even share 50.0 / 51.2 /
-// 52.4 %: 4096 x 11008 46.2 / 45.75 / 46.0, 4096 x 14336 57.1 / 57.0 / 57.5, 8192 x 28672 211.3 / 209.6 / 209.7.
-constexpr int kEvenShare = 524;
-__host__ __device__ inline int even_units(int pair) { return (pair * kEvenShare + 512) >> 10; }
-__host__ __device__ inline int first_unit(int w, int F, int W, int uneven)
-{
-    if (!uneven) return (int)((long long)w * F / W);
-    const int p0 = (int)((long long)(w & ~1) * F / W);
-    return w & 1 ? p0 + even_units((int)((long long)(w + 1) * F / W) - p0) : p0;
-}
 
 struct Stream {
     __amdgpu_buffer_rsrc_t r;
@@ -728,13 +721,6 @@ struct cf_ffn_s {
     int last_hip = 0;
 };
 
-static size_t lds_bytes_of(const cf_ffn_config &c, int bt, int nrmax)
-{
-    const size_t nck = (c.d_model + kChunk - 1) / kChunk, dp = nck * kChunk;
-    const size_t stages_ab = (size_t)bt * dp / 2 + 2 * (size_t)bt * nrmax * nck + (size_t)bt * nrmax;
-    return (stages_ab > (size_t)(8 * NT) ? stages_ab : (size_t)(8 * NT)) * sizeof(float);       // the partial output on its way out: 4096 floats
-}
-
 extern "C" {
 
 int cf_ffn_create(const cf_ffn_config *cfg, cf_ffn *out)
@@ -756,18 +742,10 @@ int cf_ffn_create(const cf_ffn_config *cfg, cf_ffn *out)
     const int cpw = (c.d_model + W - 1) / W;
     const int vbatch = c.max_batch < kVectorBatch ? c.max_batch : kVectorBatch;
     if ((size_t)cpw * vbatch > (size_t)NT) return CF_EUNSUPPORTED;            // stage C: one thread per output value
-    // (uneven shares where workgroups come in whole rounds of the dies and the larger share still fits LDS)
-    int uneven = W % 8 == 0, nrmax_v = nrmax;
-    if (uneven) {
-        nrmax_v = even_units((c.d_ff + W / 2 - 1) / (W / 2));
-        nrmax_v = nrmax_v > nrmax ? nrmax_v : nrmax;
-        int top = 1;
-        while (top < vbatch) top *= 2;
-        if (lds_bytes_of(c, top, nrmax_v) > kLdsLimit) uneven = 0, nrmax_v = nrmax;
-    }
+    const int uneven = uneven_shares(c.d_model, c.d_ff, W, batch_tile(vbatch)), nrmax_v = most_units(c.d_ff, W, uneven);
     for (int bt = 1; bt <= kVectorBatch; bt *= 2) {
         if (bt / 2 >= c.max_batch) break;
-        const size_t lds = lds_bytes_of(c, bt, nrmax_v);
+        const size_t lds = lds_bytes(c.d_model, bt, nrmax_v);
         if (lds > kLdsLimit) return CF_EUNSUPPORTED;
         int per_cu = 0;
         if ((lds > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void *>(pick(bt, c.d_model)),
@@ -858,8 +836,7 @@ int cf_ffn_decode(cf_ffn t, int32_t batch, const void *z, const void *W1, const 
     a.err = t->err;
     a.D = t->cfg.d_model, a.F = t->cfg.d_ff, a.B = batch, a.W = t->W, a.act = t->cfg.activation;
     a.nrmax = t->nrmax;
-    const int nck = (t->cfg.d_model + kChunk - 1) / kChunk;
-    a.div_nck = (uint32_t)((0x80000000ull + nck - 1) / nck);
+    a.div_nck = cf::divisor((t->cfg.d_model + kChunk - 1) / kChunk);
     a.spin_ticks = t->spin_ticks;
     if (batch >= kTilesFrom && t->lds_tiles) {
         a.xg = t->xg, a.xp = t->xp, a.NF = t->NF, a.CW = t->CW, a.nRp = t->nRp;
@@ -867,7 +844,7 @@ int cf_ffn_decode(cf_ffn t, int32_t batch, const void *z, const void *W1, const 
     } else {
         const int bt = batch_tile(batch);
         a.nrmax = t->nrmax_v, a.uneven = t->uneven;
-        hipLaunchKernelGGL(pick(bt, t->cfg.d_model), dim3(t->W), dim3(NT), lds_bytes_of(t->cfg, bt, t->nrmax_v),
+        hipLaunchKernelGGL(pick(bt, t->cfg.d_model), dim3(t->W), dim3(NT), lds_bytes(t->cfg.d_model, bt, t->nrmax_v),
                            static_cast<hipStream_t>(stream), a);
     }
     hipError_t e = hipGetLastError();

@@ -35,6 +35,7 @@
 #include "cf_lanes_device.h"
 #include "cf_mfma_device.h"
 #include "cf_mla_internal.h"
+#include "cf_plan_arith.h"
 #include "cf_rope_device.h"
 #include "cf_team_device.h"
 
@@ -757,7 +758,6 @@ namespace {
 
 // 64-column tiles of [W_Q | W_KV] (those of W_Q are rounded up: W_KV fills nine)
 int tiles_of(const cf_mla_config &c) { return (c.n_heads * (c.nope_dim + R) + 63) / 64 + LR / 64; }
-uint32_t divisor(int d) { return (uint32_t)((0x80000000ull + d - 1) / d); }      // what cf::qdiv takes
 
 // token ranges of a call: NS ranges of tps cached rows per batch row; and the heads per attention item: as few as
 // the number of workgroups allows (an item fetches the queries and publishes the partial results of its heads only:
@@ -891,7 +891,7 @@ int cf_mla_decode(cf_mla t, int32_t batch, const void *x, const void *W_q, const
         h.D = c.d_model, h.nh = c.n_heads, h.n = c.nope_dim, h.v = c.v_head_dim, h.pos = pos, h.W = t->W;
         (void)cf::mla::slices(c, &h.ksa, &h.rows);
         h.tiles = tiles_of(c), h.CW = (c.d_model + t->W - 1) / t->W;
-        h.div_t = divisor(h.tiles), h.div_cw = divisor(h.CW);
+        h.div_t = cf::divisor(h.tiles), h.div_cw = cf::divisor(h.CW);
         h.scale_log2e = 1.4426950408889634f / std::sqrt((float)(c.nope_dim + R));
         h.log2_base = std::log2((double)c.rope_base);
         h.spin_ticks = t->spin_ticks;

@@ -3,12 +3,21 @@
 #ifndef CF_PLAN_ARITH_H
 #define CF_PLAN_ARITH_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 namespace cf {
 
 constexpr int kMaxRows = 16;               // batch rows of a call at most
 constexpr int kMaxKvSplits = 64;           // splits of a batch row's cached tokens at most
+
+constexpr size_t kLdsLimit = 160 * 1024 - 256;       // LDS per workgroup on gfx950, minus what a kernel declares statically
+
+// Division by a plan constant d, m = divisor(d) = ceil(2^31 / d): the high half of 2 n m is n / d for n d < 2^31.  Integer division by
+// a run-time value costs some thirty instructions.
+constexpr uint32_t divisor(int d) { return (uint32_t)((0x80000000ull + d - 1) / d); }
+constexpr int qdiv(int n, uint32_t m) { return (int)(((uint64_t)((uint32_t)n + (uint32_t)n) * m) >> 32); }
+constexpr int qmod(int n, int d, uint32_t m) { return n - qdiv(n, m) * d; }
 
 // n / d for r = 1 / d to within an ulp or two: n + 1/2 is 0.5 / d away from a multiple, so the quotient is exact for n < 2^20.
 // Beyond that it can be one off and more, in either direction.
@@ -72,6 +81,40 @@ constexpr TokenRange dealt_range(const Wave &w, int len, int s, int ns, int memb
     const int td = pairmap && t >= 256 ? 32 : 0;
     return {s == 0 ? 0 : smaller(s * t + (member & 1 ? td : 0), len), s == ns - 1 ? len : smaller(s * t + t + (member & 1 ? 0 : td), len)};
 }
+
+// ---- Hidden units of the FFN block's workgroups (vector kernel).  Workgroup w runs on die w % 8, and the odd dies get 3 to 10 % less
+// memory bandwidth than the even ones: of the units of two neighbours the even one takes 524 of 1024.  Us a layer, even share 50.0 /
+// 51.2 / 52.4 %: 4096 x 11008 46.2 / 45.75 / 46.0, 4096 x 14336 57.1 / 57.0 / 57.5, 8192 x 28672 211.3 / 209.6 / 209.7.
+namespace ffn {
+constexpr int kThreads = 512;
+constexpr int kPiece = 512;                // columns of a row that a wavefront takes in one step
+constexpr int kEvenShare = 524;
+constexpr int even_units(int pair) { return (pair * kEvenShare + 512) >> 10; }
+// first unit of workgroup w of W (even where the shares are uneven)
+constexpr int first_unit(int w, int F, int W, int uneven)
+{
+    if (!uneven) return (int)((long long)w * F / W);
+    const int p0 = (int)((long long)(w & ~1) * F / W);
+    return w & 1 ? p0 + even_units((int)((long long)(w + 1) * F / W) - p0) : p0;
+}
+constexpr int most_units(int F, int W, int uneven)       // of a workgroup
+{
+    const int equal = (F + W - 1) / W;
+    return uneven ? larger(even_units((F + W / 2 - 1) / (W / 2)), equal) : equal;
+}
+// LDS of a batch tile: rows of z, sums of the pieces, g; or the partial output on its way out, 4096 floats
+constexpr size_t lds_bytes(int d_model, int batch_tile, int units)
+{
+    const size_t nck = (d_model + kPiece - 1) / kPiece, dp = nck * kPiece;
+    const size_t stages_ab = (size_t)batch_tile * dp / 2 + 2 * (size_t)batch_tile * units * nck + (size_t)batch_tile * units;
+    return (stages_ab > (size_t)(8 * kThreads) ? stages_ab : (size_t)(8 * kThreads)) * sizeof(float);
+}
+// Uneven shares where workgroups come in whole rounds of the dies and the larger share still fits LDS at the largest batch tile.
+constexpr int uneven_shares(int d_model, int F, int W, int largest_tile)
+{
+    return W % 8 == 0 && lds_bytes(d_model, largest_tile, most_units(F, W, 1)) <= kLdsLimit;
+}
+}  // namespace ffn
 
 }  // namespace cf
 

@@ -1,4 +1,4 @@
-// Device helpers the kernels share: 128-bit loads from a part of a read-only tensor, divisions without an integer division.
+// Device helpers the kernels share: 128-bit loads from a part of a read-only tensor, reciprocals.
 #ifndef CF_STREAM_DEVICE_H
 #define CF_STREAM_DEVICE_H
 
@@ -32,10 +32,6 @@ struct Part {
     __device__ __forceinline__ h8 ld(uint32_t off) const { return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX)); }
 };
 
-// Division by a plan constant d, m = ceil(2^31 / d): the high half of 2 n m is n / d for n d < 2^31.  Integer division by a
-// run-time value costs some thirty instructions.
-__device__ __forceinline__ int qdiv(int n, uint32_t m) { return (int)__umulhi((uint32_t)n + (uint32_t)n, m); }
-__device__ __forceinline__ int qmod(int n, int d, uint32_t m) { return n - qdiv(n, m) * d; }
 // What fdiv takes for a divisor of this workgroup.
 __device__ __forceinline__ float reciprocal(int d) { return __builtin_amdgcn_rcpf((float)d); }
 

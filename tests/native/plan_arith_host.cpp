@@ -30,7 +30,25 @@ extern "C" {
 
 int pa_ragged_gain(int head_dim) { return cf::ragged_gain(head_dim); }
 
-int pa_fdiv(int n, int d, int ulps) { return cf::fdiv(n, reciprocal(d, ulps)); }
+// The first n of `count` values whose quotient by d is not the integer one, or -1.
+int pa_qdiv_differs(const int *n, int count, int d)
+{
+    for (int i = 0; i < count; ++i)
+        if (cf::qdiv(n[i], cf::divisor(d)) != n[i] / d || cf::qmod(n[i], d, cf::divisor(d)) != n[i] % d) return n[i];
+    return -1;
+}
+int pa_fdiv_differs(const int *n, int count, int d, int ulps)
+{
+    for (int i = 0; i < count; ++i)
+        if (cf::fdiv(n[i], reciprocal(d, ulps)) != n[i] / d) return n[i];
+    return -1;
+}
+
+int pa_first_unit(int w, int F, int W, int uneven) { return cf::ffn::first_unit(w, F, W, uneven); }
+int pa_most_units(int F, int W, int uneven) { return cf::ffn::most_units(F, W, uneven); }
+int pa_uneven_shares(int d_model, int F, int W, int tile) { return cf::ffn::uneven_shares(d_model, F, W, tile); }
+int pa_lds_bytes(int d_model, int tile, int units) { return (int)cf::ffn::lds_bytes(d_model, tile, units); }
+int pa_lds_limit() { return (int)cf::kLdsLimit; }
 
 // Deals `rows` rows of the given lengths.  Returns the number of items (0: the plan's); `splits`: per row; `range`: t0, t1 of every
 // item in order (room for 16 * 64).

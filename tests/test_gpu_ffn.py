@@ -212,3 +212,15 @@ def test_pieces_taken_from_a_counter(d_model, d_ff, batch):
     blk.status(stream)
     blk.close()
     assert all(torch.equal(out, outs[0]) for out in outs[1:])
+
+
+@pytest.mark.parametrize("batch", [3, 4])
+@pytest.mark.parametrize("units,uneven", [(3246, 1), (3247, 0), (3322, 0)])
+def test_shares_at_the_limit_of_lds(units, uneven, batch):
+    """The largest numbers of hidden units a workgroup can own: uneven shares while the larger one fits LDS, equal ones beyond."""
+    import plan_arith
+    lib = plan_arith.load()
+    d_ff = 256 * units
+    assert lib.pa_uneven_shares(8, d_ff, 256, 4) == uneven
+    assert lib.pa_lds_bytes(8, 4, lib.pa_most_units(d_ff, 256, uneven)) <= lib.pa_lds_limit()
+    _run(cf_inputs.FfnShape("limit", 8, d_ff), batch, 0, seed=500 + batch, scale_rows=True)
