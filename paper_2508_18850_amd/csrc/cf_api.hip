@@ -175,7 +175,7 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
             p->TD = is_long(p->TPS) ? long_difference(p->TPS) : 0;
         }
     }
-    // output projection: G heads x NC3 column blocks x RS3 row splits per team.  A member walks its items chunk by chunk
+    // output projection: G heads x NC3 column blocks x 2^LRS3 row splits per team.  A member walks its items chunk by chunk
     // (512 columns); the first chunk is on its way since the attention, every further one costs its bytes and a load
     // latency, about that of 96 rows (2.4 us a chunk of 8 rows: 2056 columns as 2 blocks of 3 chunks x 8 row splits took
     // 27.5 us in all at batch 3, as 5 blocks of one chunk x 2 row splits 22.3 us).
@@ -203,7 +203,8 @@ int make_plan(const cf_handle_s *h, int batch, int pos, Params *p, bool even_sli
     }
     // Rows of different lengths: NS splits of the longest one for every row leave the members of the short rows' last splits idle
     // (four rows of 5120 to 8192 tokens, 32 members: 7 without a token, the others 1024 each where 832 would do).  Where every member
-    // has at most one item, the kernel deals the items by the rows' lengths instead.
+    // has at most one item, the kernel deals the items by the rows' lengths instead (not with more rows than members, nor with a tuned number of
+    // splits: the plan's equal splits then, idle members and all).
     p->ragged = p->row_pos && batch <= TS && h->tune_ns == 0 && p->TPS >= 4 * cf::ragged_gain(hd) ? 1 : 0;
     p->DSEL = TS / p->KS;
     p->div_nkv = divisor(c.n_kv_heads);

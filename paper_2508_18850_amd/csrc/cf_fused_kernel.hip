@@ -4,8 +4,8 @@
 // Mapping.  The paper maps one attention head to a cluster of thread blocks and
 // resolves the dependencies between the blocks of a cluster with ClusterGather
 // and ClusterReduce over distributed shared memory.  gfx950 has no clusters, so
-// a "team" of workgroups (all workgroups whose index is congruent modulo
-// n_kv_heads; with 8 | n_kv_heads they share one XCD) serves one KV head
+// a "team" of workgroups (with an even number of members and 4 | n_kv_heads on
+// one pair of XCDs) serves one KV head
 // together with the query heads that use it.  Every member streams, in this
 // order, so that each dependency falls behind a stream that does not need it:
 //   1a  its slice of the reduction dimension of the team's W_q columns
@@ -1059,9 +1059,9 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
 // where the other members were no later than this one, the sum costs no further round trip.  Covers
 // value e = threadIdx.x of up to kEarly k-slices; anything else takes the polling path.
 // (Eight in the one-launch stack, whose registers hold the next layer's weights too.  Of more slices nothing is requested: eight
-// of ten cost a stack 1.2 - 3 % and could not be used; us a pass, eight requested / none: eight layers, 4096 columns, 8 heads, 512
-// rows, 10 slices 123.4 / 121.1, 8 heads over 4, 2048 rows, 16 slices 143.7 / 139.3; sixteen of 21 in a single launch, 8192 columns, 4
-// heads, two layers 34.6 / 32.8.)
+// of ten cost a stack 1 - 4 % and could not be used; us a pass, eight requested / none: eight layers, 4096 columns, 8 heads, 512
+// rows, 10 slices 123.5 / 120.9, 8 heads over 4, 2048 rows, 16 slices 144.6 / 138.9; sixteen of 21 in a single launch, 8192 columns, 4
+// heads, two layers 34.6 / 32.6.)
 template <int kEarly>
 struct EarlyQ {
     static_assert(kEarly == 8 || kEarly == 16, "loads in groups of eight");
@@ -1592,7 +1592,7 @@ __device__ __forceinline__ void p2_item(const Params &p, const LayerPtrs &lp, in
 
 // ---------------------------------------------------------------------------
 // Phase 3: merge the split-KV partials of head hq (Alg. 3 steps 5-7), multiply by
-// rows [rs*HD/RS3, (rs+1)*HD/RS3) x columns [c3*CW3, (c3+1)*CW3) of that head's
+// rows [rs*n, (rs+1)*n), n = HD >> LRS3, x columns [c3*CW3, (c3+1)*CW3) of that head's
 // W_o block (step 8) and leave a per-head partial of the output.  The first
 // 512-column chunk is loaded into registers before the attention result is needed.
 // ---------------------------------------------------------------------------
@@ -1964,7 +1964,7 @@ __device__ __forceinline__ void p3_item(const Params &p, const LayerPtrs &lp, in
 }
 
 // ---------------------------------------------------------------------------
-// Phase 4: every workgroup owns ceil(D/W) output columns and adds the per-head
+// Phase 4: every workgroup owns CPW output columns (ceil(D/W), rounded up to an even number) and adds the per-head
 // partials of those columns in slot order (the cross-head reduction that the paper
 // does with atomicAdd), then writes fp16.
 // ---------------------------------------------------------------------------
@@ -2095,12 +2095,6 @@ constexpr size_t p3_lds_floats(int hd, int bt)
 template <int HD, int G, int BT>
 constexpr size_t kRowTable = p2_lds_floats(HD, G) > p3_lds_floats(HD, BT) ? p2_lds_floats(HD, G) : p3_lds_floats(HD, BT);
 
-// One launch = n_layers decode steps in a row (1 for the plain entry points).  Layer l > 0 takes its weights and
-// caches from tab[l] and its input from the slots xslots, where the final reduction of layer l - 1 left its result;
-// the last layer writes `out`.  Nothing separates the layers but those slots: a workgroup goes on as soon as the
-// rows of the input it needs have arrived.  The exchange areas need no second set: a workgroup can post values of
-// layer l + 1 only after it has taken in that layer's input, which exists only when every workgroup has finished
-// reading what layer l exchanged.
 // The kernel's arguments, through a pointer the compiler cannot connect with an earlier one (see decode_steps).
 //
 // At small shapes the time between two hand-overs is the time to issue the instructions in between (one every four to eight
@@ -2117,6 +2111,12 @@ __device__ __forceinline__ const Params &kernarg_params()
     return *(const Params *)pk;
 }
 
+// One launch = n_layers decode steps in a row (1 for the plain entry points).  Layer l > 0 takes its weights and
+// caches from tab[l] and its input from the slots xslots, where the final reduction of layer l - 1 left its result;
+// the last layer writes `out`.  Nothing separates the layers but those slots: a workgroup goes on as soon as the
+// rows of the input it needs have arrived.  The exchange areas need no second set: a workgroup can post values of
+// layer l + 1 only after it has taken in that layer's input, which exists only when every workgroup has finished
+// reading what layer l exchanged.
 template <int HD, int G, int BT, bool STACK>
 __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *tab, int n_layers_in, uint64_t *xslots)
 {
@@ -2138,7 +2138,7 @@ __device__ __forceinline__ void decode_steps(const Params &p0, const LayerPtrs *
     const int tid = threadIdx.x;
     // Workgroup w runs on die (XCD) w % 8, and the odd dies get about a tenth less memory
     // bandwidth than the even ones.  With pairmap a team sits on one pair of dies, members with an
-    // even index on the even die: those take the longer slices and splits.
+    // even index on the even die: those take the longer splits of the cached rows.
 #if CF_STAMPS
     if (tid < kStamps) s_ts[tid] = 0;       // same wavefront as thread 0: ordered before its stamps
 #endif

@@ -65,7 +65,9 @@ struct Params {
     uint32_t *err;         // set to 1 when a spin gave up
     // exchange slots: 64-bit {fp32 bits, launch stamp} pairs
     uint64_t *p1;          // [k_splits][B][Nqkv] partial projections
-    uint64_t *p2;          // [B][n_q][kv_splits][head_dim + kP2Stride] split-KV partials
+    uint64_t *p2;          // split-KV partials of head_dim + kP2Stride slots: number (first item of the row) * n_q + head * splits of the
+                           // row + split, for the plan's items [B][n_q][kv_splits] (dealt or not, a row has kMaxKvSplits at most, which is
+                           // what a handle has room for)
     uint64_t *p3;          // [n_q * row_splits][B][D] per-head partial outputs
     double rope_log2_base; // log2 of the RoPE base: the kernel computes the frequencies base^(-2i/d) itself
     float *dbg_q, *dbg_attn;   // [B][n_q][head_dim] or null

@@ -77,14 +77,18 @@ constexpr TokenRange dealt_range(const Wave &w, int len, int s, int ns, int memb
     // (the split with the new token is shorter, by about what the token costs)
     int t = up(len + (ns > 1 ? 64 : 0), ns);
     if (t * (ns - 1) > len) t = up(len, ns);
-    // (an item of an odd member, on a slower die, is 2 TD shorter than its neighbours: a boundary in front of one is TD further)
+    // (An item of an odd member, on a slower die, is 2 td shorter than its neighbours: a boundary in front of one is td further.  What it
+    // is worth depends on the lengths and is small: us a pass, td 32 / 16 / 0, Llama-3-8B shape, 860 tokens a member 79.1 / 78.6 / 78.6, 280
+    // 62.8 / 63.4 / 63.4, 480 67.8 / 68.0 / 68.2, 400 66.5 / 66.3 / 65.9, eight rows, 700 41.7 / 41.4 / 41.1, 1000 59.1 / 59.3 / 59.9; Llama-2-7B
+    // shape, 576 83.9 / 83.7 / 84.2; Llama-2-70B shape, 1100 85.0 / 85.1 / 85.3; 32 heads of 64 over 8, 1170 30.4 / 30.1 / 29.9.)
     const int td = pairmap && t >= 256 ? 32 : 0;
     return {s == 0 ? 0 : smaller(s * t + (member & 1 ? td : 0), len), s == ns - 1 ? len : smaller(s * t + t + (member & 1 ? 0 : td), len)};
 }
 
 // ---- Hidden units of the FFN block's workgroups (vector kernel).  Workgroup w runs on die w % 8, and the odd dies get 3 to 10 % less
-// memory bandwidth than the even ones: of the units of two neighbours the even one takes 524 of 1024.  Us a layer, even share 50.0 /
-// 51.2 / 52.4 %: 4096 x 11008 46.2 / 45.75 / 46.0, 4096 x 14336 57.1 / 57.0 / 57.5, 8192 x 28672 211.3 / 209.6 / 209.7.
+// memory bandwidth than the even ones (on every card measured; where they do not, an even share is 2.4 % longer than it need be):
+// of the units of two neighbours the even one takes 524 of 1024.  Us a layer, even share 50.0 / 51.2 / 52.4 %: 4096 x 11008 46.2 /
+// 45.75 / 46.0, 4096 x 14336 57.1 / 57.0 / 57.5, 8192 x 28672 211.3 / 209.6 / 209.7.
 namespace ffn {
 constexpr int kThreads = 512;
 constexpr int kPiece = 512;                // columns of a row that a wavefront takes in one step

@@ -442,7 +442,7 @@ def test_longest_slices_of_head_dim_64(d_model, batch, workgroups):
 
 
 # Splits of eight batches (2048 rows) or more at head dimension 128, one per member: the even ones are longer by three in 64.  Lengths that
-# divide into whole batches and that do not, the last length with the common difference, attention on the vector and the matrix units.
+# divide into whole batches and that do not, the fourth length (splits of 2047 rows) with the common difference, attention on the vector and the matrix units.
 @pytest.mark.parametrize("nq,batch,workgroups,kv_len", [(2, 1, 4, 4096), (8, 1, 4, 4096), (8, 2, 8, 4133), (2, 2, 8, 4030), (16, 5, 20, 6144)])
 def test_long_splits_of_different_length(nq, batch, workgroups, kv_len):
     shape = cf_inputs.BlockShape("s", 264, nq, 2, 128, 10000.0, kv_len)
