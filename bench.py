@@ -35,11 +35,11 @@ HBM_PEAK_GBS = 8000.0
 MEASURED_TRAFFIC = {
     # profiles/fused_decode_block_llama2_7b_kv4096_hbm_traffic.md and profiles/fused_decode_block_gqa_shapes.md:
     # (FETCH_SIZE KiB x 2.0000 + WRITE_SIZE KiB) x 1024, measured on fused_decode_block (one launch per layer)
-    "llama2_7b_b1_kv4096": 207258944,      # 100156.7, 2088.0
-    "llama3_8b_b1_kv8192": 124759007,      # 59747.5, 2340.0
-    "llama3_8b_b4_kv8192": 234898967,      # 111612.8, 6168.0
-    "llama3_8b_b16_kv8192": 674600663,     # 318654.9, 21480.0
-    "llama2_70b_b1_kv32768": 456244058,    # 219017.4, 7516.0
+    "llama2_7b_b1_kv4096": 207421235,      # 100235.9, 2088.0
+    "llama3_8b_b1_kv8192": 124662374,      # 59700.3, 2340.0
+    "llama3_8b_b4_kv8192": 235008614,      # 111666.3, 6168.0
+    "llama3_8b_b16_kv8192": 674128486,     # 318424.3, 21480.0
+    "llama2_70b_b1_kv32768": 456280064,    # 219035.0, 7516.0
 }
 
 

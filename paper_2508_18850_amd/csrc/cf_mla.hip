@@ -25,11 +25,12 @@
 // stamp of the launch; a reader polls the flags of its sources and fetches the values with 16-byte loads that, like the
 // polls, do not look into its caches.
 //
-// Measured (DeepSeek-V2-Lite shape, 4096 rows): 16 batch rows 63.8 -> 45.1 us, batch 2 / 4 / 8 36.6 / 44.1 / 52.6 ->
-// 32.5 / 33.9 / 37.9, against the kernel that sent everything through slots.  Time line at 16 rows, us from kernel
-// start, mean over the workgroups: A posted 4.5, up-projection 9.7, B posted 10.3, sources there 14.0, query operands
-// built 15.5, rows consumed 26.5 (6.9 TB/s), range posted 29.1, its sources there 33.2, z posted 35.5, a_i 40.2, partial
-// of out 41.8, end 44.3.  What bounds it is the chain of hand-overs, 2 to 4 us each.
+// Measured (DeepSeek-V2-Lite shape, 4096 rows): 16 batch rows 63.8 -> 44.8 us, batch 2 / 4 / 8 36.6 / 44.1 / 52.6 ->
+// 32.4 / 33.5 / 37.4, against the kernel that sent everything through slots.  Time line at 16 rows, us from kernel
+// start, mean / latest workgroup, launches back to back: A posted 4.5 / 7.0, up-projection 9.2, B posted 9.7 / 10.6, sources there 13.4 / 14.4,
+// query operands built 14.9, rows consumed 25.5 / 27.3 (7 TB/s), range posted 28.1 / 30.0, its sources there 32.2 / 33.4, z posted
+// 34.2 / 35.8, a_i 38.8 / 39.9, partial of out 40.3, end 42.8 / 43.4.  What bounds it is the chain of stages and hand-overs: behind B and C 3.7
+// and 4.1 us from the mean post to the mean arrival, 2.8 and 2.2 from the latest post.
 // Each stage requests its weights (or cached rows) before it waits for its input.  All waits are bounded
 // (CF_ETIMEOUT), all workgroups have to be resident at once.
 #include "cf_lanes_device.h"

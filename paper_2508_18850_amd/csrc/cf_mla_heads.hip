@@ -24,11 +24,12 @@
 // for the first load of a group before the next went out, and with both batches of rows requested in front of the product that
 // needs W_Up: a wavefront stands still while its loads are accepted; 22.6 with shuffles between lanes instead
 // of permlane swaps; 27.9 with five hand-overs: partial
-// sums of the projections, latent query, partials, partial a_i, partial out); 100 rows 17.5 us (18.6), 16000 rows 35.4 (46.7).  Stages (with shuffles), us from kernel
-// start, mean over workgroups: projections posted 3.0, q arrived 6.4, latent query ready 8.9, rows used 11.5, partial
-// folded 13.9, D posted 15.0, a_i ready 17.6, partial out posted 18.4, end 19.9.  Between the hand-overs a compute unit
-// is bound by what it loads (64 KB of A, 131 KB of W_Up, 295 KB of rows, 131 KB of W_Down): requesting W_Up or the rows
-// in front of the first hand-over moves the wait, not the end (21.2 - 21.9 us).
+// sums of the projections, latent query, partials, partial a_i, partial out); 100 rows 17.5 us (18.6), 16000 rows 35.4 (46.7).  Stages, us from kernel
+// start, mean / latest workgroup, launches back to back: projections posted 3.0 / 4.1, q arrived 6.8 / 7.6, query ready 8.3 / 9.4, rows used
+// 11.3 / 12.2, partial folded 13.8 / 14.7, D posted 14.7 / 15.5, a_i ready 17.5 / 18.3, partial out posted 17.9 / 18.7, end 19.4 / 19.9.  What
+// bounds it is this chain: the three hand-overs take 5.4 us from the latest post to the mean arrival, waiting for the latest post 2.7, the
+// stages 11.3, bound by what a compute unit loads (64 KB of A, 131 KB of W_Up, 295 KB of rows, 131 KB of W_Down): requesting W_Up or the
+// rows in front of the first hand-over moves the wait, not the end (21.2 - 21.9 us).
 // All waits are bounded (CF_ETIMEOUT), all workgroups have to be resident at once.
 #include "cf_lanes_device.h"
 #include "cf_mla_internal.h"

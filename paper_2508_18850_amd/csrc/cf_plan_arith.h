@@ -80,7 +80,8 @@ constexpr TokenRange dealt_range(const Wave &w, int len, int s, int ns, int memb
     // (An item of an odd member, on a slower die, is 2 td shorter than its neighbours: a boundary in front of one is td further.  What it
     // is worth depends on the lengths and is small: us a pass, td 32 / 16 / 0, Llama-3-8B shape, 860 tokens a member 79.1 / 78.6 / 78.6, 280
     // 62.8 / 63.4 / 63.4, 480 67.8 / 68.0 / 68.2, 400 66.5 / 66.3 / 65.9, eight rows, 700 41.7 / 41.4 / 41.1, 1000 59.1 / 59.3 / 59.9; Llama-2-7B
-    // shape, 576 83.9 / 83.7 / 84.2; Llama-2-70B shape, 1100 85.0 / 85.1 / 85.3; 32 heads of 64 over 8, 1170 30.4 / 30.1 / 29.9.)
+    // shape, 576 83.9 / 83.7 / 84.2; Llama-2-70B shape, 1100 85.0 / 85.1 / 85.3; 32 heads of 64 over 8, 1170 30.4 / 30.1 / 29.9; 8 heads of
+    // 128, batch 3, 10667 to 16000 tokens, 82.3 / 78.6 / 81.6.)
     const int td = pairmap && t >= 256 ? 32 : 0;
     return {s == 0 ? 0 : smaller(s * t + (member & 1 ? td : 0), len), s == ns - 1 ? len : smaller(s * t + t + (member & 1 ? 0 : td), len)};
 }
