@@ -710,7 +710,8 @@ __device__ __forceinline__ uint32_t p1_all(const Params &p, const LayerPtrs &lp,
             *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{f[4], f[5], f[6], f[7]};
         }
     };
-    // cos / sin of this position while x is still on its way (the same for every layer of a stack)
+    // cos / sin of this position while x is still on its way (the same for every layer of a stack).  Behind the staged x it is at most 0.7 %
+    // slower: us a pass, here / there, odd sizes at batch 3 32.5 / 32.6, 8192 columns, 4 heads, norm 33.9 / 34.1, 7B shape 70.2 / 70.2.
 #pragma unroll
     for (int k = 0; k < NE; ++k) {
         const int e = tid + k * NT, eb = e / (HD / 2), i = e % (HD / 2);
